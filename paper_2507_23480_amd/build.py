@@ -12,15 +12,18 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfastpoint_hip.so")
-SOURCES = ["sampler.hip", "ball_query.hip", "knn.hip", "excl_lists.hip", "abi.hip"]
+# (source, points per thread): the sampler is compiled once per number of points a thread holds
+SOURCES = [("sampler.hip", p) for p in (16, 8, 4, 2)] + [(f, 0) for f in ("ball_query.hip", "knn.hip", "excl_lists.hip", "abi.hip")]
 FLAGS = ["--offload-arch=gfx950", "-O3", *os.environ.get("FASTPOINT_EXTRA_FLAGS", "").split(), "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-function"]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(CSRC, os.path.splitext(src)[0] + ".o")
-    subprocess.run(["hipcc", *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj], check=True)
+def _compile(unit) -> str:
+    src, points = unit
+    obj = os.path.join(CSRC, os.path.splitext(src)[0] + ("_p%d" % points if points else "") + ".o")
+    define = ["-DFASTPOINT_SAMPLER_P=%d" % points] if points else []
+    subprocess.run(["hipcc", *FLAGS, *define, "-c", os.path.join(CSRC, src), "-o", obj], check=True)
     return obj
 
 

@@ -315,8 +315,8 @@ fp_status run_sampler(const float* xyz, int32_t B, int32_t N, int32_t n, const i
     // words (stamps start at 1 in every launch) and the chunk counters of a ball-query cache.  (A
     // cloud held by one workgroup has its counters zeroed by that workgroup.)
     if (plan.G > 1) {
-        // ... and, cell-ordered MDPS, the relation words
-        const int64_t rel_words = pruned && prm ? (int64_t)plan.groups * kRelWordsPerCloud : 0;
+        // ... and, cell-ordered, the relation words
+        const int64_t rel_words = pruned ? (int64_t)plan.groups * kRelWordsPerCloud : 0;
         if (launch_zero_words(a.ll_pk, kLlWords, bq_zero, bq_zero_words, a.ll_rel, rel_words, stream) != hipSuccess)
             return FP_ERR_DEVICE;
     }

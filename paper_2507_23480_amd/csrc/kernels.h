@@ -129,6 +129,12 @@ struct Plan {
 
 // mode 0: exact FPS only; 1: MDPS, threshold rounds of kCandPerRound candidates; 2: MDPS, rounds of
 // kCandMax candidates.  NULL for a combination that is not built.
+template <int P>
+const void* sampler_kernel_p(bool bq, bool perm, int mode);
+template <> const void* sampler_kernel_p<2>(bool bq, bool perm, int mode);
+template <> const void* sampler_kernel_p<4>(bool bq, bool perm, int mode);
+template <> const void* sampler_kernel_p<8>(bool bq, bool perm, int mode);
+template <> const void* sampler_kernel_p<16>(bool bq, bool perm, int mode);
 const void* sampler_kernel_for(int threads, int points_per_thread, bool bq, bool perm, int mode);
 // zeroes two ranges of 64-bit words (either may be empty)
 hipError_t launch_zero_words(uint64_t* p, int64_t nwords, uint64_t* p2, int64_t nwords2, uint64_t* p3,

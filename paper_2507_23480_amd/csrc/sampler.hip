@@ -66,6 +66,10 @@ __device__ __forceinline__ float unif(float v)
 {
     return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(v)));
 }
+__device__ __forceinline__ uint64_t uni64(uint64_t v)
+{
+    return ((uint64_t)uni((uint32_t)(v >> 32)) << 32) | (uint64_t)uni((uint32_t)v);
+}
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp(uint32_t v)
 {
@@ -295,6 +299,17 @@ struct Shared {
     uint64_t rel[kCandWin][9];
     uint64_t took[kCandWin / 64];
     uint16_t place[kCandWin];  // ... and of each accepted one its place among the round's picks
+    // exact rounds settled in sweeps (settle_exact)
+    uint32_t open_d[kCandWin];                  // a candidate's distance while it is open (0: out)
+    alignas(16) uint32_t pick_d[kCandWin];      // distance at which a candidate was accepted
+    alignas(16) uint64_t sets[2][16];           // after a sweep: accepted, open, lowered, left to settle_row
+    uint32_t sweep_flag[3];                     // bit 0: some candidate is open, bit 1: some are left to settle_row
+    uint32_t row_acc[kCandWin / 32], row_out[kCandWin / 32];    // settle_row: picks, out
+    // the picks in sequence: how many fall into each range of distances (zero between rounds), how many lie
+    // in the ranges before it, the picks themselves range by range (distance, place in the candidate list)
+    alignas(16) uint32_t bin_cnt[kCandWin], bin_first[kCandWin + 4];
+    uint32_t seq_d[kCandWin];
+    uint16_t seq_id[kCandWin];
     uint32_t progress;
 #ifdef FASTPOINT_PHASE_CLOCKS
     long long chain_cycles;   // shader clocks the control wave spent in the exact-FPS chain loop
@@ -1391,7 +1406,9 @@ constexpr int kWinWords = kCandWin / 64;
 
 constexpr int kRelWords = 4 * kWinWords;           // 32-bit words of a candidate's two bit sets
 
-template <int T, bool BYD>
+enum RelationKind { kByIndex, kByPlace, kByDistance };
+
+template <int T, RelationKind KIND>
 __device__ __forceinline__ void build_relations(Shared<T>& sh, const Where& wh, const SamplerArgs& a,
                                                 uint32_t seq, int total, float r2)
 {
@@ -1415,16 +1432,24 @@ __device__ __forceinline__ void build_relations(Shared<T>& sh, const Where& wh, 
     uint64_t* buf = wh.G == 1 ? nullptr : a.ll_rel + (int64_t)(wh.grp * 2 + (int)(seq & 1u)) * (kCandWin * kRelWords);
     for (int j = first; j < total; j += step) {
         const Cand pj = sh.cand[j];
-        const uint32_t kj = BYD ? pj.d : pj.idx;
+        const uint32_t kj = KIND == kByIndex ? pj.idx : pj.d;
         uint32_t pay = 0;                           // lane l: word l of (before, blockers)
 #pragma unroll
         for (int q = 0; q < kWinWords; ++q) {
             uint64_t before = 0, blockers = 0;
             if (q < nq) {
-                const bool earlier = lane + 64 * q < total && (BYD ? me[q].d : me[q].idx) < kj;
                 const float t = dist2(pj.x, pj.y, pj.z, me[q].x, me[q].y, me[q].z);
-                before = __builtin_amdgcn_ballot_w64(earlier);
-                blockers = __builtin_amdgcn_ballot_w64(earlier && t < r2);
+                if constexpr (KIND == kByDistance) {
+                    // (settle_exact: r2 is tau; kj exceeds it)
+                    const bool ahead = lane + 64 * q < total &&
+                                       (me[q].d > kj || (me[q].d == kj && me[q].idx < pj.idx));
+                    before = __builtin_amdgcn_ballot_w64(ahead && t <= r2);
+                    blockers = __builtin_amdgcn_ballot_w64(ahead && __float_as_uint(t) < kj);
+                } else {
+                    const bool earlier = lane + 64 * q < total && (KIND == kByPlace ? me[q].d : me[q].idx) < kj;
+                    before = __builtin_amdgcn_ballot_w64(earlier);
+                    blockers = __builtin_amdgcn_ballot_w64(earlier && t < r2);
+                }
             }
             set_lane(pay, lane, 2 * q, (uint32_t)before);
             set_lane(pay, lane, 2 * q + 1, (uint32_t)(before >> 32));
@@ -1531,14 +1556,16 @@ struct NearWords {
     uint64_t w[kWinWords];      // candidates to fold
     uint64_t b[kWinWords];      // of those, the ones whose ball reaches the wave's box (recording kernels)
 };
-template <int T, int P, bool BQ>
+template <int T, int P, bool BQ, bool PERM>
 __device__ __forceinline__ NearWords near_candidates(const Points<P, BQ>& pt, const Shared<T>& sh,
                                                      const Where& wh, int total, float bq_r2)
 {
     NearWords nw;
 #pragma unroll
-    for (int q = 0; q < kWinWords; ++q)
-        nw.w[q] = near_mask<P, BQ>(pt, sh.cand + 64 * q, total - 64 * q, wh.lane, bq_r2, nw.b[q]);
+    for (int q = 0; q < kWinWords; ++q) {
+        nw.w[q] = nw.b[q] = ~0ull;
+        if constexpr (PERM) nw.w[q] = near_mask<P, BQ>(pt, sh.cand + 64 * q, total - 64 * q, wh.lane, bq_r2, nw.b[q]);
+    }
     return nw;
 }
 template <int T, int P, bool BQ>
@@ -1751,9 +1778,272 @@ __device__ __forceinline__ void resolve_chain(Shared<T>& sh, const Where& wh, co
     }
 }
 
+// Exact rounds settled together.  The candidates are ALL points whose distance exceeds tau.  Taking the one
+// with the largest up-to-date distance (lowest index among equals) again and again is what Alg. 1 does,
+// but a pick only changes the candidates closer to it than their own distance, so most picks of a round
+// have nothing to do with each other and the order in which they are found does not matter:
+//
+//   * candidate i is a pick at its current distance d_i as soon as no open candidate k comes before it
+//     (d_k > d_i, or equal and a lower index) AND lies closer to it than d_i: distances only fall, so
+//     whatever is taken before i from now on leaves d_i as it is;
+//   * an accepted candidate k (at distance v_k) lowers an open candidate i to dist(i, k) exactly when
+//     dist(i, k) < v_k.  (If k precedes i in the sequence of Alg. 1 and dist(i, k) >= v_k, then
+//     d_i <= v_k already when k is taken; if i precedes k, then dist(i, k) >= d_i >= v_k, or k would
+//     have waited for i.)
+//   * a candidate whose distance has fallen to tau is none any more.
+//
+// rel[i] (build_relations) holds two bit sets over the candidates that come before i by the distances the
+// round starts with: those closer to i than its distance (words 4..7, its blockers), and those
+// closer than tau (words 0..3): once one of the latter is accepted, i is out.  A sweep decides what
+// these sets decide -- thread i of the first four waves looks at candidate i -- and leaves the rest,
+// candidates that were lowered but not to tau or that wait for such a one, to settle_row: a wave per
+// candidate looks at its distances to all others.  The open candidate that comes first is always
+// decided, so the sweeps end.  On the five workloads a round takes two to three (at most five), where
+// the chain took one step of 0.11-0.14 us per pick, 90-120 of them in a round of 256 candidates.
+// The picks are then put in sequence by their distances.
+//
+// Bound: trips through memory between the workgroups.  fps_exact_pruned with the chain -> now: million points,
+// 65536 samples 15.5 -> 5.2 ms (436 rounds of 11.8 us: scan and exchange of the candidates 4.7, relations 3.3,
+// sweeps 0.6, sequence 0.6, box tests 0.4, folds 0.5), LiDAR batch (4 x 120000 -> 16384) 4.26 -> 2.76 ms, rooms
+// (8 x 24000 -> 6000) 1.59 -> 0.87 ms.  Looking at a thread's blockers one by one instead of through the sets
+// took 5.7 us a round, counting the places by all pairs 2 us.
+template <int T>
+__device__ __forceinline__ void settle_row(Shared<T>& sh, int lane, int i, const uint64_t* sets, uint32_t tau_bits)
+{
+    const Cand me = sh.cand[i];                                     // (wave-uniform)
+    uint32_t t[kWinWords], low = 0xFFFFFFFFu;
+#pragma unroll
+    for (int w = 0; w < kWinWords; ++w) {
+        const int k = lane + 64 * w;
+        const Cand c = sh.cand[k];                                  // (past the last one: in neither set)
+        t[w] = __float_as_uint(dist2(c.x, c.y, c.z, me.x, me.y, me.z));
+        if (((sets[w] >> lane) & 1ull) != 0 && t[w] < sh.pick_d[k]) low = min(low, t[w]);
+    }
+    const uint32_t d = min(wave_min_u32(low), uni(me.d));
+    if (d <= tau_bits) {
+        if (lane == 0) atomicOr(&sh.row_out[i >> 5], 1u << (i & 31));
+        return;
+    }
+    const uint32_t my_idx = uni(me.idx);
+    uint64_t blocked = 0;
+#pragma unroll
+    for (int w = 0; w < kWinWords; ++w) {
+        const int k = lane + 64 * w;
+        // (a candidate lowered by another wave in this sweep shows either distance: both are upper bounds)
+        const uint32_t dk = sh.open_d[k];
+        const bool b = ((sets[4 + w] >> lane) & 1ull) != 0 && k != i && t[w] < d &&
+                       (dk > d || (dk == d && sh.cand[k].idx < my_idx));
+        blocked |= __builtin_amdgcn_ballot_w64(b);
+    }
+    if (lane == 0) {
+        sh.open_d[i] = d;
+        if (blocked == 0) {
+            sh.pick_d[i] = d;
+            atomicOr(&sh.row_acc[i >> 5], 1u << (i & 31));
+        }
+    }
+}
+
+// Called by all threads of the workgroup.  (The waves share four SIMDs, so an instruction that all nine
+// execute costs more than two: what is not a wave's own share is left to the waves that need it.)
+template <int T>
+__device__ __forceinline__ void settle_exact(Shared<T>& sh, const Where& wh, const CloudState& st, int total,
+                                             int limit, float tau, bool capture, int nseg)
+{
+    static_assert(T == 2 * kCandWin && kWinWords == 4, "a candidate per thread of the first half of the point waves");
+    constexpr int NW = T / 64;
+    total = uni(total);
+    limit = uni(limit);
+    const uint32_t tau_bits = uni(__float_as_uint(tau));            // tau >= 0
+    int lane = wh.lane, tid = wh.tid;
+    asm volatile("" : "+v"(lane), "+v"(tid));                       // addresses formed here: see settle_relations
+    const bool works = wh.w < kWinWords;                            // wave-uniform
+    uint64_t blockers[kWinWords], kill[kWinWords];
+    uint32_t d0 = 0;
+    if (works) {
+        const bool has = tid < total;
+        uint64_t any = 0;
+#pragma unroll
+        for (int w = 0; w < kWinWords; ++w) blockers[w] = kill[w] = 0;
+        if (has) {
+            d0 = sh.cand[tid].d;
+#pragma unroll
+            for (int w = 0; w < kWinWords; ++w) {
+                kill[w] = sh.rel[tid][w];
+                blockers[w] = sh.rel[tid][kWinWords + w];
+                any |= blockers[w];
+            }
+        }
+        const bool take = has && any == 0;
+        if (take) sh.pick_d[tid] = d0;
+        sh.open_d[tid] = has && !take ? d0 : 0u;
+        const uint64_t mt = __builtin_amdgcn_ballot_w64(take), mo = __builtin_amdgcn_ballot_w64(has && !take);
+        if (lane == 0) {
+            sh.sets[0][wh.w] = mt;
+            sh.sets[0][4 + wh.w] = mo;
+            sh.sets[0][8 + wh.w] = 0;
+            sh.row_acc[2 * wh.w] = sh.row_acc[2 * wh.w + 1] = 0;
+            sh.row_out[2 * wh.w] = sh.row_out[2 * wh.w + 1] = 0;
+        }
+    }
+    if (tid < 3) sh.sweep_flag[tid] = 0;
+#ifdef FASTPOINT_PHASE_CLOCKS
+    long long se_t = wall_clock64();
+#define SETTLE_MARK(k) do { if (wh.tid == 0) { const long long now__ = wall_clock64(); sh.scan_clk[k] += now__ - se_t; se_t = now__; } } while (0)
+#else
+#define SETTLE_MARK(k) do { } while (0)
+#endif
+    __syncthreads();
+    SETTLE_MARK(0);
+    int b = 0, slot = 0;
+    for (int sweep = 0; sweep <= 2 * kCandWin; ++sweep) {           // ends much earlier: see above
+        if (works) {
+            const uint64_t* in = sh.sets[b];
+            uint64_t killed = 0, touched = 0, waits = 0, sure = 0;
+#pragma unroll
+            for (int w = 0; w < kWinWords; ++w) {
+                const uint64_t acc = in[w], still = in[4 + w], low = in[8 + w];
+                killed |= kill[w] & acc;
+                touched |= blockers[w] & acc;
+                waits |= blockers[w] & still;
+                sure |= blockers[w] & still & ~low;                 // ahead and not lowered since: blocks
+            }
+            const uint64_t my_acc = in[wh.w], my_open = in[4 + wh.w], my_low = in[8 + wh.w];
+            // a candidate that was lowered is settled by settle_row from then on
+            const bool lowered = ((my_low >> lane) & 1ull) != 0;
+            bool open = ((my_open >> lane) & 1ull) != 0 && killed == 0;
+            const bool take = open && !lowered && touched == 0 && waits == 0;
+            open = open && !take;
+            const bool row = open && (lowered || touched != 0 || sure == 0);
+            if (take) sh.pick_d[tid] = d0;
+            if (!open) sh.open_d[tid] = 0u;
+            const uint64_t mt = __builtin_amdgcn_ballot_w64(take), mo = __builtin_amdgcn_ballot_w64(open);
+            const uint64_t mr = __builtin_amdgcn_ballot_w64(row);
+            if (lane == 0) {
+                uint64_t* out = sh.sets[b ^ 1];
+                out[wh.w] = my_acc | mt;
+                out[4 + wh.w] = mo;
+                out[8 + wh.w] = my_low | mr;
+                out[12 + wh.w] = mr;
+                if (mo != 0) atomicOr(&sh.sweep_flag[slot], mr != 0 ? 3u : 1u);
+            }
+        }
+        const int next = slot == 2 ? 0 : slot + 1;
+        if (tid == 0) sh.sweep_flag[next] = 0;                      // (read last two barriers ago)
+        __syncthreads();
+        const uint32_t flag = uni(sh.sweep_flag[slot]);
+        b ^= 1;
+        slot = next;
+        if ((flag & 1u) == 0) break;
+        if ((flag & 2u) != 0) {                                     // (a few candidates in most rounds, or none)
+            int turn = 0;
+#pragma unroll 1
+            for (int w = 0; w < kWinWords; ++w) {
+                uint64_t m = uni64(sh.sets[b][12 + w]);
+                while (m != 0) {
+                    const int i = 64 * w + first_lane(m);
+                    m &= m - 1;
+                    if (turn == wh.w) settle_row<T>(sh, lane, i, sh.sets[b], tau_bits);
+                    turn = turn == NW ? 0 : turn + 1;               // the control wave takes its share
+                }
+            }
+            __syncthreads();
+            if (works && lane == 0) {
+                const uint64_t a = ((uint64_t)sh.row_acc[2 * wh.w + 1] << 32) | sh.row_acc[2 * wh.w];
+                const uint64_t o = ((uint64_t)sh.row_out[2 * wh.w + 1] << 32) | sh.row_out[2 * wh.w];
+                sh.sets[b][wh.w] |= a;
+                sh.sets[b][4 + wh.w] &= ~(a | o);
+                sh.row_acc[2 * wh.w] = sh.row_acc[2 * wh.w + 1] = 0;
+                sh.row_out[2 * wh.w] = sh.row_out[2 * wh.w + 1] = 0;
+            }
+            __syncthreads();
+        }
+    }
+    SETTLE_MARK(1);
+    // Places.  The accepted distances are spread over kBins ranges of equal width in their bit patterns, the largest
+    // first; a candidate's place is the number of picks in the ranges before its own plus those before it in
+    // its range (one or two entries in most).  Comparing every pick with every other took 2 us a round.
+    constexpr int kBins = kCandWin;
+    const uint32_t top = uni(__float_as_uint(st.dlast));            // (no distance exceeds the last pick's)
+    const int shift = 32 - __builtin_clz(((top - tau_bits) >> 8) | 1u) ;
+    uint32_t d = 0, bin = 0, slot_in_bin = 0;
+    bool picked = false;
+    if (works) {
+        picked = ((sh.sets[b][wh.w] >> lane) & 1ull) != 0;
+        if (picked) {
+            d = sh.pick_d[tid];
+            bin = (top - d) >> shift;
+            bin = bin < kBins ? bin : kBins - 1;
+            slot_in_bin = atomicAdd(&sh.bin_cnt[bin], 1u);
+        }
+    }
+    __syncthreads();
+    if (wh.w == 0) {
+        const uint4 c = *reinterpret_cast<const uint4*>(&sh.bin_cnt[4 * lane]);
+        const int mine = (int)(c.x + c.y + c.z + c.w);
+        const int incl = wave_incl_sum(mine, lane);
+        uint4 f;
+        f.x = (uint32_t)(incl - mine);
+        f.y = f.x + c.x;
+        f.z = f.y + c.y;
+        f.w = f.z + c.z;
+        *reinterpret_cast<uint4*>(&sh.bin_first[4 * lane]) = f;
+        if (lane == 63) sh.bin_first[kBins] = (uint32_t)incl;
+    }
+    __syncthreads();
+    const int nacc = uni((int)sh.bin_first[kBins]);
+    const int taken = nacc < limit ? nacc : limit;
+    uint32_t lo = 0, hi = 0;
+    if (picked) {
+        lo = sh.bin_first[bin];
+        hi = sh.bin_first[bin + 1];
+        sh.seq_d[lo + slot_in_bin] = d;
+        sh.seq_id[lo + slot_in_bin] = (uint16_t)tid;
+    }
+    if (wh.w >= kWinWords && !wh.ctrl) sh.bin_cnt[tid - kCandWin] = 0;       // for the next round
+    __syncthreads();
+    SETTLE_MARK(2);
+    if (works) {
+        bool keep = false;
+        if (picked) {
+            const uint32_t idx = sh.cand[tid].idx;
+            int place = (int)lo;
+            if (hi - lo > 1) {
+                for (uint32_t k = lo; k < hi; ++k) {
+                    const uint32_t e = sh.seq_d[k];
+                    // (equal distances: the lower index first)
+                    place += e > d || (e == d && sh.cand[sh.seq_id[k]].idx < idx) ? 1 : 0;
+                }
+            }
+            keep = place < limit;
+            if (keep) {
+                const int pos = st.i + place;
+                stage_pick<T>(sh, pos, idx, __uint_as_float(d));
+                sh.place[tid] = (uint16_t)place;
+                if (place == taken - 1) {
+                    sh.ctrl[0] = taken;
+                    sh.ctrl[3] = (int)d;
+                }
+                if (capture) {                                      // prefix loop of Alg. 2: keep the curve
+                    if (place >= taken - 64) sh.ring[pos & 63] = __uint_as_float(d);
+                    for (int l = 0; l < nseg; ++l)
+                        if (sh.bl[l] == pos) sh.thr_meas[l] = __uint_as_float(d);
+                    if (sh.mlp_pos[0] >= 0)
+                        for (int k = 0; k < 32; ++k)
+                            if (sh.mlp_pos[k] == pos) sh.mlp_val[k] = __uint_as_float(d);
+                }
+            }
+        }
+        const uint64_t took = __builtin_amdgcn_ballot_w64(keep);
+        if (lane == 0) sh.took[wh.w] = took;
+    }
+}
+
 // ---- exact FPS for sample positions [st.i, upto) (the loop of Alg. 1), in batched rounds with
 // plain iterations as the fallback.  Returns false if a wait between workgroups expired.
-template <int T, int P, bool BQ, bool PERM, int kFpsQ>
+// kFpsQ: candidates of a round in units of 64; SWEEPS: settled together (settle_exact) instead of one after the
+// other by the control wave (resolve_chain)
+template <int T, int P, bool BQ, bool PERM, int kFpsQ, bool SWEEPS = false>
 __device__ __forceinline__ bool fps_rounds_of(Points<P, BQ>& pt, Shared<T>& sh, const Where& wh,
                                               const SamplerArgs& a, uint32_t& it, uint32_t& seq,
                                               CloudState& st, int upto, bool capture)
@@ -1794,9 +2084,32 @@ __device__ __forceinline__ bool fps_rounds_of(Points<P, BQ>& pt, Shared<T>& sh, 
         }
         {
             PHASE_BEGIN();
-            const uint32_t tag = (uint32_t)(st.resolved + 1) << kLiveShift;
-            if (wh.ctrl) resolve_chain<T, PERM, kFpsQ>(sh, wh, st, total, upto - st.i, tau, capture, a.nseg, tag);
-            else follow_picks<T, P, BQ, PERM, kFpsQ>(pt, sh, wh, a, st.i, tag, total);
+            if constexpr (SWEEPS) {
+#ifdef FASTPOINT_PHASE_CLOCKS
+                long long ex_t = wall_clock64();
+#define EX_MARK(k) do { const long long now__ = wall_clock64(); st.clk[k] += now__ - ex_t; ex_t = now__; } while (0)
+#else
+#define EX_MARK(k) do { } while (0)
+#endif
+                build_relations<T, kByDistance>(sh, wh, a, seq, total, tau);
+                __syncthreads();
+                if (uni(sh.ctrl[2]) != 0) return false;     // a wait between workgroups expired
+                EX_MARK(9);
+                NearWords nw = {};
+                if (!wh.ctrl) nw = near_candidates<T, P, BQ, PERM>(pt, sh, wh, total, a.bq_r2);
+#ifdef FASTPOINT_PHASE_CLOCKS
+                if (wh.tid == 0) sh.scan_clk[3] += wall_clock64() - ex_t;
+#endif
+                settle_exact<T>(sh, wh, st, total, upto - st.i, tau, capture, a.nseg);
+                __syncthreads();
+                EX_MARK(10);
+                if (!wh.ctrl) fold_accepted<T, P, BQ>(pt, sh, wh, a, nw, st.i);
+                EX_MARK(11);
+            } else {
+                const uint32_t tag = (uint32_t)(st.resolved + 1) << kLiveShift;
+                if (wh.ctrl) resolve_chain<T, PERM, kFpsQ>(sh, wh, st, total, upto - st.i, tau, capture, a.nseg, tag);
+                else follow_picks<T, P, BQ, PERM, kFpsQ>(pt, sh, wh, a, st.i, tag, total);
+            }
             __syncthreads();
             PHASE_END(st, 2);
         }
@@ -1804,8 +2117,10 @@ __device__ __forceinline__ bool fps_rounds_of(Points<P, BQ>& pt, Shared<T>& sh, 
         st.npend = 0;                               // folded while they were resolved
         st.dlast = __uint_as_float(uni((uint32_t)sh.ctrl[3]));
         st.i += uni(sh.ctrl[0]);
-        if (alltot < 40 * (kCandFps / kCand)) st.om = st.om * 1.15f < 0.99f ? st.om * 1.15f : 0.99f;
-        else if (alltot > 58 * (kCandFps / kCand)) st.om = st.om * 0.87f;
+        // (a cloud held by one workgroup works out all pairs of candidates itself: fewer of them)
+        const int aim = SWEEPS && wh.G == 1 ? 2 : kCandFps / kCand;
+        if (alltot < 40 * aim) st.om = st.om * 1.15f < 0.99f ? st.om * 1.15f : 0.99f;
+        else if (alltot > 58 * aim) st.om = st.om * 0.87f;
     }
     return true;
 }
@@ -1816,7 +2131,7 @@ __device__ __forceinline__ bool fps_rounds_of(Points<P, BQ>& pt, Shared<T>& sh, 
 // points per thread the chain is what a pick costs, and the wide round pays only where a scan is
 // expensive: when the cloud is spread over many workgroups (measured: 24 yes, 4 and 1 no).
 // ONE_WG: the kernel is only ever launched with one workgroup per cloud.
-template <int T, int P, bool BQ, bool PERM, bool ONE_WG>
+template <int T, int P, bool BQ, bool PERM, int MODE>
 __device__ __forceinline__ bool fps_rounds(Points<P, BQ>& pt, Shared<T>& sh, const Where& wh,
                                            const SamplerArgs& a, uint32_t& it, uint32_t& seq,
                                            CloudState& st, int upto, bool capture)
@@ -1825,7 +2140,14 @@ __device__ __forceinline__ bool fps_rounds(Points<P, BQ>& pt, Shared<T>& sh, con
     // fold takes 260 ns: the million-point cloud then needs 436 scans instead of 814, but a chain step
     // grows to 355 ns and becomes what a pick costs -- 23.2 ms either way; and a chain loop written
     // for any number of candidates per lane was a tenth slower with two than the one written for two.)
-    if constexpr (P >= 4) {
+    constexpr bool ONE_WG = MODE == 1;
+    if constexpr (PERM && MODE != 3) {
+        // (a recording call for a small cloud: with all pairs of candidates worked out by one workgroup
+        // a round costs more than its chain)
+        if constexpr (BQ && P <= 4)
+            if (wh.G == 1) return fps_rounds_of<T, P, BQ, PERM, 1>(pt, sh, wh, a, it, seq, st, upto, capture);
+        return fps_rounds_of<T, P, BQ, PERM, 4, true>(pt, sh, wh, a, it, seq, st, upto, capture);
+    } else if constexpr (P >= 4) {
         return fps_rounds_of<T, P, BQ, PERM, 2>(pt, sh, wh, a, it, seq, st, upto, capture);
     } else {
         if constexpr (!PERM && !ONE_WG) // (the cell-ordered variant gained nothing there and pays for the code)
@@ -1951,6 +2273,7 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
     }
     if (wh.tid < kCandWin + 2) sh.live[wh.tid] = 0;    // round tags start at 1 in every cloud
     if (wh.tid == 0) sh.progress = 0;
+    if (wh.tid < kCandWin) sh.bin_cnt[wh.tid] = 0;
     if (wh.tid < 32) {
         int64_t ik = ((int64_t)a.m * (wh.tid + 1)) / 32;
         sh.mlp_pos[wh.tid] = a.mlp ? (int)(ik < 1 ? 1 : ik) : -1;
@@ -2002,7 +2325,7 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
         for (int k = 0; k < 5; ++k) sh.phase_t[k] = t;
     }
 
-    bool ok = fps_rounds<T, P, BQ, PERM, MODE == 1>(pt, sh, wh, a, it, seq, st, pure_fps ? n : m + 1, !pure_fps);
+    bool ok = fps_rounds<T, P, BQ, PERM, MODE>(pt, sh, wh, a, it, seq, st, pure_fps ? n : m + 1, !pure_fps);
 
     if (wh.tid == 0) {
         const long long t = wall_clock64();
@@ -2172,7 +2495,7 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
             const long long thr_t2 = wall_clock64();
 #endif
             if constexpr (WINDOWS) {
-                build_relations<T, RANKED>(sh, wh, a, seq, total, r2);
+                build_relations<T, (RANKED ? kByPlace : kByIndex)>(sh, wh, a, seq, total, r2);
                 __syncthreads();
                 if (uni(sh.ctrl[2]) != 0) {     // a wait between workgroups expired
                     ok = false;
@@ -2184,7 +2507,7 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
 #endif
                 NearWords nw = {};
                 if (wh.ctrl) settle_relations<T>(sh, wh, st, total, limit);
-                else nw = near_candidates<T, P, BQ>(pt, sh, wh, total, a.bq_r2);
+                else nw = near_candidates<T, P, BQ, PERM>(pt, sh, wh, total, a.bq_r2);
                 __syncthreads();
 #ifdef FASTPOINT_PHASE_CLOCKS
                 const long long thr_t4 = wall_clock64();
@@ -2247,7 +2570,7 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
             //      minimum, so the remainder is exact FPS on the same registers
             et_index = st.i;
             st.dlast = -1.0f;
-            ok = fps_rounds<T, P, BQ, PERM, MODE == 1>(pt, sh, wh, a, it, seq, st, n, false);
+            ok = fps_rounds<T, P, BQ, PERM, MODE>(pt, sh, wh, a, it, seq, st, n, false);
         }
     }
     // the rows of the picks that were never folded (at least the last sample) are still missing
@@ -2335,18 +2658,6 @@ __global__ __launch_bounds__(T + kCtrlThreads) void sampler_kernel(SamplerArgs a
     }
 }
 
-// zeroes up to three ranges of words before a launch: the exchange words (stamps start at 1 in
-// every launch), the counters of a ball-query cache, the relation words of the cell-ordered sampler
-__global__ void zero_words_kernel(uint64_t* p, int64_t nwords, uint64_t* p2, int64_t nwords2, uint64_t* p3,
-                                  int64_t nwords3)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t t = i; t < nwords; t += stride) p[t] = 0;
-    for (int64_t t = i; t < nwords2; t += stride) p2[t] = 0;
-    for (int64_t t = i; t < nwords3; t += stride) p3[t] = 0;
-}
-
 template <int T, int P, bool BQ, bool PERM>
 const void* pick_mode(int mode)
 {
@@ -2381,14 +2692,38 @@ const void* pick_bq(bool bq, bool perm, int mode)
 
 }  // namespace
 
+// The file is compiled once per number of points per thread (the kernels of one take as long to compile as
+// everything else together); the unit of two points per thread also holds what is not a sampler kernel.
+#ifndef FASTPOINT_SAMPLER_P
+#error "compile with -DFASTPOINT_SAMPLER_P=2, 4, 8 and 16"
+#endif
+template <>
+const void* sampler_kernel_p<FASTPOINT_SAMPLER_P>(bool bq, bool perm, int mode)
+{
+    return pick_bq<512, FASTPOINT_SAMPLER_P>(bq, perm, mode);
+}
+
+#if FASTPOINT_SAMPLER_P == 2
+// zeroes up to three ranges of words before a launch: the exchange words (stamps start at 1 in
+// every launch), the counters of a ball-query cache, the relation words of the cell-ordered sampler
+__global__ void zero_words_kernel(uint64_t* p, int64_t nwords, uint64_t* p2, int64_t nwords2, uint64_t* p3,
+                                  int64_t nwords3)
+{
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t t = i; t < nwords; t += stride) p[t] = 0;
+    for (int64_t t = i; t < nwords2; t += stride) p2[t] = 0;
+    for (int64_t t = i; t < nwords3; t += stride) p3[t] = 0;
+}
+
 const void* sampler_kernel_for(int threads, int points_per_thread, bool bq, bool perm, int mode)
 {
     if (threads == 512) {
         switch (points_per_thread) {
-            case 2: return pick_bq<512, 2>(bq, perm, mode);
-            case 4: return pick_bq<512, 4>(bq, perm, mode);
-            case 8: return pick_bq<512, 8>(bq, perm, mode);
-            case 16: return pick_bq<512, 16>(bq, perm, mode);
+            case 2: return sampler_kernel_p<2>(bq, perm, mode);
+            case 4: return sampler_kernel_p<4>(bq, perm, mode);
+            case 8: return sampler_kernel_p<8>(bq, perm, mode);
+            case 16: return sampler_kernel_p<16>(bq, perm, mode);
             default: return nullptr;
         }
     }
@@ -2431,5 +2766,7 @@ hipError_t launch_zero_words(uint64_t* p, int64_t nwords, uint64_t* p2, int64_t 
                        nwords2 > 0 ? nwords2 : 0, p3, nwords3 > 0 ? nwords3 : 0);
     return hipGetLastError();
 }
+
+#endif  // FASTPOINT_SAMPLER_P == 2
 
 }  // namespace fastpoint
