@@ -106,6 +106,8 @@ typedef struct fp_mdps_info {
 
 /* Bytes of workspace fp_fps_exact / fp_mdps_sample need for B clouds of N points
  * (0 is returned for shapes the library rejects). Alignment: 256 bytes. */
+/* (What fp_fps_exact can use: from some thousands of points on that includes the cell-ordered copy of the cloud its
+ * faster kernels work on.  The size returned for a small cloud is enough for every shape.) */
 size_t fp_workspace_bytes(int32_t B, int32_t N);
 
 /* Bytes of the ball-query cache for B clouds of N points and n samples each.

@@ -30,6 +30,7 @@ constexpr int64_t kLlCdWords = (int64_t)2 * kMaxGroup * kCandMax * kCandWords;
 constexpr int64_t kLlCtWords = (int64_t)2 * kMaxGroup;
 constexpr int64_t kLlWords = kLlPkWords + kLlCdWords + kLlCtWords;
 constexpr size_t kScratchBytes = (size_t)(kLlWords * 8);                          // 2 658 304 bytes
+constexpr size_t kExchangeBytes = kScratchBytes;
 
 // Scratch of fp_fps_exact_static: the same exchange words, but in device memory that belongs to
 // the library's code object instead of a caller's workspace, so that the call allocates nothing.
@@ -70,6 +71,19 @@ constexpr Shape kShapes[] = {{512, 2}, {512, 4}, {512, 8}, {512, 16}};
 constexpr int kNumShapes = (int)(sizeof(kShapes) / sizeof(kShapes[0]));
 constexpr int kCtrlThreads = 64;
 constexpr int kTargetPointsPerWg = 1024;
+// A cloud of up to this many points stays in one workgroup (four points per thread): an exchange between
+// workgroups costs a round several microseconds, the second thousand points a pick about 60 ns.  2048
+// points, 512 samples: fps_exact 139 us in one workgroup, 213 in two; mdps_sample 145 / 210, with record
+// 229 / 264.  3000 points in one workgroup (eight per thread): 256 / 267, with record 514 / 357.
+constexpr int kOneWgPoints = 2048;
+// From here on exact FPS and MDPS with the scattered scan order run on the cell-ordered kernels whichever entry
+// point asks for them, below it on the index-ordered ones (without a record: a record's block
+// order belongs to the entry point), MDPS with the lowest-index order from the second line on.  A quarter of
+// the points sampled, one cloud of uniform points / a room, us, index-ordered / cell-ordered (sort included):
+// exact FPS 4096: 339 / 358 and 341 / 350, 6000: 467 / 414, 8192: 513 / 420, 24000: 1381 / 764;
+// MDPS 6000: 471 / 503, 8192: 522 / 492 and 622 / 617, 12000: 833 / 797.
+constexpr int kCellOrderFrom = 5121;
+constexpr int kCellOrderFromMdps = 8192;
 
 bool shape_for(int64_t points_per_wg, Shape* s)
 {
@@ -93,6 +107,7 @@ bool make_plan(int B, int N, int cus, Plan* plan)
     if (gneed > gcap) return false;                            // cloud too large to stay resident
     int G = (int)(((int64_t)N + kTargetPointsPerWg - 1) / kTargetPointsPerWg);
     if (G > gcap) G = gcap;
+    if (N <= kOneWgPoints) G = 1;
     // keep every cloud resident when that still leaves each workgroup within its capacity
     if ((int64_t)B * G > cus) {
         int share = cus / (B < cus ? B : cus);
@@ -205,9 +220,19 @@ fp_status run_sampler(const float* xyz, int32_t B, int32_t N, int32_t n, const i
     if (walk && !pruned && fp_mdps_scattered_workspace_bytes(B, N) == 0) return FP_ERR_SHAPE;
     if (!workspace ||
         workspace_bytes < (pruned ? fp_fps_pruned_workspace_bytes(B, N)
-                                  : (walk ? fp_mdps_scattered_workspace_bytes(B, N) : fp_workspace_bytes(B, N))) ||
+                                  : (walk ? fp_mdps_scattered_workspace_bytes(B, N) : kExchangeBytes)) ||
         (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0)
         return FP_ERR_WORKSPACE;
+
+    // The layout that is faster at this size (the results are the same); exact FPS asked for in index order
+    // needs the larger workspace for it.  (The hook that forces a number of workgroups keeps the entry
+    // point's own layout, so that every kernel can be reached with clouds of any size.)
+    if (!bq_cache && g_force_wg_per_cloud.load() == 0) {
+        if (pruned && N < (prm && !walk ? kCellOrderFromMdps : kCellOrderFrom)) pruned = false;
+        else if (!pruned && !prm && N >= kCellOrderFrom && fp_fps_pruned_workspace_bytes(B, N) != 0 &&
+                 workspace_bytes >= fp_fps_pruned_workspace_bytes(B, N))
+            pruned = true;
+    }
 
     SamplerArgs a;
     memset(&a, 0, sizeof(a));
@@ -260,7 +285,7 @@ fp_status run_sampler(const float* xyz, int32_t B, int32_t N, int32_t n, const i
 
     if (pruned) {
         // the cloud in cell order, behind the exchange words
-        void* sort_ws = reinterpret_cast<unsigned char*>(workspace) + fp_workspace_bytes(B, N);
+        void* sort_ws = reinterpret_cast<unsigned char*>(workspace) + kExchangeBytes;
         if (launch_spatial_sort(xyz, B, N, sort_ws, stream) != hipSuccess) return FP_ERR_DEVICE;
         a.sorted = spatial_sorted(B, N, sort_ws);
         if (walk) a.walk_inv = (uint64_t)inverse_mod(scan_walk_stride(N), N);
@@ -273,7 +298,7 @@ fp_status run_sampler(const float* xyz, int32_t B, int32_t N, int32_t n, const i
     if (walk && !pruned && a.m < n - 1) {
         // the cloud in the order of the walk, behind the exchange words (not needed when the prefix
         // covers everything: the call is exact FPS then)
-        float4* rec = reinterpret_cast<float4*>(reinterpret_cast<unsigned char*>(workspace) + fp_workspace_bytes(B, N));
+        float4* rec = reinterpret_cast<float4*>(reinterpret_cast<unsigned char*>(workspace) + kExchangeBytes);
         if (launch_scan_walk(xyz, B, N, scan_walk_stride(N), rec, stream) != hipSuccess) return FP_ERR_DEVICE;
         a.sorted = rec;
     }
@@ -338,7 +363,8 @@ extern "C" {
 size_t fp_workspace_bytes(int32_t B, int32_t N)
 {
     if (B < 1 || N < 1) return 0;
-    return (size_t)(kLlWords * 8);
+    const size_t cell_order = N >= kCellOrderFrom ? fp_fps_pruned_workspace_bytes(B, N) : 0;
+    return cell_order > 0 ? cell_order : kExchangeBytes;
 }
 
 size_t fp_bq_cache_bytes(int32_t B, int32_t N, int32_t n, int64_t entries_per_cloud)
@@ -387,13 +413,13 @@ fp_status fp_fps_exact_static(const float* xyz, int32_t B, int32_t N, int32_t n,
 size_t fp_mdps_scattered_workspace_bytes(int32_t B, int32_t N)
 {
     if (B < 1 || N < 1 || (int64_t)B * N > ((int64_t)1 << 33)) return 0;
-    return fp_workspace_bytes(B, N) + (size_t)scan_walk_bytes(B, N);
+    return kExchangeBytes + (size_t)scan_walk_bytes(B, N);
 }
 
 size_t fp_fps_pruned_workspace_bytes(int32_t B, int32_t N)
 {
     if (B < 1 || N < 1 || B > 65535 || (int64_t)B * N > ((int64_t)1 << 33)) return 0;
-    return fp_workspace_bytes(B, N) + (size_t)spatial_sort_bytes(B, N) + (size_t)rel_exchange_bytes(B);
+    return kExchangeBytes + (size_t)spatial_sort_bytes(B, N) + (size_t)rel_exchange_bytes(B);
 }
 
 fp_status fp_fps_exact_pruned(const float* xyz, int32_t B, int32_t N, int32_t n, const int32_t* start_idx,
