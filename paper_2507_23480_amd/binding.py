@@ -224,13 +224,24 @@ def set_wait_limit_us(us: int) -> None:
 _workspaces = {}
 
 
+def _try_bytes(need: int, device: torch.device) -> Optional[torch.Tensor]:
+    """Scratch memory for a faster path, None when there is no room for it."""
+    try:
+        return torch.empty(need, dtype=torch.uint8, device=device)
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
+
 def workspace(device: torch.device, B: int, N: int) -> torch.Tensor:
     """A cached per-device workspace tensor (calls on one device must not overlap)."""
     need = int(load().fp_workspace_bytes(B, N))
     key = (device.type, device.index)
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < need:
-        ws = torch.empty(need, dtype=torch.uint8, device=device)
+        ws = _try_bytes(need, device)
+        if ws is None:                          # (what the index-ordered kernels need at any size)
+            ws = torch.empty(int(load().fp_workspace_bytes(1, 1)), dtype=torch.uint8, device=device)
         _workspaces[key] = ws
     return ws
 
@@ -403,14 +414,30 @@ def mdps_sample(xyz: torch.Tensor, n: int, prm: MdpsParams, start_idx=None, want
     return (idx, info) if want_info else idx
 
 
+# Clouds of at least this many points are queried through the uniform grid (fp_ball_query_grid, the same result)
+# when there is no record to read: below it the six launches that build the grid cost more than the scan of all
+# points.  Brute force / grid, us, the workloads' radii: 4096 points 46 / 37, but 58 / 94 on a batch of 32 objects;
+# 6000: 56 / 34 and, eight clouds, 59 / 46; 16384: 127 / 38; 24000 x 8: 339 / 89; 120000 x 4: 1889 / 352;
+# a million: 10707 / 282.  (Balls of a tenth of a scanner-ordered cloud and more, which few queries have,
+# take up to 1.5 times the scan's time: 24000 x 8 at 16 times the radius 476 / 720.)
+GRID_QUERY_FROM = 5121
+
+
 def ball_query(xyz: torch.Tensor, center_idx: torch.Tensor, radius: float, k: int,
                bq_cache: Optional[torch.Tensor] = None) -> Tuple[torch.Tensor, torch.Tensor]:
-    """Ball query: (idx [B][M][k] int32, cnt [B][M] int32)."""
+    """Ball query: (idx [B][M][k] int32, cnt [B][M] int32); with a cache from the recorded radius tests, else
+    by brute force or through a grid, whichever is faster at this size."""
     B, N = _xyz(xyz)
     if not (center_idx.is_cuda and center_idx.dtype == torch.int32 and center_idx.dim() == 2
             and center_idx.shape[0] == B and center_idx.is_contiguous()):
         raise ValueError("center_idx must be a contiguous CUDA int32 tensor [B][M]")
     M = int(center_idx.shape[1])
+    if bq_cache is None and N >= GRID_QUERY_FROM and M > 0:
+        need = int(load().fp_ball_query_grid_workspace_bytes(B, N))
+        # a workspace of its own: queries on several streams or threads may overlap
+        ws = _try_bytes(need, xyz.device) if need > 0 else None
+        if ws is not None:
+            return ball_query_grid(xyz, center_idx, radius, k, ws)
     idx = torch.empty((B, M, k), dtype=torch.int32, device=xyz.device)
     cnt = torch.empty((B, M), dtype=torch.int32, device=xyz.device)
     _check(load().fp_ball_query(xyz.data_ptr(), B, N, center_idx.data_ptr(), M, float(radius), k,

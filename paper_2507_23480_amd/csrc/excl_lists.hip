@@ -456,10 +456,11 @@ __global__ __launch_bounds__(256) void grid_scatter_kernel(const float* __restri
 // order: lanes 0..8 fetch the bounds of one run each, and the runs are then walked as one
 // sequence, so a pass is full except for the last and the loads of successive passes do not
 // wait for one another.
-template <typename F>
-__device__ __forceinline__ void for_neighbours(const ExclGrid& g, const int32_t* __restrict__ st,
-                                               const float4* __restrict__ sorted, int cx, int cy, int cz,
-                                               int lane, F f)
+struct NeighbourRuns {
+    int begin[9], pre[10];      // where each run starts, how many points the runs before it hold
+};
+__device__ __forceinline__ NeighbourRuns neighbour_runs(const ExclGrid& g, const int32_t* __restrict__ st, int cx,
+                                                        int cy, int cz, int lane)
 {
     const int x0 = cx > 0 ? cx - 1 : 0;
     const int x1 = cx < g.dim[0] - 1 ? cx + 1 : g.dim[0] - 1;
@@ -472,23 +473,35 @@ __device__ __forceinline__ void for_neighbours(const ExclGrid& g, const int32_t*
             mylen = st[c0 + (x1 - x0) + 1] - mybegin;
         }
     }
-    int begin[9], pre[10];
-    pre[0] = 0;
+    NeighbourRuns n;
+    n.pre[0] = 0;
 #pragma unroll
     for (int r = 0; r < 9; ++r) {
-        begin[r] = (int)rdlane((uint32_t)mybegin, r);
-        pre[r + 1] = pre[r] + (int)rdlane((uint32_t)mylen, r);
+        n.begin[r] = (int)rdlane((uint32_t)mybegin, r);
+        n.pre[r + 1] = n.pre[r] + (int)rdlane((uint32_t)mylen, r);
     }
-    const int total = pre[9];
+    return n;
+}
+template <typename F>
+__device__ __forceinline__ void walk_runs(const NeighbourRuns& n, const float4* __restrict__ sorted, int lane, F f)
+{
+    const int total = n.pre[9];
     for (int t0 = 0; t0 < total; t0 += 64) {
         const int t = t0 + lane;
         const bool valid = t < total;
-        int at = begin[0] + t;
+        int at = n.begin[0] + t;
 #pragma unroll
-        for (int r = 1; r < 9; ++r) at = t >= pre[r] ? begin[r] + (t - pre[r]) : at;
+        for (int r = 1; r < 9; ++r) at = t >= n.pre[r] ? n.begin[r] + (t - n.pre[r]) : at;
         const float4 rec = sorted[valid ? at : 0];
         if (!f(rec, valid)) break;
     }
+}
+template <typename F>
+__device__ __forceinline__ void for_neighbours(const ExclGrid& g, const int32_t* __restrict__ st,
+                                               const float4* __restrict__ sorted, int cx, int cy, int cz,
+                                               int lane, F f)
+{
+    walk_runs(neighbour_runs(g, st, cx, cy, cz, lane), sorted, lane, f);
 }
 
 // The same walk run by run (a last pass per run that may be partly empty; no search for the run a
@@ -880,7 +893,12 @@ __global__ __launch_bounds__(kHeavyWaves * 64) void excl_fill_heavy_kernel(
 // indices among the hits (in keep, ascending): once it has k of them the largest is a bound, and
 // only hits with an index below it are collected; when the collection fills, and at the end, the
 // k lowest of kept and collected values are taken one at a time (a point is in the ball once, so
-// the values differ).  A ball of any size is answered from its 27 cells.
+// the values differ).
+// A centre whose 27 cells hold C points of N has its k hits among the first k N / (its ball's share of the points),
+// if hits are spread evenly over the indices, and the ball is a sixth to a third of its cells.  Where 8 k N / C
+// points are at most half of C the wave looks at that many in index order first and is mostly done; if not,
+// it has the lowest hits and walks the cells for the others.  (A radius that covers half of a cloud of 24000
+// points would have every wave walk most of the cloud.)
 constexpr int kGridBatch = 256;        // hits collected between two selections of the k lowest
 
 __global__ __launch_bounds__(kWaves * 64) void bq_grid_kernel(
@@ -936,18 +954,39 @@ __global__ __launch_bounds__(kWaves * 64) void bq_grid_kernel(
         fresh = 0;
         bound = kept == k ? mn : 0x7FFFFFFF;
     };
-    for_neighbours(g, cell_start + (int64_t)b * (maxcells + 1), sorted + (int64_t)b * N, cx, cy, cz, lane,
-                   [&](const float4& r, bool valid) {
-                       const int32_t j = __float_as_int(r.w);
-                       const bool hit = valid && dist2(px, py, pz, r.x, r.y, r.z) < r2 && j < bound;
-                       const uint64_t mk = __builtin_amdgcn_ballot_w64(hit);
-                       if (mk != 0) {
-                           if (hit) hits[fresh + lanes_below(mk)] = j;
-                           fresh += __builtin_popcountll(mk);
-                           if (fresh > kGridBatch - 64) take_lowest();
-                       }
-                       return true;
-                   });
+    const NeighbourRuns runs = neighbour_runs(g, cell_start + (int64_t)b * (maxcells + 1), cx, cy, cz, lane);
+    const int cells_hold = runs.pre[9];
+    int from = 0;                                       // points looked at in index order
+    if ((int64_t)cells_hold * cells_hold >= (int64_t)16 * k * N) {
+        const int64_t want = (int64_t)8 * k * N / cells_hold;
+        const int upto = want < N ? (int)want : N;
+        for (; from < upto && kept < k; from += 64) {
+            const int j = from + lane;
+            bool hit = false;
+            if (j < N) {
+                const float* pj = cloud + (int64_t)j * 3;
+                hit = dist2(px, py, pz, pj[0], pj[1], pj[2]) < r2;
+            }
+            const uint64_t mk = __builtin_amdgcn_ballot_w64(hit);
+            const int at = kept + lanes_below(mk);
+            if (hit && at < k) keep[at] = j;
+            kept += (int)__builtin_popcountll(mk);
+        }
+        kept = kept < k ? kept : k;
+    }
+    if (kept < k && from < N) {
+        walk_runs(runs, sorted + (int64_t)b * N, lane, [&](const float4& r, bool valid) {
+            const int32_t j = __float_as_int(r.w);
+            const bool hit = valid && dist2(px, py, pz, r.x, r.y, r.z) < r2 && j < bound && j >= from;
+            const uint64_t mk = __builtin_amdgcn_ballot_w64(hit);
+            if (mk != 0) {
+                if (hit) hits[fresh + lanes_below(mk)] = j;
+                fresh += __builtin_popcountll(mk);
+                if (fresh > kGridBatch - 64) take_lowest();
+            }
+            return true;
+        });
+    }
     if (fresh > 0) take_lowest();
     const int first = kept > 0 ? keep[0] : -1;
     for (int t = lane; t < k; t += 64) row[t] = t < kept ? keep[t] : first;
