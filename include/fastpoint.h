@@ -285,6 +285,18 @@ fp_status fp_knn(const float* xyz, int32_t B, int32_t N, const int32_t* sample_i
                  int32_t k, int32_t* out_pos, float* out_d2, const void* bq_cache,
                  int32_t* out_deferred, void* workspace, size_t workspace_bytes, void* stream);
 
+/* Bytes of workspace fp_knn_search needs (0 for shapes the library rejects).  Alignment: 256 bytes. */
+size_t fp_knn_search_workspace_bytes(int32_t B, int32_t N, int32_t n);
+
+/*
+ * The result of fp_knn without a cache, through a grid over the samples whose cells follow their
+ * density; points it does not settle are searched by brute force (out_deferred [B] int32 or NULL:
+ * their number per cloud).
+ */
+fp_status fp_knn_search(const float* xyz, int32_t B, int32_t N, const int32_t* sample_idx, int32_t n,
+                        int32_t k, int32_t* out_pos, float* out_d2, int32_t* out_deferred,
+                        void* workspace, size_t workspace_bytes, void* stream);
+
 #define FP_EXCL_MAX_LEVELS 17   /* FP_MAX_SEG thresholds and the ball-query radius */
 
 /* Bytes of workspace fp_excl_count / fp_excl_fill need (0 for shapes the library rejects).

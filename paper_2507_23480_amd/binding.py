@@ -18,7 +18,7 @@ LIB_PATH = os.path.join(HERE, "libfastpoint_hip.so")
 MAX_SEG = 16
 
 EXPORTS = ["fp_mdps_scattered_workspace_bytes", "fp_bq_cache_entries", "fp_fps_exact_static", "fp_fps_pruned_workspace_bytes", "fp_fps_exact_pruned", "fp_mdps_sample_pruned", "fp_workspace_bytes", "fp_bq_cache_bytes", "fp_fps_exact", "fp_mdps_sample",
-           "fp_ball_query", "fp_ball_query_grid_workspace_bytes", "fp_ball_query_grid", "fp_knn_workspace_bytes", "fp_knn", "fp_knn_grid_workspace_bytes", "fp_knn_grid", "fp_excl_workspace_bytes", "fp_excl_count",
+           "fp_ball_query", "fp_ball_query_grid_workspace_bytes", "fp_ball_query_grid", "fp_knn_workspace_bytes", "fp_knn", "fp_knn_search_workspace_bytes", "fp_knn_search", "fp_knn_grid_workspace_bytes", "fp_knn_grid", "fp_excl_workspace_bytes", "fp_excl_count",
            "fp_excl_fill", "fp_ball_query_lists", "fp_gather_xyz", "fp_coverage", "fp_probe_fp32_rate", "fp_plan", "fp_set_wg_per_cloud",
            "fp_set_wait_limit_us", "fp_set_cooperative_launch", "fp_status_string"]
 
@@ -133,6 +133,10 @@ def load() -> ctypes.CDLL:
     lib.fp_knn_workspace_bytes.restype = ctypes.c_size_t
     lib.fp_knn.argtypes = [vp, i32, i32, vp, i32, i32, vp, vp, vp, vp, vp, ctypes.c_size_t, vp]
     lib.fp_knn.restype = i32
+    lib.fp_knn_search_workspace_bytes.argtypes = [i32, i32, i32]
+    lib.fp_knn_search_workspace_bytes.restype = ctypes.c_size_t
+    lib.fp_knn_search.argtypes = [vp, i32, i32, vp, i32, i32, vp, vp, vp, vp, ctypes.c_size_t, vp]
+    lib.fp_knn_search.restype = i32
     lib.fp_knn_grid_workspace_bytes.argtypes = [i32, i32, i32]
     lib.fp_knn_grid_workspace_bytes.restype = ctypes.c_size_t
     lib.fp_knn_grid.argtypes = [vp, i32, i32, vp, i32, i32, f32, vp, vp, vp, vp, ctypes.c_size_t, vp]
@@ -471,6 +475,14 @@ def ball_query_grid(xyz: torch.Tensor, center_idx: torch.Tensor, radius: float, 
     return idx, cnt
 
 
+# From this many samples and points on the k nearest samples are searched through a grid over the samples
+# (fp_knn_search, the same result): below it the thirteen launches cost more than comparing all pairs.  All pairs /
+# grid, us, k = 3, samples of exact FPS: 16 clouds of 1024 points and 512 samples 74 / 93; 4096 and 1024: 133 / 105;
+# 8 x 24000 and 6000: 608 / 127; 4 x 120000 and 16384: 1388 / 327; a million and 65536: 11276 / 462.
+# Samples taken at random, whose cells are filled unevenly: 325 / 263 (4 x 20000), 1458 / 1198 (4 x 120000).
+KNN_SEARCH_FROM = (1024, 4096)
+
+
 def knn(xyz: torch.Tensor, sample_idx: torch.Tensor, k: int, bq_cache: Optional[torch.Tensor] = None,
         want_deferred: bool = False):
     """k nearest samples of every point: (pos [B][N][k] int32 positions into sample_idx,
@@ -484,6 +496,13 @@ def knn(xyz: torch.Tensor, sample_idx: torch.Tensor, k: int, bq_cache: Optional[
     pos = torch.empty((B, N, k), dtype=torch.int32, device=xyz.device)
     d2 = torch.empty((B, N, k), dtype=torch.float32, device=xyz.device)
     ws, ws_bytes, deferred = None, 0, None
+    if bq_cache is None and n >= KNN_SEARCH_FROM[0] and N >= KNN_SEARCH_FROM[1]:
+        need = int(load().fp_knn_search_workspace_bytes(B, N, n))
+        ws = _try_bytes(need, xyz.device) if need > 0 else None
+        if ws is not None:
+            _check(load().fp_knn_search(xyz.data_ptr(), B, N, sample_idx.data_ptr(), n, k, pos.data_ptr(),
+                                        d2.data_ptr(), None, ws.data_ptr(), need, _stream()), "fp_knn_search")
+            return (pos, d2, deferred) if want_deferred else (pos, d2)
     if bq_cache is not None:
         entries = int(load().fp_bq_cache_entries(bq_cache.numel(), B, N, n))
         ws_bytes = int(load().fp_knn_workspace_bytes(B, N, entries))

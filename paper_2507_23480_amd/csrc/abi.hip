@@ -550,6 +550,33 @@ fp_status fp_knn(const float* xyz, int32_t B, int32_t N, const int32_t* sample_i
     return err == hipSuccess ? FP_OK : FP_ERR_DEVICE;
 }
 
+size_t fp_knn_search_workspace_bytes(int32_t B, int32_t N, int32_t n)
+{
+    if (B < 1 || N < 1 || n < 1 || B > 65535 || (int64_t)B * N > ((int64_t)1 << 33)) return 0;
+    return fp_knn_workspace_bytes(B, N, 0) + (size_t)knn_search_bytes(B, n);
+}
+
+fp_status fp_knn_search(const float* xyz, int32_t B, int32_t N, const int32_t* sample_idx, int32_t n, int32_t k,
+                        int32_t* out_pos, float* out_d2, int32_t* out_deferred, void* workspace,
+                        size_t workspace_bytes, void* stream)
+{
+    if (!xyz || !sample_idx || !out_pos || !out_d2) return FP_ERR_NULL;
+    if (B < 1 || N < 1 || n < 1 || n > N || k < 1 || k > FP_KNN_MAX_K || k > n || B > 65535) return FP_ERR_SHAPE;
+    if ((int64_t)B * N > ((int64_t)1 << 33)) return FP_ERR_SHAPE;
+    if (!workspace || workspace_bytes < fp_knn_search_workspace_bytes(B, N, n) ||
+        (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0)
+        return FP_ERR_WORKSPACE;
+    unsigned char* base = reinterpret_cast<unsigned char*>(workspace);
+    const KnnLayout l = knn_layout(B, N, 0);
+    int32_t* count = reinterpret_cast<int32_t*>(base + l.count);
+    int32_t* list = reinterpret_cast<int32_t*>(base + l.list);
+    hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+    if (launch_knn_search(xyz, B, N, sample_idx, n, k, out_pos, out_d2, count, list, base + l.bytes, st) != hipSuccess)
+        return FP_ERR_DEVICE;
+    hipError_t err = launch_knn_deferred(xyz, B, N, sample_idx, n, k, out_pos, out_d2, count, list, out_deferred, st);
+    return err == hipSuccess ? FP_OK : FP_ERR_DEVICE;
+}
+
 static bool excl_shape_ok(int32_t B, int32_t N, int32_t L)
 {
     if (B < 1 || N < 1 || L < 1 || L > FP_EXCL_MAX_LEVELS || B > 65535) return false;

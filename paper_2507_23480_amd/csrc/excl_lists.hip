@@ -186,6 +186,7 @@ __global__ void grid_setup_kernel(ExclGrid* gp, int B, const float* __restrict__
     g.rmax2 = rmax2;
     g.lmax = lmax;
     g.curve_bits = 0;
+    g.cnt_shift = 0;
     gp[b] = g;
 }
 
@@ -255,6 +256,7 @@ __global__ void sort_setup_kernel(ExclGrid* gp, int B, int bits)
     g.rmax2 = 0.0f;
     g.lmax = 0;
     g.curve_bits = bits;
+    g.cnt_shift = 0;
     gp[b] = g;
 }
 
@@ -345,7 +347,7 @@ __global__ __launch_bounds__(1024) void grid_tile_sum_kernel(const ExclGrid* __r
     __shared__ int32_t wsum[16];
     const int b = (int)blockIdx.y, t = (int)blockIdx.x;
     const int ncells = gp[b].ncells;
-    const int32_t* cnt = cell_cnt + (int64_t)b * maxcells;
+    const int32_t* cnt = cell_cnt + (int64_t)b * maxcells + gp[b].cnt_shift;
     const bool wide = (reinterpret_cast<uintptr_t>(cnt) & 15u) == 0;
     int v[kCellPer];
     load_cells(cnt, t * kCellTile + (int)threadIdx.x * kCellPer, ncells, wide, v);
@@ -365,7 +367,7 @@ __global__ __launch_bounds__(1024) void grid_scan_kernel(const ExclGrid* __restr
     const int ncells = gp[b].ncells;
     const int base = t * kCellTile;
     if (base >= ncells) return;                          // uniform over the workgroup
-    int32_t* cnt = cell_cnt + (int64_t)b * maxcells;
+    int32_t* cnt = cell_cnt + (int64_t)b * maxcells + gp[b].cnt_shift;
     int32_t* st = cell_start + (int64_t)b * (maxcells + 1);
     const bool cnt_wide = (reinterpret_cast<uintptr_t>(cnt) & 15u) == 0;
     const bool st_wide = (reinterpret_cast<uintptr_t>(st) & 15u) == 0;
@@ -446,7 +448,7 @@ __global__ __launch_bounds__(256) void grid_scatter_kernel(const float* __restri
     const float x = p[0], y = p[1], z = p[2];
     int cx, cy, cz;
     const int c = cell_of(g, x, y, z, cx, cy, cz);
-    const int pos = grouped_add(cell_cur + (int64_t)b * maxcells, c, valid, (int)threadIdx.x & 63);
+    const int pos = grouped_add(cell_cur + (int64_t)b * maxcells + g.cnt_shift, c, valid, (int)threadIdx.x & 63);
     if (valid) sorted[(int64_t)b * N + pos] = make_float4(x, y, z, __int_as_float(i));
 }
 
@@ -1075,6 +1077,211 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
     }
 }
 
+// ---- k nearest samples without a search radius.  The cells follow the samples: they are counted into a fine grid (up to
+// kFinePerSample cells per sample) and into two coarser ones (cells twice and four times as wide); the
+// finest whose occupied cells hold kSamplesPerCell samples on average is searched.  (Samples on
+// surfaces fill few cells of a fine grid, samples in a volume fill many of a coarse one.)
+constexpr int kFineLevels = 3;
+constexpr int kFinePerSample = 16;
+constexpr float kSamplesPerCell = 1.5f;
+constexpr int kMaxRing = 4;            // cells away from a point's own up to which one thread searches
+
+__device__ __forceinline__ void level_of(const ExclGrid& g, int level, int (&dim)[3], float& inv_h)
+{
+    inv_h = g.inv_h;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) dim[a] = g.dim[a];
+    for (int l = 0; l < level; ++l) {
+        inv_h = inv_h * 0.5f;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) dim[a] = (dim[a] + 1) >> 1;
+    }
+}
+
+// counts: [level][cloud][maxcells]; occupied: [cloud][level]
+__global__ __launch_bounds__(256) void level_count_kernel(const float* __restrict__ xyz, int N,
+                                                          const ExclGrid* __restrict__ gp, int32_t* cell_cnt,
+                                                          int32_t* occupied, int maxcells, int64_t level_stride)
+{
+    const int b = (int)blockIdx.y;
+    const int i = (int)(blockIdx.x * 256 + threadIdx.x);
+    const bool valid = i < N;
+    const ExclGrid g = gp[b];
+    const float* p = xyz + ((int64_t)b * N + (valid ? i : 0)) * 3;
+    for (int level = 0; level < kFineLevels; ++level) {
+        int dim[3];
+        float inv_h;
+        level_of(g, level, dim, inv_h);
+        const int cx = cell_coord(p[0], g.origin[0], inv_h, dim[0]);
+        const int cy = cell_coord(p[1], g.origin[1], inv_h, dim[1]);
+        const int cz = cell_coord(p[2], g.origin[2], inv_h, dim[2]);
+        const int c = (cz * dim[1] + cy) * dim[0] + cx;
+        const int before = valid ? atomicAdd(cell_cnt + level * level_stride + (int64_t)b * maxcells + c, 1) : 1;
+        const uint64_t first = __builtin_amdgcn_ballot_w64(before == 0);
+        if ((threadIdx.x & 63) == 0 && first != 0) atomicAdd(&occupied[b * kFineLevels + level], __builtin_popcountll(first));
+    }
+}
+
+__global__ void level_pick_kernel(ExclGrid* gp, int B, const int32_t* __restrict__ occupied, int N, int64_t level_stride)
+{
+    const int b = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (b >= B) return;
+    ExclGrid g = gp[b];
+    int level = 0;
+    while (level < kFineLevels - 1 && (float)N < kSamplesPerCell * (float)occupied[b * kFineLevels + level]) ++level;
+    int dim[3];
+    float inv_h;
+    level_of(g, level, dim, inv_h);
+    g.inv_h = inv_h;
+    for (int a = 0; a < 3; ++a) g.dim[a] = dim[a];
+    g.ncells = dim[0] * dim[1] * dim[2];
+    g.cnt_shift = level * level_stride;
+    gp[b] = g;
+}
+
+// One thread per point: its own cell (ring 0), the 26 around it (ring 1), the cells at distance 2, 3, ... (in the
+// largest coordinate difference).  Every sample beyond ring r lies at least r cell widths and the point's
+// distance to the nearest face of its cell away, so the search ends when the k-th nearest found is closer
+// than that; a row of ring 1 that lies farther than the k-th found so far is passed over.  The cell coordinate is
+// rounded (at most 1024 cells per axis: by less than a thousandth of a cell), which kCellRounding allows for.
+// A point that is not done after kMaxRing rings, or whose cells hold more than an eighth of the samples, goes
+// to the list the brute-force kernels take.
+// Bound: latency of the cell bounds and the records (L2); the bounds of ring 1 are requested together.
+constexpr float kCellRounding = 0.002f;
+
+template <int K>
+__global__ __launch_bounds__(256) void knn_search_kernel(const float* __restrict__ xyz, int N, int k,
+                                                         int32_t* __restrict__ out_pos, float* __restrict__ out_d2,
+                                                         const ExclGrid* __restrict__ gp,
+                                                         const int32_t* __restrict__ cell_start,
+                                                         const float4* __restrict__ sorted, int n, int maxcells,
+                                                         int32_t* __restrict__ count, int32_t* __restrict__ list)
+{
+    const int b = (int)blockIdx.y;
+    const int j = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (j >= N) return;
+    const ExclGrid g = gp[b];
+    const float* p = xyz + ((int64_t)b * N + j) * 3;
+    const float px = p[0], py = p[1], pz = p[2];
+    const int cx = cell_coord(px, g.origin[0], g.inv_h, g.dim[0]);
+    const int cy = cell_coord(py, g.origin[1], g.inv_h, g.dim[1]);
+    const int cz = cell_coord(pz, g.origin[2], g.inv_h, g.dim[2]);
+    float bd[K];
+    int32_t bq[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+        bd[i] = __builtin_inff();
+        bq[i] = -1;
+    }
+    float kth = __builtin_inff();       // the k-th entry
+    int32_t kth_q = -1;
+    const int32_t* __restrict__ st = cell_start + (int64_t)b * (maxcells + 1);
+    const float4* __restrict__ rec = sorted + (int64_t)b * n;
+    auto visit = [&](int t, int end) {
+        for (; t < end; ++t) {
+            const float4 s = rec[t];
+            const float dd = dist2(px, py, pz, s.x, s.y, s.z);
+            const int32_t qq = __float_as_int(s.w);
+            if (!(dd < kth || (dd == kth && qq < kth_q))) continue;                    // NaN: never
+#pragma unroll
+            for (int i = K - 1; i >= 1; --i) {
+                const bool before = dd < bd[i - 1] || (dd == bd[i - 1] && qq < bq[i - 1]);
+                const bool here = dd < bd[i] || (dd == bd[i] && qq < bq[i]);
+                bd[i] = before ? bd[i - 1] : (here ? dd : bd[i]);
+                bq[i] = before ? bq[i - 1] : (here ? qq : bq[i]);
+            }
+            const bool first = dd < bd[0] || (dd == bd[0] && qq < bq[0]);
+            bd[0] = first ? dd : bd[0];
+            bq[0] = first ? qq : bq[0];
+#pragma unroll
+            for (int i = 0; i < K; ++i) {
+                kth = i == k - 1 ? bd[i] : kth;
+                kth_q = i == k - 1 ? bq[i] : kth_q;
+            }
+        }
+    };
+    const float h = g.inv_h > 0.0f ? 1.0f / g.inv_h : __builtin_inff();
+    // distances to the faces of the point's cell, in cell widths (0 to 1; a point outside the grid: to the near side)
+    auto inside = [&](float x, float lo, int c) {
+        const float f = (x - lo) * g.inv_h - (float)c;
+        return f >= 0.0f ? (f <= 1.0f ? f : 1.0f) : 0.0f;           // (NaN: 0)
+    };
+    const float fx = inside(px, g.origin[0], cx), fy = inside(py, g.origin[1], cy), fz = inside(pz, g.origin[2], cz);
+    auto gap = [&](float f) { return f > kCellRounding ? (f - kCellRounding) * h * 0.999f : 0.0f; };
+    const float near_face = fminf(fminf(fminf(fx, 1.0f - fx), fminf(fy, 1.0f - fy)), fminf(fz, 1.0f - fz));
+    bool done = false;
+    int begin[9], end[9], total = 0;
+    const int x0 = cx > 0 ? cx - 1 : 0;
+    const int x1 = cx < g.dim[0] - 1 ? cx + 1 : g.dim[0] - 1;
+#pragma unroll
+    for (int r = 0; r < 9; ++r) {
+        const int z = cz + r / 3 - 1, y = cy + r % 3 - 1;
+        const bool in = z >= 0 && z < g.dim[2] && y >= 0 && y < g.dim[1];
+        const int c0 = in ? (z * g.dim[1] + y) * g.dim[0] : 0;
+        begin[r] = in ? st[c0 + x0] : 0;
+        end[r] = in ? st[c0 + x1 + 1] : 0;
+        total += end[r] - begin[r];
+    }
+    const int own = (cz * g.dim[1] + cy) * g.dim[0] + cx;
+    const int own_begin = st[own], own_end = st[own + 1];
+    const bool crowded = total > 256 && total > n / 8;
+    if (!crowded || (own_end - own_begin <= n / 8)) {
+        visit(own_begin, own_end);
+        const float m = gap(near_face);
+        done = kth < m * m;
+    }
+    if (!done && !crowded) {
+        const float ly = gap(fy), ry = gap(1.0f - fy), lz = gap(fz), rz = gap(1.0f - fz);
+        visit(begin[4], own_begin);
+        visit(own_end, end[4]);
+#pragma unroll
+        for (int o = 0; o < 8; ++o) {
+            constexpr int kOrder[8] = {1, 3, 5, 7, 0, 2, 6, 8};     // rows that share a face with the own one first
+            const int r = kOrder[o];
+            const float gy = r % 3 == 0 ? ly : (r % 3 == 2 ? ry : 0.0f), gz = r / 3 == 0 ? lz : (r / 3 == 2 ? rz : 0.0f);
+            if (gy * gy + gz * gz <= kth) visit(begin[r], end[r]);
+        }
+        const float m = h * 0.998f + gap(near_face);
+        done = kth < m * m;
+        for (int ring = 2; ring <= kMaxRing && !done; ++ring) {
+            for (int z = cz - ring; z <= cz + ring; ++z) {
+                if (z < 0 || z >= g.dim[2]) continue;
+                for (int y = cy - ring; y <= cy + ring; ++y) {
+                    if (y < 0 || y >= g.dim[1]) continue;
+                    const int c0 = (z * g.dim[1] + y) * g.dim[0];
+                    const int xl = cx - ring, xr = cx + ring;
+                    if (z == cz - ring || z == cz + ring || y == cy - ring || y == cy + ring) {
+                        visit(st[c0 + (xl > 0 ? xl : 0)], st[c0 + (xr < g.dim[0] - 1 ? xr : g.dim[0] - 1) + 1]);
+                    } else {
+                        if (xl >= 0) visit(st[c0 + xl], st[c0 + xl + 1]);
+                        if (xr < g.dim[0]) visit(st[c0 + xr], st[c0 + xr + 1]);
+                    }
+                }
+            }
+            const float mr = h * 0.998f * (float)ring + gap(near_face);
+            done = kth < mr * mr;
+        }
+    }
+    if (done) {
+        int32_t* pos = out_pos + ((int64_t)b * N + j) * k;
+        float* d2 = out_d2 + ((int64_t)b * N + j) * k;
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+            if (i < k) {
+                pos[i] = bq[i];
+                d2[i] = bd[i];
+            }
+    }
+    const uint64_t left = __builtin_amdgcn_ballot_w64(!done);       // (of the lanes that have a point)
+    if (!done) {
+        const int lane = (int)threadIdx.x & 63, leader = __builtin_ctzll(left);
+        int at = 0;
+        if (lane == leader) at = atomicAdd(&count[b], __builtin_popcountll(left));
+        at = __builtin_amdgcn_readlane(at, leader);
+        list[(int64_t)b * N + at + lanes_below(left)] = j;
+    }
+}
+
 __global__ void zero_ints_kernel(int32_t* p, int n)
 {
     const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
@@ -1265,6 +1472,84 @@ hipError_t launch_knn_grid(const float* xyz, int B, int N, const float* sample_x
                            sorted, n, lay.maxcells, count, list);
     else
         hipLaunchKernelGGL(knn_grid_kernel<8>, pgrid, dim3(256), 0, stream, xyz, N, k, r2, out_pos, out_d2, gp, st,
+                           sorted, n, lay.maxcells, count, list);
+    return hipGetLastError();
+}
+
+// Where the parts of a search workspace lie: the samples' coordinates, the grid over them.
+struct SearchLayout {
+    int maxcells;
+    int64_t sample_off, grid_off, occ_off, cnt_off, start_off, sorted_off, tiles_off, bytes, level_stride;
+};
+static SearchLayout search_layout(int B, int n)
+{
+    SearchLayout lay;
+    int64_t mc = (int64_t)n * kFinePerSample;
+    if (mc < 64) mc = 64;
+    if (mc > ((int64_t)1 << 21)) mc = (int64_t)1 << 21;
+    lay.maxcells = (int)mc;
+    auto up = [](int64_t v) { return (v + 255) / 256 * 256; };
+    int64_t at = 0;
+    lay.sample_off = at;
+    at += up((int64_t)B * n * 12);
+    lay.grid_off = at;
+    at += up((int64_t)B * (int64_t)sizeof(ExclGrid));
+    // occupied cells and cell counts are one range, zeroed together
+    lay.occ_off = at;
+    at += up((int64_t)B * kFineLevels * 4);
+    lay.cnt_off = at;
+    lay.level_stride = (int64_t)B * mc;
+    at += up(kFineLevels * lay.level_stride * 4);
+    lay.start_off = at;
+    at += up((int64_t)B * (mc + 1) * 4);
+    lay.sorted_off = at;
+    at += up((int64_t)B * n * 16);
+    lay.tiles_off = at;
+    at += up((int64_t)B * ((mc + kCellTile - 1) / kCellTile) * 4);
+    lay.bytes = at;
+    return lay;
+}
+int64_t knn_search_bytes(int B, int n) { return search_layout(B, n).bytes; }
+
+hipError_t launch_knn_search(const float* xyz, int B, int N, const int32_t* sample_idx, int n, int k, int32_t* out_pos,
+                             float* out_d2, int32_t* count, int32_t* list, void* workspace, hipStream_t stream)
+{
+    const SearchLayout lay = search_layout(B, n);
+    unsigned char* base = reinterpret_cast<unsigned char*>(workspace);
+    float* samples = reinterpret_cast<float*>(base + lay.sample_off);
+    ExclGrid* gp = reinterpret_cast<ExclGrid*>(base + lay.grid_off);
+    int32_t* occ = reinterpret_cast<int32_t*>(base + lay.occ_off);
+    int32_t* cnt = reinterpret_cast<int32_t*>(base + lay.cnt_off);
+    int32_t* st = reinterpret_cast<int32_t*>(base + lay.start_off);
+    float4* sorted = reinterpret_cast<float4*>(base + lay.sorted_off);
+    if (launch_gather(xyz, B, N, sample_idx, n, samples, stream) != hipSuccess) return hipErrorInvalidValue;
+    const int64_t nzero = (lay.start_off - lay.occ_off) / 4;
+    int initblocks = (int)((nzero + 255) / 256 < 2048 ? (nzero + 255) / 256 : 2048);
+    if (initblocks < (B + 255) / 256) initblocks = (B + 255) / 256;
+    hipLaunchKernelGGL(zero_ints_kernel, dim3((B + 255) / 256), dim3(256), 0, stream, count, B);
+    hipLaunchKernelGGL(grid_init_kernel, dim3(initblocks), dim3(256), 0, stream, gp, B, occ, nzero);
+    int bblocks = (n + 2047) / 2048;
+    if (bblocks > 64) bblocks = 64;
+    hipLaunchKernelGGL(grid_bounds_kernel, dim3(bblocks, B), dim3(256), 0, stream, samples, n, gp);
+    // no radius: the finest grid of at most maxcells cells
+    hipLaunchKernelGGL(grid_setup_kernel, dim3((B + 63) / 64), dim3(64), 0, stream, gp, B,
+                       static_cast<const float*>(nullptr), 1, lay.maxcells, 0.0f);
+    const dim3 sgrid((unsigned)((n + 255) / 256), (unsigned)B);
+    hipLaunchKernelGGL(level_count_kernel, sgrid, dim3(256), 0, stream, samples, n, gp, cnt, occ, lay.maxcells,
+                       lay.level_stride);
+    hipLaunchKernelGGL(level_pick_kernel, dim3((B + 63) / 64), dim3(64), 0, stream, gp, B, (const int32_t*)occ, n,
+                       lay.level_stride);
+    launch_cell_scan(gp, cnt, st, reinterpret_cast<int32_t*>(base + lay.tiles_off), B, lay.maxcells, stream);
+    hipLaunchKernelGGL(grid_scatter_kernel, sgrid, dim3(256), 0, stream, samples, n, gp, cnt, sorted, lay.maxcells);
+    const dim3 pgrid((unsigned)((N + 255) / 256), (unsigned)B);
+    if (k == 1)
+        hipLaunchKernelGGL(knn_search_kernel<1>, pgrid, dim3(256), 0, stream, xyz, N, k, out_pos, out_d2, gp, st,
+                           sorted, n, lay.maxcells, count, list);
+    else if (k <= 3)
+        hipLaunchKernelGGL(knn_search_kernel<3>, pgrid, dim3(256), 0, stream, xyz, N, k, out_pos, out_d2, gp, st,
+                           sorted, n, lay.maxcells, count, list);
+    else
+        hipLaunchKernelGGL(knn_search_kernel<8>, pgrid, dim3(256), 0, stream, xyz, N, k, out_pos, out_d2, gp, st,
                            sorted, n, lay.maxcells, count, list);
     return hipGetLastError();
 }

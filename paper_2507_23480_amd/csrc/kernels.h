@@ -175,6 +175,7 @@ struct ExclGrid {
     int32_t lmax;            // its level
     int32_t curve_bits;      // 0: cells numbered x-fastest; b > 0: 2^b cells per axis, numbered along
                              // a Hilbert curve
+    int64_t cnt_shift;       // cell counts of this grid: elements behind those of the call's first grid
 };
 
 // Where the parts of an exclusion-list workspace lie (byte offsets).
@@ -199,6 +200,9 @@ hipError_t launch_knn_deferred(const float* xyz, int B, int N, const int32_t* sa
 hipError_t launch_knn_grid(const float* xyz, int B, int N, const float* sample_xyz, int n, int k, float r2,
                            int32_t* out_pos, float* out_d2, int32_t* count, int32_t* list, void* grid_ws,
                            hipStream_t stream);
+int64_t knn_search_bytes(int B, int n);
+hipError_t launch_knn_search(const float* xyz, int B, int N, const int32_t* sample_idx, int n, int k, int32_t* out_pos,
+                             float* out_d2, int32_t* count, int32_t* list, void* workspace, hipStream_t stream);
 hipError_t launch_bq_grid(const float* xyz, int B, int N, const int32_t* center_idx, int M, float r2, int k,
                           int32_t* out_idx, int32_t* out_cnt, void* workspace, hipStream_t stream);
 hipError_t launch_bq_lists(const int64_t* offsets, const int32_t* entries, int B, int N, int level,

@@ -158,7 +158,11 @@ __device__ __forceinline__ void visit_sample(Nearest<K> (&nb)[2], const float (&
 constexpr int kTile = 256;          // samples staged in LDS per pass
 constexpr int kFullTests = 1024;    // samples at the head of the list whose distances are formed in full at once
 constexpr int kPointsPerWg = 512;   // two points per thread
-constexpr int kWaveListMax = 4096;  // deferred points per cloud up to which each gets a whole wave
+// Deferred points per cloud up to which each gets a whole wave.  The tiled kernel takes about 0.1 us per sample
+// however few points it has (a workgroup owns 512), the waves about 1 ns per thousand pairs: 6000 points of a
+// 200000-point cloud against 14000 samples 2.5 ms in tiles, 0.1 ms by waves.
+constexpr int kWaveListMax = 16384;
+constexpr int kWaveListBlocks = 1024;
 
 // Brute force over all n samples.  LIST = false: the workgroup takes points
 // [blockIdx.x*512, +512) of cloud blockIdx.y.  LIST = true: it takes that range of the cloud's
@@ -270,32 +274,34 @@ __global__ __launch_bounds__(256) void knn_list_wave_kernel(const float* __restr
     const int lane = (int)threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int total = count[b];
-    const int e = (int)blockIdx.x * 4 + wave;
-    if (total > kWaveListMax || e >= total) return;  // wave-uniform; the kernel has no barrier
+    if (total > kWaveListMax) return;
     const float* __restrict__ cloud = xyz + (int64_t)b * N * 3;
     const int32_t* __restrict__ sidx = sample_idx + (int64_t)b * n;
-    const int j = __builtin_amdgcn_readfirstlane(list[(int64_t)b * N + e]);
-    const float px = cloud[(int64_t)j * 3 + 0], py = cloud[(int64_t)j * 3 + 1], pz = cloud[(int64_t)j * 3 + 2];
-    Nearest<K> nb;
-    nb.clear();
-    for (int q = lane; q < n; q += 64) {
-        const int si = sidx[q];
-        float d = __builtin_nanf("");                // no such sample: never nearer
-        if (si >= 0 && si < N)
-            d = dist2(px, py, pz, cloud[(int64_t)si * 3 + 0], cloud[(int64_t)si * 3 + 1],
-                      cloud[(int64_t)si * 3 + 2]);
-        nb.insert(d, q);
-    }
-    const int64_t o = ((int64_t)b * N + j) * k;
-    for (int t = 0; t < k; ++t) {
-        // distances are >= +0 or +inf: the unsigned order of the bit patterns is their order
-        const uint32_t head = __float_as_uint(nb.d[0]);
-        const uint32_t dmin = wave_min_u32(head);
-        const uint32_t qmin = wave_min_u32(head == dmin ? (uint32_t)nb.q[0] : 0xFFFFFFFFu);
-        if (head == dmin && (uint32_t)nb.q[0] == qmin) nb.pop();
-        if (lane == 0) {
-            out_pos[o + t] = (int32_t)qmin;          // 0xFFFFFFFF = -1: fewer than k valid samples
-            out_d2[o + t] = __uint_as_float(dmin);
+    // (wave-uniform; the kernel has no barrier)
+    for (int e = (int)blockIdx.x * 4 + wave; e < total; e += (int)gridDim.x * 4) {
+        const int j = __builtin_amdgcn_readfirstlane(list[(int64_t)b * N + e]);
+        const float px = cloud[(int64_t)j * 3 + 0], py = cloud[(int64_t)j * 3 + 1], pz = cloud[(int64_t)j * 3 + 2];
+        Nearest<K> nb;
+        nb.clear();
+        for (int q = lane; q < n; q += 64) {
+            const int si = sidx[q];
+            float d = __builtin_nanf("");                // no such sample: never nearer
+            if (si >= 0 && si < N)
+                d = dist2(px, py, pz, cloud[(int64_t)si * 3 + 0], cloud[(int64_t)si * 3 + 1],
+                          cloud[(int64_t)si * 3 + 2]);
+            nb.insert(d, q);
+        }
+        const int64_t o = ((int64_t)b * N + j) * k;
+        for (int t = 0; t < k; ++t) {
+            // distances are >= +0 or +inf: the unsigned order of the bit patterns is their order
+            const uint32_t head = __float_as_uint(nb.d[0]);
+            const uint32_t dmin = wave_min_u32(head);
+            const uint32_t qmin = wave_min_u32(head == dmin ? (uint32_t)nb.q[0] : 0xFFFFFFFFu);
+            if (head == dmin && (uint32_t)nb.q[0] == qmin) nb.pop();
+            if (lane == 0) {
+                out_pos[o + t] = (int32_t)qmin;          // 0xFFFFFFFF = -1: fewer than k valid samples
+                out_d2[o + t] = __uint_as_float(dmin);
+            }
         }
     }
 }
@@ -445,7 +451,7 @@ hipError_t launch_knn_k(const float* xyz, int B, int N, const int32_t* sample_id
     hipLaunchKernelGGL((knn_cached_kernel<K>), grid_words, dim3(256), 0, stream, xyz, N, sample_idx, n, k,
                        out_pos, out_d2, (const int32_t*)flags, count, list, (const uint32_t*)blk_off,
                        (const BqEntry*)blk_rows, blk_rows_cap);
-    hipLaunchKernelGGL((knn_list_wave_kernel<K>), dim3(kWaveListMax / 4, (unsigned)B), dim3(256), 0, stream, xyz,
+    hipLaunchKernelGGL((knn_list_wave_kernel<K>), dim3(kWaveListBlocks, (unsigned)B), dim3(256), 0, stream, xyz,
                        N, sample_idx, n, k, out_pos, out_d2, (const int32_t*)list, (const int32_t*)count);
     hipLaunchKernelGGL((knn_brute_kernel<K, true>), grid_pts, dim3(256), 0, stream, xyz, N, sample_idx, n, k,
                        out_pos, out_d2, (const int32_t*)list, (const int32_t*)count, out_deferred);
@@ -463,7 +469,7 @@ hipError_t launch_knn_deferred_k(const float* xyz, int B, int N, const int32_t* 
                                  int32_t* out_deferred, hipStream_t stream)
 {
     const dim3 grid_pts((unsigned)((N + kPointsPerWg - 1) / kPointsPerWg), (unsigned)B);
-    hipLaunchKernelGGL((knn_list_wave_kernel<K>), dim3(kWaveListMax / 4, (unsigned)B), dim3(256), 0, stream, xyz,
+    hipLaunchKernelGGL((knn_list_wave_kernel<K>), dim3(kWaveListBlocks, (unsigned)B), dim3(256), 0, stream, xyz,
                        N, sample_idx, n, k, out_pos, out_d2, (const int32_t*)list, (const int32_t*)count);
     hipLaunchKernelGGL((knn_brute_kernel<K, true>), grid_pts, dim3(256), 0, stream, xyz, N, sample_idx, n, k,
                        out_pos, out_d2, (const int32_t*)list, (const int32_t*)count, out_deferred);
