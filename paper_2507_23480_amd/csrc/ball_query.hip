@@ -311,26 +311,97 @@ __global__ __launch_bounds__(256) void bq_group_scatter_kernel(const unsigned ch
                             (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
 }
 
-// Small clouds: the three steps by one workgroup per cloud in one launch (the counts are zeroed
-// here as well).  Counts and offsets go through device-scope atomics, so that what one thread
-// wrote before a barrier is what another reads after it.
+// Small clouds: the three steps by one workgroup per cloud in one launch, the counts in LDS (dynamic, one word per
+// key).  Bound: latency -- of the chunks' reads, of which a wave keeps four in flight, and of the atomics, which
+// as device-scope ones in memory took most of the time.  A wave takes whole chunks, so that the number of
+// entries in use is one scalar read per chunk.
 template <bool BY_BLOCK>
 __global__ __launch_bounds__(1024) void bq_group_small_kernel(const unsigned char* __restrict__ cache,
                                                               int32_t* __restrict__ cnt, uint32_t* __restrict__ off,
                                                               int keys, BqEntry* __restrict__ rows, int64_t rows_cap)
 {
+    extern __shared__ int32_t lds_cnt[];                // [keys] sizes, then where the next entry of a row goes
     __shared__ uint32_t wsum[16];
     const BqHeader* h = reinterpret_cast<const BqHeader*>(cache);
     const int b = (int)blockIdx.x;
     const bool ok = h->magic == kBqMagic && b < h->B;
-    for (int t = (int)threadIdx.x; t < keys; t += 1024)
-        __hip_atomic_store(cnt + (int64_t)b * keys + t, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int t = tid; t < keys; t += 1024) lds_cnt[t] = 0;
+    const int64_t places = ok ? bq_places(h, cache, b, rows_cap) : 0;
+    const int chunks = (int)(places / kBqChunk);
+    const uint32_t* __restrict__ fill =
+        ok ? reinterpret_cast<const uint32_t*>(cache + h->fill_offset) + (int64_t)b * (h->cap / kBqChunk) : nullptr;
+    const BqRaw* __restrict__ raw =
+        ok ? reinterpret_cast<const BqRaw*>(cache + h->raw_offset) + (int64_t)b * h->cap : nullptr;
+    constexpr int kAhead = 4;
+    auto for_entries = [&](auto f) {
+        for (int c0 = wave; c0 < chunks; c0 += 16 * kAhead) {
+            BqRaw r[kAhead];
+            bool used[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int c = c0 + 16 * u;
+                used[u] = c < chunks && (uint32_t)lane < fill[c < chunks ? c : c0];
+                r[u] = raw[(int64_t)(c < chunks ? c : c0) * kBqChunk + lane];
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const uint32_t key = BY_BLOCK ? r[u].blk : r[u].q;
+                if (used[u] && key < (uint32_t)keys) f(r[u], key);
+            }
+        }
+    };
     __syncthreads();
-    if (ok) group_count<BY_BLOCK>(h, cache, b, cnt, keys, rows_cap, threadIdx.x, 1024);
+    for_entries([&](const BqRaw&, uint32_t key) { atomicAdd(&lds_cnt[key], 1); });
     __syncthreads();
-    group_scan(b, cnt, off, keys, wsum);
-    __syncthreads();
-    if (ok) group_scatter<BY_BLOCK>(h, cache, b, cnt, off, keys, rows, rows_cap, threadIdx.x, 1024);
+    // exclusive scan, 4096 keys a turn, four consecutive ones per thread
+    uint32_t* __restrict__ o = off + (int64_t)b * ((int64_t)keys + 1);
+    int32_t* __restrict__ sizes = cnt + (int64_t)b * keys;
+    uint32_t carry = 0;
+    for (int base = 0; base < keys; base += 4096) {
+        const int k0 = base + tid * 4;
+        uint32_t v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = k0 + i < keys ? (uint32_t)lds_cnt[k0 + i] : 0u;
+        const uint32_t mine = v[0] + v[1] + v[2] + v[3];
+        uint32_t incl = mine;
+#pragma unroll
+        for (int sft = 1; sft < 64; sft <<= 1) {
+            const uint32_t up = (uint32_t)__shfl_up((int)incl, sft, 64);
+            if (lane >= sft) incl += up;
+        }
+        if (lane == 63) wsum[wave] = incl;
+        __syncthreads();
+        uint32_t before = 0, total = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            const uint32_t t = wsum[w];
+            before += w < wave ? t : 0u;
+            total += t;
+        }
+        uint32_t run = carry + before + incl - mine;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (k0 + i < keys) {
+                o[k0 + i] = run;
+                sizes[k0 + i] = (int32_t)v[i];
+                lds_cnt[k0 + i] = (int32_t)run;
+            }
+            run += v[i];
+        }
+        carry += total;
+        __syncthreads();                                // wsum is written again in the next turn
+    }
+    if (tid == 0) o[keys] = carry;
+    BqEntry* __restrict__ out = rows + (int64_t)b * rows_cap;
+    for_entries([&](const BqRaw& r, uint32_t key) {
+        BqEntry g;
+        g.other = BY_BLOCK ? r.q : r.blk;
+        g.lo = (uint32_t)r.mask;
+        g.hi = (uint32_t)(r.mask >> 32);
+        out[atomicAdd(&lds_cnt[key], 1)] = g;
+    });
 }
 
 __global__ void zero_ints_kernel(int32_t* p, int64_t n)
@@ -692,15 +763,15 @@ hipError_t launch_ball_query(const float* xyz, int B, int N, const int32_t* cent
 namespace {
 // up to this size the grouping is one launch with one workgroup per cloud
 constexpr int64_t kGroupSmallEntries = 160 * 1024;
-constexpr int kGroupSmallKeys = 16 * 1024;
+constexpr int kGroupSmallKeys = 15 * 1024;      // 60 KB of LDS
 
 template <bool BY_BLOCK>
 hipError_t group_entries(const unsigned char* cache, int B, int32_t* cnt, uint32_t* off, BqEntry* rows,
                          int64_t rows_cap, int keys, hipStream_t stream)
 {
     if (rows_cap <= kGroupSmallEntries && keys <= kGroupSmallKeys) {
-        hipLaunchKernelGGL((bq_group_small_kernel<BY_BLOCK>), dim3((unsigned)B), dim3(1024), 0, stream, cache, cnt,
-                           off, keys, rows, rows_cap);
+        hipLaunchKernelGGL((bq_group_small_kernel<BY_BLOCK>), dim3((unsigned)B), dim3(1024),
+                           (size_t)keys * sizeof(int32_t), stream, cache, cnt, off, keys, rows, rows_cap);
         return hipGetLastError();
     }
     int64_t gx = (rows_cap + 2047) / 2048;                // eight entries per thread when the list is full

@@ -2273,7 +2273,8 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
     }
     if (wh.tid < kCandWin + 2) sh.live[wh.tid] = 0;    // round tags start at 1 in every cloud
     if (wh.tid == 0) sh.progress = 0;
-    if (wh.tid < kCandWin) sh.bin_cnt[wh.tid] = 0;
+    if constexpr (PERM && MODE != 3)
+        if (wh.tid < kCandWin) sh.bin_cnt[wh.tid] = 0;
     if (wh.tid < 32) {
         int64_t ik = ((int64_t)a.m * (wh.tid + 1)) / 32;
         sh.mlp_pos[wh.tid] = a.mlp ? (int)(ik < 1 ? 1 : ik) : -1;
