@@ -3,7 +3,7 @@
 
 One "step" is one pass of the whole hot path over one batch of the workload, for
 every stage of its hierarchy:
-    exact path   fps_exact -> ball_query (brute force)          (Alg. 1 + Section 3.1)
+    exact path   fps_exact -> ball_query (without a record)     (Alg. 1 + Section 3.1)
     FastPoint    mdps_sample (records the radius tests) -> ball_query (cache reader)
                                                                 (Alg. 2 + Section 4.2)
     gather of the exact-FPS samples = input of the next stage (which waits for it)
@@ -60,13 +60,12 @@ GRAPH = "four streams, step replayed as one HIP graph"
 TRAFFIC_BYTES = {"C2": {"fps_exact": 427967, "mdps_sample+record": 2364746, "ball_query_cached": 1948914,
                         "ball_query_brute": 2004582},
                  # (C4, C5: the step's recorder is the cell-ordered one, its reader the one for cell-ordered records)
-                 "C4": {"fps_exact": 91435788, "mdps_sample+record": 235871565, "ball_query_cached": 59670967,
-                        "ball_query_brute": 90643229},
-                 "C5": {"fps_exact": 167284349, "mdps_sample+record": 230724683, "ball_query_cached": 29243835,
-                        "ball_query_brute": 204117378}}
+                 "C4": {"ball_query_cached": 59670967},
+                 "C5": {"ball_query_cached": 29243835}}
 
 
 PRUNED_RECORD_FROM = 1 << 14
+CELL_ORDER_FROM = 5121              # fps_exact works on a cell-ordered copy of the cloud from here on
 
 
 def record_sampler(fp, sg):
@@ -270,18 +269,29 @@ def quality_and_rooflines(torch, fp, ctx, kernel_ms):
         point_iters = float(B) * (n - 1) * N
         pairs = float(B) * n * N
         roof = {}
-        if "fps_exact" in ms:
+        # Cell-ordered samplers pass over most pairs, so the operations of the unpruned update say nothing about
+        # them: they are priced at the bytes that have to move (what bounds them is neither, but the trips
+        # between the workgroups of a cloud).  The same goes for a ball query through the grid.
+        cells = N >= CELL_ORDER_FROM
+        moved = lambda byts, t: {"bound": "hbm", "achieved": byts / (t * 1e-3) / 1e9, "peak": HBM_PEAK_GBS,  # noqa: E731
+                                 "unit": "GB/s", "frac": byts / (t * 1e-3) / 1e9 / HBM_PEAK_GBS, "bytes": byts}
+        if "fps_exact" in ms and cells:
+            roof["fps_exact"] = moved(12.0 * B * N + 4.0 * B * n, ms["fps_exact"])
+            roof["fps_exact"]["us_per_iteration"] = ms["fps_exact"] * 1e3 / max(n - 1, 1)
+        elif "fps_exact" in ms:
             a = point_iters * OPS_PER_POINT_ITERATION / (ms["fps_exact"] * 1e-3) / 1e12
             roof["fps_exact"] = {"bound": "alu", "achieved": a, "peak": ALU_PEAK_TOPS, "unit": "TFLOP/s",
                                  "frac": a / ALU_PEAK_TOPS, "us_per_iteration": ms["fps_exact"] * 1e3 / max(n - 1, 1)}
-        if "mdps_sample+record" in ms:
+        if "mdps_sample+record" in ms and sg["pruned_record"]:
+            entries = sum(fp.bq_cache_stats(sg["cache"])["entries"])
+            roof["mdps_sample+record"] = moved(12.0 * B * N + 4.0 * B * n + 12.0 * entries, ms["mdps_sample+record"])
+        elif "mdps_sample+record" in ms:
             a = point_iters * OPS_PER_POINT_ITERATION / (ms["mdps_sample+record"] * 1e-3) / 1e12
             roof["mdps_sample+record"] = {"bound": "alu", "achieved": a, "peak": ALU_PEAK_TOPS,
                                           "unit": "TFLOP/s", "frac": a / ALU_PEAK_TOPS}
-            if sg["pruned_record"]:
-                roof["mdps_sample+record"]["note"] = ("algorithmic operations of the unpruned update / time: "
-                                                      "the cell-ordered sampler skips most of them")
-        if "ball_query_brute" in ms:
+        if "ball_query_brute" in ms and N >= fp.GRID_QUERY_FROM:
+            roof["ball_query_brute"] = moved(12.0 * B * N + 4.0 * B * n + 4.0 * B * n * (k + 1), ms["ball_query_brute"])
+        elif "ball_query_brute" in ms:
             a = pairs * OPS_PER_PAIR_TEST / (ms["ball_query_brute"] * 1e-3) / 1e12
             roof["ball_query_brute"] = {"bound": "alu", "achieved": a, "peak": ALU_PEAK_TOPS,
                                         "unit": "TFLOP/s", "frac": a / ALU_PEAK_TOPS,
@@ -307,7 +317,8 @@ def quality_and_rooflines(torch, fp, ctx, kernel_ms):
             raise RuntimeError("grid k-NN differs from the brute-force result")
         ms["knn_grid"] = kg[0]
         a = float(B) * N * n * OPS_PER_PAIR_TEST / (knn["knn_brute_ms"] * 1e-3) / 1e12
-        roof["knn_brute"] = {"bound": "alu", "achieved": a, "peak": ALU_PEAK_TOPS, "unit": "TFLOP/s",
+        roof["knn_brute"] = moved(12.0 * B * N + 4.0 * B * n + 8.0 * B * N * KNN_K, knn["knn_brute_ms"]) \
+            if n >= fp.KNN_SEARCH_FROM[0] and N >= fp.KNN_SEARCH_FROM[1] else {"bound": "alu", "achieved": a, "peak": ALU_PEAK_TOPS, "unit": "TFLOP/s",
                              "frac": a / ALU_PEAK_TOPS}
         # the redundancy-free search reads the recorded entries (regrouped by point block) and the
         # points, and writes the result
@@ -833,7 +844,7 @@ def run(args, torch, fp, inputs, calibration, extra, clock_reader=None):
         "data": "synthetic",
         "config": {"workload": "%s: %s" % (name, wl.description), "B": wl.B, "N": wl.N,
                    "stages": [{"n": st.n, "radius": st.radius, "k": st.k} for st in wl.stages],
-                   "step": "per stage: fps_exact + ball_query(brute) [+ gather]; "
+                   "step": "per stage: fps_exact + ball_query(no record) [+ gather]; "
                            "%s(+record) + ball_query(from record)"
                            % ("mdps_sample_pruned[scan order 1]" if ctx["stages"][0]["pruned_record"] else "mdps_sample"),
                    "launch": launch_mode, "mdps": {"p": calibration.P_RATIO, "nseg": calibration.NSEG}},
