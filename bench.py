@@ -60,8 +60,10 @@ GRAPH = "four streams, step replayed as one HIP graph"
 TRAFFIC_BYTES = {"C2": {"fps_exact": 427967, "mdps_sample+record": 2364746, "ball_query_cached": 1948914,
                         "ball_query_brute": 2004582},
                  # (C4, C5: the step's recorder is the cell-ordered one, its reader the one for cell-ordered records)
-                 "C4": {"ball_query_cached": 59670967},
-                 "C5": {"ball_query_cached": 29243835}}
+                 "C4": {"fps_exact": 202751712, "mdps_sample+record": 284120000, "ball_query_cached": 59760896,
+                        "ball_query_brute": 81926986},
+                 "C5": {"fps_exact": 199127232, "mdps_sample+record": 249951690, "ball_query_cached": 29248181,
+                        "ball_query_brute": 149293152}}
 
 
 PRUNED_RECORD_FROM = 1 << 14
