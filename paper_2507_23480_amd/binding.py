@@ -236,17 +236,18 @@ def _try_bytes(need: int, device: torch.device) -> Optional[torch.Tensor]:
         return None
 
 
+def _exchange_bytes() -> int:
+    """The workspace the index-ordered samplers need, the same for every shape."""
+    return int(load().fp_workspace_bytes(1, 1))
+
 
 def workspace(device: torch.device, B: int, N: int) -> torch.Tensor:
-    """A cached per-device workspace tensor (calls on one device must not overlap)."""
-    need = int(load().fp_workspace_bytes(B, N))
+    """The device's shared workspace for the index-ordered samplers (calls that use it must not overlap).  Its size
+    fits every shape, so it is never replaced: a captured graph or work on another stream may still use it."""
     key = (device.type, device.index)
     ws = _workspaces.get(key)
-    if ws is None or ws.numel() < need:
-        ws = _try_bytes(need, device)
-        if ws is None:                          # (what the index-ordered kernels need at any size)
-            ws = torch.empty(int(load().fp_workspace_bytes(1, 1)), dtype=torch.uint8, device=device)
-        _workspaces[key] = ws
+    if ws is None:
+        ws = _workspaces.setdefault(key, torch.empty(_exchange_bytes(), dtype=torch.uint8, device=device))
     return ws
 
 
@@ -256,7 +257,8 @@ def new_workspace(device: torch.device, B: int, N: int) -> torch.Tensor:
     need = int(load().fp_workspace_bytes(B, N))
     if need == 0:
         raise ValueError("shape (B=%d, N=%d) not supported" % (B, N))
-    return torch.empty(need, dtype=torch.uint8, device=device)
+    ws = _try_bytes(need, device)
+    return torch.empty(_exchange_bytes(), dtype=torch.uint8, device=device) if ws is None else ws
 
 
 def new_bq_cache(xyz: torch.Tensor, n: int, entries_per_cloud: int = 0) -> torch.Tensor:
@@ -304,14 +306,18 @@ def fps_exact(xyz: torch.Tensor, n: int, start_idx=None, want_mdc: bool = False,
               bq_radius: float = 0.0, ws: Optional[torch.Tensor] = None):
     """Exact farthest point sampling.  Returns idx [B][n] int32 (and mdc [B][n] float32,
     info bytes [B][INFO_BYTES] uint8 when asked for).  `ws`: a workspace from new_workspace
-    (default: the device's shared one)."""
+    (default: one of this call's own where the cell-ordered kernels can use it, else the device's shared one)."""
     B, N = _xyz(xyz)
     st = _start(start_idx, B, xyz.device)
     idx = torch.empty((B, n), dtype=torch.int32, device=xyz.device)
     mdc = torch.empty((B, n), dtype=torch.float32, device=xyz.device) if want_mdc else None
     info = torch.zeros((B, INFO_BYTES), dtype=torch.uint8, device=xyz.device) if want_info else None
     if ws is None:
-        ws = workspace(xyz.device, B, N)
+        need = 0 if bq_cache is not None else int(load().fp_workspace_bytes(B, N))
+        if need > _exchange_bytes():
+            ws = _try_bytes(need, xyz.device)
+        if ws is None:
+            ws = workspace(xyz.device, B, N)
     _check(load().fp_fps_exact(xyz.data_ptr(), B, N, n, _ptr(st), idx.data_ptr(), _ptr(mdc), _ptr(info),
                                _ptr(bq_cache), 0 if bq_cache is None else bq_cache.numel(), float(bq_radius),
                                ws.data_ptr(), ws.numel(), _stream()),
