@@ -299,7 +299,17 @@ struct Shared {
     uint64_t rel[kCandWin][9];
     uint64_t took[kCandWin / 64];
     uint16_t place[kCandWin];  // ... and of each accepted one its place among the round's picks
-    // exact rounds settled in sweeps (settle_exact)
+    uint32_t progress;
+#ifdef FASTPOINT_PHASE_CLOCKS
+    long long chain_cycles;   // shader clocks the control wave spent in the exact-FPS chain loop
+    long long chain_picks;
+    long long scan_clk[8];    // wall-clock ticks of thread 0 in the parts of scan_candidates (threshold scans)
+#endif
+    uint32_t st_idx[kStage];   // picks waiting to be written out (ring, by sample position)
+    float st_mdc[kStage];
+    // exact rounds settled in sweeps (settle_exact).  Behind everything the index-ordered kernels use: with these
+    // arrays further up their code is a few instructions longer (offsets that no longer fit an instruction) and,
+    // shifted against the cache lines, slower: 4096 points, fps_exact 1.5 %, mdps_sample 3-4 %.
     uint32_t open_d[kCandWin];                  // a candidate's distance while it is open (0: out)
     alignas(16) uint32_t pick_d[kCandWin];      // distance at which a candidate was accepted
     alignas(16) uint64_t sets[2][16];           // after a sweep: accepted, open, lowered, left to settle_row
@@ -310,14 +320,6 @@ struct Shared {
     alignas(16) uint32_t bin_cnt[kCandWin], bin_first[kCandWin + 4];
     uint32_t seq_d[kCandWin];
     uint16_t seq_id[kCandWin];
-    uint32_t progress;
-#ifdef FASTPOINT_PHASE_CLOCKS
-    long long chain_cycles;   // shader clocks the control wave spent in the exact-FPS chain loop
-    long long chain_picks;
-    long long scan_clk[8];    // wall-clock ticks of thread 0 in the parts of scan_candidates (threshold scans)
-#endif
-    uint32_t st_idx[kStage];   // picks waiting to be written out (ring, by sample position)
-    float st_mdc[kStage];
 };
 
 // Everything one thread needs to know about where it sits.
