@@ -29,14 +29,13 @@ constexpr int64_t kLlPkWords = (int64_t)2 * kMaxGroup * kLlSlotWords;           
 constexpr int64_t kLlCdWords = (int64_t)2 * kMaxGroup * kCandMax * kCandWords;
 constexpr int64_t kLlCtWords = (int64_t)2 * kMaxGroup;
 constexpr int64_t kLlWords = kLlPkWords + kLlCdWords + kLlCtWords;
-constexpr size_t kScratchBytes = (size_t)(kLlWords * 8);                          // 2 658 304 bytes
-constexpr size_t kExchangeBytes = kScratchBytes;
+constexpr size_t kExchangeBytes = (size_t)(kLlWords * 8);                         // 2 658 304 bytes
 
 // Scratch of fp_fps_exact_static: the same exchange words, but in device memory that belongs to
 // the library's code object instead of a caller's workspace, so that the call allocates nothing.
 // Every GPU the library runs on holds its own copy at its own address until the process ends.
 // In host code this name is only a handle for hipGetSymbolAddress, never an address.
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kExchangeBytes];
 
 constexpr int kMaxDevices = 64;
 DeviceInfo g_dev[kMaxDevices];
@@ -76,14 +75,23 @@ constexpr int kTargetPointsPerWg = 1024;
 // points, 512 samples: fps_exact 139 us in one workgroup, 213 in two; mdps_sample 145 / 210, with record
 // 229 / 264.  3000 points in one workgroup (eight per thread): 256 / 267, with record 514 / 357.
 constexpr int kOneWgPoints = 2048;
-// From here on exact FPS and MDPS with the scattered scan order run on the cell-ordered kernels whichever entry
-// point asks for them, below it on the index-ordered ones (without a record: a record's block
-// order belongs to the entry point), MDPS with the lowest-index order from the second line on.  A quarter of
-// the points sampled, one cloud of uniform points / a room, us, index-ordered / cell-ordered (sort included):
-// exact FPS 4096: 339 / 358 and 341 / 350, 6000: 467 / 414, 8192: 513 / 420, 24000: 1381 / 764;
-// MDPS 6000: 471 / 503, 8192: 522 / 492 and 622 / 617, 12000: 833 / 797.
+// Layout.  A cell-ordered run sorts the cloud first and gains on every pick after the first some hundred, so the number
+// of samples decides, much the same for clouds of 3000 and of a million points.  Time of a cell-ordered run over
+// that of an index-ordered one (sort included; uniform points to rooms, single clouds and batches of 4 to 100):
+//   samples                      256         1024        1500        2048        3000
+//   exact FPS                    1.15-1.94   0.99-1.28   0.89-1.11   0.78-0.91   0.65-0.88
+//   MDPS, scattered scan order   1.16-1.61   0.93-1.32   0.82-1.16   0.72-0.97   0.67-0.95
+//   MDPS, lowest index first     1.39-1.9    1.08-1.4    0.94-1.2    0.85-1.0    0.77-1.0
+// (MDPS, lowest index first, on rooms of 60000 points and more: 1.1-2.1 up to 3000 samples; 65536 of a million
+// clustered points 0.3.)  Where a batch leaves a cloud one or two workgroups, which then work out the relations of all
+// candidates among themselves, the line of exact FPS lies twice as high (256 x 6000 points, index-ordered / cell-ordered,
+// us: 1500 samples 771 / 971, 3000: 1474 / 1398).  A cloud with 95 % of its points in a clump is 1.0-1.4 at 1500 samples, 0.8-1.2 at 3000.
+// fp_fps_exact takes the cell order from kCellOrderFrom points on, when its workspace has room for it; the _pruned
+// entry points leave it below kCellOrderSamples, and for clouds that one workgroup holds.  A call with a record keeps
+// its entry point's layout: it is the order of the record's blocks.
 constexpr int kCellOrderFrom = 5121;
-constexpr int kCellOrderFromMdps = 8192;
+constexpr int kCellOrderSamples = 1500;
+constexpr int kCellOrderSamplesLowest = 2000;
 
 bool shape_for(int64_t points_per_wg, Shape* s)
 {
@@ -224,12 +232,13 @@ fp_status run_sampler(const float* xyz, int32_t B, int32_t N, int32_t n, const i
         (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0)
         return FP_ERR_WORKSPACE;
 
-    // The layout that is faster at this size (the results are the same); exact FPS asked for in index order
-    // needs the larger workspace for it.  (The hook that forces a number of workgroups keeps the entry
-    // point's own layout, so that every kernel can be reached with clouds of any size.)
+    // The layout that is faster at this size (the results are the same).  The hook that forces a number of
+    // workgroups keeps the entry point's own layout, so that every kernel can be reached with clouds of any size.
     if (!bq_cache && g_force_wg_per_cloud.load() == 0) {
-        if (pruned && N < (prm && !walk ? kCellOrderFromMdps : kCellOrderFrom)) pruned = false;
-        else if (!pruned && !prm && N >= kCellOrderFrom && fp_fps_pruned_workspace_bytes(B, N) != 0 &&
+        const int from = prm && !walk ? kCellOrderSamplesLowest : kCellOrderSamples;
+        const bool many = n >= (prm || plan.G > 2 ? from : 2 * from);
+        if (pruned && (!many || N <= kOneWgPoints)) pruned = false;
+        else if (!pruned && !prm && many && N >= kCellOrderFrom && fp_fps_pruned_workspace_bytes(B, N) != 0 &&
                  workspace_bytes >= fp_fps_pruned_workspace_bytes(B, N))
             pruned = true;
     }
@@ -407,7 +416,7 @@ fp_status fp_fps_exact_static(const float* xyz, int32_t B, int32_t N, int32_t n,
     void* ws = static_scratch();
     if (!ws) return FP_ERR_DEVICE;
     return run_sampler(xyz, B, N, n, start_idx, nullptr, out_idx, out_mdc, nullptr, nullptr, 0, 0.0f, ws,
-                       kScratchBytes, stream);
+                       kExchangeBytes, stream);
 }
 
 size_t fp_mdps_scattered_workspace_bytes(int32_t B, int32_t N)

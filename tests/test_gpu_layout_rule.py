@@ -1,0 +1,81 @@
+"""The number of samples decides whether a sampler sorts the cloud into cells first: either side of the lines the same
+samples, and the layout the rule names (told by the number of rounds, which the layouts do not share)."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from paper_2507_23480_amd import inputs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fp():
+    from paper_2507_23480_amd import binding
+    binding.load()
+    binding.set_wg_per_cloud(0)
+    yield binding
+    binding.set_wg_per_cloud(0)
+
+
+def in_cells(fp, x, call):
+    """call() with the entry point's own layout and the number of workgroups the library would choose."""
+    g, t, p = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
+    assert fp.load().fp_plan(x.shape[0], x.shape[1], ctypes.byref(g), ctypes.byref(t), ctypes.byref(p)) == 0
+    fp.set_wg_per_cloud(g.value)
+    try:
+        return call()
+    finally:
+        fp.set_wg_per_cloud(0)
+
+
+def rounds(fp, info):
+    return [i.rounds for i in fp.parse_info(info)]
+
+
+@pytest.mark.parametrize("B,N,n", [(2, 6000, 40), (2, 6000, 1499), (2, 6000, 1500), (1, 5120, 1500), (1, 5121, 1500),
+                                   (2, 40001, 1499), (2, 40001, 1500), (140, 5121, 2999), (140, 5121, 3000)])
+def test_exact(fp, B, N, n):
+    x = torch.from_numpy(np.stack([inputs.make_cloud("C3", 40 + b % 3, N) for b in range(B)])).cuda()
+    few = 256 // B <= 2                                     # workgroups per cloud
+    small = torch.empty(int(fp.load().fp_workspace_bytes(1, 1)), dtype=torch.uint8, device="cuda")
+    want, ordered = fp.fps_exact(x, n, ws=small, want_info=True)
+    cells, sorted_ = in_cells(fp, x, lambda: fp.fps_exact_pruned(x, n, want_info=True))
+    assert torch.equal(cells, want) and rounds(fp, sorted_) != rounds(fp, ordered)
+    many = n >= (3000 if few else 1500)
+    for f, cell_order in ((fp.fps_exact, many and N >= 5121), (fp.fps_exact_pruned, many)):
+        got, info = f(x, n, want_info=True)
+        assert torch.equal(got, want)
+        assert rounds(fp, info) == rounds(fp, sorted_ if cell_order else ordered)
+
+
+@pytest.mark.parametrize("order,n", [(0, 1999), (0, 2000), (1, 1499), (1, 1500)])
+@pytest.mark.parametrize("N", [2049, 2100, 20011])
+def test_mdps(fp, order, n, N):
+    x = torch.from_numpy(np.stack([inputs.make_cloud("C3", 60 + b, N) for b in range(2)])).cuda()
+    prm = fp.MdpsParams(exponent=0.8, bias=1.05, scan_order=order)
+    want, ordered = fp.mdps_sample(x, n, prm, want_info=True)
+    cells, sorted_ = in_cells(fp, x, lambda: fp.mdps_sample_pruned(x, n, prm, want_info=True))
+    got, info = fp.mdps_sample_pruned(x, n, prm, want_info=True)
+    assert torch.equal(cells, want) and torch.equal(got, want)
+    if rounds(fp, sorted_) != rounds(fp, ordered):
+        assert rounds(fp, info) == rounds(fp, sorted_ if n % 100 == 0 else ordered)
+
+
+@pytest.mark.parametrize("N,n", [(12000, 5100), (12000, 5110), (12000, 5120), (12000, 5130), (12000, 300)])
+@pytest.mark.parametrize("order", [0, 1])
+def test_prefix_either_side_of_the_sweeps(fp, N, n, order):
+    """A prefix of a tenth of the samples: 511 to 513 picks, and a short one, with and without a record."""
+    x = torch.from_numpy(np.stack([inputs.make_cloud("C3", 70 + b, N) for b in range(2)])).cuda()
+    prm = fp.MdpsParams(exponent=0.8, bias=1.05, scan_order=order)
+    want = fp.mdps_sample(x, n, prm)
+    cache = fp.new_bq_cache(x, n)
+    assert torch.equal(in_cells(fp, x, lambda: fp.mdps_sample_pruned(x, n, prm)), want)
+    assert torch.equal(fp.mdps_sample_pruned(x, n, prm, bq_cache=cache, bq_radius=0.1), want)
+    scan = (torch.empty((2, n, 16), dtype=torch.int32, device="cuda"), torch.empty((2, n), dtype=torch.int32, device="cuda"))
+    assert fp.load().fp_ball_query(x.data_ptr(), 2, N, want.data_ptr(), n, 0.1, 16, scan[0].data_ptr(),
+                                   scan[1].data_ptr(), None, torch.cuda.current_stream().cuda_stream) == 0
+    got = fp.ball_query(x, want, 0.1, 16, bq_cache=cache)
+    assert torch.equal(got[0], scan[0]) and torch.equal(got[1], scan[1])
