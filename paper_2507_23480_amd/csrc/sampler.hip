@@ -308,8 +308,8 @@ struct Shared {
     uint32_t st_idx[kStage];   // picks waiting to be written out (ring, by sample position)
     float st_mdc[kStage];
     // exact rounds settled in sweeps (settle_exact).  Behind everything the index-ordered kernels use: with these
-    // arrays further up their code is a few instructions longer (offsets that no longer fit an instruction) and,
-    // shifted against the cache lines, slower: 4096 points, fps_exact 1.5 %, mdps_sample 3-4 %.
+    // arrays further up their code is a few instructions longer (offsets that no longer fit an instruction) and
+    // mdps_sample of 1024 points 1-2 % slower.
     uint32_t open_d[kCandWin];                  // a candidate's distance while it is open (0: out)
     alignas(16) uint32_t pick_d[kCandWin];      // distance at which a candidate was accepted
     alignas(16) uint64_t sets[2][16];           // after a sweep: accepted, open, lowered, left to settle_row
@@ -2127,12 +2127,17 @@ __device__ __forceinline__ bool fps_rounds_of(Points<P, BQ>& pt, Shared<T>& sh, 
     return true;
 }
 
+// Picks from which on sweeps settle a cell-ordered exact phase of MDPS.  (Kernels with eight points per thread have
+// no second loop: it costs the long phases more in spilled registers than it saves the short ones.)  Prefixes of 51 to
+// 150 picks, sweeps / chain, us: 5120 points with record, 320 samples 323 / 270; 8192, 512 samples 395 / 355.
+constexpr int kSweepPicks = 512;
+
 // Rounds of 64, 128 or 256 candidates.  With four or more points per thread folding a pick takes the
 // point waves longer than finding it takes the control wave, so the longer chain step of a round
 // with two candidates per lane is hidden and the halved number of scans is a gain.  With two
 // points per thread the chain is what a pick costs, and the wide round pays only where a scan is
 // expensive: when the cloud is spread over many workgroups (measured: 24 yes, 4 and 1 no).
-// ONE_WG: the kernel is only ever launched with one workgroup per cloud.
+// (MODE 1 is only ever launched with one workgroup per cloud.)
 template <int T, int P, bool BQ, bool PERM, int MODE>
 __device__ __forceinline__ bool fps_rounds(Points<P, BQ>& pt, Shared<T>& sh, const Where& wh,
                                            const SamplerArgs& a, uint32_t& it, uint32_t& seq,
@@ -2142,17 +2147,18 @@ __device__ __forceinline__ bool fps_rounds(Points<P, BQ>& pt, Shared<T>& sh, con
     // fold takes 260 ns: the million-point cloud then needs 436 scans instead of 814, but a chain step
     // grows to 355 ns and becomes what a pick costs -- 23.2 ms either way; and a chain loop written
     // for any number of candidates per lane was a tenth slower with two than the one written for two.)
-    constexpr bool ONE_WG = MODE == 1;
     if constexpr (PERM && MODE != 3) {
-        // (a recording call for a small cloud: with all pairs of candidates worked out by one workgroup
-        // a round costs more than its chain)
-        if constexpr (BQ && P <= 4)
-            if (wh.G == 1) return fps_rounds_of<T, P, BQ, PERM, 1>(pt, sh, wh, a, it, seq, st, upto, capture);
+        // A few hundred picks (a short prefix) go through the chain: at the start of a run a sweep accepts little of
+        // a round whose relations all workgroups have to exchange.  So does a recording call on a small cloud: with
+        // all pairs of candidates worked out by one workgroup a round costs more than its chain.
+        if constexpr (MODE != 0 && (P <= 4 || (P == 16 && !BQ)))
+            if (upto - st.i < kSweepPicks || (BQ && wh.G == 1))
+                return fps_rounds_of<T, P, BQ, PERM, (P == 2 ? 1 : 2)>(pt, sh, wh, a, it, seq, st, upto, capture);
         return fps_rounds_of<T, P, BQ, PERM, 4, true>(pt, sh, wh, a, it, seq, st, upto, capture);
     } else if constexpr (P >= 4) {
         return fps_rounds_of<T, P, BQ, PERM, 2>(pt, sh, wh, a, it, seq, st, upto, capture);
     } else {
-        if constexpr (!PERM && !ONE_WG) // (the cell-ordered variant gained nothing there and pays for the code)
+        if constexpr (!PERM && MODE != 1) // (the cell-ordered variant gained nothing there and pays for the code)
             if (wh.G >= 8) return fps_rounds_of<T, P, BQ, PERM, 2>(pt, sh, wh, a, it, seq, st, upto, capture);
         return fps_rounds_of<T, P, BQ, PERM, 1>(pt, sh, wh, a, it, seq, st, upto, capture);
     }
