@@ -582,7 +582,8 @@ fp_status fp_knn_search(const float* xyz, int32_t B, int32_t N, const int32_t* s
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     if (launch_knn_search(xyz, B, N, sample_idx, n, k, out_pos, out_d2, count, list, base + l.bytes, st) != hipSuccess)
         return FP_ERR_DEVICE;
-    hipError_t err = launch_knn_deferred(xyz, B, N, sample_idx, n, k, out_pos, out_d2, count, list, out_deferred, st);
+    hipError_t err = launch_knn_deferred(xyz, B, N, sample_idx, knn_search_samples(base + l.bytes, B, n), n, k, out_pos, out_d2,
+                                         count, list, out_deferred, st);
     return err == hipSuccess ? FP_OK : FP_ERR_DEVICE;
 }
 
@@ -667,7 +668,7 @@ fp_status fp_knn_grid(const float* xyz, int32_t B, int32_t N, const int32_t* sam
     if (launch_knn_grid(xyz, B, N, sample_xyz, n, k, radius * radius, out_pos, out_d2, count, list, grid_ws, st) !=
         hipSuccess)
         return FP_ERR_DEVICE;
-    hipError_t err = launch_knn_deferred(xyz, B, N, sample_idx, n, k, out_pos, out_d2, count, list, out_deferred, st);
+    hipError_t err = launch_knn_deferred(xyz, B, N, sample_idx, sample_xyz, n, k, out_pos, out_d2, count, list, out_deferred, st);
     return err == hipSuccess ? FP_OK : FP_ERR_DEVICE;
 }
 

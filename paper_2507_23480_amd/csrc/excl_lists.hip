@@ -1510,13 +1510,17 @@ static SearchLayout search_layout(int B, int n)
     return lay;
 }
 int64_t knn_search_bytes(int B, int n) { return search_layout(B, n).bytes; }
+float* knn_search_samples(void* workspace, int B, int n)
+{
+    return reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(workspace) + search_layout(B, n).sample_off);
+}
 
 hipError_t launch_knn_search(const float* xyz, int B, int N, const int32_t* sample_idx, int n, int k, int32_t* out_pos,
                              float* out_d2, int32_t* count, int32_t* list, void* workspace, hipStream_t stream)
 {
     const SearchLayout lay = search_layout(B, n);
     unsigned char* base = reinterpret_cast<unsigned char*>(workspace);
-    float* samples = reinterpret_cast<float*>(base + lay.sample_off);
+    float* samples = knn_search_samples(workspace, B, n);
     ExclGrid* gp = reinterpret_cast<ExclGrid*>(base + lay.grid_off);
     int32_t* occ = reinterpret_cast<int32_t*>(base + lay.occ_off);
     int32_t* cnt = reinterpret_cast<int32_t*>(base + lay.cnt_off);

@@ -158,10 +158,18 @@ __device__ __forceinline__ void visit_sample(Nearest<K> (&nb)[2], const float (&
 constexpr int kTile = 256;          // samples staged in LDS per pass
 constexpr int kFullTests = 1024;    // samples at the head of the list whose distances are formed in full at once
 constexpr int kPointsPerWg = 512;   // two points per thread
-// Deferred points per cloud up to which each gets a whole wave.  The tiled kernel takes about 0.1 us per sample
-// however few points it has (a workgroup owns 512), the waves about 1 ns per thousand pairs: 6000 points of a
-// 200000-point cloud against 14000 samples 2.5 ms in tiles, 0.1 ms by waves.
-constexpr int kWaveListMax = 16384;
+// Deferred points per cloud up to which each gets a whole wave.  The tiled kernel (a workgroup owns 512 points) takes
+// 0.10 us (k = 1) to 0.14 us (k = 3) per sample however few points a batch has.  The waves take 2.5 to 3.3 ns per thousand
+// pairs of all clouds together where the samples are read scattered over the cloud (8 x 13700 points against 6000
+// samples: 580 us in tiles, 2200 by waves; 1 x 8100 against 1500: 190 and 40) and 0.7 to 1.5 ns from gathered
+// coordinates (8 x 16384 against 4096: 550 to 920 us, 340 to 890; against 1024, where merging the lanes' lists weighs
+// more, 190 to 350 and 190 to 370).  So the waves take some 32768, 65536 or 131072 points of a batch, a cloud's
+// share being 4096 to 16384.
+inline int wave_list_max(int B, int n, bool gathered)
+{
+    const int share = (!gathered ? 32768 : (n < 4096 ? 65536 : 131072)) / B;
+    return share < 4096 ? 4096 : (share > 16384 ? 16384 : share);
+}
 constexpr int kWaveListBlocks = 1024;
 
 // Brute force over all n samples.  LIST = false: the workgroup takes points
@@ -173,7 +181,7 @@ __global__ __launch_bounds__(256) void knn_brute_kernel(const float* __restrict_
                                                         int32_t* __restrict__ out_pos,
                                                         float* __restrict__ out_d2,
                                                         const int32_t* __restrict__ list,
-                                                        const int32_t* __restrict__ count,
+                                                        const int32_t* __restrict__ count, int wave_max,
                                                         int32_t* __restrict__ out_deferred)
 {
     __shared__ float4 smp[kTile];
@@ -185,7 +193,7 @@ __global__ __launch_bounds__(256) void knn_brute_kernel(const float* __restrict_
     if (LIST) {
         total = count[b];
         if (blockIdx.x == 0 && tid == 0 && out_deferred) out_deferred[b] = total;
-        if (total <= kWaveListMax) return;           // short lists are searched a wave per point
+        if (total <= wave_max) return;               // short lists are searched a wave per point
     }
     const int e0 = (int)blockIdx.x * kPointsPerWg;
     if (e0 >= total) return;                         // same for the whole workgroup
@@ -262,19 +270,22 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v)
 // k times the smallest head (lower position among equal distances).  A point searched by one
 // thread would walk all n samples alone, which takes far longer than the cached search it
 // follows.
+// samples: their coordinates in order of position, NaN for a sample that does not exist; without them (NULL)
+// they are looked up through sample_idx.
 template <int K>
 __global__ __launch_bounds__(256) void knn_list_wave_kernel(const float* __restrict__ xyz, int N,
-                                                            const int32_t* __restrict__ sample_idx, int n, int k,
+                                                            const int32_t* __restrict__ sample_idx,
+                                                            const float* __restrict__ samples, int n, int k,
                                                             int32_t* __restrict__ out_pos,
                                                             float* __restrict__ out_d2,
                                                             const int32_t* __restrict__ list,
-                                                            const int32_t* __restrict__ count)
+                                                            const int32_t* __restrict__ count, int wave_max)
 {
     const int b = (int)blockIdx.y;
     const int lane = (int)threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int total = count[b];
-    if (total > kWaveListMax) return;
+    if (total > wave_max) return;
     const float* __restrict__ cloud = xyz + (int64_t)b * N * 3;
     const int32_t* __restrict__ sidx = sample_idx + (int64_t)b * n;
     // (wave-uniform; the kernel has no barrier)
@@ -284,11 +295,16 @@ __global__ __launch_bounds__(256) void knn_list_wave_kernel(const float* __restr
         Nearest<K> nb;
         nb.clear();
         for (int q = lane; q < n; q += 64) {
-            const int si = sidx[q];
             float d = __builtin_nanf("");                // no such sample: never nearer
-            if (si >= 0 && si < N)
-                d = dist2(px, py, pz, cloud[(int64_t)si * 3 + 0], cloud[(int64_t)si * 3 + 1],
-                          cloud[(int64_t)si * 3 + 2]);
+            if (samples) {
+                const float* s = samples + ((int64_t)b * n + q) * 3;
+                d = dist2(px, py, pz, s[0], s[1], s[2]);
+            } else {
+                const int si = sidx[q];
+                if (si >= 0 && si < N)
+                    d = dist2(px, py, pz, cloud[(int64_t)si * 3 + 0], cloud[(int64_t)si * 3 + 1],
+                              cloud[(int64_t)si * 3 + 2]);
+            }
             nb.insert(d, q);
         }
         const int64_t o = ((int64_t)b * N + j) * k;
@@ -435,7 +451,7 @@ hipError_t launch_knn_k(const float* xyz, int B, int N, const int32_t* sample_id
     const dim3 grid_pts((unsigned)((N + kPointsPerWg - 1) / kPointsPerWg), (unsigned)B);
     if (!bq_cache) {
         hipLaunchKernelGGL((knn_brute_kernel<K, false>), grid_pts, dim3(256), 0, stream, xyz, N, sample_idx, n,
-                           k, out_pos, out_d2, (const int32_t*)nullptr, (const int32_t*)nullptr,
+                           k, out_pos, out_d2, (const int32_t*)nullptr, (const int32_t*)nullptr, 0,
                            (int32_t*)nullptr);
         return hipGetLastError();
     }
@@ -452,9 +468,10 @@ hipError_t launch_knn_k(const float* xyz, int B, int N, const int32_t* sample_id
                        out_pos, out_d2, (const int32_t*)flags, count, list, (const uint32_t*)blk_off,
                        (const BqEntry*)blk_rows, blk_rows_cap);
     hipLaunchKernelGGL((knn_list_wave_kernel<K>), dim3(kWaveListBlocks, (unsigned)B), dim3(256), 0, stream, xyz,
-                       N, sample_idx, n, k, out_pos, out_d2, (const int32_t*)list, (const int32_t*)count);
+                       N, sample_idx, (const float*)nullptr, n, k, out_pos, out_d2, (const int32_t*)list, (const int32_t*)count,
+                       wave_list_max(B, n, false));
     hipLaunchKernelGGL((knn_brute_kernel<K, true>), grid_pts, dim3(256), 0, stream, xyz, N, sample_idx, n, k,
-                       out_pos, out_d2, (const int32_t*)list, (const int32_t*)count, out_deferred);
+                       out_pos, out_d2, (const int32_t*)list, (const int32_t*)count, wave_list_max(B, n, false), out_deferred);
     return hipGetLastError();
 }
 
@@ -464,30 +481,31 @@ hipError_t launch_knn_k(const float* xyz, int B, int N, const int32_t* sample_id
 // pass that could not settle them): a wave per point while the list is short, the tiled kernel for
 // the rest.
 template <int K>
-hipError_t launch_knn_deferred_k(const float* xyz, int B, int N, const int32_t* sample_idx, int n, int k,
+hipError_t launch_knn_deferred_k(const float* xyz, int B, int N, const int32_t* sample_idx, const float* samples, int n, int k,
                                  int32_t* out_pos, float* out_d2, int32_t* count, int32_t* list,
                                  int32_t* out_deferred, hipStream_t stream)
 {
     const dim3 grid_pts((unsigned)((N + kPointsPerWg - 1) / kPointsPerWg), (unsigned)B);
     hipLaunchKernelGGL((knn_list_wave_kernel<K>), dim3(kWaveListBlocks, (unsigned)B), dim3(256), 0, stream, xyz,
-                       N, sample_idx, n, k, out_pos, out_d2, (const int32_t*)list, (const int32_t*)count);
+                       N, sample_idx, samples, n, k, out_pos, out_d2, (const int32_t*)list, (const int32_t*)count,
+                       wave_list_max(B, n, true));
     hipLaunchKernelGGL((knn_brute_kernel<K, true>), grid_pts, dim3(256), 0, stream, xyz, N, sample_idx, n, k,
-                       out_pos, out_d2, (const int32_t*)list, (const int32_t*)count, out_deferred);
+                       out_pos, out_d2, (const int32_t*)list, (const int32_t*)count, wave_list_max(B, n, true), out_deferred);
     return hipGetLastError();
 }
 
-hipError_t launch_knn_deferred(const float* xyz, int B, int N, const int32_t* sample_idx, int n, int k,
+hipError_t launch_knn_deferred(const float* xyz, int B, int N, const int32_t* sample_idx, const float* samples, int n, int k,
                                int32_t* out_pos, float* out_d2, int32_t* count, int32_t* list,
                                int32_t* out_deferred, hipStream_t stream)
 {
     if (k == 1)
-        return launch_knn_deferred_k<1>(xyz, B, N, sample_idx, n, k, out_pos, out_d2, count, list, out_deferred,
+        return launch_knn_deferred_k<1>(xyz, B, N, sample_idx, samples, n, k, out_pos, out_d2, count, list, out_deferred,
                                         stream);
     if (k <= 3)
-        return launch_knn_deferred_k<3>(xyz, B, N, sample_idx, n, k, out_pos, out_d2, count, list, out_deferred,
+        return launch_knn_deferred_k<3>(xyz, B, N, sample_idx, samples, n, k, out_pos, out_d2, count, list, out_deferred,
                                         stream);
     if (k <= 8)
-        return launch_knn_deferred_k<8>(xyz, B, N, sample_idx, n, k, out_pos, out_d2, count, list, out_deferred,
+        return launch_knn_deferred_k<8>(xyz, B, N, sample_idx, samples, n, k, out_pos, out_d2, count, list, out_deferred,
                                         stream);
     return hipErrorInvalidValue;
 }
