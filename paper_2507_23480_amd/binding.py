@@ -482,11 +482,15 @@ def ball_query_grid(xyz: torch.Tensor, center_idx: torch.Tensor, radius: float, 
 
 
 # From this many samples and points on the k nearest samples are searched through a grid over the samples
-# (fp_knn_search, the same result): below it the thirteen launches cost more than comparing all pairs.  All pairs /
-# grid, us, k = 3, samples of exact FPS: 16 clouds of 1024 points and 512 samples 74 / 93; 4096 and 1024: 133 / 105;
-# 8 x 24000 and 6000: 608 / 127; 4 x 120000 and 16384: 1388 / 327; a million and 65536: 11276 / 462.
-# Samples taken at random, whose cells are filled unevenly: 325 / 263 (4 x 20000), 1458 / 1198 (4 x 120000).
+# (fp_knn_search, the same result), for more than three neighbours from KNN_SEARCH_FROM_MANY samples on: below it the
+# thirteen launches cost more than comparing all pairs.  All pairs / grid, us, samples of exact FPS, k = 3: 16 clouds of
+# 1024 points and 512 samples 74 / 93; 4096 and 1024: 130 / 105; 8 x 24000 and 6000: 600 / 119; 4 x 120000 and
+# 16384: 1400 / 285; a million and 65536: 11276 / 470.  k = 8, 8 x 24000 and 1100: 160 / 184, 2000: 254 / 170.
+# Other samples gain less or lose.  4 x 120000 points of a scanner, k = 3, samples taken at random: 16384: 1440 / 730,
+# 4096: 405 / 415, 1024: 135 / 200; samples of one corner only, 4096: 680 / 1050; 95 % of the samples in a clump
+# (8 x 24000): 1100: 151 / 200, 6000: 905 / 980.
 KNN_SEARCH_FROM = (1024, 4096)
+KNN_SEARCH_FROM_MANY = 2048
 
 
 def knn(xyz: torch.Tensor, sample_idx: torch.Tensor, k: int, bq_cache: Optional[torch.Tensor] = None,
@@ -502,7 +506,7 @@ def knn(xyz: torch.Tensor, sample_idx: torch.Tensor, k: int, bq_cache: Optional[
     pos = torch.empty((B, N, k), dtype=torch.int32, device=xyz.device)
     d2 = torch.empty((B, N, k), dtype=torch.float32, device=xyz.device)
     ws, ws_bytes, deferred = None, 0, None
-    if bq_cache is None and n >= KNN_SEARCH_FROM[0] and N >= KNN_SEARCH_FROM[1]:
+    if bq_cache is None and n >= (KNN_SEARCH_FROM[0] if k <= 3 else KNN_SEARCH_FROM_MANY) and N >= KNN_SEARCH_FROM[1]:
         need = int(load().fp_knn_search_workspace_bytes(B, N, n))
         ws = _try_bytes(need, xyz.device) if need > 0 else None
         if ws is not None:

@@ -1086,6 +1086,10 @@ constexpr int kFinePerSample = 16;
 constexpr float kSamplesPerCell = 1.5f;
 constexpr int kMaxRing = 4;            // cells away from a point's own up to which one thread searches
 
+// A thread looks at no more samples than this: a point beside a clump would walk all of it while its wave waits.  A cloud
+// whose samples have a quarter of that many others in their own cell on average is not searched through the grid.
+__device__ __forceinline__ int most_visited(int n) { return n / 8 > 256 ? n / 8 : 256; }
+
 __device__ __forceinline__ void level_of(const ExclGrid& g, int level, int (&dim)[3], float& inv_h)
 {
     inv_h = g.inv_h;
@@ -1098,14 +1102,17 @@ __device__ __forceinline__ void level_of(const ExclGrid& g, int level, int (&dim
     }
 }
 
-// counts: [level][cloud][maxcells]; occupied: [cloud][level]
+// counts: [level][cloud][maxcells]; occupied, pairs (samples that share a cell, ordered pairs with themselves):
+// [cloud][level]
 __global__ __launch_bounds__(256) void level_count_kernel(const float* __restrict__ xyz, int N,
                                                           const ExclGrid* __restrict__ gp, int32_t* cell_cnt,
-                                                          int32_t* occupied, int maxcells, int64_t level_stride)
+                                                          int32_t* occupied, unsigned long long* pairs, int maxcells,
+                                                          int64_t level_stride)
 {
     const int b = (int)blockIdx.y;
     const int i = (int)(blockIdx.x * 256 + threadIdx.x);
     const bool valid = i < N;
+    const int lane = (int)threadIdx.x & 63;
     const ExclGrid g = gp[b];
     const float* p = xyz + ((int64_t)b * N + (valid ? i : 0)) * 3;
     for (int level = 0; level < kFineLevels; ++level) {
@@ -1116,13 +1123,35 @@ __global__ __launch_bounds__(256) void level_count_kernel(const float* __restric
         const int cy = cell_coord(p[1], g.origin[1], inv_h, dim[1]);
         const int cz = cell_coord(p[2], g.origin[2], inv_h, dim[2]);
         const int c = (cz * dim[1] + cy) * dim[0] + cx;
-        const int before = valid ? atomicAdd(cell_cnt + level * level_stride + (int64_t)b * maxcells + c, 1) : 1;
+        // Lanes that share a cell with one of four leaders leave the adding to it: bunched samples put most of a wave
+        // into one cell, whose counter takes its atomics one after the other (0.4 us each: 973 of 1024 samples in
+        // one cell took the three levels 1.1 ms).
+        int add = valid ? 1 : 0;
+        uint64_t open = __builtin_amdgcn_ballot_w64(valid);
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            if (open == 0) break;
+            const int leader = __builtin_ctzll(open);
+            const int c0 = (int)rdlane((uint32_t)c, leader);
+            const uint64_t same = __builtin_amdgcn_ballot_w64(c == c0) & open;
+            if (c == c0 && ((open >> lane) & 1ull) != 0) add = lane == leader ? (int)__builtin_popcountll(same) : 0;
+            open &= ~same;
+        }
+        const int before = add > 0 ? atomicAdd(cell_cnt + level * level_stride + (int64_t)b * maxcells + c, add) : 1;
         const uint64_t first = __builtin_amdgcn_ballot_w64(before == 0);
-        if ((threadIdx.x & 63) == 0 && first != 0) atomicAdd(&occupied[b * kFineLevels + level], __builtin_popcountll(first));
+        float sq = add > 0 ? (float)add * (2.0f * (float)before + (float)add) : 0.0f;     // grows to the squared count
+#pragma unroll
+        for (int sft = 32; sft > 0; sft >>= 1) sq += __shfl_xor(sq, sft, 64);
+        if (lane == 0 && sq > 0.0f) {
+            if (first != 0) atomicAdd(&occupied[b * kFineLevels + level], __builtin_popcountll(first));
+            atomicAdd(&pairs[b * kFineLevels + level], (unsigned long long)sq);
+        }
     }
 }
 
-__global__ void level_pick_kernel(ExclGrid* gp, int B, const int32_t* __restrict__ occupied, int N, int64_t level_stride)
+// (lmax: 1 if the samples are bunched, and every point of the cloud is left to the all-pairs kernels)
+__global__ void level_pick_kernel(ExclGrid* gp, int B, const int32_t* __restrict__ occupied,
+                                  const unsigned long long* __restrict__ pairs, int N, int64_t level_stride)
 {
     const int b = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (b >= B) return;
@@ -1136,6 +1165,7 @@ __global__ void level_pick_kernel(ExclGrid* gp, int B, const int32_t* __restrict
     for (int a = 0; a < 3; ++a) g.dim[a] = dim[a];
     g.ncells = dim[0] * dim[1] * dim[2];
     g.cnt_shift = level * level_stride;
+    g.lmax = (float)pairs[b * kFineLevels + level] > (float)N * (float)(most_visited(N) / 4) ? 1 : 0;
     gp[b] = g;
 }
 
@@ -1144,8 +1174,8 @@ __global__ void level_pick_kernel(ExclGrid* gp, int B, const int32_t* __restrict
 // distance to the nearest face of its cell away, so the search ends when the k-th nearest found is closer
 // than that; a row of ring 1 that lies farther than the k-th found so far is passed over.  The cell coordinate is
 // rounded (at most 1024 cells per axis: by less than a thousandth of a cell), which kCellRounding allows for.
-// A point that is not done after kMaxRing rings, or whose cells hold more than an eighth of the samples, goes
-// to the list the brute-force kernels take.
+// A point that is not done after the last ring, that lies farther from the samples' box than the rings reach, or whose
+// cells hold more than an eighth of the samples (256 at least) goes to the list the brute-force kernels take.
 // Bound: latency of the cell bounds and the records (L2); the bounds of ring 1 are requested together.
 constexpr float kCellRounding = 0.002f;
 
@@ -1161,6 +1191,11 @@ __global__ __launch_bounds__(256) void knn_search_kernel(const float* __restrict
     const int j = (int)(blockIdx.x * 256 + threadIdx.x);
     if (j >= N) return;
     const ExclGrid g = gp[b];
+    if (g.lmax != 0) {                  // (uniform over the cloud)
+        list[(int64_t)b * N + j] = j;
+        if (j == 0) count[b] = N;
+        return;
+    }
     const float* p = xyz + ((int64_t)b * N + j) * 3;
     const float px = p[0], py = p[1], pz = p[2];
     const int cx = cell_coord(px, g.origin[0], g.inv_h, g.dim[0]);
@@ -1209,6 +1244,15 @@ __global__ __launch_bounds__(256) void knn_search_kernel(const float* __restrict
     const float fx = inside(px, g.origin[0], cx), fy = inside(py, g.origin[1], cy), fz = inside(pz, g.origin[2], cz);
     auto gap = [&](float f) { return f > kCellRounding ? (f - kCellRounding) * h * 0.999f : 0.0f; };
     const float near_face = fminf(fminf(fminf(fx, 1.0f - fx), fminf(fy, 1.0f - fy)), fminf(fz, 1.0f - fz));
+    const int most = most_visited(n);
+    // distance to the samples' box, per axis, in cell widths: out of reach of the rings?
+    auto outside = [&](float x, float lo, int dim) {
+        const float f = (x - lo) * g.inv_h;
+        return f < 0.0f ? -f : (f > (float)dim ? f - (float)dim : 0.0f);            // (NaN: 0)
+    };
+    const float ox = outside(px, g.origin[0], g.dim[0]), oy = outside(py, g.origin[1], g.dim[1]),
+                oz = outside(pz, g.origin[2], g.dim[2]);
+    const bool far = ox * ox + oy * oy + oz * oz > (float)(kMaxRing * kMaxRing);
     bool done = false;
     int begin[9], end[9], total = 0;
     const int x0 = cx > 0 ? cx - 1 : 0;
@@ -1224,13 +1268,13 @@ __global__ __launch_bounds__(256) void knn_search_kernel(const float* __restrict
     }
     const int own = (cz * g.dim[1] + cy) * g.dim[0] + cx;
     const int own_begin = st[own], own_end = st[own + 1];
-    const bool crowded = total > 256 && total > n / 8;
-    if (!crowded || (own_end - own_begin <= n / 8)) {
+    const bool crowded = total > most;
+    if (!far && own_end - own_begin <= most) {
         visit(own_begin, own_end);
         const float m = gap(near_face);
         done = kth < m * m;
     }
-    if (!done && !crowded) {
+    if (!done && !far && !crowded) {
         const float ly = gap(fy), ry = gap(1.0f - fy), lz = gap(fz), rz = gap(1.0f - fz);
         visit(begin[4], own_begin);
         visit(own_end, end[4]);
@@ -1243,7 +1287,11 @@ __global__ __launch_bounds__(256) void knn_search_kernel(const float* __restrict
         }
         const float m = h * 0.998f + gap(near_face);
         done = kth < m * m;
-        for (int ring = 2; ring <= kMaxRing && !done; ++ring) {
+        auto within = [&](int from, int to) {
+            total += to - from;
+            if (total <= most) visit(from, to);
+        };
+        for (int ring = 2; ring <= kMaxRing && !done && total <= most; ++ring) {
             for (int z = cz - ring; z <= cz + ring; ++z) {
                 if (z < 0 || z >= g.dim[2]) continue;
                 for (int y = cy - ring; y <= cy + ring; ++y) {
@@ -1251,15 +1299,15 @@ __global__ __launch_bounds__(256) void knn_search_kernel(const float* __restrict
                     const int c0 = (z * g.dim[1] + y) * g.dim[0];
                     const int xl = cx - ring, xr = cx + ring;
                     if (z == cz - ring || z == cz + ring || y == cy - ring || y == cy + ring) {
-                        visit(st[c0 + (xl > 0 ? xl : 0)], st[c0 + (xr < g.dim[0] - 1 ? xr : g.dim[0] - 1) + 1]);
+                        within(st[c0 + (xl > 0 ? xl : 0)], st[c0 + (xr < g.dim[0] - 1 ? xr : g.dim[0] - 1) + 1]);
                     } else {
-                        if (xl >= 0) visit(st[c0 + xl], st[c0 + xl + 1]);
-                        if (xr < g.dim[0]) visit(st[c0 + xr], st[c0 + xr + 1]);
+                        if (xl >= 0) within(st[c0 + xl], st[c0 + xl + 1]);
+                        if (xr < g.dim[0]) within(st[c0 + xr], st[c0 + xr + 1]);
                     }
                 }
             }
             const float mr = h * 0.998f * (float)ring + gap(near_face);
-            done = kth < mr * mr;
+            done = total <= most && kth < mr * mr;
         }
     }
     if (done) {
@@ -1479,7 +1527,7 @@ hipError_t launch_knn_grid(const float* xyz, int B, int N, const float* sample_x
 // Where the parts of a search workspace lie: the samples' coordinates, the grid over them.
 struct SearchLayout {
     int maxcells;
-    int64_t sample_off, grid_off, occ_off, cnt_off, start_off, sorted_off, tiles_off, bytes, level_stride;
+    int64_t sample_off, grid_off, occ_off, pairs_off, cnt_off, start_off, sorted_off, tiles_off, bytes, level_stride;
 };
 static SearchLayout search_layout(int B, int n)
 {
@@ -1494,9 +1542,11 @@ static SearchLayout search_layout(int B, int n)
     at += up((int64_t)B * n * 12);
     lay.grid_off = at;
     at += up((int64_t)B * (int64_t)sizeof(ExclGrid));
-    // occupied cells and cell counts are one range, zeroed together
+    // occupied cells, pairs and cell counts are one range, zeroed together
     lay.occ_off = at;
     at += up((int64_t)B * kFineLevels * 4);
+    lay.pairs_off = at;
+    at += up((int64_t)B * kFineLevels * 8);
     lay.cnt_off = at;
     lay.level_stride = (int64_t)B * mc;
     at += up(kFineLevels * lay.level_stride * 4);
@@ -1523,6 +1573,7 @@ hipError_t launch_knn_search(const float* xyz, int B, int N, const int32_t* samp
     float* samples = knn_search_samples(workspace, B, n);
     ExclGrid* gp = reinterpret_cast<ExclGrid*>(base + lay.grid_off);
     int32_t* occ = reinterpret_cast<int32_t*>(base + lay.occ_off);
+    unsigned long long* pairs = reinterpret_cast<unsigned long long*>(base + lay.pairs_off);
     int32_t* cnt = reinterpret_cast<int32_t*>(base + lay.cnt_off);
     int32_t* st = reinterpret_cast<int32_t*>(base + lay.start_off);
     float4* sorted = reinterpret_cast<float4*>(base + lay.sorted_off);
@@ -1539,10 +1590,10 @@ hipError_t launch_knn_search(const float* xyz, int B, int N, const int32_t* samp
     hipLaunchKernelGGL(grid_setup_kernel, dim3((B + 63) / 64), dim3(64), 0, stream, gp, B,
                        static_cast<const float*>(nullptr), 1, lay.maxcells, 0.0f);
     const dim3 sgrid((unsigned)((n + 255) / 256), (unsigned)B);
-    hipLaunchKernelGGL(level_count_kernel, sgrid, dim3(256), 0, stream, samples, n, gp, cnt, occ, lay.maxcells,
-                       lay.level_stride);
-    hipLaunchKernelGGL(level_pick_kernel, dim3((B + 63) / 64), dim3(64), 0, stream, gp, B, (const int32_t*)occ, n,
-                       lay.level_stride);
+    hipLaunchKernelGGL(level_count_kernel, sgrid, dim3(256), 0, stream, samples, n, gp, cnt, occ, pairs,
+                       lay.maxcells, lay.level_stride);
+    hipLaunchKernelGGL(level_pick_kernel, dim3((B + 63) / 64), dim3(64), 0, stream, gp, B, (const int32_t*)occ,
+                       (const unsigned long long*)pairs, n, lay.level_stride);
     launch_cell_scan(gp, cnt, st, reinterpret_cast<int32_t*>(base + lay.tiles_off), B, lay.maxcells, stream);
     hipLaunchKernelGGL(grid_scatter_kernel, sgrid, dim3(256), 0, stream, samples, n, gp, cnt, sorted, lay.maxcells);
     const dim3 pgrid((unsigned)((N + 255) / 256), (unsigned)B);

@@ -98,7 +98,7 @@ def test_lists_of_both_lengths(fp):
         s = torch.arange(0, 1200, dtype=torch.int32, device="cuda")[None].contiguous()
         xd = torch.from_numpy(x).cuda()
         got = search(fp, xd, s, 4)
-        assert got[2][0] > N // 4
+        assert N // 4 < got[2][0] <= 16384 if N == 9000 else got[2][0] > 16384
         assert same(got, all_pairs(fp, xd, s, 4))
 
 
