@@ -425,12 +425,24 @@ def mdps_sample(xyz: torch.Tensor, n: int, prm: MdpsParams, start_idx=None, want
 
 
 # Clouds of at least this many points are queried through the uniform grid (fp_ball_query_grid, the same result)
-# when there is no record to read: below it the six launches that build the grid cost more than the scan of all
-# points.  Brute force / grid, us, the workloads' radii: 4096 points 46 / 37, but 58 / 94 on a batch of 32 objects;
-# 6000: 56 / 34 and, eight clouds, 59 / 46; 16384: 127 / 38; 24000 x 8: 339 / 89; 120000 x 4: 1889 / 352;
-# a million: 10707 / 282.  (Balls of a tenth of a scanner-ordered cloud and more, which few queries have,
-# take up to 1.5 times the scan's time: 24000 x 8 at 16 times the radius 476 / 720.)
+# when there is no record to read: below it the launches that build the grid cost more than the scan of all points.  A
+# batch of more than GRID_QUERY_BATCH clouds and a call for fewer than GRID_QUERY_CENTRES centres fill the chip, or end,
+# early enough in the scan that the line lies higher for them.  Scan / grid, us, k = 16, a quarter of the points as centres,
+# balls of some ten points: 4096 points 46 / 42, but 58 / 99 on a batch of 32 objects; 5121 uniform points 53 / 40 and, eight
+# clouds, 53 / 54, of a scanner 52 / 66 and 52 / 84; 64 x 5121: 103 / 107 and 133 / 150; 16 x 12000: 130 / 82 and 162 / 178;
+# 24000 x 8: 240 / 96; 120000 x 4: 3372 / 1413 (1 m balls of a scanner); a million: 10707 / 290.  One centre: 5121: 22 / 32;
+# 12000: 44 / 31; a million: 6070 / 160.  Where cells do not help (balls of a good part of the cloud, one point far from all
+# others) the grid query looks at the points in index order; what is left of its launches then costs a call that
+# the scan answers in 12 us up to 25 us, and small balls beside a far point take 1.2 to 2 times the scan's time.
 GRID_QUERY_FROM = 5121
+GRID_QUERY_BATCH, GRID_QUERY_FROM_BATCH = 8, 10000
+GRID_QUERY_CENTRES, GRID_QUERY_FROM_CENTRES = 64, 12000
+
+
+def grid_query(B: int, N: int, M: int) -> bool:
+    """Whether ball_query without a record goes through the grid."""
+    return N >= max(GRID_QUERY_FROM, GRID_QUERY_FROM_BATCH if B > GRID_QUERY_BATCH else 0,
+                    GRID_QUERY_FROM_CENTRES if M < GRID_QUERY_CENTRES else 0)
 
 
 def ball_query(xyz: torch.Tensor, center_idx: torch.Tensor, radius: float, k: int,
@@ -442,7 +454,7 @@ def ball_query(xyz: torch.Tensor, center_idx: torch.Tensor, radius: float, k: in
             and center_idx.shape[0] == B and center_idx.is_contiguous()):
         raise ValueError("center_idx must be a contiguous CUDA int32 tensor [B][M]")
     M = int(center_idx.shape[1])
-    if bq_cache is None and N >= GRID_QUERY_FROM and M > 0:
+    if bq_cache is None and M > 0 and grid_query(B, N, M):
         need = int(load().fp_ball_query_grid_workspace_bytes(B, N))
         # a workspace of its own: queries on several streams or threads may overlap
         ws = _try_bytes(need, xyz.device) if need > 0 else None

@@ -100,11 +100,10 @@ __global__ void grid_init_kernel(ExclGrid* gp, int B, int32_t* cell_cnt, int64_t
     for (; t < ncnt; t += stride) cell_cnt[t] = 0;
 }
 
-__global__ __launch_bounds__(256) void grid_bounds_kernel(const float* __restrict__ xyz, int N, ExclGrid* gp)
+// Bounds of the points a workgroup of 256 threads takes (of gridDim.x that share a cloud), in threads 0..2: axis tid.
+__device__ __forceinline__ void block_bounds(const float* __restrict__ cloud, int N, uint32_t& out_lo, uint32_t& out_hi)
 {
     __shared__ uint32_t slo[4][3], shi[4][3];
-    const int b = (int)blockIdx.y;
-    const float* __restrict__ cloud = xyz + (int64_t)b * N * 3;
     uint32_t lo[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, hi[3] = {0u, 0u, 0u};
     for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < N; i += (int)gridDim.x * 256) {
 #pragma unroll
@@ -129,29 +128,27 @@ __global__ __launch_bounds__(256) void grid_bounds_kernel(const float* __restric
         }
     }
     __syncthreads();
-    if (threadIdx.x < 3) {              // one atomic pair per axis and workgroup
+    if (threadIdx.x < 3) {
         const int a = (int)threadIdx.x;
-        atomicMin(&gp[b].lo[a], min(min(slo[0][a], slo[1][a]), min(slo[2][a], slo[3][a])));
-        atomicMax(&gp[b].hi[a], max(max(shi[0][a], shi[1][a]), max(shi[2][a], shi[3][a])));
+        out_lo = min(min(slo[0][a], slo[1][a]), min(slo[2][a], slo[3][a]));
+        out_hi = max(max(shi[0][a], shi[1][a]), max(shi[2][a], shi[3][a]));
     }
 }
 
-// One thread per cloud: the largest radius, the cell width and the grid dimensions.
-__global__ void grid_setup_kernel(ExclGrid* gp, int B, const float* __restrict__ thr2, int L, int maxcells,
-                                  float r2_all)
+__global__ __launch_bounds__(256) void grid_bounds_kernel(const float* __restrict__ xyz, int N, ExclGrid* gp)
 {
-    const int b = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (b >= B) return;
-    ExclGrid g = gp[b];
-    float rmax2 = 0.0f;
-    int lmax = 0;
-    for (int l = 0; l < L; ++l) {
-        const float t = thr2 ? thr2[(int64_t)b * L + l] : r2_all;      // no table: one radius for all clouds
-        if (t > rmax2) {            // NaN and values <= 0 never win
-            rmax2 = t;
-            lmax = l;
-        }
+    const int b = (int)blockIdx.y;
+    uint32_t lo = 0, hi = 0;
+    block_bounds(xyz + (int64_t)b * N * 3, N, lo, hi);
+    if (threadIdx.x < 3) {              // one atomic pair per axis and workgroup
+        atomicMin(&gp[b].lo[threadIdx.x], lo);
+        atomicMax(&gp[b].hi[threadIdx.x], hi);
     }
+}
+
+// Cell width and grid dimensions for a largest squared radius rmax2 (of level lmax).
+__device__ __forceinline__ void grid_for_radius(ExclGrid& g, float rmax2, int lmax, int maxcells)
+{
     float ext[3];
     for (int a = 0; a < 3; ++a) {
         g.origin[a] = ord2f(g.lo[a]);
@@ -186,7 +183,27 @@ __global__ void grid_setup_kernel(ExclGrid* gp, int B, const float* __restrict__
     g.rmax2 = rmax2;
     g.lmax = lmax;
     g.curve_bits = 0;
+    g.skip = 0;
     g.cnt_shift = 0;
+}
+
+// One thread per cloud: the largest radius and the grid for it.
+__global__ void grid_setup_kernel(ExclGrid* gp, int B, const float* __restrict__ thr2, int L, int maxcells,
+                                  float r2_all)
+{
+    const int b = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (b >= B) return;
+    ExclGrid g = gp[b];
+    float rmax2 = 0.0f;
+    int lmax = 0;
+    for (int l = 0; l < L; ++l) {
+        const float t = thr2 ? thr2[(int64_t)b * L + l] : r2_all;      // no table: one radius for all clouds
+        if (t > rmax2) {            // NaN and values <= 0 never win
+            rmax2 = t;
+            lmax = l;
+        }
+    }
+    grid_for_radius(g, rmax2, lmax, maxcells);
     gp[b] = g;
 }
 
@@ -256,6 +273,7 @@ __global__ void sort_setup_kernel(ExclGrid* gp, int B, int bits)
     g.rmax2 = 0.0f;
     g.lmax = 0;
     g.curve_bits = bits;
+    g.skip = 0;
     g.cnt_shift = 0;
     gp[b] = g;
 }
@@ -295,6 +313,7 @@ __global__ __launch_bounds__(256) void grid_count_kernel(const float* __restrict
     const int i = (int)(blockIdx.x * 256 + threadIdx.x);
     const bool valid = i < N;
     const ExclGrid g = gp[b];
+    if (g.skip != 0) return;                             // uniform over the workgroup
     const float* p = xyz + ((int64_t)b * N + (valid ? i : 0)) * 3;
     int cx, cy, cz;
     const int c = cell_of(g, p[0], p[1], p[2], cx, cy, cz);
@@ -347,6 +366,7 @@ __global__ __launch_bounds__(1024) void grid_tile_sum_kernel(const ExclGrid* __r
     __shared__ int32_t wsum[16];
     const int b = (int)blockIdx.y, t = (int)blockIdx.x;
     const int ncells = gp[b].ncells;
+    if (gp[b].skip != 0) return;                         // uniform over the workgroup
     const int32_t* cnt = cell_cnt + (int64_t)b * maxcells + gp[b].cnt_shift;
     const bool wide = (reinterpret_cast<uintptr_t>(cnt) & 15u) == 0;
     int v[kCellPer];
@@ -366,7 +386,7 @@ __global__ __launch_bounds__(1024) void grid_scan_kernel(const ExclGrid* __restr
     const int b = (int)blockIdx.y, t = (int)blockIdx.x;
     const int ncells = gp[b].ncells;
     const int base = t * kCellTile;
-    if (base >= ncells) return;                          // uniform over the workgroup
+    if (base >= ncells || gp[b].skip != 0) return;       // uniform over the workgroup
     int32_t* cnt = cell_cnt + (int64_t)b * maxcells + gp[b].cnt_shift;
     int32_t* st = cell_start + (int64_t)b * (maxcells + 1);
     const bool cnt_wide = (reinterpret_cast<uintptr_t>(cnt) & 15u) == 0;
@@ -444,6 +464,7 @@ __global__ __launch_bounds__(256) void grid_scatter_kernel(const float* __restri
     const int i = (int)(blockIdx.x * 256 + threadIdx.x);
     const bool valid = i < N;
     const ExclGrid g = gp[b];
+    if (g.skip != 0) return;                             // uniform over the workgroup
     const float* p = xyz + ((int64_t)b * N + (valid ? i : 0)) * 3;
     const float x = p[0], y = p[1], z = p[2];
     int cx, cy, cz;
@@ -901,7 +922,227 @@ __global__ __launch_bounds__(kHeavyWaves * 64) void excl_fill_heavy_kernel(
 // points are at most half of C the wave looks at that many in index order first and is mostly done; if not,
 // it has the lowest hits and walks the cells for the others.  (A radius that covers half of a cloud of 24000
 // points would have every wave walk most of the cloud.)
+//
+// A grid does not pay everywhere: balls that hold a good part of a cloud have their first k hits at the head of the index
+// order, and a cloud with one far point or with balls as wide as itself puts most points into a few cells, whose
+// counters take their atomics one after the other (0.2 us each).  bq_setup_kernel therefore tests kProbePoints points
+// against kProbeCentres of the centres, works out from the hits and from the points in the centre's cells what either
+// way would take, and marks a cloud (skip) that is answered faster by looking at all points in index order, a wave
+// for kScanCentres centres.  (The constants are those of the kernels, us: per point of a wave's way, per pair, per atomic.)
+// Cells always / with the choice / scan of fp_ball_query, us, k = 16: a million uniform points, 1024 centres, balls of a
+// quarter of the cloud 9105 / 39 / 48; 4 x 120000 points and one far one, 30000 centres, 0.4 % balls 18135 / 382 / 3319,
+// balls of three points 18128 / 3048 / 2320; 4 x 120000 of a scanner, 4 m balls 5248 / 2774 / 3958, 1 m balls
+// 1420 / 1413 / 3372; rooms (8 x 24000, 6000 centres) 90 / 96 / 240.
 constexpr int kGridBatch = 256;        // hits collected between two selections of the k lowest
+constexpr int kProbeCentres = 32;
+constexpr int kProbePoints = 512;
+constexpr int kScanCentres = 8;
+constexpr int kMaxBoundBlocks = 256;
+
+// First step: the cell counters are zeroed, and every workgroup leaves the bounds of its points in part (six words).
+__global__ __launch_bounds__(256) void bq_bounds_kernel(const float* __restrict__ xyz, int N, int32_t* __restrict__ cell_cnt,
+                                                        uint32_t* __restrict__ part, int maxcells)
+{
+    const int b = (int)blockIdx.y;
+    for (int t = (int)(blockIdx.x * 256 + threadIdx.x); t < maxcells; t += (int)gridDim.x * 256)
+        cell_cnt[(int64_t)b * maxcells + t] = 0;
+    uint32_t lo = 0, hi = 0;
+    block_bounds(xyz + (int64_t)b * N * 3, N, lo, hi);
+    if (threadIdx.x < 3) {
+        uint32_t* out = part + (int64_t)b * (maxcells + 1) + blockIdx.x * 6;
+        out[threadIdx.x] = lo;
+        out[3 + threadIdx.x] = hi;
+    }
+}
+
+// Second step, a workgroup per cloud: its grid, and whether to use it.
+__global__ __launch_bounds__(kProbePoints) void bq_setup_kernel(ExclGrid* gp, int B, const float* __restrict__ xyz, int N,
+                                                                const int32_t* __restrict__ center_idx, int M, float r2,
+                                                                int k, const uint32_t* __restrict__ part, int parts,
+                                                                int maxcells)
+{
+    __shared__ ExclGrid sg;
+    __shared__ float ctr[kProbeCentres][3];
+    __shared__ int cell[kProbeCentres][3];
+    __shared__ int hits[kProbeCentres], near[kProbeCentres], own[kProbeCentres];
+    __shared__ int same;                                // of kProbePoints points, those whose neighbour has their cell
+    static_assert(kMaxBoundBlocks <= kProbePoints, "a thread per part");
+    const int b = (int)blockIdx.x, tid = (int)threadIdx.x, lane = tid & 63;
+    const float* __restrict__ cloud = xyz + (int64_t)b * N * 3;
+    const int probes = M < kProbeCentres ? M : kProbeCentres;
+    // a thread's points: one of kProbePoints spread over the cloud, one of eight runs of 64 that follow each other
+    const float* p = cloud + ((int64_t)tid * N / kProbePoints) * 3;
+    const float x = p[0], y = p[1], z = p[2];
+    int64_t run = (int64_t)(tid >> 6) * N / (kProbePoints / 64) + lane;
+    run = run < N ? run : N - 1;
+    const float rx = cloud[run * 3 + 0], ry = cloud[run * 3 + 1], rz = cloud[run * 3 + 2];
+    uint32_t lo[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, hi[3] = {0u, 0u, 0u};
+    if (tid < parts) {
+        const uint32_t* q = part + (int64_t)b * (maxcells + 1) + tid * 6;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = q[a];
+            hi[a] = q[3 + a];
+        }
+    }
+    if (tid < 3) {
+        sg.lo[tid] = 0xFFFFFFFFu;
+        sg.hi[tid] = 0u;
+    }
+    if (tid == 0) same = 0;
+    if (tid < kProbeCentres) {
+        const int c = tid < probes ? center_idx[(int64_t)b * M + (int64_t)tid * M / probes] : -1;
+        const bool ok = c >= 0 && c < N;
+        for (int a = 0; a < 3; ++a) ctr[tid][a] = ok ? cloud[(int64_t)c * 3 + a] : __builtin_nanf("");
+        hits[tid] = near[tid] = own[tid] = 0;
+    }
+    __syncthreads();
+    if ((tid & ~63) < parts) {                          // (uniform over the wave)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            for (int s = 32; s > 0; s >>= 1) {
+                lo[a] = min(lo[a], (uint32_t)__shfl_xor((int)lo[a], s, 64));
+                hi[a] = max(hi[a], (uint32_t)__shfl_xor((int)hi[a], s, 64));
+            }
+            if (lane == 0) {
+                atomicMin(&sg.lo[a], lo[a]);
+                atomicMax(&sg.hi[a], hi[a]);
+            }
+        }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        ExclGrid g = sg;
+        grid_for_radius(g, r2 > 0.0f ? r2 : 0.0f, 0, maxcells);
+        sg = g;
+    }
+    __syncthreads();
+    const ExclGrid g = sg;
+    if (tid < kProbeCentres)
+        for (int a = 0; a < 3; ++a) cell[tid][a] = cell_coord(ctr[tid][a], g.origin[a], g.inv_h, g.dim[a]);
+    {
+        const int c = (cell_coord(rz, g.origin[2], g.inv_h, g.dim[2]) * g.dim[1] +
+                       cell_coord(ry, g.origin[1], g.inv_h, g.dim[1])) * g.dim[0] + cell_coord(rx, g.origin[0], g.inv_h, g.dim[0]);
+        const uint64_t eq = __builtin_amdgcn_ballot_w64(c == __shfl_xor(c, 1, 64));
+        if (lane == 0) atomicAdd(&same, (int)__builtin_popcountll(eq));
+    }
+    __syncthreads();
+    const int cx = cell_coord(x, g.origin[0], g.inv_h, g.dim[0]);
+    const int cy = cell_coord(y, g.origin[1], g.inv_h, g.dim[1]);
+    const int cz = cell_coord(z, g.origin[2], g.inv_h, g.dim[2]);
+    for (int e = 0; e < probes; ++e) {
+        const int dx = abs(cx - cell[e][0]), dy = abs(cy - cell[e][1]), dz = abs(cz - cell[e][2]);
+        const uint64_t mn = __builtin_amdgcn_ballot_w64(dx <= 1 && dy <= 1 && dz <= 1);
+        if (mn == 0) continue;                          // (no point in the cells: none in the ball)
+        const uint64_t mo = __builtin_amdgcn_ballot_w64(dx == 0 && dy == 0 && dz == 0);
+        const uint64_t mh = __builtin_amdgcn_ballot_w64(dist2(ctr[e][0], ctr[e][1], ctr[e][2], x, y, z) < r2);
+        if (lane == 0) {
+            atomicAdd(&near[e], (int)__builtin_popcountll(mn));
+            if (mo != 0) atomicAdd(&own[e], (int)__builtin_popcountll(mo));
+            if (mh != 0) atomicAdd(&hits[e], (int)__builtin_popcountll(mh));
+        }
+    }
+    __syncthreads();
+    if (tid >= 64) return;
+    // points that follow each other in the cloud and share a cell send one atomic together (grouped_add)
+    const float grouped = 1.0f / (1.02f - (float)same * (1.0f / (float)kProbePoints));
+    const float per = (float)N / (float)kProbePoints, all = (float)N, kk = (float)k;
+    // lane e: points to look at in index order until centre e has k hits, points of its 27 cells, of its own cell
+    float length = 0.0f, longest = 0.0f, walk = 0.0f, crowd = 0.0f;
+    if (lane < probes) {
+        const float c = (float)near[lane] * per;
+        const float h = fmaxf((float)hits[lane] * per, 0.08f * c);       // (half the share a ball has of its cells)
+        length = longest = h > 0.0f ? fminf(all, 1.5f * kk * all / h) : all;
+        walk = h > 0.0f && c * c >= 16.0f * kk * all ? fminf(c, 4.0f * kk * all / h) : c;   // (see bq_grid_kernel)
+        crowd = (float)own[lane] * per;
+    }
+    for (int sft = 32; sft > 0; sft >>= 1) {
+        length += __shfl_xor(length, sft, 64);
+        longest = fmaxf(longest, __shfl_xor(longest, sft, 64));
+        walk += __shfl_xor(walk, sft, 64);
+        crowd += __shfl_xor(crowd, sft, 64);
+    }
+    if (lane == 0) {
+        const float share = 1.0f / (float)probes, centres = (float)B * (float)M;
+        const float scan_us = 20.0f + (M < 2 * kScanCentres ? 4.0e-3f : 7.5e-3f) * longest + 1.9e-7f * centres * length * share;
+        const float grid_us = 20.0f + 1.0e-4f * (float)B * all + 0.4f * fminf(crowd * share / grouped, all / 64.0f) +
+                              1.25e-6f * centres * walk * share;
+        ExclGrid out = g;
+        out.skip = 1.2f * scan_us + 10.0f < grid_us ? 1 : 0;
+        gp[b] = out;
+    }
+}
+
+// Clouds marked by bq_setup_kernel: a wave looks at all points of the cloud in index order for kScanCentres centres.
+// (A kernel of its own: inside bq_grid_kernel its registers cost that kernel a fifth of its time.)
+__global__ __launch_bounds__(kWaves * 64) void bq_index_order_kernel(const float* __restrict__ xyz, int N,
+                                                                     const int32_t* __restrict__ center_idx, int M, float r2,
+                                                                     int k, int32_t* __restrict__ out_idx,
+                                                                     int32_t* __restrict__ out_cnt,
+                                                                     const ExclGrid* __restrict__ gp)
+{
+    const int b = (int)blockIdx.y, lane = (int)threadIdx.x & 63;
+    if (gp[b].skip == 0) return;
+    const int q0 = uni(((int)blockIdx.x * kWaves + ((int)threadIdx.x >> 6)) * kScanCentres);
+    if (q0 >= M) return;
+    const float* __restrict__ cloud = xyz + (int64_t)b * N * 3;
+    float cx[kScanCentres], cy[kScanCentres], cz[kScanCentres];
+    int cnt[kScanCentres], first[kScanCentres];
+    int open = 0;
+#pragma unroll
+    for (int q = 0; q < kScanCentres; ++q) {
+        const int c = q0 + q < M ? uni(center_idx[(int64_t)b * M + q0 + q]) : -1;
+        const bool ok = c >= 0 && c < N;
+        cx[q] = ok ? cloud[(int64_t)c * 3 + 0] : 0.0f;
+        cy[q] = ok ? cloud[(int64_t)c * 3 + 1] : 0.0f;
+        cz[q] = ok ? cloud[(int64_t)c * 3 + 2] : 0.0f;
+        cnt[q] = ok ? 0 : -1;                                       // (-1: no such centre)
+        first[q] = -1;
+        open += ok ? 1 : 0;
+    }
+    int32_t* row = out_idx + ((int64_t)b * M + q0) * k;
+    constexpr int kAhead = 4;                                       // reads in flight
+    for (int j0 = 0; j0 < N && open > 0; j0 += 64 * kAhead) {
+        float x[kAhead], y[kAhead], z[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int j = j0 + 64 * u + lane;
+            const float* p = cloud + (int64_t)(j < N ? j : 0) * 3;
+            x[u] = j < N ? p[0] : __builtin_nanf("");               // (past the last point: in no ball)
+            y[u] = p[1];
+            z[u] = p[2];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+#pragma unroll
+            for (int q = 0; q < kScanCentres; ++q) {
+                if (cnt[q] < 0 || cnt[q] >= k) continue;            // uniform
+                // the sums of dist2, term by term; they only grow, so most points are decided by two terms
+                const float dx = cx[q] - x[u], dy = cy[q] - y[u];
+                float t = dx * dx;
+                t = t + dy * dy;
+                if (__builtin_amdgcn_ballot_w64(t < r2) == 0) continue;
+                const float dz = cz[q] - z[u];
+                t = t + dz * dz;
+                const bool hit = t < r2;
+                const uint64_t mk = __builtin_amdgcn_ballot_w64(hit);
+                if (mk == 0) continue;
+                const int at = cnt[q] + lanes_below(mk);
+                if (hit && at < k) row[(int64_t)q * k + at] = j0 + 64 * u + lane;
+                if (cnt[q] == 0) first[q] = j0 + 64 * u + (int)__builtin_ctzll(mk);
+                cnt[q] = uni(cnt[q] + (int)__builtin_popcountll(mk));
+                open -= cnt[q] >= k ? 1 : 0;
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < kScanCentres; ++q) {
+        if (q0 + q >= M) break;
+        const int have = cnt[q] < 0 ? 0 : (cnt[q] < k ? cnt[q] : k);
+        for (int t = have + lane; t < k; t += 64) row[(int64_t)q * k + t] = first[q];
+        if (lane == 0 && out_cnt) out_cnt[(int64_t)b * M + q0 + q] = have;
+    }
+}
 
 __global__ __launch_bounds__(kWaves * 64) void bq_grid_kernel(
     const float* __restrict__ xyz, int N, const int32_t* __restrict__ center_idx, int M, float r2, int k,
@@ -914,7 +1155,7 @@ __global__ __launch_bounds__(kWaves * 64) void bq_grid_kernel(
     const int lane = (int)threadIdx.x & 63;
     const int w = uni((int)threadIdx.x >> 6);
     const int q = uni((int)blockIdx.x * kWaves + w);
-    if (q >= M) return;
+    if (q >= M || gp[b].skip != 0) return;
     const int c = uni(center_idx[(int64_t)b * M + q]);
     int32_t* row = out_idx + ((int64_t)b * M + q) * k;
     if (c < 0 || c >= N) {
@@ -1149,7 +1390,7 @@ __global__ __launch_bounds__(256) void level_count_kernel(const float* __restric
     }
 }
 
-// (lmax: 1 if the samples are bunched, and every point of the cloud is left to the all-pairs kernels)
+// (skip: the samples are bunched, and every point of the cloud is left to the all-pairs kernels)
 __global__ void level_pick_kernel(ExclGrid* gp, int B, const int32_t* __restrict__ occupied,
                                   const unsigned long long* __restrict__ pairs, int N, int64_t level_stride)
 {
@@ -1165,7 +1406,7 @@ __global__ void level_pick_kernel(ExclGrid* gp, int B, const int32_t* __restrict
     for (int a = 0; a < 3; ++a) g.dim[a] = dim[a];
     g.ncells = dim[0] * dim[1] * dim[2];
     g.cnt_shift = level * level_stride;
-    g.lmax = (float)pairs[b * kFineLevels + level] > (float)N * (float)(most_visited(N) / 4) ? 1 : 0;
+    g.skip = (float)pairs[b * kFineLevels + level] > (float)N * (float)(most_visited(N) / 4) ? 1 : 0;
     gp[b] = g;
 }
 
@@ -1191,7 +1432,7 @@ __global__ __launch_bounds__(256) void knn_search_kernel(const float* __restrict
     const int j = (int)(blockIdx.x * 256 + threadIdx.x);
     if (j >= N) return;
     const ExclGrid g = gp[b];
-    if (g.lmax != 0) {                  // (uniform over the cloud)
+    if (g.skip != 0) {                  // (uniform over the cloud)
         list[(int64_t)b * N + j] = j;
         if (j == 0) count[b] = N;
         return;
@@ -1619,21 +1860,22 @@ hipError_t launch_bq_grid(const float* xyz, int B, int N, const int32_t* center_
     int32_t* cnt = reinterpret_cast<int32_t*>(base + lay.cnt_off);
     int32_t* st = reinterpret_cast<int32_t*>(base + lay.start_off);
     float4* sorted = reinterpret_cast<float4*>(base + lay.sorted_off);
-    const int64_t ncnt = (int64_t)B * lay.maxcells;
-    int initblocks = (int)((ncnt + 255) / 256);
-    if (initblocks > 2048) initblocks = 2048;
-    hipLaunchKernelGGL(grid_init_kernel, dim3(initblocks), dim3(256), 0, stream, gp, B, cnt, ncnt);
-    int bblocks = (N + 2047) / 2048;
-    if (bblocks > 64) bblocks = 64;
-    hipLaunchKernelGGL(grid_bounds_kernel, dim3(bblocks, B), dim3(256), 0, stream, xyz, N, gp);
-    hipLaunchKernelGGL(grid_setup_kernel, dim3((B + 63) / 64), dim3(64), 0, stream, gp, B,
-                       static_cast<const float*>(nullptr), 1, lay.maxcells, r2);
+    int parts = (N + 1023) / 1024;
+    if (parts > kMaxBoundBlocks) parts = kMaxBoundBlocks;
+    uint32_t* part = reinterpret_cast<uint32_t*>(st);           // 6 x parts words, until the cells' starts come there
+    hipLaunchKernelGGL(bq_bounds_kernel, dim3((unsigned)parts, (unsigned)B), dim3(256), 0, stream, xyz, N, cnt, part,
+                       lay.maxcells);
+    hipLaunchKernelGGL(bq_setup_kernel, dim3((unsigned)B), dim3(kProbePoints), 0, stream, gp, B, xyz, N, center_idx, M, r2, k,
+                       (const uint32_t*)part, parts, lay.maxcells);
     const dim3 pgrid((unsigned)((N + 255) / 256), (unsigned)B);
     hipLaunchKernelGGL(grid_count_kernel, pgrid, dim3(256), 0, stream, xyz, N, gp, cnt, lay.maxcells);
     launch_cell_scan(gp, cnt, st, reinterpret_cast<int32_t*>(base + lay.tiles_off), B, lay.maxcells, stream);
     hipLaunchKernelGGL(grid_scatter_kernel, pgrid, dim3(256), 0, stream, xyz, N, gp, cnt, sorted, lay.maxcells);
     hipLaunchKernelGGL(bq_grid_kernel, dim3((unsigned)((M + kWaves - 1) / kWaves), (unsigned)B), dim3(kWaves * 64), 0,
                        stream, xyz, N, center_idx, M, r2, k, out_idx, out_cnt, gp, st, sorted, lay.maxcells);
+    constexpr int per = kWaves * kScanCentres;
+    hipLaunchKernelGGL(bq_index_order_kernel, dim3((unsigned)((M + per - 1) / per), (unsigned)B), dim3(kWaves * 64), 0,
+                       stream, xyz, N, center_idx, M, r2, k, out_idx, out_cnt, gp);
     return hipGetLastError();
 }
 

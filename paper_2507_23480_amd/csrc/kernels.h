@@ -175,6 +175,7 @@ struct ExclGrid {
     int32_t lmax;            // its level
     int32_t curve_bits;      // 0: cells numbered x-fastest; b > 0: 2^b cells per axis, numbered along
                              // a Hilbert curve
+    int32_t skip;            // 1: nothing is put into the cells; the call takes its other route for this cloud
     int64_t cnt_shift;       // cell counts of this grid: elements behind those of the call's first grid
 };
 
