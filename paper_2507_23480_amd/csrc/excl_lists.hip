@@ -961,16 +961,19 @@ __global__ __launch_bounds__(kProbePoints) void bq_setup_kernel(ExclGrid* gp, in
                                                                 int k, const uint32_t* __restrict__ part, int parts,
                                                                 int maxcells)
 {
-    __shared__ ExclGrid sg;
-    __shared__ float ctr[kProbeCentres][3];
-    __shared__ int cell[kProbeCentres][3];
+    constexpr int kShare = kProbePoints / kProbeCentres;        // threads per centre
+    static_assert(kMaxBoundBlocks <= kProbePoints && kShare == 16, "a thread per part; shuffles inside 16 lanes");
+    __shared__ uint32_t box[6];
+    __shared__ float4 pts[kProbePoints];                // a probed point and its cell, ten bits per axis
     __shared__ int hits[kProbeCentres], near[kProbeCentres], own[kProbeCentres];
     __shared__ int same;                                // of kProbePoints points, those whose neighbour has their cell
-    static_assert(kMaxBoundBlocks <= kProbePoints, "a thread per part");
     const int b = (int)blockIdx.x, tid = (int)threadIdx.x, lane = tid & 63;
     const float* __restrict__ cloud = xyz + (int64_t)b * N * 3;
     const int probes = M < kProbeCentres ? M : kProbeCentres;
-    // a thread's points: one of kProbePoints spread over the cloud, one of eight runs of 64 that follow each other
+    // a thread's points: one of kProbePoints spread over the cloud, one of eight runs of 64 that follow each other,
+    // the centre it shares with 15 others
+    const int e = tid / kShare;
+    const int c = e < probes ? center_idx[(int64_t)b * M + (int64_t)e * M / probes] : -1;
     const float* p = cloud + ((int64_t)tid * N / kProbePoints) * 3;
     const float x = p[0], y = p[1], z = p[2];
     int64_t run = (int64_t)(tid >> 6) * N / (kProbePoints / 64) + lane;
@@ -985,17 +988,12 @@ __global__ __launch_bounds__(kProbePoints) void bq_setup_kernel(ExclGrid* gp, in
             hi[a] = q[3 + a];
         }
     }
-    if (tid < 3) {
-        sg.lo[tid] = 0xFFFFFFFFu;
-        sg.hi[tid] = 0u;
-    }
-    if (tid == 0) same = 0;
-    if (tid < kProbeCentres) {
-        const int c = tid < probes ? center_idx[(int64_t)b * M + (int64_t)tid * M / probes] : -1;
-        const bool ok = c >= 0 && c < N;
-        for (int a = 0; a < 3; ++a) ctr[tid][a] = ok ? cloud[(int64_t)c * 3 + a] : __builtin_nanf("");
-        hits[tid] = near[tid] = own[tid] = 0;
-    }
+    const bool okc = c >= 0 && c < N;
+    const float mx = okc ? cloud[(int64_t)c * 3 + 0] : __builtin_nanf("");
+    const float my = okc ? cloud[(int64_t)c * 3 + 1] : __builtin_nanf("");
+    const float mz = okc ? cloud[(int64_t)c * 3 + 2] : __builtin_nanf("");
+    if (tid < 6) box[tid] = tid < 3 ? 0xFFFFFFFFu : 0u;
+    if (tid == 6) same = 0;
     __syncthreads();
     if ((tid & ~63) < parts) {                          // (uniform over the wave)
 #pragma unroll
@@ -1005,42 +1003,54 @@ __global__ __launch_bounds__(kProbePoints) void bq_setup_kernel(ExclGrid* gp, in
                 hi[a] = max(hi[a], (uint32_t)__shfl_xor((int)hi[a], s, 64));
             }
             if (lane == 0) {
-                atomicMin(&sg.lo[a], lo[a]);
-                atomicMax(&sg.hi[a], hi[a]);
+                atomicMin(&box[a], lo[a]);
+                atomicMax(&box[3 + a], hi[a]);
             }
         }
     }
     __syncthreads();
-    if (tid == 0) {
-        ExclGrid g = sg;
-        grid_for_radius(g, r2 > 0.0f ? r2 : 0.0f, 0, maxcells);
-        sg = g;
+    ExclGrid g;                                         // (every thread works it out)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        g.lo[a] = box[a];
+        g.hi[a] = box[3 + a];
     }
-    __syncthreads();
-    const ExclGrid g = sg;
-    if (tid < kProbeCentres)
-        for (int a = 0; a < 3; ++a) cell[tid][a] = cell_coord(ctr[tid][a], g.origin[a], g.inv_h, g.dim[a]);
+    grid_for_radius(g, r2 > 0.0f ? r2 : 0.0f, 0, maxcells);
+    const int px = cell_coord(x, g.origin[0], g.inv_h, g.dim[0]);
+    const int py = cell_coord(y, g.origin[1], g.inv_h, g.dim[1]);
+    const int pz = cell_coord(z, g.origin[2], g.inv_h, g.dim[2]);
+    pts[tid] = make_float4(x, y, z, __int_as_float(px | (py << 10) | (pz << 20)));
+    const int cx = cell_coord(mx, g.origin[0], g.inv_h, g.dim[0]);
+    const int cy = cell_coord(my, g.origin[1], g.inv_h, g.dim[1]);
+    const int cz = cell_coord(mz, g.origin[2], g.inv_h, g.dim[2]);
     {
-        const int c = (cell_coord(rz, g.origin[2], g.inv_h, g.dim[2]) * g.dim[1] +
-                       cell_coord(ry, g.origin[1], g.inv_h, g.dim[1])) * g.dim[0] + cell_coord(rx, g.origin[0], g.inv_h, g.dim[0]);
-        const uint64_t eq = __builtin_amdgcn_ballot_w64(c == __shfl_xor(c, 1, 64));
+        const int cc = (cell_coord(rz, g.origin[2], g.inv_h, g.dim[2]) * g.dim[1] +
+                        cell_coord(ry, g.origin[1], g.inv_h, g.dim[1])) * g.dim[0] +
+                       cell_coord(rx, g.origin[0], g.inv_h, g.dim[0]);
+        const uint64_t eq = __builtin_amdgcn_ballot_w64(cc == __shfl_xor(cc, 1, 64));
         if (lane == 0) atomicAdd(&same, (int)__builtin_popcountll(eq));
     }
     __syncthreads();
-    const int cx = cell_coord(x, g.origin[0], g.inv_h, g.dim[0]);
-    const int cy = cell_coord(y, g.origin[1], g.inv_h, g.dim[1]);
-    const int cz = cell_coord(z, g.origin[2], g.inv_h, g.dim[2]);
-    for (int e = 0; e < probes; ++e) {
-        const int dx = abs(cx - cell[e][0]), dy = abs(cy - cell[e][1]), dz = abs(cz - cell[e][2]);
-        const uint64_t mn = __builtin_amdgcn_ballot_w64(dx <= 1 && dy <= 1 && dz <= 1);
-        if (mn == 0) continue;                          // (no point in the cells: none in the ball)
-        const uint64_t mo = __builtin_amdgcn_ballot_w64(dx == 0 && dy == 0 && dz == 0);
-        const uint64_t mh = __builtin_amdgcn_ballot_w64(dist2(ctr[e][0], ctr[e][1], ctr[e][2], x, y, z) < r2);
-        if (lane == 0) {
-            atomicAdd(&near[e], (int)__builtin_popcountll(mn));
-            if (mo != 0) atomicAdd(&own[e], (int)__builtin_popcountll(mo));
-            if (mh != 0) atomicAdd(&hits[e], (int)__builtin_popcountll(mh));
-        }
+    int nh = 0, nn = 0, no = 0;
+#pragma unroll 4
+    for (int i = tid % kShare; i < kProbePoints; i += kShare) {
+        const float4 q = pts[i];
+        const int w = __float_as_int(q.w);
+        const int dx = abs((w & 1023) - cx), dy = abs(((w >> 10) & 1023) - cy), dz = abs((w >> 20) - cz);
+        nn += dx <= 1 && dy <= 1 && dz <= 1 ? 1 : 0;
+        no += dx + dy + dz == 0 ? 1 : 0;
+        nh += dist2(mx, my, mz, q.x, q.y, q.z) < r2 ? 1 : 0;
+    }
+#pragma unroll
+    for (int s = kShare / 2; s > 0; s >>= 1) {
+        nh += __shfl_xor(nh, s, 64);
+        nn += __shfl_xor(nn, s, 64);
+        no += __shfl_xor(no, s, 64);
+    }
+    if (tid % kShare == 0) {
+        hits[e] = nh;
+        near[e] = nn;
+        own[e] = no;
     }
     __syncthreads();
     if (tid >= 64) return;
@@ -1050,10 +1060,10 @@ __global__ __launch_bounds__(kProbePoints) void bq_setup_kernel(ExclGrid* gp, in
     // lane e: points to look at in index order until centre e has k hits, points of its 27 cells, of its own cell
     float length = 0.0f, longest = 0.0f, walk = 0.0f, crowd = 0.0f;
     if (lane < probes) {
-        const float c = (float)near[lane] * per;
-        const float h = fmaxf((float)hits[lane] * per, 0.08f * c);       // (half the share a ball has of its cells)
+        const float cells = (float)near[lane] * per;
+        const float h = fmaxf((float)hits[lane] * per, 0.08f * cells);       // (half the share a ball has of its cells)
         length = longest = h > 0.0f ? fminf(all, 1.5f * kk * all / h) : all;
-        walk = h > 0.0f && c * c >= 16.0f * kk * all ? fminf(c, 4.0f * kk * all / h) : c;   // (see bq_grid_kernel)
+        walk = h > 0.0f && cells * cells >= 16.0f * kk * all ? fminf(cells, 4.0f * kk * all / h) : cells;   // (see bq_grid_kernel)
         crowd = (float)own[lane] * per;
     }
     for (int sft = 32; sft > 0; sft >>= 1) {

@@ -2127,9 +2127,9 @@ __device__ __forceinline__ bool fps_rounds_of(Points<P, BQ>& pt, Shared<T>& sh, 
     return true;
 }
 
-// Picks from which on sweeps settle a cell-ordered exact phase of MDPS.  (Kernels with eight points per thread have
-// no second loop: it costs the long phases more in spilled registers than it saves the short ones.)  Prefixes of 51 to
-// 150 picks, sweeps / chain, us: 5120 points with record, 320 samples 323 / 270; 8192, 512 samples 395 / 355.
+// Picks up to which the chain settles a cell-ordered exact phase of MDPS: a short prefix.  (The remainder after the
+// threshold phase goes through sweeps however short it is: by then a round accepts most of its candidates.)  Prefixes of 51
+// to 150 picks, sweeps / chain, us: 5120 points with record, 320 samples 323 / 270; 8192, 512 samples 395 / 355.
 constexpr int kSweepPicks = 512;
 
 // Rounds of 64, 128 or 256 candidates.  With four or more points per thread folding a pick takes the
@@ -2149,11 +2149,14 @@ __device__ __forceinline__ bool fps_rounds(Points<P, BQ>& pt, Shared<T>& sh, con
     // for any number of candidates per lane was a tenth slower with two than the one written for two.)
     if constexpr (PERM && MODE != 3) {
         // A few hundred picks (a short prefix) go through the chain: at the start of a run a sweep accepts little of
-        // a round whose relations all workgroups have to exchange.  So does a recording call on a small cloud: with
-        // all pairs of candidates worked out by one workgroup a round costs more than its chain.
-        if constexpr (MODE != 0 && (P <= 4 || (P == 16 && !BQ)))
-            if (upto - st.i < kSweepPicks || (BQ && wh.G == 1))
-                return fps_rounds_of<T, P, BQ, PERM, (P == 2 ? 1 : 2)>(pt, sh, wh, a, it, seq, st, upto, capture);
+        // a round whose relations all workgroups have to exchange.  (Not in the recording kernels for more than two points
+        // per thread and those for eight: the second loop, in registers, costs their long phases 4 % -- LiDAR batch
+        // with record 4.53 -> 4.72 ms.)  A recording call on a small cloud stays with the chain: with all pairs of
+        // candidates worked out by one workgroup a round costs more than it.
+        constexpr bool SHORT = MODE != 0 && (P == 2 || (!BQ && P != 8)), SMALL = BQ && P <= 4;
+        if constexpr (SHORT || SMALL)
+            if ((SHORT && upto < kSweepPicks) || (SMALL && wh.G == 1))
+                return fps_rounds_of<T, P, BQ, PERM, (P == 2 || BQ ? 1 : 2)>(pt, sh, wh, a, it, seq, st, upto, capture);
         return fps_rounds_of<T, P, BQ, PERM, 4, true>(pt, sh, wh, a, it, seq, st, upto, capture);
     } else if constexpr (P >= 4) {
         return fps_rounds_of<T, P, BQ, PERM, 2>(pt, sh, wh, a, it, seq, st, upto, capture);
