@@ -3,7 +3,7 @@ index order: the bytes are those of the scan either way, also where a batch hold
 import numpy as np
 import pytest
 
-from tests.test_gpu_ball_query_route import brute
+from tests.routes import scan
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -42,7 +42,7 @@ def test_same_bytes(fp, kinds, N):
             c[0, 2], c[B - 1, 6] = -1, N
         c = torch.from_numpy(c).cuda()
         for r, k in ((0.5, 16), (0.02, 5), (3.0, 254), (0.2, 1), (1e30, 65)):
-            want = brute(fp, x, c, r, k)
+            want = scan(fp, x, c, r, k)
             for f in (fp.ball_query, fp.ball_query_grid):
                 got = f(x, c, r, k)
                 assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), (M, r, k)
@@ -55,7 +55,7 @@ def test_without_counts(fp):
     idx = torch.empty((1, 300, 12), dtype=torch.int32, device="cuda")
     assert fp.load().fp_ball_query_grid(x.data_ptr(), 1, 6000, c.data_ptr(), 300, 0.6, 12, idx.data_ptr(), None,
                                         ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream) == 0
-    assert torch.equal(idx, brute(fp, x, c, 0.6, 12)[0])
+    assert torch.equal(idx, scan(fp, x, c, 0.6, 12)[0])
 
 
 def test_lines_of_the_route(fp):

@@ -7,6 +7,7 @@ import pytest
 
 from oracle import ref
 from paper_2507_23480_amd import inputs
+from tests.routes import scan
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -34,7 +35,7 @@ def check(fp, batch, centres, radius, k):
     x = dev(np.ascontiguousarray(batch, dtype=np.float32))
     c = dev(np.ascontiguousarray(centres, dtype=np.int32))
     idx, cnt = fp.ball_query_grid(x, c, radius, k)
-    bidx, bcnt = fp.ball_query(x, c, radius, k)
+    bidx, bcnt = scan(fp, x, c, radius, k)
     torch.cuda.synchronize()
     assert torch.equal(idx, bidx) and torch.equal(cnt, bcnt), "grid differs from brute force"
     for b in range(batch.shape[0]):
@@ -99,14 +100,16 @@ def test_no_centres_and_argument_checks(fp):
 
 @pytest.mark.parametrize("name", ["C1", "C2", "C3", "C4", "C5"])
 def test_workloads_equal_the_brute_force_kernel(fp, name):
-    """Stage 0 at full size over the exact-FPS samples: the bytes of fp_ball_query, which the
-    workload tests pin to the oracle."""
+    """Stage 0 at full size over the exact-FPS samples: the bytes of fp_ball_query, and of fp.ball_query (which the
+    workload tests pin to the oracle)."""
     say("grid ball query at workload", name)
     wl = inputs.WORKLOADS[name]
     st = wl.stages[0]
     x = dev(inputs.make_batch(name))
     centres = fp.fps_exact(x, st.n)
     idx, cnt = fp.ball_query_grid(x, centres, st.radius, st.k)
-    bidx, bcnt = fp.ball_query(x, centres, st.radius, st.k)
+    bidx, bcnt = scan(fp, x, centres, st.radius, st.k)
+    cidx, ccnt = fp.ball_query(x, centres, st.radius, st.k)
     torch.cuda.synchronize()
     assert torch.equal(idx, bidx) and torch.equal(cnt, bcnt)
+    assert torch.equal(cidx, bidx) and torch.equal(ccnt, bcnt)

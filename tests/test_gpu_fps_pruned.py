@@ -9,6 +9,7 @@ import pytest
 
 from oracle import ref
 from paper_2507_23480_amd import inputs
+from tests.routes import exact_by_index, in_cells, own_workgroups
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -34,7 +35,8 @@ def say(*a):
 
 
 def check(fp, batch, n, start=None, G=0):
-    fp.set_wg_per_cloud(G)
+    # (forced: by itself the call takes the index-ordered kernels for so few samples)
+    fp.set_wg_per_cloud(G or own_workgroups(fp, batch.shape[0], batch.shape[1]))
     try:
         B = batch.shape[0]
         starts = [0] * B if start is None else list(start)
@@ -117,15 +119,18 @@ def test_argument_checks(fp):
 
 @pytest.mark.parametrize("name", ["C1", "C2", "C3", "C4", "C5"])
 def test_workloads_equal_fps_exact(fp, name):
-    """Full size, the configuration bench.py times: identical to fps_exact (which the workload
-    tests pin to the oracle), and sampled curve values recomputed by the oracle's definition."""
+    """Full size, the configuration bench.py times: the cell-ordered and the index-ordered kernels give the same samples
+    and curve, and so does fps_exact (which the workload tests pin to the oracle)."""
     say("pruned fps at workload", name)
     wl = inputs.WORKLOADS[name]
     st = wl.stages[0]
     x = dev(inputs.make_batch(name))
-    a, amdc = fp.fps_exact(x, st.n, want_mdc=True)
-    b, bmdc, info = fp.fps_exact_pruned(x, st.n, want_mdc=True, want_info=True)
+    a, amdc, ainfo = exact_by_index(fp, x, st.n, want_mdc=True, want_info=True)
+    b, bmdc, info = in_cells(fp, x, lambda: fp.fps_exact_pruned(x, st.n, want_mdc=True, want_info=True))
+    c, cmdc = fp.fps_exact(x, st.n, want_mdc=True)
     torch.cuda.synchronize()
-    assert all(i.status == 0 for i in fp.parse_info(info))
-    assert torch.equal(a, b)
-    assert torch.equal(amdc, bmdc)
+    ainfo, info = fp.parse_info(ainfo), fp.parse_info(info)
+    assert all(i.status == 0 for i in info)
+    assert [i.rounds for i in ainfo] != [i.rounds for i in info]        # two kernels
+    assert torch.equal(a, b) and torch.equal(a, c)
+    assert torch.equal(amdc, bmdc) and torch.equal(amdc, cmdc)

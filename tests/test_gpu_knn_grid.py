@@ -8,6 +8,7 @@ import pytest
 
 from oracle import ref
 from paper_2507_23480_amd import inputs
+from tests.routes import all_pairs
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -35,7 +36,7 @@ def check(fp, batch, sidx, k, radius):
     x = dev(np.ascontiguousarray(batch, dtype=np.float32))
     s = dev(np.ascontiguousarray(sidx, dtype=np.int32))
     pos, d2, deferred = fp.knn_grid(x, s, k, radius, want_deferred=True)
-    bpos, bd2 = fp.knn(x, s, k)
+    bpos, bd2 = all_pairs(fp, x, s, k)
     torch.cuda.synchronize()
     assert torch.equal(pos, bpos) and torch.equal(d2, bd2), "grid differs from brute force"
     for b in range(batch.shape[0]):
@@ -99,8 +100,8 @@ def test_argument_checks(fp):
 @pytest.mark.parametrize("name", ["C1", "C2", "C3", "C4", "C5"])
 def test_workloads_equal_the_brute_force_kernel(fp, name):
     """Stage 0 at full size, the three nearest exact-FPS samples of every point, search radius
-    three times the samples' coverage radius: the bytes of fp_knn without a cache (which the
-    workload tests pin to the oracle), and nearly every point settled in the grid."""
+    three times the samples' coverage radius: the bytes of fp_knn without a cache and of
+    fp.knn (which the workload tests pin to the oracle), and nearly every point settled in the grid."""
     say("grid knn at workload", name)
     wl = inputs.WORKLOADS[name]
     st = wl.stages[0]
@@ -108,7 +109,9 @@ def test_workloads_equal_the_brute_force_kernel(fp, name):
     sidx = fp.fps_exact(x, st.n)
     radius = 3.0 * float(fp.coverage2(x, sidx).max().sqrt())
     pos, d2, deferred = fp.knn_grid(x, sidx, 3, radius, want_deferred=True)
-    bpos, bd2 = fp.knn(x, sidx, 3)
+    bpos, bd2 = all_pairs(fp, x, sidx, 3)
+    cpos, cd2 = fp.knn(x, sidx, 3)
     torch.cuda.synchronize()
     assert torch.equal(pos, bpos) and torch.equal(d2, bd2)
+    assert torch.equal(cpos, bpos) and torch.equal(cd2, bd2)
     say("  deferred share %.4f" % (float(deferred.sum()) / (wl.B * wl.N)))

@@ -3,7 +3,8 @@ points of batches of every size, and the lines between the routes; the result is
 import numpy as np
 import pytest
 
-from tests.test_gpu_knn_search import all_pairs, same, search
+from tests.routes import all_pairs
+from tests.test_gpu_knn_search import same, search
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu

@@ -1,11 +1,10 @@
 """The number of samples decides whether a sampler sorts the cloud into cells first: either side of the lines the same
 samples, and the layout the rule names (told by the number of rounds, which the layouts do not share)."""
-import ctypes
-
 import numpy as np
 import pytest
 
 from paper_2507_23480_amd import inputs
+from tests.routes import exact_by_index, in_cells, scan
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -20,17 +19,6 @@ def fp():
     binding.set_wg_per_cloud(0)
 
 
-def in_cells(fp, x, call):
-    """call() with the entry point's own layout and the number of workgroups the library would choose."""
-    g, t, p = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
-    assert fp.load().fp_plan(x.shape[0], x.shape[1], ctypes.byref(g), ctypes.byref(t), ctypes.byref(p)) == 0
-    fp.set_wg_per_cloud(g.value)
-    try:
-        return call()
-    finally:
-        fp.set_wg_per_cloud(0)
-
-
 def rounds(fp, info):
     return [i.rounds for i in fp.parse_info(info)]
 
@@ -40,8 +28,7 @@ def rounds(fp, info):
 def test_exact(fp, B, N, n):
     x = torch.from_numpy(np.stack([inputs.make_cloud("C3", 40 + b % 3, N) for b in range(B)])).cuda()
     few = 256 // B <= 2                                     # workgroups per cloud
-    small = torch.empty(int(fp.load().fp_workspace_bytes(1, 1)), dtype=torch.uint8, device="cuda")
-    want, ordered = fp.fps_exact(x, n, ws=small, want_info=True)
+    want, ordered = exact_by_index(fp, x, n, want_info=True)
     cells, sorted_ = in_cells(fp, x, lambda: fp.fps_exact_pruned(x, n, want_info=True))
     assert torch.equal(cells, want) and rounds(fp, sorted_) != rounds(fp, ordered)
     many = n >= (3000 if few else 1500)
@@ -74,8 +61,6 @@ def test_prefix_either_side_of_the_sweeps(fp, N, n, order):
     cache = fp.new_bq_cache(x, n)
     assert torch.equal(in_cells(fp, x, lambda: fp.mdps_sample_pruned(x, n, prm)), want)
     assert torch.equal(fp.mdps_sample_pruned(x, n, prm, bq_cache=cache, bq_radius=0.1), want)
-    scan = (torch.empty((2, n, 16), dtype=torch.int32, device="cuda"), torch.empty((2, n), dtype=torch.int32, device="cuda"))
-    assert fp.load().fp_ball_query(x.data_ptr(), 2, N, want.data_ptr(), n, 0.1, 16, scan[0].data_ptr(),
-                                   scan[1].data_ptr(), None, torch.cuda.current_stream().cuda_stream) == 0
+    wanted = scan(fp, x, want, 0.1, 16)
     got = fp.ball_query(x, want, 0.1, 16, bq_cache=cache)
-    assert torch.equal(got[0], scan[0]) and torch.equal(got[1], scan[1])
+    assert torch.equal(got[0], wanted[0]) and torch.equal(got[1], wanted[1])

@@ -14,6 +14,7 @@ import pytest
 
 from oracle import ref
 from paper_2507_23480_amd import inputs
+from tests.routes import in_cells, own_workgroups
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -51,7 +52,8 @@ def rparams(prm):
 
 def check(fp, batch, n, prm, start=None, G=0, order=0):
     prm = dataclasses.replace(prm, scan_order=order)
-    fp.set_wg_per_cloud(G)
+    # (forced: by itself the call takes the index-ordered kernels for so few samples)
+    fp.set_wg_per_cloud(G or own_workgroups(fp, batch.shape[0], batch.shape[1]))
     try:
         B = batch.shape[0]
         starts = [0] * B if start is None else list(start)
@@ -133,12 +135,13 @@ def test_batches_and_start_indices(fp, order):
 
 def test_mlp_estimator(fp):
     from paper_2507_23480_amd import mlp_estimator
-    x = inputs.make_batch("C1")
+    x = dev(inputs.make_batch("C1"))
     prm = mlp_estimator.params_for("C1", 0)
-    a = fp.mdps_sample(dev(x), 1024, prm)
-    b = fp.mdps_sample_pruned(dev(x), 1024, prm)
+    a, ainfo = fp.mdps_sample(x, 1024, prm, want_info=True)
+    b, binfo = in_cells(fp, x, lambda: fp.mdps_sample_pruned(x, 1024, prm, want_info=True))
     torch.cuda.synchronize()
     assert torch.equal(a, b)
+    assert fp.parse_info(ainfo)[0].rounds != fp.parse_info(binfo)[0].rounds         # two kernels
 
 
 def test_argument_checks(fp):
@@ -169,7 +172,7 @@ def test_workloads_equal_mdps_sample(fp, order, name):
     x = dev(inputs.make_batch(name))
     prm = dataclasses.replace(calibration.params_for(name, 0), scan_order=order)
     a, ainfo = fp.mdps_sample(x, st.n, prm, want_info=True)
-    b, binfo = fp.mdps_sample_pruned(x, st.n, prm, want_info=True)
+    b, binfo = in_cells(fp, x, lambda: fp.mdps_sample_pruned(x, st.n, prm, want_info=True))
     torch.cuda.synchronize()
     assert torch.equal(a, b)
     for ia, ib in zip(fp.parse_info(ainfo), fp.parse_info(binfo)):
