@@ -104,10 +104,10 @@ typedef struct fp_mdps_info {
                                            exact FPS after early termination                      */
 } fp_mdps_info;
 
-/* Bytes of workspace fp_fps_exact / fp_mdps_sample need for B clouds of N points
- * (0 is returned for shapes the library rejects). Alignment: 256 bytes. */
-/* (What fp_fps_exact can use: from some thousands of points on that includes the cell-ordered copy of the cloud its
- * faster kernels work on.  The size returned for a small cloud is enough for every shape.) */
+/* Bytes of workspace fp_fps_exact can use for B clouds of N points (0 is returned for shapes the library rejects):
+ * from some thousands of points on that includes the cell-ordered copy of the cloud on which calls for many samples
+ * are faster.  What fp_fps_exact and fp_mdps_sample (scan order 0) need is the size returned for a small cloud, such
+ * as fp_workspace_bytes(1, 1); it is enough for every shape.  Alignment: 256 bytes. */
 size_t fp_workspace_bytes(int32_t B, int32_t N);
 
 /* Bytes of the ball-query cache for B clouds of N points and n samples each.
@@ -172,7 +172,8 @@ fp_status fp_fps_exact_static(const float* xyz, int32_t B, int32_t N, int32_t n,
  * grid traversed along a Hilbert curve, so that the points a wavefront holds lie in a small
  * box; a new sample is folded into a wavefront's distances only if it is closer to that box
  * than the largest distance the wavefront still holds.  Arguments as fp_fps_exact without the
- * ball-query cache; the workspace is larger (it also receives the reordered cloud).
+ * ball-query cache; the workspace is larger (it also receives the reordered cloud).  Calls for fewer samples than
+ * earn the sort back run on the cloud as it is.
  */
 size_t fp_fps_pruned_workspace_bytes(int32_t B, int32_t N);
 fp_status fp_fps_exact_pruned(const float* xyz, int32_t B, int32_t N, int32_t n,
@@ -227,7 +228,8 @@ fp_status fp_mdps_sample_pruned(const float* xyz, int32_t B, int32_t N, int32_t 
  * (strict, binary32), ascending, first k kept; unused slots repeat the first
  * hit; out_cnt = min(hits, k).  1 <= k <= 254.
  *   center_idx [B][M] int32, out_idx [B][M][k] int32, out_cnt [B][M] int32 or NULL
- *   bq_cache   NULL = brute force over all N points.  Otherwise a cache filled
+ *   bq_cache   NULL = brute force over all N points (fp_ball_query_grid gives the same bytes several times faster
+ *              from some 5000 points on).  Otherwise a cache filled
  *              by fp_fps_exact / fp_mdps_sample / fp_mdps_sample_pruned on the same xyz: centres that
  *              are the cached samples (same position q, same radius) are read
  *              from the cache with no distance evaluation (redundancy-free ball
@@ -247,7 +249,8 @@ fp_status fp_ball_query(const float* xyz, int32_t B, int32_t N,
  * byte, for any centre set, from the 27 grid cells around a centre instead of all N points
  * (cells as wide as the radius; of the hits the k lowest indices are kept, in ascending order,
  * which is what the scan over all points finds first).  The grid is built in the workspace by
- * every call.
+ * every call.  A cloud it would not help (balls of a good part of the cloud, a point far from all others) is looked
+ * at in index order instead, as a probe of some centres and points tells on the device.
  */
 size_t fp_ball_query_grid_workspace_bytes(int32_t B, int32_t N);
 fp_status fp_ball_query_grid(const float* xyz, int32_t B, int32_t N, const int32_t* center_idx,
@@ -267,7 +270,8 @@ size_t fp_knn_workspace_bytes(int32_t B, int32_t N, int64_t cache_entries);
  *   sample_idx [B][n] int32 indices into the cloud (a sampler's output), 1 <= k <= min(n, 8)
  *   out_pos    [B][N][k] int32 positions q into sample_idx
  *   out_d2     [B][N][k] float32 squared distances, ascending
- *   bq_cache   NULL = every point is compared with all n samples.  Otherwise a cache
+ *   bq_cache   NULL = every point is compared with all n samples (fp_knn_search gives the same bytes several times
+ *              faster from some 1000 evenly spread samples on).  Otherwise a cache
  *              filled by fp_fps_exact / fp_mdps_sample on the same xyz whose samples are
  *              sample_idx (redundancy-free k-NN, Section 4.2): the search space of a point
  *              is the samples whose recorded ball contains it, which are its k nearest
@@ -291,7 +295,7 @@ size_t fp_knn_search_workspace_bytes(int32_t B, int32_t N, int32_t n);
 /*
  * The result of fp_knn without a cache, through a grid over the samples whose cells follow their
  * density; points it does not settle are searched by brute force (out_deferred [B] int32 or NULL:
- * their number per cloud).
+ * their number per cloud; all points of a cloud whose samples are bunched).
  */
 fp_status fp_knn_search(const float* xyz, int32_t B, int32_t N, const int32_t* sample_idx, int32_t n,
                         int32_t k, int32_t* out_pos, float* out_d2, int32_t* out_deferred,
