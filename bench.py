@@ -58,16 +58,14 @@ GRAPH = "four streams, step replayed as one HIP graph"
 # samplers keep the cloud in registers: what they move beyond reading it once is the polling of the
 # words exchanged between the workgroups of a cloud.
 TRAFFIC_BYTES = {"C2": {"fps_exact": 427967, "mdps_sample+record": 2364746, "ball_query_cached": 1948914,
-                        "ball_query_brute": 2004582},
+                        "ball_query": 2004582},
                  # (C4, C5: the step's recorder is the cell-ordered one, its reader the one for cell-ordered records)
-                 "C4": {"fps_exact": 202751712, "mdps_sample+record": 284120000, "ball_query_cached": 59760896,
-                        "ball_query_brute": 81926986},
-                 "C5": {"fps_exact": 199127232, "mdps_sample+record": 249951690, "ball_query_cached": 29248181,
-                        "ball_query_brute": 149293152}}
+                 "C4": {"fps_exact": 202751712, "mdps_sample+record": 284120000, "ball_query_cached": 59760896},
+                 "C5": {"fps_exact": 199127232, "mdps_sample+record": 249951690, "ball_query_cached": 29248181}}
 
 
 PRUNED_RECORD_FROM = 1 << 14
-CELL_ORDER_FROM = 5121              # fps_exact works on a cell-ordered copy of the cloud from here on
+CELL_ORDER_FROM = 5121, 1500        # points and samples from which on fps_exact works on a cell-ordered copy of the cloud
 
 
 def record_sampler(fp, sg):
@@ -155,7 +153,7 @@ def run_step(fp, ctx, timer, keep=None):
         n, r, k = sg["n"], sg["radius"], sg["k"]
         xs = x
         idx = timer.call("fps_exact/s%d" % s, lambda: fp.fps_exact(xs, n))
-        bq = timer.call("ball_query_brute/s%d" % s, lambda: fp.ball_query(xs, idx, r, k))
+        bq = timer.call("ball_query/s%d" % s, lambda: fp.ball_query(xs, idx, r, k))
         midx = timer.call("mdps_sample+record/s%d" % s,
                           lambda: record_sampler(fp, sg)(xs, n, sg["step_prm"], bq_cache=sg["cache"], bq_radius=r))
         mbq = timer.call("ball_query_cached/s%d" % s,
@@ -171,7 +169,7 @@ def run_step_streams(torch, fp, ctx, keep=None):
     fits on the device side by side).  What has to happen in order is exact FPS of stage s ->
     gather -> the samplers of stage s+1: that chain runs on the current stream.  mdps_sample
     (with recording) and the cache reader that follows it run on a stream per stage, two in
-    turn, as soon as the stage's input is there; the brute-force ball queries, which nothing
+    turn, as soon as the stage's input is there; the ball queries without a record, which nothing
     waits for, on a stream of their own."""
     main = torch.cuda.current_stream()
     lanes = [ctx["side"], ctx["aux"]]
@@ -264,7 +262,7 @@ def quality_and_rooflines(torch, fp, ctx, kernel_ms):
         torch.cuda.synchronize()
         infos = fp.parse_info(info)
         ratio = (cov_m / cov_f)
-        brute_m = fp.ball_query(x, midx, sg["radius"], k)
+        brute_m = scan_query(torch, fp, x, midx, sg["radius"], k)
         torch.cuda.synchronize()
         cached_equal = bool(torch.equal(brute_m[0], mbq[0]) and torch.equal(brute_m[1], mbq[1]))
         ms = {key.split("/")[0]: v for key, v in kernel_ms.items() if key.endswith("/s%d" % s)}
@@ -274,7 +272,7 @@ def quality_and_rooflines(torch, fp, ctx, kernel_ms):
         # Cell-ordered samplers pass over most pairs, so the operations of the unpruned update say nothing about
         # them: they are priced at the bytes that have to move (what bounds them is neither, but the trips
         # between the workgroups of a cloud).  The same goes for a ball query through the grid.
-        cells = N >= CELL_ORDER_FROM
+        cells = N >= CELL_ORDER_FROM[0] and n >= CELL_ORDER_FROM[1]
         moved = lambda byts, t: {"bound": "hbm", "achieved": byts / (t * 1e-3) / 1e9, "peak": HBM_PEAK_GBS,  # noqa: E731
                                  "unit": "GB/s", "frac": byts / (t * 1e-3) / 1e9 / HBM_PEAK_GBS, "bytes": byts}
         if "fps_exact" in ms and cells:
@@ -291,11 +289,11 @@ def quality_and_rooflines(torch, fp, ctx, kernel_ms):
             a = point_iters * OPS_PER_POINT_ITERATION / (ms["mdps_sample+record"] * 1e-3) / 1e12
             roof["mdps_sample+record"] = {"bound": "alu", "achieved": a, "peak": ALU_PEAK_TOPS,
                                           "unit": "TFLOP/s", "frac": a / ALU_PEAK_TOPS}
-        if "ball_query_brute" in ms and N >= fp.GRID_QUERY_FROM:
-            roof["ball_query_brute"] = moved(12.0 * B * N + 4.0 * B * n + 4.0 * B * n * (k + 1), ms["ball_query_brute"])
-        elif "ball_query_brute" in ms:
-            a = pairs * OPS_PER_PAIR_TEST / (ms["ball_query_brute"] * 1e-3) / 1e12
-            roof["ball_query_brute"] = {"bound": "alu", "achieved": a, "peak": ALU_PEAK_TOPS,
+        if "ball_query" in ms and fp.grid_query(B, N, n):
+            roof["ball_query"] = moved(12.0 * B * N + 4.0 * B * n + 4.0 * B * n * (k + 1), ms["ball_query"])
+        elif "ball_query" in ms:
+            a = pairs * OPS_PER_PAIR_TEST / (ms["ball_query"] * 1e-3) / 1e12
+            roof["ball_query"] = {"bound": "alu", "achieved": a, "peak": ALU_PEAK_TOPS,
                                         "unit": "TFLOP/s", "frac": a / ALU_PEAK_TOPS,
                                         "note": "pair tests priced at the 9 operations of the full test / time: "
                                                 "most pairs are decided after 6"}
@@ -310,16 +308,16 @@ def quality_and_rooflines(torch, fp, ctx, kernel_ms):
                                          "cache_bytes": cstats["bytes"], "cache_entries": cstats["entries"],
                                          "cache_incomplete": cstats["incomplete"]}
         knn = time_knn(torch, fp, x, sg, midx)
-        for kname in ("knn_brute", "knn_cached"):
+        for kname in ("knn", "knn_all_pairs", "knn_cached"):
             ms[kname] = knn[kname + "_ms"]
         # the same k-NN through a grid over the samples, search radius 3 x their coverage radius
         kg_radius = 3.0 * float(cov_m.max())
         kg = time_call(torch, lambda: fp.knn_grid(x, knn["samples"], KNN_K, kg_radius, want_deferred=True))
-        if not (torch.equal(kg[1][0], knn["knn_brute"][0]) and torch.equal(kg[1][1], knn["knn_brute"][1])):
+        if not (torch.equal(kg[1][0], knn["pairs"][0]) and torch.equal(kg[1][1], knn["pairs"][1])):
             raise RuntimeError("grid k-NN differs from the brute-force result")
         ms["knn_grid"] = kg[0]
-        a = float(B) * N * n * OPS_PER_PAIR_TEST / (knn["knn_brute_ms"] * 1e-3) / 1e12
-        roof["knn_brute"] = moved(12.0 * B * N + 4.0 * B * n + 8.0 * B * N * KNN_K, knn["knn_brute_ms"]) \
+        a = float(B) * N * n * OPS_PER_PAIR_TEST / (knn["knn_ms"] * 1e-3) / 1e12
+        roof["knn"] = moved(12.0 * B * N + 4.0 * B * n + 8.0 * B * N * KNN_K, knn["knn_ms"]) \
             if n >= fp.KNN_SEARCH_FROM[0] and N >= fp.KNN_SEARCH_FROM[1] else {"bound": "alu", "achieved": a, "peak": ALU_PEAK_TOPS, "unit": "TFLOP/s",
                              "frac": a / ALU_PEAK_TOPS}
         # the redundancy-free search reads the recorded entries (regrouped by point block) and the
@@ -329,10 +327,14 @@ def quality_and_rooflines(torch, fp, ctx, kernel_ms):
         roof["knn_cached"] = {"bound": "hbm", "achieved": a, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                               "frac": a / HBM_PEAK_GBS, "bytes": byts,
                               "points_searched_by_brute_force": knn["deferred_fraction"]}
-        # ball query through the uniform grid (outside the timed step): the brute-force result
+        # the scan of all points and the ball query through the uniform grid (outside the timed step): the same
+        # result, as is the step's own query, which takes one of the two
+        sq = time_call(torch, lambda: scan_query(torch, fp, x, idx, sg["radius"], k))
+        ms["ball_query_scan"] = sq[0]
         gq = time_call(torch, lambda: fp.ball_query_grid(x, idx, sg["radius"], k))
-        if not (torch.equal(gq[1][0], bq[0]) and torch.equal(gq[1][1], bq[1])):
-            raise RuntimeError("ball_query_grid differs from the brute-force ball query")
+        for label, got in (("ball_query_grid", gq[1]), ("ball_query", bq)):
+            if not (torch.equal(got[0], sq[1][0]) and torch.equal(got[1], sq[1][1])):
+                raise RuntimeError(label + " differs from the scan of all points")
         ms["ball_query_grid"] = gq[0]
         byts = 12.0 * B * N + 4.0 * B * n + 4.0 * B * n * (k + 1)
         a = byts / (gq[0] * 1e-3) / 1e9
@@ -563,9 +565,31 @@ def time_excl_lists(torch, fp, x, sg, infos, midx, mbq, reps=3):
     return res
 
 
+def scan_query(torch, fp, x, centres, radius, k):
+    """The ball query by a scan of all points, whichever route fp.ball_query takes at this size."""
+    idx = torch.empty((x.shape[0], centres.shape[1], k), dtype=torch.int32, device=x.device)
+    cnt = torch.empty(centres.shape, dtype=torch.int32, device=x.device)
+    status = fp.load().fp_ball_query(x.data_ptr(), x.shape[0], x.shape[1], centres.data_ptr(), centres.shape[1], float(radius),
+                                     k, idx.data_ptr(), cnt.data_ptr(), None, torch.cuda.current_stream().cuda_stream)
+    if status != 0:
+        raise RuntimeError("fp_ball_query: %d" % status)
+    return idx, cnt
+
+
+def all_pairs_knn(torch, fp, x, samples, k):
+    """The k nearest samples by comparing all pairs, whichever route fp.knn takes at this size."""
+    pos = torch.empty((x.shape[0], x.shape[1], k), dtype=torch.int32, device=x.device)
+    d2 = torch.empty(pos.shape, dtype=torch.float32, device=x.device)
+    status = fp.load().fp_knn(x.data_ptr(), x.shape[0], x.shape[1], samples.data_ptr(), samples.shape[1], k, pos.data_ptr(),
+                              d2.data_ptr(), None, None, None, 0, torch.cuda.current_stream().cuda_stream)
+    if status != 0:
+        raise RuntimeError("fp_knn: %d" % status)
+    return pos, d2
+
+
 def time_knn(torch, fp, x, sg, midx, reps=3):
-    """k nearest MDPS samples of every point of a stage: brute force and through the recorded
-    ball bitmaps (both give the same result; checked here).  Not part of the timed step."""
+    """k nearest MDPS samples of every point of a stage: without a record (fp.knn's own route), by all pairs and through
+    the recorded ball bitmaps (all give the same result; checked here).  Not part of the timed step."""
     res = {}
     kcache = sg["cache"]
     if sg["pruned_record"]:
@@ -573,25 +597,13 @@ def time_knn(torch, fp, x, sg, midx, reps=3):
         # with the index-ordered sampler (its samples are those of the same constants with scan order 0)
         kcache = torch.empty_like(sg["cache"])
         midx = fp.mdps_sample(x, midx.shape[1], sg["prm"], bq_cache=kcache, bq_radius=sg["radius"])
-    for kname, cache in (("knn_brute", None), ("knn_cached", kcache)):
-        fp.knn(x, midx, KNN_K, bq_cache=cache)
-        torch.cuda.synchronize()
-        best = None
-        for _ in range(reps):
-            a = torch.cuda.Event(enable_timing=True)
-            b = torch.cuda.Event(enable_timing=True)
-            a.record()
-            out = fp.knn(x, midx, KNN_K, bq_cache=cache, want_deferred=cache is not None)
-            b.record()
-            torch.cuda.synchronize()
-            t = a.elapsed_time(b)
-            best = t if best is None else min(best, t)
-        res[kname + "_ms"] = best
-        res[kname] = out
-    same = torch.equal(res["knn_brute"][0], res["knn_cached"][0]) and \
-        torch.equal(res["knn_brute"][1], res["knn_cached"][1])
-    if not same:
-        raise RuntimeError("redundancy-free k-NN differs from the brute-force result")
+    for kname, call in (("knn", lambda: fp.knn(x, midx, KNN_K)), ("knn_all_pairs", lambda: all_pairs_knn(torch, fp, x, midx, KNN_K)),
+                        ("knn_cached", lambda: fp.knn(x, midx, KNN_K, bq_cache=kcache, want_deferred=True))):
+        res[kname + "_ms"], res[kname] = time_call(torch, call, reps)
+    res["pairs"] = res["knn_all_pairs"]
+    for kname in ("knn", "knn_cached"):
+        if not (torch.equal(res["pairs"][0], res[kname][0]) and torch.equal(res["pairs"][1], res[kname][1])):
+            raise RuntimeError(kname + " differs from the brute-force result")
     res["deferred_fraction"] = float(res["knn_cached"][2].sum().item()) / (x.shape[0] * x.shape[1])
     res["samples"] = midx
     res["cache"] = kcache
@@ -749,13 +761,13 @@ def other_workloads(name, detail_file):
 
 
 def path_summary(wl, detail, ms_per_step, launch_mode, roof):
-    """The short entry of one workload: time of the exact path (fps_exact + brute-force ball query
+    """The short entry of one workload: time of the exact path (fps_exact + ball query without a record
     [+ gather of the next stage's input]) and of the FastPoint path (mdps_sample recording the
     radius tests + ball query from the record), summed over the stages, each kernel timed alone."""
     exact = fast = fast_grid = best = 0.0
     for st in detail["stages"]:
         ms = st["kernel_ms"]
-        exact += ms["fps_exact"] + ms["ball_query_brute"] + ms.get("gather", 0.0)
+        exact += ms["fps_exact"] + ms["ball_query"] + ms.get("gather", 0.0)
         fast += ms["mdps_sample+record"] + ms["ball_query_cached"]
         # the same samples and neighbours without the record: plain MDPS, then the grid ball query
         fast_grid += ms["mdps_sample"] + ms["ball_query_grid"]
@@ -808,7 +820,7 @@ def run(args, torch, fp, inputs, calibration, extra, clock_reader=None):
     s0 = detail["stages"][0]
     # dominant kernel of the step: the one with the largest share of the time
     in_step = [kname for kname in s0["roofline"]
-               if kname in ("fps_exact", "mdps_sample+record", "ball_query_brute", "ball_query_cached")]
+               if kname in ("fps_exact", "mdps_sample+record", "ball_query", "ball_query_cached")]
     dom = max(in_step, key=lambda kname: s0["kernel_ms"].get(kname, 0.0))
     roof = dict(s0["roofline"][dom])
     roof["kernel"] = dom + " (stage 0)"
