@@ -65,3 +65,20 @@ def test_prefix_either_side_of_the_sweeps(fp, N, n, order):
     wanted = scan(fp, x, want, 0.1, 16)
     got = fp.ball_query(x, want, 0.1, 16, bq_cache=cache)
     assert torch.equal(got[0], wanted[0]) and torch.equal(got[1], wanted[1])
+
+
+@pytest.mark.parametrize("places", [1, 6, 7, 12, 13, 27, 60])
+def test_a_far_point_leaves_few_cells(fp, places):
+    """Waves whose points share that many cells, and a last wave that is not full: the sort into cells loses no point."""
+    N, n = 5185, 1600
+    rng = np.random.default_rng(places)
+    x = rng.random((2, N, 3)).astype(np.float32)
+    x[..., 0] += 15.625 * rng.integers(0, places, (2, N))
+    x[:, N // 3, 0] = 1000.0
+    x = torch.from_numpy(x).cuda()
+    want = exact_by_index(fp, x, n)
+    assert torch.equal(in_cells(fp, x, lambda: fp.fps_exact_pruned(x, n)), want) and torch.equal(fp.fps_exact(x, n), want)
+    c = want[:, ::7].contiguous()
+    for r in (0.05, 0.3):
+        for a, b in zip(fp.ball_query_grid(x, c, r, 16), scan(fp, x, c, r, 16)):
+            assert torch.equal(a, b)
