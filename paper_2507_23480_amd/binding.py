@@ -498,9 +498,9 @@ def ball_query_grid(xyz: torch.Tensor, center_idx: torch.Tensor, radius: float, 
 # thirteen launches cost more than comparing all pairs.  All pairs / grid, us, samples of exact FPS, k = 3: 16 clouds of
 # 1024 points and 512 samples 74 / 93; 4096 and 1024: 130 / 105; 8 x 24000 and 6000: 600 / 119; 4 x 120000 and
 # 16384: 1400 / 285; a million and 65536: 11276 / 470.  k = 8, 8 x 24000 and 1100: 160 / 184, 2000: 254 / 170.
-# Other samples gain less or lose.  4 x 120000 points of a scanner, k = 3, samples taken at random: 16384: 1440 / 730,
-# 4096: 405 / 415, 1024: 135 / 200; samples of one corner only, 4096: 680 / 1050; 95 % of the samples in a clump
-# (8 x 24000): 1100: 151 / 200, 6000: 905 / 980.
+# Other samples gain less or lose.  4 x 120000 points of a scanner, k = 3, samples taken at random: 16384: 1420 / 731,
+# 4096: 384 / 296, 1024: 122 / 167 (k = 8, 4096: 480 / 966); the first of each cloud, which lie together: 16384: 2074 / 2778,
+# 4096: 628 / 982, 1024: 211 / 460; 95 % of the samples in a clump (8 x 24000): 1100: 146 / 178, 6000: 880 / 933.
 KNN_SEARCH_FROM = (1024, 4096)
 KNN_SEARCH_FROM_MANY = 2048
 

@@ -85,7 +85,9 @@ constexpr int kOneWgPoints = 2048;
 // (MDPS, lowest index first, on rooms of 60000 points and more: 1.1-2.1 up to 3000 samples; 65536 of a million
 // clustered points 0.3.)  Where a batch leaves a cloud one or two workgroups, which then work out the relations of all
 // candidates among themselves, the line of exact FPS lies twice as high (256 x 6000 points, index-ordered / cell-ordered,
-// us: 1500 samples 771 / 971, 3000: 1474 / 1398).  A cloud with 95 % of its points in a clump is 1.0-1.4 at 1500 samples, 0.8-1.2 at 3000.
+// us: 1500 samples 771 / 971, 3000: 1474 / 1398).  Scanner clouds are 1.09-1.19 at 1500 samples (exact FPS), 0.91-1.04 at
+// 3000; a cloud with 95 % of its points in a clump 1.1-1.4 and 0.8-1.2; one with a far point 1.1-1.3 and 0.9-1.1 (of a
+// million points, whose counters then queue up, 1.4-2.0 and 1.2-1.4).
 // fp_fps_exact takes the cell order from kCellOrderFrom points on, when its workspace has room for it; the _pruned
 // entry points leave it below kCellOrderSamples, and for clouds that one workgroup holds.  A call with a record keeps
 // its entry point's layout: it is the order of the record's blocks.
