@@ -31,7 +31,7 @@ def scene(kind, N, rng):
 
 @pytest.mark.parametrize("kinds", [("wide",), ("far_point",), ("one_place",), ("odd",), ("wide", "spread", "far_point"),
                                    ("spread", "wide")])
-@pytest.mark.parametrize("N", [1, 63, 300, 5200, 13001])
+@pytest.mark.parametrize("N", [1, 63, 300, 4096, 4097, 5200, 13001])
 def test_same_bytes(fp, kinds, N):
     rng = np.random.default_rng([len(kinds), N])
     B = len(kinds)
