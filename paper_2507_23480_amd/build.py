@@ -13,7 +13,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfastpoint_hip.so")
 # (source, points per thread): the sampler is compiled once per number of points a thread holds
-SOURCES = [("sampler.hip", p) for p in (16, 8, 4, 2)] + [(f, 0) for f in ("ball_query.hip", "knn.hip", "excl_lists.hip", "abi.hip")]
+SOURCES = [("sampler.hip", p) for p in (16, 8, 4, 2)] + [(f, 0) for f in ("local_sampler.hip", "ball_query.hip", "knn.hip", "excl_lists.hip", "abi.hip")]
 FLAGS = ["--offload-arch=gfx950", "-O3", *os.environ.get("FASTPOINT_EXTRA_FLAGS", "").split(), "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-function"]

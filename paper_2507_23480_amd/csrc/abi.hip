@@ -30,6 +30,14 @@ constexpr int64_t kLlCdWords = (int64_t)2 * kMaxGroup * kCandMax * kCandWords;
 constexpr int64_t kLlCtWords = (int64_t)2 * kMaxGroup;
 constexpr int64_t kLlWords = kLlPkWords + kLlCdWords + kLlCtWords;
 constexpr size_t kExchangeBytes = (size_t)(kLlWords * 8);                         // 2 658 304 bytes
+// ... and the words of the sampler by local decisions in the same place
+constexpr int64_t kLocalHdrWords = (int64_t)4 * kMaxGroup;
+constexpr int64_t kLocalMaskAll = (int64_t)2 * kMaxGroup * kLocalMaskWords;
+constexpr int64_t kLocalWords = kLlPkWords + kLocalHdrWords + kLocalMaskAll;
+static_assert(kLocalWords <= kLlWords, "the exchange words of one sampler or the other");
+// ... the candidates it publishes, behind the sorted cloud
+constexpr int64_t kLocalWgWords = (int64_t)4 * (kLocalOwn + 1) * kLocalCandWords;
+constexpr size_t kLocalListBytes = (size_t)(kMaxGroup * kLocalWgWords * 8);
 
 // Scratch of fp_fps_exact_static: the same exchange words, but in device memory that belongs to
 // the library's code object instead of a caller's workspace, so that the call allocates nothing.
@@ -206,7 +214,58 @@ int64_t rel_exchange_bytes(int32_t B)
 #endif
 }
 
+// Candidates of a round of the sampler by local decisions: every workgroup decides a share of the list, so a longer one
+// saves rounds where many share it and costs more than it saves where few do.  fps_exact, us, at lists of 500 / 1000 / 1500 /
+// 2000 / 3000 / 4096: 8 x 24000 -> 6000 (24 workgroups a cloud) 576 / 542 / 562 / 667 / 867 / 1127; 4 x 120000 -> 16384 (64)
+// 1426 / 1119 / 1061 / 1040 / 1067 / 1153; 1000000 -> 65536 (245) 3248 / 2300 / 1949 / 1839 / 1734 / 1710.  (At most 32 units of
+// eight candidates a workgroup, which is what it can publish.)
+int local_aim(int G)
+{
+    const int aim = 256 + 32 * G, most = G > 1 && 256 * G < kLocalList ? 256 * G : kLocalList;
+    return aim < most ? aim : most;
+}
+
 int64_t scan_walk_bytes(int32_t B, int32_t N) { return align_up((int64_t)B * N * (int64_t)sizeof(float4), 256); }
+
+// Exact FPS in cell order: the sort, the sampler by local decisions, the samples put in sequence.  `a`: what the
+// samplers share; workspace of fp_fps_pruned_workspace_bytes.
+fp_status run_local(const SamplerArgs& s, const Plan& plan, void* workspace, hipStream_t stream)
+{
+    void* sort_ws = reinterpret_cast<unsigned char*>(workspace) + kExchangeBytes;
+    if (launch_spatial_sort(s.xyz, s.B, s.N, sort_ws, stream) != hipSuccess) return FP_ERR_DEVICE;
+    LocalArgs a;
+    memset(&a, 0, sizeof(a));
+    a.xyz = s.xyz;
+    a.start_idx = s.start_idx;
+    a.sorted = spatial_sorted(s.B, s.N, sort_ws);
+    a.found = spatial_sort_spare(s.B, s.N, sort_ws);
+    a.info = s.info;
+    a.B = s.B;
+    a.N = s.N;
+    a.n = s.n;
+    a.G = plan.G;
+    a.aim = local_aim(plan.G);
+    while ((plan.G << (a.own_shift + 1)) <= kLocalThreads) ++a.own_shift;
+    a.ll_pk = reinterpret_cast<uint64_t*>(workspace);
+    a.ll_hdr = a.ll_pk + kLlPkWords;
+    a.ll_mask = a.ll_hdr + kLocalHdrWords;
+    a.ll_list = reinterpret_cast<uint64_t*>(reinterpret_cast<unsigned char*>(sort_ws) + spatial_sort_bytes(s.B, s.N));
+    a.wait_ticks = s.wait_ticks;
+    const void* fn = local_fps_kernel_for(plan.T * plan.P / kLocalThreads);
+    if (!fn) return FP_ERR_SHAPE;
+    void* kargs[] = {&a};
+    const dim3 grid((unsigned)(plan.groups * plan.G)), block((unsigned)kLocalThreads);
+    hipError_t err;
+    if (plan.G > 1) {
+        if (launch_zero_words(a.ll_pk, kLocalWords, a.ll_list, (int64_t)plan.groups * plan.G * kLocalWgWords, nullptr, 0,
+                              stream) != hipSuccess)
+            return FP_ERR_DEVICE;
+    }
+    if (plan.G > 1 && g_cooperative.load()) err = hipLaunchCooperativeKernel(fn, grid, block, kargs, 0, stream);
+    else err = hipLaunchKernel(fn, grid, block, kargs, 0, stream);
+    if (err == hipSuccess) err = launch_order_samples(a.found, s.start_idx, s.B, s.n, s.out_idx, s.out_mdc, stream);
+    return err == hipSuccess ? FP_OK : FP_ERR_DEVICE;
+}
 
 fp_status run_sampler(const float* xyz, int32_t B, int32_t N, int32_t n, const int32_t* start_idx,
                       const fp_mdps_params* prm, int32_t* out_idx, float* out_mdc, fp_mdps_info* info,
@@ -294,6 +353,7 @@ fp_status run_sampler(const float* xyz, int32_t B, int32_t N, int32_t n, const i
     a.ll_ct = a.ll_cd + kLlCdWords;
     a.wait_ticks = g_wait_limit_us.load() * di.wall_khz / 1000;
 
+    if (pruned && !prm) return run_local(a, plan, workspace, stream);
     if (pruned) {
         // the cloud in cell order, behind the exchange words
         void* sort_ws = reinterpret_cast<unsigned char*>(workspace) + kExchangeBytes;
@@ -430,7 +490,8 @@ size_t fp_mdps_scattered_workspace_bytes(int32_t B, int32_t N)
 size_t fp_fps_pruned_workspace_bytes(int32_t B, int32_t N)
 {
     if (B < 1 || N < 1 || B > 65535 || (int64_t)B * N > ((int64_t)1 << 33)) return 0;
-    return kExchangeBytes + (size_t)spatial_sort_bytes(B, N) + (size_t)rel_exchange_bytes(B);
+    const size_t rel = (size_t)rel_exchange_bytes(B);
+    return kExchangeBytes + (size_t)spatial_sort_bytes(B, N) + (rel > kLocalListBytes ? rel : kLocalListBytes);
 }
 
 fp_status fp_fps_exact_pruned(const float* xyz, int32_t B, int32_t N, int32_t n, const int32_t* start_idx,

@@ -1669,6 +1669,12 @@ const float4* spatial_sorted(int B, int N, const void* workspace)
                                            excl_layout(B, N, 1).sorted_off);
 }
 
+// (the counts and starts of the cells, side by side: four bytes per cell and at least N cells each)
+uint64_t* spatial_sort_spare(int B, int N, void* workspace)
+{
+    return reinterpret_cast<uint64_t*>(reinterpret_cast<unsigned char*>(workspace) + excl_layout(B, N, 1).cnt_off);
+}
+
 hipError_t launch_spatial_sort(const float* xyz, int B, int N, void* workspace, hipStream_t stream)
 {
     const ExclLayout lay = excl_layout(B, N, 1);

@@ -122,6 +122,32 @@ struct SamplerArgs {
     uint64_t walk_inv;              // scattered scan order on cell-ordered records: 1/A mod N (place t of index j = j/A mod N)
 };
 
+// Exact FPS by local decisions (local_sampler.hip).
+constexpr int kLocalThreads = 1024;     // of a workgroup
+constexpr int kLocalList = 4096;        // candidates of a round
+constexpr int kLocalOwn = 191;          // ... of half a workgroup
+constexpr int kLocalCandWords = 3;      // words of a published candidate
+constexpr int kLocalMaskWords = 8;      // words of 32 decisions a workgroup publishes
+constexpr int kOrderMost = 4096;        // keys a workgroup puts in order
+struct LocalArgs {
+    const float* xyz;
+    const int32_t* start_idx;
+    const float4* sorted;               // [B][N] records (x, y, z, index bits) in cell order
+    uint64_t* found;                    // [B][n]: [0] status and number of samples, then the samples, in no order
+    fp_mdps_info* info;
+    int32_t B, N, n, G;
+    int32_t aim;                        // candidates a round takes at most
+    int32_t own_shift;                  // 2^own_shift threads of a workgroup per workgroup of the cloud
+    uint64_t* ll_pk;                    // [groups][2][G][kLlSlotWords]
+    uint64_t* ll_hdr;                   // [groups][2][2 G] counts
+    uint64_t* ll_mask;                  // [groups][2][G][kLocalMaskWords] decisions
+    uint64_t* ll_list;                  // [groups][2][2 G][kLocalOwn + 1][kLocalCandWords] candidates
+    int64_t wait_ticks;
+};
+const void* local_fps_kernel_for(int points_per_thread);
+hipError_t launch_order_samples(const uint64_t* found, const int32_t* start_idx, int B, int n, int32_t* out_idx,
+                                float* out_mdc, hipStream_t stream);
+
 struct Plan {
     int G, T, P;        // workgroups per cloud, threads per workgroup, points per thread
     int groups;         // clouds resident at once
@@ -191,6 +217,8 @@ ExclLayout excl_layout(int B, int N, int L);
 hipError_t launch_spatial_sort(const float* xyz, int B, int N, void* workspace, hipStream_t stream);
 int64_t spatial_sort_bytes(int B, int N);
 const float4* spatial_sorted(int B, int N, const void* workspace);
+// Room for [B][N] 64-bit words in the same workspace that the sorted records do not need (N up to 2^21).
+uint64_t* spatial_sort_spare(int B, int N, void* workspace);
 hipError_t launch_excl_count(const float* xyz, int B, int N, const float* thr2, int L, int64_t* offsets,
                              void* workspace, hipStream_t stream);
 hipError_t launch_excl_fill(const float* xyz, int B, int N, const float* thr2, int L, const int64_t* offsets,

@@ -1,0 +1,1015 @@
+// Exact farthest point sampling (Algorithm 1 of FastPoint, arXiv 2507.23480) by local decisions, for gfx950.
+//
+// The sequence of Alg. 1 is found without following it.  d_i is a point's squared distance to the samples found
+// so far.  Say k comes before i when d_k > d_i, or d_k == d_i and k has the lower index.  Then
+//
+//   * i is a sample, found at distance d_i, as soon as no point that comes before it lies closer to it than d_i:
+//     distances only fall, so whatever Alg. 1 takes before i comes before i now, and leaves d_i as it is;
+//   * a sample k found at v_k lowers a point j to dist(j, k) exactly when dist(j, k) < min(d_j, v_k).  (If dist(j, k)
+//     >= v_k, every distance is at most v_k <= dist(j, k) by the time Alg. 1 takes k.  If dist(j, k) < v_k and Alg. 1
+//     took j before k, j would come before k now and k would have waited.)
+//   * Alg. 1 takes the samples in the order (v descending, index ascending).
+//
+// So all points that are the first of their own neighbourhood are taken at once, wherever they lie, and the
+// samples are put in sequence at the end (order_samples_kernel).  A round looks at the candidates, all points
+// with d > tau; tau falls as the list has room.  To end with exactly n samples a candidate is only taken
+// when the candidates that come before it leave room for it.
+//
+// One cloud is held by G workgroups for the whole call, points and distances in registers, in the order of a Hilbert
+// curve.  Per round:
+//   scan     every workgroup counts its points above four falling levels of tau and publishes the counts and the
+//            points, the ones above the highest level first;
+//   list     all workgroups read the counts, agree on the lowest level at which the list fits (the first level is the
+//            last round's tau, whose list can only have got shorter), and fetch that list into LDS, with a box around
+//            every 64 candidates (neighbours in the list are neighbours along the curve);
+//   decide   each workgroup takes an equal share of the list, a wave per candidate, which is compared with the chunks
+//            whose box it reaches; the decisions, one bit per candidate, go to the other workgroups;
+//   fold     every wave folds the samples near the boxes of its points.
+// Where the list does not help (many equal distances, infinities) one sample is taken by a plain arg-max.
+//
+// Bound: latency.  A round takes 10 us on 24 workgroups, 15 on 245: three trips through memory (counts, list, decisions) of
+// 1.2-2 us each, and the rest of its parts 1-2 us each.  The rounds are as many as the samples' dependences are deep:
+// 40, 65 and 94 for the workloads below, against 82, 207 and 436 rounds of 256 candidates settled in sweeps before.
+// fps_exact_pruned, us, before -> now: million points -> 65536 5190 -> 1720, 4 x 120000 -> 16384 2750 -> 1020,
+// 8 x 24000 -> 6000 850 -> 540 (1024 threads; with 512 and twice the points per thread 1880, 1100, 530).
+// Comparing a candidate with the whole list instead of the chunks near it took 10-20 us a round.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "kernels.h"
+#include "wave.h"
+
+#pragma clang fp contract(off)
+
+namespace fastpoint {
+namespace {
+
+constexpr int kT = kLocalThreads, kNW = kT / 64, kHW = kNW / 2;
+constexpr int kList = kLocalList;           // candidates of a round
+constexpr int kChunks = kList / 64;
+constexpr int kOwn = kLocalOwn;             // candidates half a workgroup lists
+constexpr int kWords = kLocalMaskWords;     // words of 32 decisions a workgroup publishes
+constexpr int kUnit = 8;                    // the list is dealt out in units of 8 candidates for the decisions
+constexpr int kLevels = 4;
+static_assert(kLocalList == 4096 && kOwn < 255, "8 bits for a count, 255: more than that");
+static_assert(kChunks == 64, "a lane per chunk");
+
+struct LocalShared {
+    float4 cand[kList];                     // x, y, z, index bits
+    uint32_t dist[kList];                   // zero behind the last candidate, to the end of its chunk
+    float box[7][kChunks];                  // per chunk of 64 candidates: lower corner, upper corner, largest distance
+    uint64_t took[kChunks];                 // the round's samples, a bit per candidate
+    uint64_t wcnt[kNW];                     // per wave: points above each level, 16 bits each
+    int32_t inc[2][2 * kMaxGroup];          // sums of the halves' counts inside 64 of them, two levels in a word
+    int32_t tot[2][kMaxGroup / 32];
+    uint32_t full[kMaxGroup / 32];
+    uint32_t acc[kList / 32];               // decisions on the candidates of this workgroup's part of the list
+    int32_t fail;
+    Rec wrec[2][kNW];
+    Rec win[2];
+};
+
+struct Box {
+    float lox, loy, loz, hix, hiy, hiz;
+};
+
+template <int P>
+struct Held {
+    float x[P], y[P], z[P], d[P];
+    uint32_t oi[P];                         // index in the caller's cloud
+    Box a, b;                               // boxes of the wave's points, before and behind the widest gap in their run
+    float ub;                               // largest distance among them
+};
+
+#ifdef FASTPOINT_PHASE_CLOCKS
+__shared__ long long clk[16];               // tuning builds: ticks of thread 0 in the parts of a round, in info.thr2
+__shared__ long long clk_at;
+#define MARK(k) do { if (threadIdx.x == 0) { const long long now__ = wall_clock64(); clk[k] += now__ - clk_at; clk_at = now__; } } while (0)
+#else
+#define MARK(k) do { } while (0)
+#endif
+
+// Half a workgroup, its first or last kHW waves, holds 512 P records that follow each other; the halves of a workgroup lie half
+// the cloud apart (space is filled unevenly, and a workgroup is as slow as its busiest waves).
+struct Seat {
+    int tid, lane, w, g, G, grp, c;
+    int half;                               // half of the cloud's 2 G the wave belongs to: its place along the curve
+};
+
+// Evaluated like dist2 with the nearest box coordinate per axis: rounding is monotone, so no point of the box is closer.
+__device__ __forceinline__ float sum_sq(float dx, float dy, float dz)
+{
+    float t = dx * dx;
+    t = t + dy * dy;
+    t = t + dz * dz;
+    return t;
+}
+__device__ __forceinline__ float box_dist2(const Box& h, float cx, float cy, float cz)
+{
+    return sum_sq(fmaxf(fmaxf(h.lox - cx, cx - h.hix), 0.0f), fmaxf(fmaxf(h.loy - cy, cy - h.hiy), 0.0f),
+                  fmaxf(fmaxf(h.loz - cz, cz - h.hiz), 0.0f));
+}
+__device__ __forceinline__ float box_box2(const Box& h, const Box& o)
+{
+    return sum_sq(fmaxf(fmaxf(h.lox - o.hix, o.lox - h.hix), 0.0f), fmaxf(fmaxf(h.loy - o.hiy, o.loy - h.hiy), 0.0f),
+                  fmaxf(fmaxf(h.loz - o.hiz, o.loz - h.hiz), 0.0f));
+}
+// floats as integers of the same order
+__device__ __forceinline__ uint32_t f2ord(float v)
+{
+    const uint32_t u = __float_as_uint(v);
+    return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+}
+__device__ __forceinline__ float ord2f(uint32_t u)
+{
+    return __uint_as_float(u ^ ((u >> 31) != 0 ? 0x80000000u : 0xFFFFFFFFu));
+}
+// smallest and largest of the lanes' values, over those that count
+__device__ __forceinline__ void wave_range(float v, bool counts, float& lo, float& hi)
+{
+    const uint32_t u = f2ord(v);
+    lo = ord2f(wave_min_u32(counts ? u : 0xFF800000u));     // +inf
+    hi = ord2f(wave_max_u32(counts ? u : 0x007FFFFFu));     // -inf
+}
+
+// (a distance that is not a number is larger than any other as an integer: such a point keeps its distance)
+template <int P>
+__device__ __forceinline__ void fold(Held<P>& h, float cx, float cy, float cz, float v)
+{
+    if (v >= h.ub) {                        // uniform: no distance of the wave exceeds v
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const uint32_t t = __float_as_uint(dist2(cx, cy, cz, h.x[p], h.y[p], h.z[p]));
+            h.d[p] = __uint_as_float(min(__float_as_uint(h.d[p]), t));
+        }
+    } else {
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const float t = dist2(cx, cy, cz, h.x[p], h.y[p], h.z[p]);
+            const float m = __uint_as_float(min(__float_as_uint(h.d[p]), __float_as_uint(t)));
+            h.d[p] = t < v ? m : h.d[p];
+        }
+    }
+}
+
+template <int P>
+__device__ __forceinline__ void refresh_bound(Held<P>& h)
+{
+    uint32_t m = __float_as_uint(h.d[0]);   // distances are >= +0: unsigned order
+#pragma unroll
+    for (int p = 1; p < P; ++p) m = max(m, __float_as_uint(h.d[p]));
+    h.ub = __uint_as_float(wave_max_u32(m));
+}
+
+// Loads the wave's points and finds their boxes.  (Where the curve leaves a thin layer of occupied cells and comes back
+// elsewhere, one box would span the cloud and the wave would fold every sample: 7000 to 10000 of 16384 instead of
+// some 400 for one or two waves of a LiDAR sweep.)
+template <int P>
+__device__ __forceinline__ void load_points(Held<P>& h, const Seat& me, const LocalArgs& a)
+{
+    const float4* __restrict__ rec = a.sorted + (int64_t)me.c * a.N;
+    const int base = (me.half * kHW + (me.w & (kHW - 1))) * P * 64;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int j = base + p * 64 + me.lane;
+        h.x[p] = h.y[p] = h.z[p] = kPadCoord;
+        h.oi[p] = kNoIdx;
+        h.d[p] = 0.0f;
+        if (j < a.N) {
+            const float4 r = rec[j];
+            h.x[p] = r.x;
+            h.y[p] = r.y;
+            h.z[p] = r.z;
+            h.oi[p] = __float_as_uint(r.w);
+            h.d[p] = __builtin_inff();
+        }
+    }
+    // the widest gap between two records that follow each other
+    uint32_t gap = 0, at = 0;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        float nx = __shfl_down(h.x[p], 1), ny = __shfl_down(h.y[p], 1), nz = __shfl_down(h.z[p], 1);
+        const int q = p + 1 < P ? p + 1 : p;
+        if (me.lane == 63) {
+            nx = rdlane_f(h.x[q], 0);
+            ny = rdlane_f(h.y[q], 0);
+            nz = rdlane_f(h.z[q], 0);
+        }
+        const int j = base + p * 64 + me.lane;
+        const uint32_t t = __float_as_uint(dist2(h.x[p], h.y[p], h.z[p], nx, ny, nz));
+        if (j + 1 < a.N && (me.lane < 63 || p + 1 < P) && t > gap) {
+            gap = t;
+            at = (uint32_t)(p * 64 + me.lane);
+        }
+    }
+    const uint32_t widest = wave_max_u32(gap);
+    const uint32_t cut = rdlane(at, first_lane(__builtin_amdgcn_ballot_w64(gap == widest)));
+    uint32_t lo[2][3], hi[2][3];
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            lo[s][k] = 0xFF800000u;
+            hi[s][k] = 0x007FFFFFu;
+        }
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const uint32_t c[3] = {f2ord(h.x[p]), f2ord(h.y[p]), f2ord(h.z[p])};
+        const bool in = base + p * 64 + me.lane < a.N, second = (uint32_t)(p * 64 + me.lane) > cut;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            if (in && !second) {
+                lo[0][k] = min(lo[0][k], c[k]);
+                hi[0][k] = max(hi[0][k], c[k]);
+            }
+            if (in && second) {
+                lo[1][k] = min(lo[1][k], c[k]);
+                hi[1][k] = max(hi[1][k], c[k]);
+            }
+        }
+    }
+    h.a.lox = ord2f(wave_min_u32(lo[0][0]));
+    h.a.loy = ord2f(wave_min_u32(lo[0][1]));
+    h.a.loz = ord2f(wave_min_u32(lo[0][2]));
+    h.a.hix = ord2f(wave_max_u32(hi[0][0]));
+    h.a.hiy = ord2f(wave_max_u32(hi[0][1]));
+    h.a.hiz = ord2f(wave_max_u32(hi[0][2]));
+    h.b.lox = ord2f(wave_min_u32(lo[1][0]));
+    h.b.loy = ord2f(wave_min_u32(lo[1][1]));
+    h.b.loz = ord2f(wave_min_u32(lo[1][2]));
+    h.b.hix = ord2f(wave_max_u32(hi[1][0]));
+    h.b.hiy = ord2f(wave_max_u32(hi[1][1]));
+    h.b.hiz = ord2f(wave_max_u32(hi[1][2]));
+}
+
+// One iteration of Alg. 1 on up-to-date distances: arg-max over the cloud, lowest index among equals.
+template <int P>
+__device__ __forceinline__ Rec plain_pick(const Held<P>& h, LocalShared& sh, const Seat& me, const LocalArgs& a,
+                                          uint32_t& it, uint32_t& seq)
+{
+    uint32_t bits = __float_as_uint(h.d[0]), boi = h.oi[0];
+    float bx = h.x[0], by = h.y[0], bz = h.z[0];
+#pragma unroll
+    for (int p = 1; p < P; ++p) {
+        const uint32_t v = __float_as_uint(h.d[p]);
+        if (v > bits || (v == bits && h.oi[p] < boi)) {
+            bits = v;
+            boi = h.oi[p];
+            bx = h.x[p];
+            by = h.y[p];
+            bz = h.z[p];
+        }
+    }
+    Rec r;
+    r.d = bits;
+    r.idx = boi;
+    r.x = bx;
+    r.y = by;
+    r.z = bz;
+    r.fail = r.pad0 = r.pad1 = 0;
+    r = reduce_recs(r, true);
+    const int buf = (int)(it & 1u);
+    ++it;
+    if (me.lane == 0) sh.wrec[buf][me.w] = r;
+    __syncthreads();
+    r = reduce_recs(sh.wrec[buf][me.lane < kNW ? me.lane : 0], me.lane < kNW);
+    if (me.G == 1) return r;
+    ++seq;
+    if (me.w == 0) {
+        uint64_t* base = a.ll_pk + ((int64_t)(me.grp * 2 + (int)(seq & 1u)) * me.G) * kLlSlotWords;
+        uint32_t v = r.d;
+        v = me.lane == 1 ? r.idx : v;
+        v = me.lane == 2 ? __float_as_uint(r.x) : v;
+        v = me.lane == 3 ? __float_as_uint(r.y) : v;
+        v = me.lane == 4 ? __float_as_uint(r.z) : v;
+        if (me.lane < 5) ll_store(base + (int64_t)me.g * kLlSlotWords + me.lane, v, seq);
+        Rec best = {};
+        best.idx = kNoIdx;
+        bool have = false;
+        for (int t = me.lane; t < me.G; t += 64) {
+            uint32_t val[5];
+            if (!ll_wait<5>(base + (int64_t)t * kLlSlotWords, seq, val, a.wait_ticks)) {
+                best.fail = 1;
+            } else if (!have || val[0] > best.d || (val[0] == best.d && val[1] < best.idx)) {
+                best.d = val[0];
+                best.idx = val[1];
+                best.x = __uint_as_float(val[2]);
+                best.y = __uint_as_float(val[3]);
+                best.z = __uint_as_float(val[4]);
+            }
+            have = true;
+        }
+        const Rec all = reduce_recs(best, have);
+        if (me.lane == 0) sh.win[buf] = all;
+    }
+    __syncthreads();
+    return sh.win[buf];
+}
+
+// A published candidate: three words with a stamp of 14 bits each around distance (31 bits, it is not negative),
+// coordinates and index (21 bits).  The stamp is never 0 and does not come twice within kWipeRounds rounds, after which
+// the words are cleared.
+constexpr int kCandWords3 = kLocalCandWords;
+constexpr uint32_t kWipeRounds = 0x3FFFu;
+static_assert(kMaxGroup * 8192 <= 1 << 21, "21 bits for an index");
+constexpr int64_t kHalfWords = (int64_t)(kOwn + 1) * kCandWords3;
+__device__ __forceinline__ uint64_t* half_list(const LocalArgs& a, const Seat& me, int par, int half)
+{
+    return a.ll_list + ((int64_t)(me.grp * 2 + par) * (2 * me.G) + half) * kHalfWords;
+}
+__device__ __forceinline__ void word_store(uint64_t* p, uint64_t v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void cand_store(uint64_t* p, uint32_t stamp, float x, float y, float z, uint32_t idx, uint32_t d)
+{
+    const uint64_t st = (uint64_t)stamp << 50;
+    const uint32_t yb = __float_as_uint(y);
+    word_store(p, st | ((uint64_t)(idx & 0x7FFFFu) << 31) | d);
+    word_store(p + 1, st | ((uint64_t)(yb >> 14) << 32) | __float_as_uint(x));
+    word_store(p + 2, st | ((uint64_t)(yb & 0x3FFFu) << 34) | ((uint64_t)(idx >> 19) << 32) | __float_as_uint(z));
+}
+__device__ __forceinline__ bool cand_wait(const uint64_t* p, uint32_t stamp, uint64_t (&v)[kCandWords3], int64_t wait_ticks)
+{
+    int64_t t0 = 0;
+    for (uint32_t spin = 0; (uint32_t)(v[0] >> 50) != stamp || (uint32_t)(v[1] >> 50) != stamp || (uint32_t)(v[2] >> 50) != stamp;
+         ++spin) {
+        if ((spin & 63u) == 63u || wait_ticks <= 0) {
+            const int64_t now = (int64_t)wall_clock64();
+            if (t0 == 0) t0 = now;
+            else if (now - t0 > wait_ticks) return false;
+        }
+        __builtin_amdgcn_s_sleep(1);
+#pragma unroll
+        for (int k = 0; k < kCandWords3; ++k) v[k] = ll_load(p + k);
+    }
+    return true;
+}
+__device__ __forceinline__ float4 cand_unpack(const uint64_t (&v)[kCandWords3], uint32_t& d)
+{
+    d = (uint32_t)v[0] & 0x7FFFFFFFu;
+    const uint32_t idx = ((uint32_t)(v[0] >> 31) & 0x7FFFFu) | (((uint32_t)(v[2] >> 32) & 3u) << 19);
+    const uint32_t yb = (((uint32_t)(v[1] >> 32) & 0x3FFFFu) << 14) | ((uint32_t)(v[2] >> 34) & 0x3FFFu);
+    return make_float4(__uint_as_float((uint32_t)v[1]), __uint_as_float(yb), __uint_as_float((uint32_t)v[2]), __uint_as_float(idx));
+}
+
+// Box and largest distance of a chunk, whose candidates the lanes of a wave hold.
+// (Eight maxima over the wave at once: pairs of lanes share the eight values out, then groups of four lanes, so that
+// each lane reduces two of them over its row of 16; 50 instructions instead of 95 for one after the other.)
+__device__ __forceinline__ void chunk_box(LocalShared& sh, int chunk, int lane, const float4& c, uint32_t d, bool has)
+{
+    uint32_t v[8];
+    v[0] = f2ord(c.x);
+    v[1] = f2ord(c.y);
+    v[2] = f2ord(c.z);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        v[4 + k] = has ? v[k] : 0u;
+        v[k] = has ? ~v[k] : 0u;
+    }
+    v[3] = has ? d : 0u;
+    v[7] = 0u;
+    uint32_t r[4], q[2];
+    const bool odd = (lane & 1) != 0, upper = (lane & 2) != 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t keep = odd ? v[4 + k] : v[k], give = odd ? v[k] : v[4 + k];
+        r[k] = max(keep, dpp<0xB1>(give));              // quad_perm [1,0,3,2]
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const uint32_t keep = upper ? r[2 + k] : r[k], give = upper ? r[k] : r[2 + k];
+        q[k] = max(keep, dpp<0x4E>(give));              // quad_perm [2,3,0,1]
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        q[k] = max(q[k], dpp<0x124>(q[k]));             // row_ror:4
+        q[k] = max(q[k], dpp<0x128>(q[k]));             // row_ror:8
+        q[k] = max(q[k], (uint32_t)__shfl_xor((int)q[k], 16));
+        q[k] = max(q[k], (uint32_t)__shfl_xor((int)q[k], 32));
+    }
+    if (lane < 4) {
+        // lane 0: lower x, y; 2: lower z, distance; 1: upper x, y; 3: upper z
+        const int first = (odd ? 4 : 0) + (upper ? 2 : 0);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int e = first + k;
+            const float f = e < 3 ? ord2f(~q[k]) : (e == 3 ? __uint_as_float(q[k]) : ord2f(q[k]));
+            if (e != 7) sh.box[e < 3 ? e : (e == 3 ? 6 : e - 1)][chunk] = f;
+        }
+    }
+}
+__device__ __forceinline__ Box box_of_chunk(const LocalShared& sh, int chunk)
+{
+    return Box{sh.box[0][chunk], sh.box[1][chunk], sh.box[2][chunk], sh.box[3][chunk], sh.box[4][chunk], sh.box[5][chunk]};
+}
+
+// Scan and list of a round.  lv: four falling levels.  Returns the length of the list (-1: a wait expired) and the level
+// chosen.
+template <int P>
+__device__ __forceinline__ int make_list(const Held<P>& h, LocalShared& sh, const Seat& me, const LocalArgs& a,
+                                         uint32_t round, const float (&lv)[kLevels], int& level)
+{
+    uint32_t c[kLevels] = {};
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const uint64_t m = __builtin_amdgcn_ballot_w64(h.d[p] > lv[kLevels - 1]);
+        if (m != 0) {
+            c[kLevels - 1] += __builtin_popcountll(m);
+#pragma unroll
+            for (int j = 0; j < kLevels - 1; ++j) c[j] += __builtin_popcountll(__builtin_amdgcn_ballot_w64(h.d[p] > lv[j]));
+        }
+    }
+    if (me.lane == 0)
+        sh.wcnt[me.w] = (uint64_t)c[0] | ((uint64_t)c[1] << 16) | ((uint64_t)c[2] << 32) | ((uint64_t)c[3] << 48);
+    __syncthreads();
+    MARK(0);
+    if (me.tid < kList / 32) sh.acc[me.tid] = 0;            // (last looked at before the barrier)
+    if (me.tid < kChunks) sh.took[me.tid] = 0;
+    // a half's points above level j lie behind those above level j - 1, in the order of its waves (one workgroup for
+    // the cloud: no halves)
+    uint64_t sum = 0, before = 0;
+    const int w0 = me.G > 1 ? me.w & kHW : 0, w1 = me.G > 1 ? w0 + kHW : kNW;
+#pragma unroll
+    for (int k = 0; k < kNW; ++k) {
+        const uint64_t v = k >= w0 && k < w1 ? sh.wcnt[k] : 0;
+        sum += v;
+        if (k < me.w) before += v - (v << 16);
+    }
+    sum = uni64(sum);
+    const uint64_t start = uni64((sum << 16) + before);
+    uint32_t at[kLevels];
+    int tot[kLevels];
+#pragma unroll
+    for (int j = 0; j < kLevels; ++j) {
+        at[j] = (uint32_t)(start >> (16 * j)) & 0xFFFFu;
+        tot[j] = (int)((uint32_t)(sum >> (16 * j)) & 0xFFFFu);
+    }
+    const int par = (int)(round & 1u);
+    const int halves = 2 * me.G;
+    uint64_t* const hdr = a.ll_hdr + (int64_t)(me.grp * 2 + par) * halves;
+    const uint32_t stamp = ((round & kWipeRounds) >> 1) + 1u;
+    if (me.G > 1) {
+        if (me.lane == 0 && (me.w & (kHW - 1)) == 0) {
+            uint32_t v = 0;
+#pragma unroll
+            for (int j = 0; j < kLevels; ++j) v |= (uint32_t)(tot[j] <= kOwn ? tot[j] : 255) << (8 * j);
+            ll_store(hdr + me.half, v, round);
+        }
+        level = kLevels - 1;
+    } else {
+        level = 0;
+#pragma unroll
+        for (int j = 1; j < kLevels; ++j) level = tot[j] <= a.aim ? j : level;
+    }
+    if (c[kLevels - 1] != 0) {
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const uint64_t m = __builtin_amdgcn_ballot_w64(h.d[p] > lv[kLevels - 1]);
+            if (m == 0) continue;
+            int pos = kList;
+            uint64_t seen = 0;
+#pragma unroll
+            for (int j = 0; j < kLevels; ++j) {
+                const uint64_t mj = (j == kLevels - 1 ? m : __builtin_amdgcn_ballot_w64(h.d[p] > lv[j])) & ~seen;
+                seen |= mj;
+                if (mj != 0 && j <= level) {
+                    if (((mj >> me.lane) & 1ull) != 0) pos = (int)at[j] + lanes_below(mj);
+                    at[j] += __builtin_popcountll(mj);
+                }
+            }
+            if (me.G > 1) {
+                if (pos < kOwn)
+                    cand_store(half_list(a, me, par, me.half) + pos * kCandWords3, stamp, h.x[p], h.y[p], h.z[p], h.oi[p],
+                               __float_as_uint(h.d[p]));
+            } else if (pos < kList) {
+                sh.cand[pos] = make_float4(h.x[p], h.y[p], h.z[p], __uint_as_float(h.oi[p]));
+                sh.dist[pos] = __float_as_uint(h.d[p]);
+            }
+        }
+    }
+    MARK(1);
+    int total;
+    if (me.G == 1) {
+        total = tot[0];
+#pragma unroll
+        for (int j = 1; j < kLevels; ++j) total = j == level ? tot[j] : total;
+        if (me.tid < (-total & 63)) sh.dist[total + me.tid] = 0;
+        __syncthreads();
+        for (int k = me.w; 64 * k < total; k += kNW) {
+            const int r = 64 * k + me.lane;
+            chunk_box(sh, k, me.lane, sh.cand[r], sh.dist[r], r < total);
+        }
+    } else {
+        const int nwv = (halves + 63) >> 6;                // waves that hold counts
+        if (me.w < nwv) {
+            uint32_t val[1] = {0};
+            bool bad = false;
+            if (me.tid < halves) bad = !ll_wait<1>(hdr + me.tid, round, val, a.wait_ticks);
+            const uint32_t v = bad ? 0u : val[0];
+            const int s01 = wave_incl_sum((int)((v & 0xFFu) | ((v & 0xFF00u) << 8)), me.lane);
+            const int s23 = wave_incl_sum((int)(((v >> 16) & 0xFFu) | ((v >> 8) & 0xFF0000u)), me.lane);
+            uint32_t full = 0;
+#pragma unroll
+            for (int j = 0; j < kLevels; ++j)
+                full |= __builtin_amdgcn_ballot_w64(((v >> (8 * j)) & 0xFFu) == 255u) != 0 ? 1u << j : 0u;
+            sh.inc[0][me.tid] = s01;
+            sh.inc[1][me.tid] = s23;
+            if (me.lane == 63) {
+                sh.tot[0][me.w] = s01;
+                sh.tot[1][me.w] = s23;
+                sh.full[me.w] = full;
+            }
+            if (__builtin_amdgcn_ballot_w64(bad) != 0 && me.lane == 0) sh.fail = 1;
+        }
+        __syncthreads();
+        MARK(2);
+        int t01 = 0, t23 = 0;
+        uint32_t full = 0;
+        for (int k = 0; k < nwv; ++k) {
+            t01 += sh.tot[0][k];
+            t23 += sh.tot[1][k];
+            full |= sh.full[k];
+        }
+        t01 = uni(t01);
+        t23 = uni(t23);
+        full = uni(full);
+        level = 0;
+        total = t01 & 0xFFFF;
+        if ((full & 2u) == 0 && (int)((uint32_t)t01 >> 16) <= a.aim) level = 1, total = (int)((uint32_t)t01 >> 16);
+        if ((full & 4u) == 0 && (t23 & 0xFFFF) <= a.aim) level = 2, total = t23 & 0xFFFF;
+        if ((full & 8u) == 0 && (int)((uint32_t)t23 >> 16) <= a.aim) level = 3, total = (int)((uint32_t)t23 >> 16);
+        const int shift = (level & 1) * 16;
+        const int32_t* const inc = sh.inc[level >> 1];
+        // candidates listed before each 64 halves
+        constexpr int NB = kMaxGroup / 32;
+        int bases[NB];
+        {
+            const int32_t* const t = sh.tot[level >> 1];
+            bases[0] = 0;
+#pragma unroll
+            for (int k = 1; k < NB; ++k)
+                bases[k] = k < nwv ? uni(bases[k - 1] + (int)(((uint32_t)t[k - 1] >> shift) & 0xFFFFu)) : kList;
+        }
+        if (uni(sh.fail) == 0) {
+            constexpr int NE = 2;           // chunks a wave has under way at a time
+            for (int k0 = me.w; 64 * k0 < total; k0 += NE * kNW) {
+                uint64_t got[NE][kCandWords3];
+                const uint64_t* src[NE];
+#pragma unroll
+                for (int u = 0; u < NE; ++u) {
+                    const int r = 64 * (k0 + u * kNW) + me.lane;
+                    src[u] = nullptr;
+#pragma unroll
+                    for (int e = 0; e < kCandWords3; ++e) got[u][e] = 0;
+                    if (r < total) {
+                        // the half that lists the r-th candidate: the first whose sum exceeds r
+                        int q = 0, rr = r;
+#pragma unroll
+                        for (int k = 1; k < NB; ++k)
+                            if (r >= bases[k]) {
+                                q = k;
+                                rr = r - bases[k];
+                            }
+                        int g = 0;
+#pragma unroll
+                        for (int s = 32; s > 0; s >>= 1)
+                            if ((int)(((uint32_t)inc[64 * q + g + s - 1] >> shift) & 0xFFFFu) <= rr) g += s;
+                        const int first = g > 0 ? (int)(((uint32_t)inc[64 * q + g - 1] >> shift) & 0xFFFFu) : 0;
+                        src[u] = half_list(a, me, par, 64 * q + g) + (rr - first) * kCandWords3;
+#pragma unroll
+                        for (int e = 0; e < kCandWords3; ++e) got[u][e] = ll_load(src[u] + e);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < NE; ++u) {
+                    const int k = k0 + u * kNW, r = 64 * k + me.lane;
+                    if (64 * k >= total) break;             // uniform
+                    float4 c = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    uint32_t d = 0;
+                    if (r < total) {
+                        if (cand_wait(src[u], stamp, got[u], a.wait_ticks)) c = cand_unpack(got[u], d);
+                        else sh.fail = 1;
+                    }
+                    sh.cand[r] = c;
+                    sh.dist[r] = d;
+                    chunk_box(sh, k, me.lane, c, d, r < total);
+                }
+            }
+        }
+    }
+    __syncthreads();
+    MARK(4);
+    return uni(sh.fail) != 0 ? -1 : total;
+}
+
+// Decides this workgroup's part of the list and leaves the round's samples, of all workgroups, in sh.took.
+// Returns their number, -1 if a wait expired.
+__device__ __forceinline__ int decide(LocalShared& sh, const Seat& me, const LocalArgs& a, uint32_t round, int total,
+                                      int room)
+{
+    const bool ranked = room < total;                   // uniform
+    const int units = (total + kUnit - 1) / kUnit, chunks = (total + 63) >> 6;
+    const int lo = (int)((uint32_t)(units * me.g) / (uint32_t)me.G) * kUnit;
+    int hi = (int)((uint32_t)(units * (me.g + 1)) / (uint32_t)me.G) * kUnit;
+    hi = hi < total ? hi : total;
+    const int mine = me.lane < chunks ? me.lane : 0;    // lane l: chunk l
+    const Box cb = box_of_chunk(sh, mine);
+    const uint32_t far = me.lane < chunks ? __float_as_uint(sh.box[6][mine]) : 0u;
+    for (int i = lo + me.w; i < hi; i += kNW) {
+        const float4 mc = sh.cand[i];
+        const uint32_t md = uni(sh.dist[i]), mi = __float_as_uint(mc.w);
+        uint64_t todo = __builtin_amdgcn_ballot_w64(far >= md && box_dist2(cb, mc.x, mc.y, mc.z) < __uint_as_float(md));
+        uint64_t blocked = 0;
+        int k = i >> 6;                                 // its own chunk first
+        while (true) {
+            const float4 oc = sh.cand[64 * k + me.lane];
+            const uint32_t od = sh.dist[64 * k + me.lane];
+            const bool ahead = od > md || (od == md && __float_as_uint(oc.w) < mi);
+            blocked = __builtin_amdgcn_ballot_w64(ahead && __float_as_uint(dist2(oc.x, oc.y, oc.z, mc.x, mc.y, mc.z)) < md);
+            todo &= ~(1ull << k);
+            if (blocked != 0 || todo == 0) break;
+            k = first_lane(todo);
+        }
+        int rank = 0;
+        if (blocked == 0 && ranked) {
+            for (uint64_t m = __builtin_amdgcn_ballot_w64(far >= md); m != 0; m &= m - 1) {
+                const int r = 64 * first_lane(m) + me.lane;
+                const uint32_t od = sh.dist[r];
+                rank += __builtin_popcountll(
+                    __builtin_amdgcn_ballot_w64(od > md || (od == md && __float_as_uint(sh.cand[r].w) < mi)));
+            }
+        }
+        if (blocked == 0 && rank < room && me.lane == 0) atomicOr(&sh.acc[(i - lo) >> 5], 1u << ((i - lo) & 31));
+    }
+    __syncthreads();
+    MARK(5);
+    if (me.G > 1) {
+        uint64_t* const msk = a.ll_mask + (int64_t)(me.grp * 2 + (int)(round & 1u)) * me.G * kWords;
+        if (me.tid * 32 < hi - lo) ll_store(msk + (int64_t)me.g * kWords + me.tid, sh.acc[me.tid], round);
+        const int words = ((units + me.G - 1) / me.G + 3) >> 2;             // the most a workgroup publishes
+        const int g = me.tid >> a.own_shift;
+        if (g < me.G) {
+            const int from = (int)((uint32_t)(units * g) / (uint32_t)me.G);
+            const int to = (int)((uint32_t)(units * (g + 1)) / (uint32_t)me.G);
+            for (int q = me.tid & ((1 << a.own_shift) - 1); q < words; q += 1 << a.own_shift) {
+                const int u0 = from + 4 * q;
+                if (u0 >= to) break;
+                uint32_t val[1] = {0};
+                if (!ll_wait<1>(msk + (int64_t)g * kWords + q, round, val, a.wait_ticks)) sh.fail = 1;
+                for (int u = 0; u < 4 && u0 + u < to; ++u)
+                    reinterpret_cast<uint8_t*>(sh.took)[u0 + u] = (uint8_t)(val[0] >> (8 * u));
+            }
+        }
+    } else if (me.tid < 2 * kChunks) {
+        reinterpret_cast<uint32_t*>(sh.took)[me.tid] = sh.acc[me.tid];
+    }
+    __syncthreads();
+    MARK(6);
+    if (uni(sh.fail) != 0) return -1;
+    const int cnt = __builtin_popcountll(sh.took[me.lane]);
+    return (int)rdlane((uint32_t)wave_incl_sum(cnt, me.lane), 63);
+}
+
+// Folds the round's samples into the wave's distances.
+template <int P>
+__device__ __forceinline__ void fold_samples(Held<P>& h, const LocalShared& sh, const Seat& me, int total)
+{
+    const int chunks = (total + 63) >> 6, mine = me.lane < chunks ? me.lane : 0;
+    const Box cb = box_of_chunk(sh, mine);
+    const float far = sh.box[6][mine];
+    const float bb = fminf(box_box2(h.a, cb), box_box2(h.b, cb));
+    uint64_t todo = __builtin_amdgcn_ballot_w64(me.lane < chunks && sh.took[mine] != 0 && bb < fminf(h.ub, far));
+    bool lowered = false;
+    for (; todo != 0; todo &= todo - 1) {
+        const int k = first_lane(todo);
+        const float4 c = sh.cand[64 * k + me.lane];
+        const float v = __uint_as_float(sh.dist[64 * k + me.lane]);
+        const float bd = fminf(box_dist2(h.a, c.x, c.y, c.z), box_dist2(h.b, c.x, c.y, c.z));
+        uint64_t near = __builtin_amdgcn_ballot_w64(bd < fminf(h.ub, v)) & uni64(sh.took[k]);
+        lowered = lowered || near != 0;
+        for (; near != 0; near &= near - 1) {
+            const int l = first_lane(near);
+            fold<P>(h, rdlane_f(c.x, l), rdlane_f(c.y, l), rdlane_f(c.z, l), rdlane_f(v, l));
+        }
+    }
+    if (lowered) refresh_bound<P>(h);
+}
+
+// Clears the candidates this workgroup has published; they are gone once the workgroups have met.
+__device__ __forceinline__ void clear_lists(const LocalArgs& a, const Seat& me)
+{
+    for (int par = 0; par < 2; ++par) {
+        uint64_t* own = half_list(a, me, par, me.half);
+        for (int t = me.tid & (kT / 2 - 1); t < kHalfWords; t += kT / 2) word_store(own + t, 0ull);
+    }
+    __threadfence();
+    __syncthreads();
+}
+
+// What order_samples_kernel has to know: whether the cloud's samples are valid (2 bits), their number, and a distance
+// none of them was found below (31 bits).
+__device__ __forceinline__ uint64_t found_state(int status, int count, float low)
+{
+    return ((uint64_t)(uint32_t)status << 62) | ((uint64_t)__float_as_uint(low) << 31) | (uint32_t)count;
+}
+
+template <int P>
+__device__ __forceinline__ void run_cloud(const LocalArgs& a, LocalShared& sh, const Seat& me, uint32_t& it,
+                                          uint32_t& seq, uint32_t& round, int& wipe)
+{
+    const int n = a.n, N = a.N;
+    uint64_t* const found = a.found + (int64_t)me.c * n;        // [0]: found_state; then the samples
+    const int start = uni(a.start_idx ? a.start_idx[me.c] : 0);
+    const long long t0 = wall_clock64();
+    int status = 0, np = 1, rounds = 0;
+    float low = __builtin_inff();           // no sample was found at a distance below
+    if (start < 0 || start >= N) {
+        status = 1;                                             // uniform over the group
+    } else {
+        Held<P> h;
+        load_points<P>(h, me, a);
+        if (me.tid == 0) sh.fail = 0;
+        const float* s = a.xyz + ((int64_t)me.c * N + start) * 3;
+        h.ub = __builtin_inff();
+        fold<P>(h, s[0], s[1], s[2], __builtin_inff());
+        refresh_bound<P>(h);
+        __syncthreads();
+#ifdef FASTPOINT_PHASE_CLOCKS
+        if (me.tid == 0) {
+            for (int k = 0; k < 16; ++k) clk[k] = 0;
+            clk_at = wall_clock64();
+        }
+#endif
+        float tau = -1.0f;                  // every distance above it is in the next list; < 0: not known
+        float step = 0.8f;                  // ratio of a round's levels
+        int dry = 0, most_dry = 3;
+        while (np < n) {
+            if ((round & kWipeRounds) == kWipeRounds) {
+                ++round;                    // the stamps of published candidates start again
+                wipe = 2;
+                tau = -1.0f;
+            }
+            if (!(tau > 0.0f)) {
+                const Rec r = plain_pick<P>(h, sh, me, a, it, seq);
+                if (uni(r.fail) != 0) {
+                    status = 2;
+                    break;
+                }
+                if (wipe == 2 && me.G > 1) {
+                    // All workgroups are done with the words of the last list; they are gone before the workgroups
+                    // have met once more.
+                    clear_lists(a, me);
+                }
+                wipe = wipe > 0 ? wipe - 1 : 0;
+                const float v = unif(__uint_as_float(r.d));
+                ++rounds;
+                if (v == 0.0f) break;       // every point lies on a sample: Alg. 1 takes index 0 from here on
+                if (me.g == 0 && me.tid == 0) found[np] = ((uint64_t)(~r.d) << 32) | r.idx;
+                ++np;
+                low = fminf(low, v);
+                fold<P>(h, unif(r.x), unif(r.y), unif(r.z), v);
+                refresh_bound<P>(h);
+                tau = v < __builtin_inff() && wipe == 0 ? v : -1.0f;
+                dry = 0;
+                continue;
+            }
+            ++round;
+            ++rounds;
+            float lv[kLevels];
+            lv[0] = tau;
+#pragma unroll
+            for (int j = 1; j < kLevels; ++j) lv[j] = lv[j - 1] * step;
+            int level;
+            const int total = make_list<P>(h, sh, me, a, round, lv, level);
+            if (total < 0) {
+                status = 2;
+                break;
+            }
+#pragma unroll
+            for (int j = 1; j < kLevels; ++j) tau = j == level ? lv[j] : tau;
+            if (level == kLevels - 1) step = fmaxf(step * step, 0.3f);
+            else if (level == 0) step = sqrtf(step);
+            else if (level == 1) step = sqrtf(sqrtf(step) * step);
+            if (total == 0) {
+                if (++dry >= most_dry) {
+                    tau = -1.0f;
+                    most_dry = 1;           // (until a list is of use again)
+                }
+                continue;
+            }
+            dry = 0;
+            most_dry = 3;
+            low = fminf(low, tau);
+            const int got = decide(sh, me, a, round, total, n - np);
+            if (got < 0) {
+                status = 2;
+                break;
+            }
+            fold_samples<P>(h, sh, me, total);
+            if ((int)(round % (uint32_t)me.G) == me.g) {
+                // this workgroup notes the round's samples
+                int at = np;
+                for (int k = 0; 64 * k < total; ++k) {
+                    const uint64_t m = uni64(sh.took[k]);
+                    if (k % kNW == me.w && ((m >> me.lane) & 1ull) != 0)
+                        found[at + lanes_below(m)] = ((uint64_t)(~sh.dist[64 * k + me.lane]) << 32) |
+                                                     __float_as_uint(sh.cand[64 * k + me.lane].w);
+                    at += __builtin_popcountll(m);
+                }
+            }
+            np += got;
+            MARK(7);
+        }
+    }
+#ifdef FASTPOINT_PHASE_CLOCKS
+    if (me.tid == 0)
+        for (int k = 0; k < 16; ++k)
+            a.ll_mask[(int64_t)2 * kMaxGroup * kWords + blockIdx.x * 16 + k] = (uint64_t)clk[k];
+#endif
+    if (me.g == 0 && me.tid == 0) {
+        found[0] = found_state(status, np, low);
+        if (a.info) {
+            fp_mdps_info inf = {};
+            if (status != 1) {
+                inf.m = n - 1;
+                inf.et_index = n;
+                for (int l = 0; l < FP_MAX_SEG; ++l) inf.level_start[l] = -1;
+                inf.rounds = rounds;
+                inf.phase_ticks[0] = (int32_t)(wall_clock64() - t0);
+            }
+            inf.status = status;
+            a.info[me.c] = inf;
+        }
+    }
+    __syncthreads();
+}
+
+template <int P>
+__global__ __launch_bounds__(kT) void local_fps_kernel(LocalArgs a)
+{
+    __shared__ LocalShared sh;
+    Seat me;
+    me.tid = (int)threadIdx.x;
+    me.lane = me.tid & 63;
+    me.w = uni(me.tid >> 6);
+    me.G = a.G;
+    me.grp = (int)blockIdx.x / a.G;
+    me.g = (int)blockIdx.x % a.G;
+    const int ngroups = (int)gridDim.x / a.G;
+    me.half = me.g + (me.w >= kHW ? me.G : 0);
+    uint32_t it = 0, seq = 0, round = 0;
+    int wipe = 0;
+    for (int c = me.grp; c < a.B; c += ngroups) {
+        me.c = c;
+        run_cloud<P>(a, sh, me, it, seq, round, wipe);
+    }
+}
+
+// ---- the samples in the sequence of Alg. 1: ascending keys (inverted distance bits, index).  The inverses of the
+// distances are spread over 4096 ranges of equal width (the n-th of evenly spread samples is found at a distance that
+// falls with 1 / n on surfaces, with n ** (-2 / 3) in space).  Every workgroup counts all keys by range (65536 keys are 0.5 MB, read
+// by 32 workgroups), takes the ranges that begin in its share of the sequence, gathers their keys in LDS and
+// places each among those of its range (a few dozen at most in the workloads).  Bound: the two passes over the keys.
+constexpr int kOrderT = 1024;
+constexpr int kRanges = 4096;                   // 2^12
+
+__global__ __launch_bounds__(kOrderT) void order_samples_kernel(const uint64_t* __restrict__ found_all,
+                                                                const int32_t* __restrict__ start_idx, int n, int Q,
+                                                                int32_t* __restrict__ out_idx, float* __restrict__ out_mdc)
+{
+    __shared__ uint64_t key[kOrderMost];
+    __shared__ int32_t first[kRanges + 1];              // counts, then keys in front of the range
+    __shared__ int32_t next[kRanges];
+    __shared__ int32_t sums[kOrderT / 64];
+    __shared__ int32_t mine[2];
+    const int b = (int)blockIdx.y, q = (int)blockIdx.x, tid = (int)threadIdx.x, lane = tid & 63;
+    const uint64_t* found = found_all + (int64_t)b * n;
+    const uint64_t state = found[0];
+    const int status = (int)(state >> 62), np = (int)(state & 0x7FFFFFFFu);
+    int32_t* idx = out_idx + (int64_t)b * n;
+    float* mdc = out_mdc ? out_mdc + (int64_t)b * n : nullptr;
+    if (status != 0) {
+        for (int t = q * kOrderT + tid; t < n; t += Q * kOrderT) idx[t] = -1;
+        return;
+    }
+    for (int t = np + q * kOrderT + tid; t < n; t += Q * kOrderT) {        // every point lies on a sample
+        idx[t] = 0;
+        if (mdc) mdc[t] = 0.0f;
+    }
+    if (q == 0 && tid == 0) {
+        idx[0] = start_idx ? start_idx[b] : 0;
+        if (mdc) mdc[0] = __builtin_inff();
+    }
+    const int m = np - 1;
+    if (m == 0) return;                                                    // uniform
+    const uint64_t* keys = found + 1;
+    // 1 - f / 2 in place of 1 / (1 + f) inside a power of two: all in whole numbers, and falling with the distance
+    const int low = (int)((uint32_t)(state >> 54) & 0xFFu);                // exponent of the bound
+    auto range_of = [&](uint64_t k) {
+        const uint32_t v = ~(uint32_t)(k >> 32);
+        const int o = (int)(v >> 23) - low;
+        const int r = o < 12 ? (int)(((1u << 24) - (v & 0x7FFFFFu)) >> (12 + o)) : 0;
+        return r < kRanges ? r : kRanges - 1;
+    };
+    for (int t = tid; t < kRanges; t += kOrderT) {
+        first[t] = 0;
+        next[t] = 0;
+    }
+    __syncthreads();
+    constexpr int U = 16;                                                  // loads a thread has under way
+    for (int t0 = tid; t0 < m; t0 += kOrderT * U) {
+        uint64_t k[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) k[u] = t0 + u * kOrderT < m ? keys[t0 + u * kOrderT] : 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (t0 + u * kOrderT < m) atomicAdd(&first[range_of(k[u])], 1);
+    }
+    __syncthreads();
+    int c[4], sum = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        c[u] = first[4 * tid + u];
+        sum += c[u];
+    }
+    const int incl = wave_incl_sum(sum, lane);
+    if (lane == 63) sums[tid >> 6] = incl;
+    __syncthreads();
+    int at = incl - sum;
+    for (int w = 0; w < (tid >> 6); ++w) at += sums[w];
+    // the ranges that begin in [q m / Q, (q + 1) m / Q)
+    const int share0 = (int)((int64_t)m * q / Q), share1 = (int)((int64_t)m * (q + 1) / Q);
+    if (tid < 2) mine[tid] = kRanges;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int r = 4 * tid + u;
+        first[r] = at;
+        // (the first range that does not begin before a border: one thread finds it, or none)
+        if (at < share0 && at + c[u] >= share0) mine[0] = r + 1;
+        if (at < share1 && at + c[u] >= share1) mine[1] = r + 1;
+        at += c[u];
+    }
+    if (tid == kOrderT - 1) first[kRanges] = at;
+    __syncthreads();
+    const int r0 = q == 0 ? 0 : mine[0], r1 = mine[1];
+    if (r0 >= r1) return;                                                  // uniform: nothing begins there
+    const int from = first[r0], count = first[r1] - from;
+    if (count <= kOrderMost) {
+        for (int t0 = tid; t0 < m; t0 += kOrderT * U) {
+            uint64_t k[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) k[u] = t0 + u * kOrderT < m ? keys[t0 + u * kOrderT] : 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int r = range_of(k[u]);
+                if (t0 + u * kOrderT < m && r >= r0 && r < r1) key[first[r] - from + atomicAdd(&next[r], 1)] = k[u];
+            }
+        }
+        __syncthreads();
+        for (int t = tid; t < count; t += kOrderT) {
+            const uint64_t k = key[t];
+            const int r = range_of(k), lo = first[r] - from, hi = first[r + 1] - from;
+            int place = first[r];
+            for (int e = lo; e < hi; ++e) place += key[e] < k || (key[e] == k && e < t) ? 1 : 0;
+            idx[1 + place] = (int32_t)(uint32_t)k;
+            if (mdc) mdc[1 + place] = __uint_as_float(~(uint32_t)(k >> 32));
+        }
+        return;
+    }
+    // many equal distances: each of these keys is counted against all
+    for (int t = tid; t < m; t += kOrderT) {
+        const uint64_t k = keys[t];
+        const int r = range_of(k);
+        if (r < r0 || r >= r1) continue;
+        int place = 0;
+        for (int e = 0; e < m; ++e) place += keys[e] < k || (keys[e] == k && e < t) ? 1 : 0;
+        idx[1 + place] = (int32_t)(uint32_t)k;
+        if (mdc) mdc[1 + place] = __uint_as_float(~(uint32_t)(k >> 32));
+    }
+}
+
+}  // namespace
+
+const void* local_fps_kernel_for(int points_per_thread)
+{
+    switch (points_per_thread) {
+        case 1: return reinterpret_cast<const void*>(&local_fps_kernel<1>);
+        case 2: return reinterpret_cast<const void*>(&local_fps_kernel<2>);
+        case 4: return reinterpret_cast<const void*>(&local_fps_kernel<4>);
+        case 8: return reinterpret_cast<const void*>(&local_fps_kernel<8>);
+        default: return nullptr;
+    }
+}
+
+hipError_t launch_order_samples(const uint64_t* found, const int32_t* start_idx, int B, int n, int32_t* out_idx,
+                                float* out_mdc, hipStream_t stream)
+{
+    const int Q = n <= kOrderMost ? 1 : (n + kOrderMost / 2 - 1) / (kOrderMost / 2);
+    hipLaunchKernelGGL(order_samples_kernel, dim3((unsigned)Q, (unsigned)B), dim3(kOrderT), 0, stream, found, start_idx,
+                       n, Q, out_idx, out_mdc);
+    return hipGetLastError();
+}
+
+}  // namespace fastpoint
