@@ -103,6 +103,15 @@ constexpr int kCellOrderFrom = 5121;
 constexpr int kCellOrderSamples = 1500;
 constexpr int kCellOrderSamplesLowest = 2000;
 
+// Cell-ordered MDPS by local decisions: its rounds (prefix and six levels: 70 to 150) and its launches are as many for few
+// samples as for many, while rounds of 256 candidates settled in order grow with them.  By local decisions over in order, single
+// clouds to batches of 128, without and with a record (rooms, uniform cubes, scanner clouds):
+//   samples                      1500-2000   3000        4100        5000        6000        12000       30000
+//   lowest index first           1.1-1.5     0.9-1.3     0.9-1.1     0.8-1.0     0.7-1.0     0.5-0.8     0.4-0.6
+//   scattered scan order         1.0-1.4     0.9-1.3     0.9-1.1     0.8-1.0     0.8-1.0     0.5-0.8     0.4-0.6
+// Exact FPS gains from the first size on at which the sort pays.
+constexpr int kLocalMdpsSamples = 5000;
+
 bool shape_for(int64_t points_per_wg, Shape* s)
 {
     for (int i = 0; i < kNumShapes; ++i)
@@ -227,44 +236,73 @@ int local_aim(int G)
 
 int64_t scan_walk_bytes(int32_t B, int32_t N) { return align_up((int64_t)B * N * (int64_t)sizeof(float4), 256); }
 
-// Exact FPS in cell order: the sort, the sampler by local decisions, the samples put in sequence.  `a`: what the
-// samplers share; workspace of fp_fps_pruned_workspace_bytes.
-fp_status run_local(const SamplerArgs& s, const Plan& plan, void* workspace, hipStream_t stream)
+// Where the sampler by local decisions keeps its things behind the sorted cloud (byte offsets).
+struct LocalLayout {
+    int64_t list, cloud, dist, curve, inv, bq_at, bytes;
+};
+LocalLayout local_layout(int32_t B, int32_t N)
 {
-    void* sort_ws = reinterpret_cast<unsigned char*>(workspace) + kExchangeBytes;
+    LocalLayout l;
+    l.list = 0;
+    l.cloud = (int64_t)kLocalListBytes;
+    l.dist = l.cloud + align_up((int64_t)B * (int64_t)sizeof(LocalCloud), 256);
+    l.curve = l.dist + align_up((int64_t)B * N * 4, 256);
+    l.inv = l.curve + align_up((int64_t)B * N * 4, 256);
+    l.bq_at = l.inv + align_up((int64_t)B * N * 4, 256);
+    l.bytes = l.bq_at + align_up((int64_t)B * (((int64_t)N + 63) / 64) * 8, 256);      // a wave holds 64 points or more
+    return l;
+}
+
+// The cell-ordered samplers by local decisions: the sort, the sampler, the samples put in sequence; for MDPS the sampler
+// runs once for the prefix, whose curve has to be in sequence for the thresholds, and once for the rest.  `s`: what the
+// samplers share; workspace of fp_fps_pruned_workspace_bytes; zero: words of a cache that have to start at zero.
+fp_status run_local(const SamplerArgs& s, const Plan& plan, bool mdps, void* workspace, uint64_t* zero, int64_t zero_words,
+                    void* bq_cache, hipStream_t stream)
+{
+    unsigned char* sort_ws = reinterpret_cast<unsigned char*>(workspace) + kExchangeBytes;
+    unsigned char* own = sort_ws + spatial_sort_bytes(s.B, s.N);
+    const LocalLayout lay = local_layout(s.B, s.N);
     if (launch_spatial_sort(s.xyz, s.B, s.N, sort_ws, stream) != hipSuccess) return FP_ERR_DEVICE;
+    const bool prefix = mdps && s.m < s.n - 1;
     LocalArgs a;
     memset(&a, 0, sizeof(a));
-    a.xyz = s.xyz;
-    a.start_idx = s.start_idx;
+    static_cast<SamplerArgs&>(a) = s;
     a.sorted = spatial_sorted(s.B, s.N, sort_ws);
     a.found = spatial_sort_spare(s.B, s.N, sort_ws);
-    a.info = s.info;
-    a.B = s.B;
-    a.N = s.N;
-    a.n = s.n;
-    a.G = plan.G;
+    a.cloud = reinterpret_cast<LocalCloud*>(own + lay.cloud);
+    a.stop = prefix ? s.m + 1 : s.n;
     a.aim = local_aim(plan.G);
     while ((plan.G << (a.own_shift + 1)) <= kLocalThreads) ++a.own_shift;
-    a.ll_pk = reinterpret_cast<uint64_t*>(workspace);
     a.ll_hdr = a.ll_pk + kLlPkWords;
     a.ll_mask = a.ll_hdr + kLocalHdrWords;
-    a.ll_list = reinterpret_cast<uint64_t*>(reinterpret_cast<unsigned char*>(sort_ws) + spatial_sort_bytes(s.B, s.N));
-    a.wait_ticks = s.wait_ticks;
-    const void* fn = local_fps_kernel_for(plan.T * plan.P / kLocalThreads);
-    if (!fn) return FP_ERR_SHAPE;
-    void* kargs[] = {&a};
-    const dim3 grid((unsigned)(plan.groups * plan.G)), block((unsigned)kLocalThreads);
-    hipError_t err;
-    if (plan.G > 1) {
-        if (launch_zero_words(a.ll_pk, kLocalWords, a.ll_list, (int64_t)plan.groups * plan.G * kLocalWgWords, nullptr, 0,
-                              stream) != hipSuccess)
+    a.ll_list = reinterpret_cast<uint64_t*>(own + lay.list);
+    a.dist = prefix ? reinterpret_cast<float*>(own + lay.dist) : nullptr;
+    a.curve = reinterpret_cast<float*>(own + lay.curve);
+    a.bq_at = reinterpret_cast<uint2*>(own + lay.bq_at);
+    int32_t* const inv = bq_cache ? reinterpret_cast<int32_t*>(own + lay.inv) : nullptr;
+    const int P = plan.T * plan.P / kLocalThreads;
+    for (int part = 0; part < (prefix ? 2 : 1); ++part) {
+        const void* fn = local_kernel_for(P, bq_cache != nullptr, part == 1);
+        if (!fn) return FP_ERR_SHAPE;
+        const int64_t list_words = plan.G > 1 ? (int64_t)plan.groups * plan.G * kLocalWgWords : 0;
+        if (plan.G > 1 || (zero_words > 0 && part == 0)) {
+            if (launch_zero_words(a.ll_pk, plan.G > 1 ? kLocalWords : 0, a.ll_list, list_words, zero, part == 0 ? zero_words : 0,
+                                  stream) != hipSuccess)
+                return FP_ERR_DEVICE;
+        }
+        void* kargs[] = {&a};
+        const dim3 grid((unsigned)(plan.groups * plan.G)), block((unsigned)kLocalThreads);
+        const hipError_t err = plan.G > 1 && g_cooperative.load()
+                                   ? hipLaunchCooperativeKernel(fn, grid, block, kargs, 0, stream)
+                                   : hipLaunchKernel(fn, grid, block, kargs, 0, stream);
+        if (err != hipSuccess) return FP_ERR_DEVICE;
+        const bool last = part == (prefix ? 1 : 0);
+        if (launch_order_samples(a.found, a.cloud, s.start_idx, s.B, s.N, s.n, last ? s.n : a.stop, last, s.out_idx,
+                                 last ? s.out_mdc : a.curve, s.bq_idx, inv, stream) != hipSuccess)
             return FP_ERR_DEVICE;
     }
-    if (plan.G > 1 && g_cooperative.load()) err = hipLaunchCooperativeKernel(fn, grid, block, kargs, 0, stream);
-    else err = hipLaunchKernel(fn, grid, block, kargs, 0, stream);
-    if (err == hipSuccess) err = launch_order_samples(a.found, s.start_idx, s.B, s.n, s.out_idx, s.out_mdc, stream);
-    return err == hipSuccess ? FP_OK : FP_ERR_DEVICE;
+    if (bq_cache && launch_bq_group_by_sample(bq_cache, s.B, s.N, s.n, s.bq_cap, inv, stream) != hipSuccess) return FP_ERR_DEVICE;
+    return FP_OK;
 }
 
 fp_status run_sampler(const float* xyz, int32_t B, int32_t N, int32_t n, const int32_t* start_idx,
@@ -353,8 +391,9 @@ fp_status run_sampler(const float* xyz, int32_t B, int32_t N, int32_t n, const i
     a.ll_ct = a.ll_cd + kLlCdWords;
     a.wait_ticks = g_wait_limit_us.load() * di.wall_khz / 1000;
 
-    if (pruned && !prm) return run_local(a, plan, workspace, stream);
-    if (pruned) {
+    const bool local = pruned && (!prm || n >= kLocalMdpsSamples);
+    if (local && walk) a.walk_inv = (uint64_t)inverse_mod(scan_walk_stride(N), N);
+    if (pruned && !local) {
         // the cloud in cell order, behind the exchange words
         void* sort_ws = reinterpret_cast<unsigned char*>(workspace) + kExchangeBytes;
         if (launch_spatial_sort(xyz, B, N, sort_ws, stream) != hipSuccess) return FP_ERR_DEVICE;
@@ -398,6 +437,8 @@ fp_status run_sampler(const float* xyz, int32_t B, int32_t N, int32_t n, const i
         bq_zero_words = (lay.rowoff_offset - lay.cursor_offset) / 8;      // cursors, flags, counts, chunk fills
     }
 
+    if (local) return run_local(a, plan, prm != nullptr, workspace, bq_zero, bq_zero_words, bq_cache, stream);
+
     // MDPS threshold rounds with two candidates per control-wave lane: measured faster except
     // where one workgroup both holds the cloud and records the radius tests
     const int mode = prm == nullptr ? 0
@@ -420,7 +461,7 @@ fp_status run_sampler(const float* xyz, int32_t B, int32_t N, int32_t n, const i
         err = hipLaunchCooperativeKernel(fn, dim3(grid), dim3((unsigned)(plan.T + kCtrlThreads)), kargs, 0, stream);
     else
         err = hipLaunchKernel(fn, dim3(grid), dim3((unsigned)(plan.T + kCtrlThreads)), kargs, 0, stream);
-    if (err == hipSuccess && bq) err = launch_bq_group_by_sample(bq_cache, B, N, n, a.bq_cap, stream);
+    if (err == hipSuccess && bq) err = launch_bq_group_by_sample(bq_cache, B, N, n, a.bq_cap, nullptr, stream);
     return err == hipSuccess ? FP_OK : FP_ERR_DEVICE;
 }
 
@@ -490,8 +531,8 @@ size_t fp_mdps_scattered_workspace_bytes(int32_t B, int32_t N)
 size_t fp_fps_pruned_workspace_bytes(int32_t B, int32_t N)
 {
     if (B < 1 || N < 1 || B > 65535 || (int64_t)B * N > ((int64_t)1 << 33)) return 0;
-    const size_t rel = (size_t)rel_exchange_bytes(B);
-    return kExchangeBytes + (size_t)spatial_sort_bytes(B, N) + (rel > kLocalListBytes ? rel : kLocalListBytes);
+    const size_t rel = (size_t)rel_exchange_bytes(B), local = (size_t)local_layout(B, N).bytes;
+    return kExchangeBytes + (size_t)spatial_sort_bytes(B, N) + (rel > local ? rel : local);
 }
 
 fp_status fp_fps_exact_pruned(const float* xyz, int32_t B, int32_t N, int32_t n, const int32_t* start_idx,

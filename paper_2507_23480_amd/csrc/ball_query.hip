@@ -195,17 +195,26 @@ __device__ __forceinline__ bool bq_place_used(const BqHeader* h, const unsigned 
     return (uint32_t)(e % kBqChunk) < fill[e / kBqChunk];
 }
 
+// An entry's key.  inv: the samplers by local decisions know a sample's position only at the end, their entries name it by
+// its index.
+template <bool BY_BLOCK>
+__device__ __forceinline__ uint32_t bq_key(const BqHeader* h, const BqRaw& r, const int32_t* inv, int b)
+{
+    if (BY_BLOCK) return r.blk;
+    return inv ? (uint32_t)inv[(int64_t)b * h->N + r.q] : r.q;
+}
+
 // The three steps for the threads `tid` of `nthreads` that share cloud b (a whole grid row, or one
 // workgroup).
 template <bool BY_BLOCK>
 __device__ __forceinline__ void group_count(const BqHeader* h, const unsigned char* cache, int b, int32_t* cnt,
-                                            int keys, int64_t rows_cap, int64_t tid, int64_t nthreads)
+                                            int keys, int64_t rows_cap, const int32_t* inv, int64_t tid, int64_t nthreads)
 {
     const int64_t E = bq_places(h, cache, b, rows_cap);
     const BqRaw* __restrict__ raw = reinterpret_cast<const BqRaw*>(cache + h->raw_offset) + (int64_t)b * h->cap;
     for (int64_t e = tid; e < E; e += nthreads) {
         if (!bq_place_used(h, cache, b, e)) continue;
-        const uint32_t key = BY_BLOCK ? raw[e].blk : raw[e].q;
+        const uint32_t key = bq_key<BY_BLOCK>(h, raw[e], inv, b);
         if (key < (uint32_t)keys) atomicAdd(cnt + (int64_t)b * keys + key, 1);
     }
 }
@@ -213,7 +222,7 @@ __device__ __forceinline__ void group_count(const BqHeader* h, const unsigned ch
 template <bool BY_BLOCK>
 __device__ __forceinline__ void group_scatter(const BqHeader* h, const unsigned char* cache, int b, int32_t* cnt,
                                               const uint32_t* off, int keys, BqEntry* rows, int64_t rows_cap,
-                                              int64_t tid, int64_t nthreads)
+                                              const int32_t* inv, int64_t tid, int64_t nthreads)
 {
     const int64_t E = bq_places(h, cache, b, rows_cap);
     const BqRaw* __restrict__ raw = reinterpret_cast<const BqRaw*>(cache + h->raw_offset) + (int64_t)b * h->cap;
@@ -221,7 +230,7 @@ __device__ __forceinline__ void group_scatter(const BqHeader* h, const unsigned 
     for (int64_t e = tid; e < E; e += nthreads) {
         if (!bq_place_used(h, cache, b, e)) continue;
         const BqRaw r = raw[e];
-        const uint32_t key = BY_BLOCK ? r.blk : r.q;
+        const uint32_t key = bq_key<BY_BLOCK>(h, r, inv, b);
         if (key >= (uint32_t)keys) continue;
         const uint32_t first = __hip_atomic_load(off + (int64_t)b * ((int64_t)keys + 1) + key, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT);
@@ -284,12 +293,13 @@ __device__ __forceinline__ void group_scan(int b, int32_t* cnt, uint32_t* off, i
 
 template <bool BY_BLOCK>
 __global__ __launch_bounds__(256) void bq_group_count_kernel(const unsigned char* __restrict__ cache,
-                                                             int32_t* __restrict__ cnt, int keys, int64_t rows_cap)
+                                                             int32_t* __restrict__ cnt, int keys, int64_t rows_cap,
+                                                             const int32_t* __restrict__ inv)
 {
     const BqHeader* h = reinterpret_cast<const BqHeader*>(cache);
     if (h->magic != kBqMagic || (int)blockIdx.y >= h->B) return;
-    group_count<BY_BLOCK>(h, cache, (int)blockIdx.y, cnt, keys, rows_cap, (int64_t)blockIdx.x * 256 + threadIdx.x,
-                          (int64_t)gridDim.x * 256);
+    group_count<BY_BLOCK>(h, cache, (int)blockIdx.y, cnt, keys, rows_cap, inv,
+                          (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
 }
 
 __global__ __launch_bounds__(1024) void bq_group_scan_kernel(int32_t* __restrict__ cnt, uint32_t* __restrict__ off,
@@ -303,11 +313,12 @@ template <bool BY_BLOCK>
 __global__ __launch_bounds__(256) void bq_group_scatter_kernel(const unsigned char* __restrict__ cache,
                                                                int32_t* __restrict__ cnt,
                                                                const uint32_t* __restrict__ off, int keys,
-                                                               BqEntry* __restrict__ rows, int64_t rows_cap)
+                                                               BqEntry* __restrict__ rows, int64_t rows_cap,
+                                                               const int32_t* __restrict__ inv)
 {
     const BqHeader* h = reinterpret_cast<const BqHeader*>(cache);
     if (h->magic != kBqMagic || (int)blockIdx.y >= h->B) return;
-    group_scatter<BY_BLOCK>(h, cache, (int)blockIdx.y, cnt, off, keys, rows, rows_cap,
+    group_scatter<BY_BLOCK>(h, cache, (int)blockIdx.y, cnt, off, keys, rows, rows_cap, inv,
                             (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
 }
 
@@ -318,7 +329,8 @@ __global__ __launch_bounds__(256) void bq_group_scatter_kernel(const unsigned ch
 template <bool BY_BLOCK>
 __global__ __launch_bounds__(1024) void bq_group_small_kernel(const unsigned char* __restrict__ cache,
                                                               int32_t* __restrict__ cnt, uint32_t* __restrict__ off,
-                                                              int keys, BqEntry* __restrict__ rows, int64_t rows_cap)
+                                                              int keys, BqEntry* __restrict__ rows, int64_t rows_cap,
+                                                              const int32_t* __restrict__ inv)
 {
     extern __shared__ int32_t lds_cnt[];                // [keys] sizes, then where the next entry of a row goes
     __shared__ uint32_t wsum[16];
@@ -347,7 +359,7 @@ __global__ __launch_bounds__(1024) void bq_group_small_kernel(const unsigned cha
             }
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
-                const uint32_t key = BY_BLOCK ? r[u].blk : r[u].q;
+                const uint32_t key = used[u] ? bq_key<BY_BLOCK>(h, r[u], inv, b) : 0u;
                 if (used[u] && key < (uint32_t)keys) f(r[u], key);
             }
         }
@@ -767,11 +779,11 @@ constexpr int kGroupSmallKeys = 15 * 1024;      // 60 KB of LDS
 
 template <bool BY_BLOCK>
 hipError_t group_entries(const unsigned char* cache, int B, int32_t* cnt, uint32_t* off, BqEntry* rows,
-                         int64_t rows_cap, int keys, hipStream_t stream)
+                         int64_t rows_cap, int keys, const int32_t* inv, hipStream_t stream)
 {
     if (rows_cap <= kGroupSmallEntries && keys <= kGroupSmallKeys) {
         hipLaunchKernelGGL((bq_group_small_kernel<BY_BLOCK>), dim3((unsigned)B), dim3(1024),
-                           (size_t)keys * sizeof(int32_t), stream, cache, cnt, off, keys, rows, rows_cap);
+                           (size_t)keys * sizeof(int32_t), stream, cache, cnt, off, keys, rows, rows_cap, inv);
         return hipGetLastError();
     }
     int64_t gx = (rows_cap + 2047) / 2048;                // eight entries per thread when the list is full
@@ -784,21 +796,21 @@ hipError_t group_entries(const unsigned char* cache, int B, int32_t* cnt, uint32
         if (zb > 1024) zb = 1024;
         hipLaunchKernelGGL(zero_ints_kernel, dim3((unsigned)zb), dim3(256), 0, stream, cnt, words);
     }
-    hipLaunchKernelGGL((bq_group_count_kernel<BY_BLOCK>), grid, dim3(256), 0, stream, cache, cnt, keys, rows_cap);
+    hipLaunchKernelGGL((bq_group_count_kernel<BY_BLOCK>), grid, dim3(256), 0, stream, cache, cnt, keys, rows_cap, inv);
     hipLaunchKernelGGL(bq_group_scan_kernel, dim3((unsigned)B), dim3(1024), 0, stream, cnt, off, keys);
     hipLaunchKernelGGL((bq_group_scatter_kernel<BY_BLOCK>), grid, dim3(256), 0, stream, cache, cnt,
-                       (const uint32_t*)off, keys, rows, rows_cap);
+                       (const uint32_t*)off, keys, rows, rows_cap, inv);
     return hipGetLastError();
 }
 }  // namespace
 
-hipError_t launch_bq_group_by_sample(void* bq_cache, int B, int N, int n, int64_t cap, hipStream_t stream)
+hipError_t launch_bq_group_by_sample(void* bq_cache, int B, int N, int n, int64_t cap, const int32_t* inv, hipStream_t stream)
 {
     unsigned char* cache = reinterpret_cast<unsigned char*>(bq_cache);
     const BqHeader lay = bq_layout(B, N, n, 1.0f, cap);
     return group_entries<false>(cache, B, reinterpret_cast<int32_t*>(cache + lay.rowcnt_offset),
                                 reinterpret_cast<uint32_t*>(cache + lay.rowoff_offset),
-                                reinterpret_cast<BqEntry*>(cache + lay.rows_offset), lay.cap, n, stream);
+                                reinterpret_cast<BqEntry*>(cache + lay.rows_offset), lay.cap, n, inv, stream);
 }
 
 hipError_t launch_bq_group_by_block(const void* bq_cache, int B, int N, int32_t* cnt, uint32_t* off,
@@ -806,7 +818,7 @@ hipError_t launch_bq_group_by_block(const void* bq_cache, int B, int N, int32_t*
 {
     const int blocks = (int)(((int64_t)N + 63) / 64);
     return group_entries<true>(reinterpret_cast<const unsigned char*>(bq_cache), B, cnt, off, rows, rows_cap,
-                               blocks, stream);
+                               blocks, nullptr, stream);
 }
 
 hipError_t launch_gather(const float* xyz, int B, int N, const int32_t* idx, int M, float* out,

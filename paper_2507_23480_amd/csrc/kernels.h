@@ -122,31 +122,42 @@ struct SamplerArgs {
     uint64_t walk_inv;              // scattered scan order on cell-ordered records: 1/A mod N (place t of index j = j/A mod N)
 };
 
-// Exact FPS by local decisions (local_sampler.hip).
+// The sampler by local decisions (local_sampler.hip).
 constexpr int kLocalThreads = 1024;     // of a workgroup
 constexpr int kLocalList = 4096;        // candidates of a round
 constexpr int kLocalOwn = 191;          // ... of half a workgroup
 constexpr int kLocalCandWords = 3;      // words of a published candidate
 constexpr int kLocalMaskWords = 8;      // words of 32 decisions a workgroup publishes
 constexpr int kOrderMost = 4096;        // keys a workgroup puts in order
-struct LocalArgs {
-    const float* xyz;
-    const int32_t* start_idx;
-    const float4* sorted;               // [B][N] records (x, y, z, index bits) in cell order
-    uint64_t* found;                    // [B][n]: [0] status and number of samples, then the samples, in no order
-    fp_mdps_info* info;
-    int32_t B, N, n, G;
+constexpr int kLocalRuns = FP_MAX_SEG + 2;
+// What the launches of a call hand on per cloud: the samples found, in runs that follow each other in the output and are
+// put in sequence one by one.
+struct LocalCloud {
+    int32_t status, count, rounds, ticks;
+    int32_t runs;
+    int32_t begin[kLocalRuns + 1];      // sample positions; begin[runs] = count
+    uint32_t low[kLocalRuns];           // distance bits that none of the run's samples was found below; ~0: keys in place of distances
+};
+struct LocalArgs : SamplerArgs {
+    uint64_t* found;                    // [B][n]: per sample priority (31 bits; inverted distance or key) << 21 | index
+    LocalCloud* cloud;                  // [B]
+    int32_t stop;                       // exact FPS ends with this many samples
     int32_t aim;                        // candidates a round takes at most
     int32_t own_shift;                  // 2^own_shift threads of a workgroup per workgroup of the cloud
-    uint64_t* ll_pk;                    // [groups][2][G][kLlSlotWords]
     uint64_t* ll_hdr;                   // [groups][2][2 G] counts
     uint64_t* ll_mask;                  // [groups][2][G][kLocalMaskWords] decisions
     uint64_t* ll_list;                  // [groups][2][2 G][kLocalOwn + 1][kLocalCandWords] candidates
-    int64_t wait_ticks;
+    float* dist;                        // [B][N] distances after the prefix, in cell order (NULL: exact FPS alone)
+    float* curve;                       // [B][n] distances of the prefix in sequence
+    uint2* bq_at;                       // [B][waves] where a wave's chunk of the record has got to
 };
-const void* local_fps_kernel_for(int points_per_thread);
-hipError_t launch_order_samples(const uint64_t* found, const int32_t* start_idx, int B, int n, int32_t* out_idx,
-                                float* out_mdc, hipStream_t stream);
+// mdps: what follows the prefix
+const void* local_kernel_for(int points_per_thread, bool bq, bool mdps);
+// Positions [from, cloud.count) of every cloud; fill: and the rest up to n.  curve: distances, [B][n] (NULL: none);
+// inv: [B][N], position of a sample by its index (NULL: not wanted)
+hipError_t launch_order_samples(const uint64_t* found, const LocalCloud* cloud, const int32_t* start_idx, int B, int N, int n,
+                                int most, bool fill, int32_t* out_idx, float* out_mdc, int32_t* bq_idx, int32_t* inv,
+                                hipStream_t stream);
 
 struct Plan {
     int G, T, P;        // workgroups per cloud, threads per workgroup, points per thread
@@ -170,7 +181,8 @@ hipError_t launch_zero_words(uint64_t* p, int64_t nwords, uint64_t* p2, int64_t 
 hipError_t launch_scan_walk(const float* xyz, int B, int N, int64_t stride, float4* out, hipStream_t stream);
 // puts the entries the sampler appended to a cache of `cap` entries per cloud into sample order
 // (rows in compressed-row form)
-hipError_t launch_bq_group_by_sample(void* bq_cache, int B, int N, int n, int64_t cap, hipStream_t stream);
+// inv: the entries name samples by index, inv[B][N] gives their positions (NULL: by position)
+hipError_t launch_bq_group_by_sample(void* bq_cache, int B, int N, int n, int64_t cap, const int32_t* inv, hipStream_t stream);
 // the same entries by point block, in caller memory: cnt int32 [B][blocks], off uint32 [B][blocks + 1],
 // rows BqEntry [B][rows_cap]; clouds with more entries than rows_cap are left out (the caller does
 // not read their rows); `cnt` ends up holding the row sizes

@@ -1,4 +1,4 @@
-// Exact farthest point sampling (Algorithm 1 of FastPoint, arXiv 2507.23480) by local decisions, for gfx950.
+// Exact farthest point sampling and MDPS (Algorithms 1 and 2 of FastPoint, arXiv 2507.23480) by local decisions, for gfx950.
 //
 // The sequence of Alg. 1 is found without following it.  d_i is a point's squared distance to the samples found
 // so far.  Say k comes before i when d_k > d_i, or d_k == d_i and k has the lower index.  Then
@@ -27,15 +27,21 @@
 //   fold     every wave folds the samples near the boxes of its points.
 // Where the list does not help (many equal distances, infinities) one sample is taken by a plain arg-max.
 //
-// Bound: latency.  A round takes 10 us on 24 workgroups, 15 on 245: three trips through memory (counts, list, decisions) of
-// 1.2-2 us each, and the rest of its parts 1-2 us each.  The rounds are as many as the samples' dependences are deep:
-// 40, 65 and 94 for the workloads below, against 82, 207 and 436 rounds of 256 candidates settled in sweeps before.
-// fps_exact_pruned, us, before -> now: million points -> 65536 5190 -> 1720, 4 x 120000 -> 16384 2750 -> 1020,
-// 8 x 24000 -> 6000 850 -> 540 (1024 threads; with 512 and twice the points per thread 1880, 1100, 530).
-// Comparing a candidate with the whole list instead of the chunks near it took 10-20 us a round.
+// The threshold phase of Algorithm 2 runs in the same rounds (threshold_rounds): there a point comes before another by its
+// key, and the radius is the level's.  MDPS takes two launches, for the prefix and for the rest: the thresholds need the
+// prefix's curve in sequence.
+//
+// Bound: latency.  A round takes 9 us on 24 workgroups, 14 on 245: three trips through memory (counts, list, decisions) of
+// 1-2 us each, and the rest of its parts about 1 us each.  The rounds are as many as the samples' dependences are deep:
+// 43, 67 and 95 of exact FPS for the workloads below, against 82, 207 and 436 rounds of 256 candidates settled in sweeps before.
+// us, before -> now: fps_exact_pruned million points -> 65536 5190 -> 1710, 4 x 120000 -> 16384 2750 -> 1020, 8 x 24000 -> 6000
+// 850 -> 525; mdps_sample_pruned in the scattered order with record 6250 -> 2340, 4530 -> 2490, 1070 -> 880.  (1024 threads; with
+// 512 and twice the points per thread exact FPS took 1880, 1100, 530.)  Comparing a candidate with the whole list instead
+// of the chunks near it took 10-20 us a round.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "estimator.h"
 #include "kernels.h"
 #include "wave.h"
 
@@ -54,12 +60,17 @@ constexpr int kLevels = 4;
 static_assert(kLocalList == 4096 && kOwn < 255, "8 bits for a count, 255: more than that");
 static_assert(kChunks == 64, "a lane per chunk");
 
+struct Box {
+    float lox, loy, loz, hix, hiy, hiz;
+};
+
 struct LocalShared {
+    Box wbox[kNW][2];                       // boxes of a wave's points, before and behind the widest gap in their run
     float4 cand[kList];                     // x, y, z, index bits
     uint32_t dist[kList];                   // zero behind the last candidate, to the end of its chunk
     float box[7][kChunks];                  // per chunk of 64 candidates: lower corner, upper corner, largest distance
     uint64_t took[kChunks];                 // the round's samples, a bit per candidate
-    uint64_t wcnt[kNW];                     // per wave: points above each level, 16 bits each
+    unsigned long long cnt[2][2];           // per half, points above each level, 16 bits each (of this round and of the next)
     int32_t inc[2][2 * kMaxGroup];          // sums of the halves' counts inside 64 of them, two levels in a word
     int32_t tot[2][kMaxGroup / 32];
     uint32_t full[kMaxGroup / 32];
@@ -69,15 +80,23 @@ struct LocalShared {
     Rec win[2];
 };
 
-struct Box {
-    float lox, loy, loz, hix, hiy, hiz;
+// Threshold phase: where the thresholds are worked out, and the bookkeeping of the levels.
+struct LevelShared {
+    float ring[64];
+    float thr_meas[FP_MAX_SEG], thr[FP_MAX_SEG];
+    double terms[64], powb[FP_MAX_SEG];
+    float mlp_val[32];
+    double mlp_a[128], mlp_b[128];
+    int32_t level_start[FP_MAX_SEG], level_exhausted[FP_MAX_SEG];
 };
 
 template <int P>
 struct Held {
     float x[P], y[P], z[P], d[P];
     uint32_t oi[P];                         // index in the caller's cloud
-    Box a, b;                               // boxes of the wave's points, before and behind the widest gap in their run
+    uint32_t key[P];                        // threshold phase: place in the scan order
+    uint32_t bq_next, bq_room;              // recording: next entry of the wave's chunk, entries left in it
+    bool bq_dead;                           // ... no chunk was left: nothing more is recorded for this cloud
     float ub;                               // largest distance among them
 };
 
@@ -152,6 +171,58 @@ __device__ __forceinline__ void fold(Held<P>& h, float cx, float cy, float cz, f
     }
 }
 
+// The same for a sample whose ball reaches the wave: with the radius test of Section 4.2.  The hits of each block of 64 records
+// become an entry of the cloud's list (kernels.h) under the sample's index; lane p hands on block p.  A wave fills a chunk
+// of entries at a time and waits for the next one to be handed out.
+template <int P>
+__device__ __forceinline__ void fold_record(Held<P>& h, const Seat& me, const LocalArgs& a, float cx, float cy, float cz, float v,
+                                            uint32_t idx)
+{
+    uint32_t lo = 0, hi = 0;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const float t = dist2(cx, cy, cz, h.x[p], h.y[p], h.z[p]);
+        const float m = __uint_as_float(min(__float_as_uint(h.d[p]), __float_as_uint(t)));
+        h.d[p] = t < v ? m : h.d[p];
+        const uint64_t hits = __builtin_amdgcn_ballot_w64(t < a.bq_r2);
+        set_lane(lo, me.lane, p, (uint32_t)hits);
+        set_lane(hi, me.lane, p, (uint32_t)(hits >> 32));
+    }
+    const uint64_t some = __builtin_amdgcn_ballot_w64((lo | hi) != 0);
+    if (some == 0 || h.bq_dead) return;     // uniform
+    const uint32_t nchunks = (uint32_t)(a.bq_cap / kBqChunk);
+    uint32_t* const fill = a.bq_fill + (int64_t)me.c * nchunks;
+    const int total = (int)__builtin_popcountll(some), place = lanes_below(some);
+    int done = 0;
+    while (done < total) {
+        if (h.bq_room == 0) {
+            uint32_t ch = 0;
+            if (me.lane == 0) ch = __hip_atomic_fetch_add(a.bq_cursor + me.c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            ch = uni(ch);
+            if (ch >= nchunks) {
+                if (me.lane == 0) a.bq_ovf[me.c] = 1u;
+                h.bq_dead = true;
+                return;
+            }
+            h.bq_next = ch * (uint32_t)kBqChunk;
+            h.bq_room = (uint32_t)kBqChunk;
+        }
+        const int take = total - done < (int)h.bq_room ? total - done : (int)h.bq_room;
+        const int i = place - done;
+        if (((some >> me.lane) & 1ull) != 0 && i >= 0 && i < take) {
+            BqRaw e;
+            e.mask = ((uint64_t)hi << 32) | lo;
+            e.blk = (uint32_t)((me.half * kHW + (me.w & (kHW - 1))) * P + me.lane);
+            e.q = idx;
+            a.bq_raw[(int64_t)me.c * a.bq_cap + h.bq_next + (uint32_t)i] = e;
+        }
+        h.bq_next += (uint32_t)take;
+        h.bq_room -= (uint32_t)take;
+        done += take;
+        if (h.bq_room == 0 && me.lane == 0) fill[h.bq_next / (uint32_t)kBqChunk - 1u] = (uint32_t)kBqChunk;
+    }
+}
+
 template <int P>
 __device__ __forceinline__ void refresh_bound(Held<P>& h)
 {
@@ -164,8 +235,14 @@ __device__ __forceinline__ void refresh_bound(Held<P>& h)
 // Loads the wave's points and finds their boxes.  (Where the curve leaves a thin layer of occupied cells and comes back
 // elsewhere, one box would span the cloud and the wave would fold every sample: 7000 to 10000 of 16384 instead of
 // some 400 for one or two waves of a LiDAR sweep.)
-template <int P>
-__device__ __forceinline__ void load_points(Held<P>& h, const Seat& me, const LocalArgs& a)
+// Where a wave with points keeps its place in the record from one launch to the next.
+__device__ __forceinline__ uint2& bq_place(const LocalArgs& a, const Seat& me, int P)
+{
+    return a.bq_at[(int64_t)me.c * ((a.N + 64 * P - 1) / (64 * P)) + me.half * kHW + (me.w & (kHW - 1))];
+}
+
+template <int P, bool BQ, bool MDPS>
+__device__ __forceinline__ void load_points(Held<P>& h, LocalShared& sh, const Seat& me, const LocalArgs& a)
 {
     const float4* __restrict__ rec = a.sorted + (int64_t)me.c * a.N;
     const int base = (me.half * kHW + (me.w & (kHW - 1))) * P * 64;
@@ -181,7 +258,20 @@ __device__ __forceinline__ void load_points(Held<P>& h, const Seat& me, const Lo
             h.y[p] = r.y;
             h.z[p] = r.z;
             h.oi[p] = __float_as_uint(r.w);
-            h.d[p] = __builtin_inff();
+            h.d[p] = MDPS ? a.dist[(int64_t)me.c * a.N + j] : __builtin_inff();
+            if constexpr (BQ && !MDPS) a.bq_map[(int64_t)me.c * a.N + j] = (int32_t)h.oi[p];
+        }
+        if constexpr (MDPS)                 // place t of index j in the walk j = (t A) mod N, or the index itself
+            h.key[p] = a.walk_inv != 0 && j < a.N ? (uint32_t)(((uint64_t)h.oi[p] * a.walk_inv) % (uint64_t)a.N) : h.oi[p];
+    }
+    h.bq_dead = false;
+    h.bq_next = h.bq_room = 0;
+    if constexpr (BQ && MDPS) {
+        if (base < a.N) {                   // (a wave without points records nothing)
+            const uint2 at = bq_place(a, me, P);
+            h.bq_next = uni(at.x);
+            h.bq_room = uni(at.y) & 0xFFu;
+            h.bq_dead = (uni(at.y) >> 8) != 0;
         }
     }
     // the widest gap between two records that follow each other
@@ -228,18 +318,17 @@ __device__ __forceinline__ void load_points(Held<P>& h, const Seat& me, const Lo
             }
         }
     }
-    h.a.lox = ord2f(wave_min_u32(lo[0][0]));
-    h.a.loy = ord2f(wave_min_u32(lo[0][1]));
-    h.a.loz = ord2f(wave_min_u32(lo[0][2]));
-    h.a.hix = ord2f(wave_max_u32(hi[0][0]));
-    h.a.hiy = ord2f(wave_max_u32(hi[0][1]));
-    h.a.hiz = ord2f(wave_max_u32(hi[0][2]));
-    h.b.lox = ord2f(wave_min_u32(lo[1][0]));
-    h.b.loy = ord2f(wave_min_u32(lo[1][1]));
-    h.b.loz = ord2f(wave_min_u32(lo[1][2]));
-    h.b.hix = ord2f(wave_max_u32(hi[1][0]));
-    h.b.hiy = ord2f(wave_max_u32(hi[1][1]));
-    h.b.hiz = ord2f(wave_max_u32(hi[1][2]));
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        Box b;
+        b.lox = ord2f(wave_min_u32(lo[e][0]));
+        b.loy = ord2f(wave_min_u32(lo[e][1]));
+        b.loz = ord2f(wave_min_u32(lo[e][2]));
+        b.hix = ord2f(wave_max_u32(hi[e][0]));
+        b.hiy = ord2f(wave_max_u32(hi[e][1]));
+        b.hiz = ord2f(wave_max_u32(hi[e][2]));
+        if (me.lane == 0) sh.wbox[me.w][e] = b;             // (read by this wave alone)
+    }
 }
 
 // One iteration of Alg. 1 on up-to-date distances: arg-max over the cloud, lowest index among equals.
@@ -404,48 +493,51 @@ __device__ __forceinline__ Box box_of_chunk(const LocalShared& sh, int chunk)
     return Box{sh.box[0][chunk], sh.box[1][chunk], sh.box[2][chunk], sh.box[3][chunk], sh.box[4][chunk], sh.box[5][chunk]};
 }
 
-// Scan and list of a round.  lv: four falling levels.  Returns the length of the list (-1: a wait expired) and the level
-// chosen.
-template <int P>
+// A round's candidates.  Exact FPS: the points with d > level, the farther first, which are samples unless a point before
+// them lies closer than their own distance.  Threshold phase (KEYED): the available points, d >= r2, with keys in front
+// of a window's end, the lower key first, samples unless one before them lies closer than r2.  A candidate goes by
+// its priority, the distance bits or kTopKey - key.
+constexpr uint32_t kTopKey = 0x7FFFFFFFu;
+struct Levels {
+    float r2;                               // KEYED: the level's squared radius
+    float d[kLevels];                       // four falling levels ...
+    uint32_t end[kLevels];                  // ... or growing windows
+};
+template <bool KEYED, int P>
+__device__ __forceinline__ bool listed(const Held<P>& h, const Levels& lv, int p, int j)
+{
+    if constexpr (KEYED) return h.d[p] >= lv.r2 && h.key[p] < lv.end[j];
+    return h.d[p] > lv.d[j];
+}
+
+// Scan and list of a round.  Returns the length of the list (-1: a wait expired) and the level chosen.
+template <int P, bool KEYED>
 __device__ __forceinline__ int make_list(const Held<P>& h, LocalShared& sh, const Seat& me, const LocalArgs& a,
-                                         uint32_t round, const float (&lv)[kLevels], int& level)
+                                         uint32_t round, const Levels& lv, int& level)
 {
     uint32_t c[kLevels] = {};
 #pragma unroll
     for (int p = 0; p < P; ++p) {
-        const uint64_t m = __builtin_amdgcn_ballot_w64(h.d[p] > lv[kLevels - 1]);
+        const uint64_t m = __builtin_amdgcn_ballot_w64(listed<KEYED>(h, lv, p, kLevels - 1));
         if (m != 0) {
             c[kLevels - 1] += __builtin_popcountll(m);
 #pragma unroll
-            for (int j = 0; j < kLevels - 1; ++j) c[j] += __builtin_popcountll(__builtin_amdgcn_ballot_w64(h.d[p] > lv[j]));
+            for (int j = 0; j < kLevels - 1; ++j)
+                c[j] += __builtin_popcountll(__builtin_amdgcn_ballot_w64(listed<KEYED>(h, lv, p, j)));
         }
     }
-    if (me.lane == 0)
-        sh.wcnt[me.w] = (uint64_t)c[0] | ((uint64_t)c[1] << 16) | ((uint64_t)c[2] << 32) | ((uint64_t)c[3] << 48);
+    // where the wave's points lie among those of its half, in the order the waves get here (one workgroup for the cloud:
+    // no halves)
+    const int par = (int)(round & 1u), hf = me.G > 1 && me.w >= kHW ? 1 : 0;
+    uint64_t before = 0;
+    if (me.lane == 0 && c[kLevels - 1] != 0)
+        before = atomicAdd(&sh.cnt[par][hf], (uint64_t)c[0] | ((uint64_t)c[1] << 16) | ((uint64_t)c[2] << 32) | ((uint64_t)c[3] << 48));
     __syncthreads();
     MARK(0);
-    if (me.tid < kList / 32) sh.acc[me.tid] = 0;            // (last looked at before the barrier)
-    if (me.tid < kChunks) sh.took[me.tid] = 0;
-    // a half's points above level j lie behind those above level j - 1, in the order of its waves (one workgroup for
-    // the cloud: no halves)
-    uint64_t sum = 0, before = 0;
-    const int w0 = me.G > 1 ? me.w & kHW : 0, w1 = me.G > 1 ? w0 + kHW : kNW;
-#pragma unroll
-    for (int k = 0; k < kNW; ++k) {
-        const uint64_t v = k >= w0 && k < w1 ? sh.wcnt[k] : 0;
-        sum += v;
-        if (k < me.w) before += v - (v << 16);
-    }
-    sum = uni64(sum);
-    const uint64_t start = uni64((sum << 16) + before);
-    uint32_t at[kLevels];
+    const uint64_t sum = uni64(sh.cnt[par][hf]);
     int tot[kLevels];
 #pragma unroll
-    for (int j = 0; j < kLevels; ++j) {
-        at[j] = (uint32_t)(start >> (16 * j)) & 0xFFFFu;
-        tot[j] = (int)((uint32_t)(sum >> (16 * j)) & 0xFFFFu);
-    }
-    const int par = (int)(round & 1u);
+    for (int j = 0; j < kLevels; ++j) tot[j] = (int)((uint32_t)(sum >> (16 * j)) & 0xFFFFu);
     const int halves = 2 * me.G;
     uint64_t* const hdr = a.ll_hdr + (int64_t)(me.grp * 2 + par) * halves;
     const uint32_t stamp = ((round & kWipeRounds) >> 1) + 1u;
@@ -462,16 +554,25 @@ __device__ __forceinline__ int make_list(const Held<P>& h, LocalShared& sh, cons
 #pragma unroll
         for (int j = 1; j < kLevels; ++j) level = tot[j] <= a.aim ? j : level;
     }
+    if (me.tid < kList / 32) sh.acc[me.tid] = 0;            // (last looked at before the barrier)
+    if (me.tid < kChunks) sh.took[me.tid] = 0;
+    if (me.tid < 2) sh.cnt[par ^ 1][me.tid] = 0;
     if (c[kLevels - 1] != 0) {
+        // the points above level j lie behind those above level j - 1
+        const uint64_t start = uni64((sum << 16) + before - (before << 16));
+        uint32_t at[kLevels];
+#pragma unroll
+        for (int j = 0; j < kLevels; ++j) at[j] = (uint32_t)(start >> (16 * j)) & 0xFFFFu;
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-            const uint64_t m = __builtin_amdgcn_ballot_w64(h.d[p] > lv[kLevels - 1]);
+            const uint64_t m = __builtin_amdgcn_ballot_w64(listed<KEYED>(h, lv, p, kLevels - 1));
             if (m == 0) continue;
+            const uint32_t prio = KEYED ? kTopKey - h.key[p] : __float_as_uint(h.d[p]);
             int pos = kList;
             uint64_t seen = 0;
 #pragma unroll
             for (int j = 0; j < kLevels; ++j) {
-                const uint64_t mj = (j == kLevels - 1 ? m : __builtin_amdgcn_ballot_w64(h.d[p] > lv[j])) & ~seen;
+                const uint64_t mj = (j == kLevels - 1 ? m : __builtin_amdgcn_ballot_w64(listed<KEYED>(h, lv, p, j))) & ~seen;
                 seen |= mj;
                 if (mj != 0 && j <= level) {
                     if (((mj >> me.lane) & 1ull) != 0) pos = (int)at[j] + lanes_below(mj);
@@ -481,10 +582,10 @@ __device__ __forceinline__ int make_list(const Held<P>& h, LocalShared& sh, cons
             if (me.G > 1) {
                 if (pos < kOwn)
                     cand_store(half_list(a, me, par, me.half) + pos * kCandWords3, stamp, h.x[p], h.y[p], h.z[p], h.oi[p],
-                               __float_as_uint(h.d[p]));
+                               prio);
             } else if (pos < kList) {
                 sh.cand[pos] = make_float4(h.x[p], h.y[p], h.z[p], __uint_as_float(h.oi[p]));
-                sh.dist[pos] = __float_as_uint(h.d[p]);
+                sh.dist[pos] = prio;
             }
         }
     }
@@ -503,10 +604,10 @@ __device__ __forceinline__ int make_list(const Held<P>& h, LocalShared& sh, cons
     } else {
         const int nwv = (halves + 63) >> 6;                // waves that hold counts
         if (me.w < nwv) {
-            uint32_t val[1] = {0};
+            uint32_t v = 0;
             bool bad = false;
-            if (me.tid < halves) bad = !ll_wait<1>(hdr + me.tid, round, val, a.wait_ticks);
-            const uint32_t v = bad ? 0u : val[0];
+            if (me.tid < halves) bad = !ll_wait_close(hdr + me.tid, round, v, a.wait_ticks);
+            v = bad ? 0u : v;
             const int s01 = wave_incl_sum((int)((v & 0xFFu) | ((v & 0xFF00u) << 8)), me.lane);
             const int s23 = wave_incl_sum((int)(((v >> 16) & 0xFFu) | ((v >> 8) & 0xFF0000u)), me.lane);
             uint32_t full = 0;
@@ -605,8 +706,9 @@ __device__ __forceinline__ int make_list(const Held<P>& h, LocalShared& sh, cons
 
 // Decides this workgroup's part of the list and leaves the round's samples, of all workgroups, in sh.took.
 // Returns their number, -1 if a wait expired.
+template <bool KEYED>
 __device__ __forceinline__ int decide(LocalShared& sh, const Seat& me, const LocalArgs& a, uint32_t round, int total,
-                                      int room)
+                                      int room, float r2)
 {
     const bool ranked = room < total;                   // uniform
     const int units = (total + kUnit - 1) / kUnit, chunks = (total + 63) >> 6;
@@ -619,14 +721,15 @@ __device__ __forceinline__ int decide(LocalShared& sh, const Seat& me, const Loc
     for (int i = lo + me.w; i < hi; i += kNW) {
         const float4 mc = sh.cand[i];
         const uint32_t md = uni(sh.dist[i]), mi = __float_as_uint(mc.w);
-        uint64_t todo = __builtin_amdgcn_ballot_w64(far >= md && box_dist2(cb, mc.x, mc.y, mc.z) < __uint_as_float(md));
+        const uint32_t rad = KEYED ? __float_as_uint(r2) : md;
+        uint64_t todo = __builtin_amdgcn_ballot_w64(far >= md && box_dist2(cb, mc.x, mc.y, mc.z) < __uint_as_float(rad));
         uint64_t blocked = 0;
         int k = i >> 6;                                 // its own chunk first
         while (true) {
             const float4 oc = sh.cand[64 * k + me.lane];
             const uint32_t od = sh.dist[64 * k + me.lane];
             const bool ahead = od > md || (od == md && __float_as_uint(oc.w) < mi);
-            blocked = __builtin_amdgcn_ballot_w64(ahead && __float_as_uint(dist2(oc.x, oc.y, oc.z, mc.x, mc.y, mc.z)) < md);
+            blocked = __builtin_amdgcn_ballot_w64(ahead && __float_as_uint(dist2(oc.x, oc.y, oc.z, mc.x, mc.y, mc.z)) < rad);
             todo &= ~(1ull << k);
             if (blocked != 0 || todo == 0) break;
             k = first_lane(todo);
@@ -655,10 +758,10 @@ __device__ __forceinline__ int decide(LocalShared& sh, const Seat& me, const Loc
             for (int q = me.tid & ((1 << a.own_shift) - 1); q < words; q += 1 << a.own_shift) {
                 const int u0 = from + 4 * q;
                 if (u0 >= to) break;
-                uint32_t val[1] = {0};
-                if (!ll_wait<1>(msk + (int64_t)g * kWords + q, round, val, a.wait_ticks)) sh.fail = 1;
+                uint32_t val = 0;
+                if (!ll_wait_close(msk + (int64_t)g * kWords + q, round, val, a.wait_ticks)) sh.fail = 1;
                 for (int u = 0; u < 4 && u0 + u < to; ++u)
-                    reinterpret_cast<uint8_t*>(sh.took)[u0 + u] = (uint8_t)(val[0] >> (8 * u));
+                    reinterpret_cast<uint8_t*>(sh.took)[u0 + u] = (uint8_t)(val >> (8 * u));
             }
         }
     } else if (me.tid < 2 * kChunks) {
@@ -672,21 +775,34 @@ __device__ __forceinline__ int decide(LocalShared& sh, const Seat& me, const Loc
 }
 
 // Folds the round's samples into the wave's distances.
-template <int P>
-__device__ __forceinline__ void fold_samples(Held<P>& h, const LocalShared& sh, const Seat& me, int total)
+template <int P, bool BQ, bool KEYED>
+__device__ __forceinline__ void fold_samples(Held<P>& h, const LocalShared& sh, const Seat& me, const LocalArgs& a, int total)
 {
     const int chunks = (total + 63) >> 6, mine = me.lane < chunks ? me.lane : 0;
     const Box cb = box_of_chunk(sh, mine);
-    const float far = sh.box[6][mine];
-    const float bb = fminf(box_box2(h.a, cb), box_box2(h.b, cb));
-    uint64_t todo = __builtin_amdgcn_ballot_w64(me.lane < chunks && sh.took[mine] != 0 && bb < fminf(h.ub, far));
+    float reach = KEYED ? h.ub : fminf(h.ub, sh.box[6][mine]);
+    if constexpr (BQ) reach = fmaxf(reach, a.bq_r2);
+    const Box a0 = sh.wbox[me.w][0], a1 = sh.wbox[me.w][1];
+    const float bb = fminf(box_box2(a0, cb), box_box2(a1, cb));
+    uint64_t todo = __builtin_amdgcn_ballot_w64(me.lane < chunks && sh.took[mine] != 0 && bb < reach);
     bool lowered = false;
     for (; todo != 0; todo &= todo - 1) {
         const int k = first_lane(todo);
         const float4 c = sh.cand[64 * k + me.lane];
-        const float v = __uint_as_float(sh.dist[64 * k + me.lane]);
-        const float bd = fminf(box_dist2(h.a, c.x, c.y, c.z), box_dist2(h.b, c.x, c.y, c.z));
-        uint64_t near = __builtin_amdgcn_ballot_w64(bd < fminf(h.ub, v)) & uni64(sh.took[k]);
+        const float v = KEYED ? __builtin_inff() : __uint_as_float(sh.dist[64 * k + me.lane]);
+        const float bd = fminf(box_dist2(a0, c.x, c.y, c.z), box_dist2(a1, c.x, c.y, c.z));
+        const uint64_t took = uni64(sh.took[k]);
+        uint64_t near = __builtin_amdgcn_ballot_w64(bd < fminf(h.ub, v)) & took;
+        if constexpr (BQ) {
+            uint64_t ball = __builtin_amdgcn_ballot_w64(bd < a.bq_r2) & took;
+            near &= ~ball;
+            lowered = lowered || ball != 0;
+            for (; ball != 0; ball &= ball - 1) {
+                const int l = first_lane(ball);
+                fold_record<P>(h, me, a, rdlane_f(c.x, l), rdlane_f(c.y, l), rdlane_f(c.z, l), rdlane_f(v, l),
+                               rdlane(__float_as_uint(c.w), l));
+            }
+        }
         lowered = lowered || near != 0;
         for (; near != 0; near &= near - 1) {
             const int l = first_lane(near);
@@ -694,6 +810,17 @@ __device__ __forceinline__ void fold_samples(Held<P>& h, const LocalShared& sh, 
         }
     }
     if (lowered) refresh_bound<P>(h);
+}
+
+// A sample found by itself.
+template <int P, bool BQ>
+__device__ __forceinline__ void fold_one(Held<P>& h, const LocalShared& sh, const Seat& me, const LocalArgs& a, float cx, float cy, float cz, float v,
+                                         uint32_t idx)
+{
+    // (a coordinate that is not finite makes the bound one that is not: recorded by the exact test, or not at all)
+    if (BQ && fminf(box_dist2(sh.wbox[me.w][0], cx, cy, cz), box_dist2(sh.wbox[me.w][1], cx, cy, cz)) < a.bq_r2) fold_record<P>(h, me, a, cx, cy, cz, v, idx);
+    else fold<P>(h, cx, cy, cz, v);
+    refresh_bound<P>(h);
 }
 
 // Clears the candidates this workgroup has published; they are gone once the workgroups have met.
@@ -707,33 +834,230 @@ __device__ __forceinline__ void clear_lists(const LocalArgs& a, const Seat& me)
     __syncthreads();
 }
 
-// What order_samples_kernel has to know: whether the cloud's samples are valid (2 bits), their number, and a distance
-// none of them was found below (31 bits).
-__device__ __forceinline__ uint64_t found_state(int status, int count, float low)
+// The stamps of published candidates start again: all workgroups meet when they are done with the last list, clear
+// their words and meet once more.  False if a wait expired.
+template <int P>
+__device__ __forceinline__ bool renew_stamps(const Held<P>& h, LocalShared& sh, const Seat& me, const LocalArgs& a, uint32_t& it,
+                                             uint32_t& seq)
 {
-    return ((uint64_t)(uint32_t)status << 62) | ((uint64_t)__float_as_uint(low) << 31) | (uint32_t)count;
+    if (me.G == 1) return true;
+    for (int k = 0; k < 2; ++k) {
+        const Rec r = plain_pick<P>(h, sh, me, a, it, seq);
+        if (uni(r.fail) != 0) return false;
+        if (k == 0) clear_lists(a, me);
+    }
+    return true;
 }
 
-template <int P>
-__device__ __forceinline__ void run_cloud(const LocalArgs& a, LocalShared& sh, const Seat& me, uint32_t& it,
-                                          uint32_t& seq, uint32_t& round, int& wipe)
+// Progress of one cloud; every field is uniform over all workgroups of the cloud.
+struct Progress {
+    int np;                 // samples found
+    int rounds;
+    float low;              // no sample of the run was found at a distance below
+    uint32_t it, seq, round;
+};
+
+__device__ __forceinline__ uint64_t found_word(uint32_t prio, uint32_t idx)
+{
+    return ((uint64_t)(~prio & kTopKey) << 21) | idx;
+}
+
+// Notes the round's samples (one workgroup).
+__device__ __forceinline__ void note_samples(const LocalShared& sh, const Seat& me, uint64_t* found, int np, int total)
+{
+    int at = np;
+    for (int k = 0; 64 * k < total; ++k) {
+        const uint64_t m = uni64(sh.took[k]);
+        if (k % kNW == me.w && ((m >> me.lane) & 1ull) != 0)
+            found[at + lanes_below(m)] = found_word(sh.dist[64 * k + me.lane], __float_as_uint(sh.cand[64 * k + me.lane].w));
+        at += __builtin_popcountll(m);
+    }
+}
+
+// Exact FPS up to `stop` samples.  Returns the status: 0, 2 if a wait expired.  (Fewer samples at status 0: every point lies
+// on a sample, Alg. 1 takes index 0 from there on.)
+template <int P, bool BQ>
+__device__ __forceinline__ int exact_rounds(Held<P>& h, LocalShared& sh, const Seat& me, const LocalArgs& a, Progress& st,
+                                            uint64_t* found, int stop)
+{
+    float tau = -1.0f;                      // every distance above it is in the next list; < 0: not known
+    float step = 0.8f;                      // ratio of a round's levels
+    int dry = 0, most_dry = 3;
+    while (st.np < stop) {
+        if ((st.round & kWipeRounds) == kWipeRounds) {
+            ++st.round;
+            if (!renew_stamps<P>(h, sh, me, a, st.it, st.seq)) return 2;
+        }
+        if (!(tau > 0.0f)) {
+            const Rec r = plain_pick<P>(h, sh, me, a, st.it, st.seq);
+            if (uni(r.fail) != 0) return 2;
+            const float v = unif(__uint_as_float(r.d));
+            ++st.rounds;
+            if (v == 0.0f) {
+                if (a.dist) {               // a prefix has all its samples
+                    if (me.g == 0)
+                        for (int t = st.np + me.tid; t < stop; t += kT) found[t] = found_word(0u, 0u);
+                    st.np = stop;
+                }
+                return 0;
+            }
+            if (me.g == 0 && me.tid == 0) found[st.np] = found_word(r.d, r.idx);
+            ++st.np;
+            st.low = fminf(st.low, v);
+            fold_one<P, BQ>(h, sh, me, a, unif(r.x), unif(r.y), unif(r.z), v, uni(r.idx));
+            tau = v < __builtin_inff() ? v : -1.0f;
+            dry = 0;
+            continue;
+        }
+        ++st.round;
+        ++st.rounds;
+        Levels lv;
+        lv.r2 = 0.0f;
+        lv.d[0] = tau;
+#pragma unroll
+        for (int j = 1; j < kLevels; ++j) lv.d[j] = lv.d[j - 1] * step;
+        int level;
+        const int total = make_list<P, false>(h, sh, me, a, st.round, lv, level);
+        if (total < 0) return 2;
+#pragma unroll
+        for (int j = 1; j < kLevels; ++j) tau = j == level ? lv.d[j] : tau;
+        if (level == kLevels - 1) step = fmaxf(step * step, 0.3f);
+        else if (level == 0) step = sqrtf(step);
+        else if (level == 1) step = sqrtf(sqrtf(step) * step);
+        if (total == 0) {
+            if (++dry >= most_dry) {
+                tau = -1.0f;
+                most_dry = 1;               // (until a list is of use again)
+            }
+            continue;
+        }
+        dry = 0;
+        most_dry = 3;
+        st.low = fminf(st.low, tau);
+        const int got = decide<false>(sh, me, a, st.round, total, stop - st.np, 0.0f);
+        if (got < 0) return 2;
+        fold_samples<P, BQ, false>(h, sh, me, a, total);
+        if ((int)(st.round % (uint32_t)me.G) == me.g) note_samples(sh, me, found, st.np, total);
+        st.np += got;
+        MARK(7);
+    }
+    return 0;
+}
+
+// The first thread of the cloud's first workgroup: where a run of samples begins.
+__device__ __forceinline__ void begin_run(const LocalArgs& a, const Seat& me, int& runs, int at, uint32_t low)
+{
+    if (me.g == 0 && me.tid == 0 && runs < kLocalRuns) {
+        a.cloud[me.c].begin[runs] = at;
+        a.cloud[me.c].low[runs] = low;
+    }
+    ++runs;
+}
+
+// Threshold sampling (main loop of Alg. 2): the available points, d >= R_l^2, in the order of their keys.  Within a
+// level the points with the lowest key of their neighbourhood are taken at once: a point that is not available never
+// becomes so, and one that no available point with a lower key lies closer to than R_l stays available until its
+// turn.  A round's list holds all available points in front of a window's end; the window grows as there is room.
+// `seg`, the level (from 1), is left at nseg + 1 when the last one is exhausted.
+template <int P, bool BQ>
+__device__ __forceinline__ int threshold_rounds(Held<P>& h, LocalShared& sh, LevelShared& ls, const Seat& me, const LocalArgs& a,
+                                                Progress& st, uint64_t* found, int& seg, int& runs)
+{
+    const int n = a.n;
+    int level_end = 0;                      // first position the quota rule puts above the level: ceil(n l / nseg)
+    uint32_t end = 0, len = 1;
+    auto enter = [&]() {
+        level_end = (int)(((int64_t)n * seg + a.nseg - 1) / a.nseg);
+        if (me.tid == 0 && ls.level_start[seg - 1] < 0) ls.level_start[seg - 1] = st.np;
+        begin_run(a, me, runs, st.np, ~0u);
+        end = 0;
+        len = (uint32_t)(a.N / 64 + 1);
+    };
+    while (st.np < n) {
+        if (st.np >= level_end) {
+            while (st.np >= level_end) {
+                ++seg;
+                level_end = (int)(((int64_t)n * seg + a.nseg - 1) / a.nseg);
+            }
+            enter();
+        }
+        if ((st.round & kWipeRounds) == kWipeRounds) {
+            ++st.round;
+            if (!renew_stamps<P>(h, sh, me, a, st.it, st.seq)) return 2;
+        }
+        ++st.round;
+        ++st.rounds;
+        const int room = (level_end < n ? level_end : n) - st.np;
+        Levels lv;
+        lv.r2 = unif(ls.thr[seg - 1]);
+        lv.end[0] = end;
+#pragma unroll
+        for (int j = 1; j < kLevels; ++j) {
+            const uint64_t e = (uint64_t)end + ((uint64_t)len << (j - 1));
+            lv.end[j] = e < (uint64_t)a.N ? (uint32_t)e : (uint32_t)a.N;
+        }
+        if (lv.end[2] == (uint32_t)a.N) lv.end[1] = end + ((uint32_t)a.N - end) / 2;
+        int level;
+        const int total = make_list<P, true>(h, sh, me, a, st.round, lv, level);
+        if (total < 0) return 2;
+#pragma unroll
+        for (int j = 1; j < kLevels; ++j) end = j == level ? lv.end[j] : end;
+        if (level == kLevels - 1) len = len < 0x40000000u ? len * 2u : len;
+        else if (level == 0) len = len / 4u + 1u;
+        else if (level == 1) len = len / 2u + 1u;
+        if (total == 0) {
+            if (end < (uint32_t)a.N) continue;
+            if (me.tid == 0) ls.level_exhausted[seg - 1] = 1;
+            ++seg;
+            if (seg > a.nseg) return 0;     // early termination
+            enter();
+            continue;
+        }
+        const int got = decide<true>(sh, me, a, st.round, total, room, lv.r2);
+        if (got < 0) return 2;
+        fold_samples<P, BQ, true>(h, sh, me, a, total);
+        if ((int)(st.round % (uint32_t)me.G) == me.g) note_samples(sh, me, found, st.np, total);
+        st.np += got;
+        MARK(7);
+    }
+    return 0;
+}
+
+// MDPS false: exact FPS up to a.stop samples; with a.dist, the prefix of Alg. 2, whose distances are kept there.  MDPS true:
+// what follows the prefix -- thresholds, threshold sampling, exact FPS for what remains when the last level is exhausted.
+template <int P, bool BQ, bool MDPS>
+__device__ __forceinline__ void run_cloud(const LocalArgs& a, LocalShared& sh, LevelShared* ls, const Seat& me, Progress& st)
 {
     const int n = a.n, N = a.N;
-    uint64_t* const found = a.found + (int64_t)me.c * n;        // [0]: found_state; then the samples
+    uint64_t* const found = a.found + (int64_t)me.c * n;
+    LocalCloud* const cl = a.cloud + me.c;
     const int start = uni(a.start_idx ? a.start_idx[me.c] : 0);
     const long long t0 = wall_clock64();
-    int status = 0, np = 1, rounds = 0;
-    float low = __builtin_inff();           // no sample was found at a distance below
-    if (start < 0 || start >= N) {
-        status = 1;                                             // uniform over the group
-    } else {
+    long long t1 = t0, t2 = t0, t3 = t0;
+    int status = MDPS ? uni(cl->status) : (start < 0 || start >= N ? 1 : 0);        // uniform over the group
+    int runs = 0, et_index = n, prefix_ticks = 0;
+    st.np = 1;
+    st.rounds = 0;
+    st.low = __builtin_inff();
+    if constexpr (MDPS) {
+        if (me.tid < FP_MAX_SEG) {
+            ls->level_start[me.tid] = -1;
+            ls->level_exhausted[me.tid] = 0;
+            ls->thr[me.tid] = 0.0f;
+        }
+    }
+    if (status == 0) {
         Held<P> h;
-        load_points<P>(h, me, a);
+        load_points<P, BQ, MDPS>(h, sh, me, a);
         if (me.tid == 0) sh.fail = 0;
-        const float* s = a.xyz + ((int64_t)me.c * N + start) * 3;
-        h.ub = __builtin_inff();
-        fold<P>(h, s[0], s[1], s[2], __builtin_inff());
-        refresh_bound<P>(h);
+        if (me.tid < 4) sh.cnt[me.tid >> 1][me.tid & 1] = 0;
+        if constexpr (!MDPS) {
+            const float* s = a.xyz + ((int64_t)me.c * N + start) * 3;
+            h.ub = __builtin_inff();
+            fold_one<P, BQ>(h, sh, me, a, s[0], s[1], s[2], __builtin_inff(), (uint32_t)start);
+        } else {
+            refresh_bound<P>(h);
+        }
         __syncthreads();
 #ifdef FASTPOINT_PHASE_CLOCKS
         if (me.tid == 0) {
@@ -741,85 +1065,56 @@ __device__ __forceinline__ void run_cloud(const LocalArgs& a, LocalShared& sh, c
             clk_at = wall_clock64();
         }
 #endif
-        float tau = -1.0f;                  // every distance above it is in the next list; < 0: not known
-        float step = 0.8f;                  // ratio of a round's levels
-        int dry = 0, most_dry = 3;
-        while (np < n) {
-            if ((round & kWipeRounds) == kWipeRounds) {
-                ++round;                    // the stamps of published candidates start again
-                wipe = 2;
-                tau = -1.0f;
+        if constexpr (!MDPS) {
+            begin_run(a, me, runs, 1, 0);
+            status = exact_rounds<P, BQ>(h, sh, me, a, st, found, a.stop);
+            if (me.g == 0 && me.tid == 0) cl->low[0] = __float_as_uint(st.low);
+        } else {
+            st.np = uni(cl->count);
+            st.rounds = uni(cl->rounds);
+            prefix_ticks = uni(cl->ticks);
+            int seg = 0;
+            const float* curve = a.curve + (int64_t)me.c * n;
+            if (me.tid < 64 && a.m - me.tid >= 1) ls->ring[(a.m - me.tid) & 63] = curve[a.m - me.tid];
+            if (me.tid < FP_MAX_SEG) {
+                const int b = me.tid < a.nseg ? boundary_index(n, a.nseg, me.tid + 1) : n;
+                ls->thr_meas[me.tid] = b <= a.m ? curve[b] : 0.0f;
             }
-            if (!(tau > 0.0f)) {
-                const Rec r = plain_pick<P>(h, sh, me, a, it, seq);
-                if (uni(r.fail) != 0) {
-                    status = 2;
-                    break;
-                }
-                if (wipe == 2 && me.G > 1) {
-                    // All workgroups are done with the words of the last list; they are gone before the workgroups
-                    // have met once more.
-                    clear_lists(a, me);
-                }
-                wipe = wipe > 0 ? wipe - 1 : 0;
-                const float v = unif(__uint_as_float(r.d));
-                ++rounds;
-                if (v == 0.0f) break;       // every point lies on a sample: Alg. 1 takes index 0 from here on
-                if (me.g == 0 && me.tid == 0) found[np] = ((uint64_t)(~r.d) << 32) | r.idx;
-                ++np;
-                low = fminf(low, v);
-                fold<P>(h, unif(r.x), unif(r.y), unif(r.z), v);
-                refresh_bound<P>(h);
-                tau = v < __builtin_inff() && wipe == 0 ? v : -1.0f;
-                dry = 0;
-                continue;
+            if (me.tid < 32) {
+                const int64_t ik = ((int64_t)a.m * (me.tid + 1)) / 32;
+                ls->mlp_val[me.tid] = curve[ik < 1 ? 1 : ik];
             }
-            ++round;
-            ++rounds;
-            float lv[kLevels];
-            lv[0] = tau;
+            __syncthreads();
+            predict_thresholds(a, *ls, me.tid);
+            __syncthreads();
+            t1 = wall_clock64();
+            status = threshold_rounds<P, BQ>(h, sh, *ls, me, a, st, found, seg, runs);
+            t2 = wall_clock64();
+            if (status == 0 && st.np < n) {
+                et_index = st.np;
+                const int tail = runs;
+                begin_run(a, me, runs, st.np, 0);
+                st.low = __builtin_inff();
+                status = exact_rounds<P, BQ>(h, sh, me, a, st, found, n);
+                if (me.g == 0 && me.tid == 0) cl->low[tail] = __float_as_uint(st.low);
+            }
+            t3 = wall_clock64();
+        }
+        if constexpr (!MDPS)
+            if (a.dist) {
+                const int base = (me.half * kHW + (me.w & (kHW - 1))) * P * 64;
 #pragma unroll
-            for (int j = 1; j < kLevels; ++j) lv[j] = lv[j - 1] * step;
-            int level;
-            const int total = make_list<P>(h, sh, me, a, round, lv, level);
-            if (total < 0) {
-                status = 2;
-                break;
+                for (int p = 0; p < P; ++p)
+                    if (base + p * 64 + me.lane < N) a.dist[(int64_t)me.c * N + base + p * 64 + me.lane] = h.d[p];
             }
-#pragma unroll
-            for (int j = 1; j < kLevels; ++j) tau = j == level ? lv[j] : tau;
-            if (level == kLevels - 1) step = fmaxf(step * step, 0.3f);
-            else if (level == 0) step = sqrtf(step);
-            else if (level == 1) step = sqrtf(sqrtf(step) * step);
-            if (total == 0) {
-                if (++dry >= most_dry) {
-                    tau = -1.0f;
-                    most_dry = 1;           // (until a list is of use again)
-                }
-                continue;
+        if constexpr (BQ) {
+            if (me.lane == 0) {
+                if (!MDPS && a.dist && (me.half * kHW + (me.w & (kHW - 1))) * P * 64 < N)
+                    bq_place(a, me, P) = make_uint2(h.bq_next, h.bq_room | (h.bq_dead ? 0x100u : 0u));
+                if (h.bq_room != 0)
+                    a.bq_fill[(int64_t)me.c * (a.bq_cap / kBqChunk) + h.bq_next / (uint32_t)kBqChunk] =
+                        (uint32_t)kBqChunk - h.bq_room;
             }
-            dry = 0;
-            most_dry = 3;
-            low = fminf(low, tau);
-            const int got = decide(sh, me, a, round, total, n - np);
-            if (got < 0) {
-                status = 2;
-                break;
-            }
-            fold_samples<P>(h, sh, me, total);
-            if ((int)(round % (uint32_t)me.G) == me.g) {
-                // this workgroup notes the round's samples
-                int at = np;
-                for (int k = 0; 64 * k < total; ++k) {
-                    const uint64_t m = uni64(sh.took[k]);
-                    if (k % kNW == me.w && ((m >> me.lane) & 1ull) != 0)
-                        found[at + lanes_below(m)] = ((uint64_t)(~sh.dist[64 * k + me.lane]) << 32) |
-                                                     __float_as_uint(sh.cand[64 * k + me.lane].w);
-                    at += __builtin_popcountll(m);
-                }
-            }
-            np += got;
-            MARK(7);
         }
     }
 #ifdef FASTPOINT_PHASE_CLOCKS
@@ -827,16 +1122,34 @@ __device__ __forceinline__ void run_cloud(const LocalArgs& a, LocalShared& sh, c
         for (int k = 0; k < 16; ++k)
             a.ll_mask[(int64_t)2 * kMaxGroup * kWords + blockIdx.x * 16 + k] = (uint64_t)clk[k];
 #endif
+    __syncthreads();
     if (me.g == 0 && me.tid == 0) {
-        found[0] = found_state(status, np, low);
-        if (a.info) {
+        const int ticks = (int)(wall_clock64() - t0);
+        cl->status = status;
+        cl->count = st.np;
+        cl->rounds = st.rounds;
+        cl->ticks = ticks;
+        cl->runs = runs;
+        cl->begin[runs < kLocalRuns ? runs : kLocalRuns] = st.np;
+        if (a.info && (MDPS || !a.dist)) {
             fp_mdps_info inf = {};
             if (status != 1) {
-                inf.m = n - 1;
-                inf.et_index = n;
-                for (int l = 0; l < FP_MAX_SEG; ++l) inf.level_start[l] = -1;
-                inf.rounds = rounds;
-                inf.phase_ticks[0] = (int32_t)(wall_clock64() - t0);
+                inf.m = MDPS ? a.m : n - 1;
+                inf.et_index = et_index;
+                for (int l = 0; l < FP_MAX_SEG; ++l) {
+                    inf.level_start[l] = MDPS ? ls->level_start[l] : -1;
+                    if constexpr (MDPS) {
+                        inf.level_exhausted[l] = ls->level_exhausted[l];
+                        inf.thr2[l] = ls->thr[l];
+                    }
+                }
+                inf.rounds = st.rounds;
+                inf.phase_ticks[0] = MDPS ? prefix_ticks : ticks;
+                if constexpr (MDPS) {
+                    inf.phase_ticks[1] = (int32_t)(t1 - t0);
+                    inf.phase_ticks[2] = (int32_t)(t2 - t1);
+                    inf.phase_ticks[3] = (int32_t)(t3 - t2);
+                }
             }
             inf.status = status;
             a.info[me.c] = inf;
@@ -845,10 +1158,11 @@ __device__ __forceinline__ void run_cloud(const LocalArgs& a, LocalShared& sh, c
     __syncthreads();
 }
 
-template <int P>
-__global__ __launch_bounds__(kT) void local_fps_kernel(LocalArgs a)
+template <int P, bool BQ, bool MDPS>
+__global__ __launch_bounds__(kT) void local_kernel(LocalArgs a)
 {
     __shared__ LocalShared sh;
+    __shared__ LevelShared ls[1];
     Seat me;
     me.tid = (int)threadIdx.x;
     me.lane = me.tid & 63;
@@ -856,13 +1170,18 @@ __global__ __launch_bounds__(kT) void local_fps_kernel(LocalArgs a)
     me.G = a.G;
     me.grp = (int)blockIdx.x / a.G;
     me.g = (int)blockIdx.x % a.G;
-    const int ngroups = (int)gridDim.x / a.G;
     me.half = me.g + (me.w >= kHW ? me.G : 0);
-    uint32_t it = 0, seq = 0, round = 0;
-    int wipe = 0;
+    const int ngroups = (int)gridDim.x / a.G;
+    if constexpr (BQ && !MDPS) {
+        // the header of the ball-query cache
+        if (blockIdx.x == 0 && threadIdx.x == 0)
+            *reinterpret_cast<BqHeader*>(a.bq_base) = bq_layout(a.B, a.N, a.n, a.bq_r2, a.bq_cap, 1);
+    }
+    Progress st;
+    st.it = st.seq = st.round = 0;
     for (int c = me.grp; c < a.B; c += ngroups) {
         me.c = c;
-        run_cloud<P>(a, sh, me, it, seq, round, wipe);
+        run_cloud<P, BQ, MDPS>(a, sh, ls, me, st);
     }
 }
 
@@ -875,8 +1194,11 @@ constexpr int kOrderT = 1024;
 constexpr int kRanges = 4096;                   // 2^12
 
 __global__ __launch_bounds__(kOrderT) void order_samples_kernel(const uint64_t* __restrict__ found_all,
-                                                                const int32_t* __restrict__ start_idx, int n, int Q,
-                                                                int32_t* __restrict__ out_idx, float* __restrict__ out_mdc)
+                                                                const LocalCloud* __restrict__ clouds,
+                                                                const int32_t* __restrict__ start_idx, int N, int n, int Q,
+                                                                bool fill, int32_t* __restrict__ out_idx,
+                                                                float* __restrict__ out_mdc, int32_t* __restrict__ bq_idx,
+                                                                int32_t* __restrict__ inv)
 {
     __shared__ uint64_t key[kOrderMost];
     __shared__ int32_t first[kRanges + 1];              // counts, then keys in front of the range
@@ -884,131 +1206,157 @@ __global__ __launch_bounds__(kOrderT) void order_samples_kernel(const uint64_t* 
     __shared__ int32_t sums[kOrderT / 64];
     __shared__ int32_t mine[2];
     const int b = (int)blockIdx.y, q = (int)blockIdx.x, tid = (int)threadIdx.x, lane = tid & 63;
-    const uint64_t* found = found_all + (int64_t)b * n;
-    const uint64_t state = found[0];
-    const int status = (int)(state >> 62), np = (int)(state & 0x7FFFFFFFu);
-    int32_t* idx = out_idx + (int64_t)b * n;
-    float* mdc = out_mdc ? out_mdc + (int64_t)b * n : nullptr;
-    if (status != 0) {
-        for (int t = q * kOrderT + tid; t < n; t += Q * kOrderT) idx[t] = -1;
+    const LocalCloud& cl = clouds[b];
+    const int np = cl.count, runs = cl.runs;
+    // again: a point that is a sample already (index 0, found at distance 0); the record has no row for it
+    auto put = [&](int pos, uint32_t dbits, uint32_t i, bool again) {
+        out_idx[(int64_t)b * n + pos] = (int32_t)i;
+        if (out_mdc) out_mdc[(int64_t)b * n + pos] = __uint_as_float(dbits);
+        if (bq_idx) bq_idx[(int64_t)b * n + pos] = again ? -1 : (int32_t)i;
+        if (inv && !again) inv[(int64_t)b * N + i] = pos;
+    };
+    if (cl.status != 0) {
+        if (fill)
+            for (int t = q * kOrderT + tid; t < n; t += Q * kOrderT) {
+                out_idx[(int64_t)b * n + t] = -1;
+                if (bq_idx) bq_idx[(int64_t)b * n + t] = -1;               // no centre matches this cloud's record
+            }
         return;
     }
-    for (int t = np + q * kOrderT + tid; t < n; t += Q * kOrderT) {        // every point lies on a sample
-        idx[t] = 0;
-        if (mdc) mdc[t] = 0.0f;
-    }
-    if (q == 0 && tid == 0) {
-        idx[0] = start_idx ? start_idx[b] : 0;
-        if (mdc) mdc[0] = __builtin_inff();
-    }
-    const int m = np - 1;
-    if (m == 0) return;                                                    // uniform
-    const uint64_t* keys = found + 1;
-    // 1 - f / 2 in place of 1 / (1 + f) inside a power of two: all in whole numbers, and falling with the distance
-    const int low = (int)((uint32_t)(state >> 54) & 0xFFu);                // exponent of the bound
-    auto range_of = [&](uint64_t k) {
-        const uint32_t v = ~(uint32_t)(k >> 32);
-        const int o = (int)(v >> 23) - low;
-        const int r = o < 12 ? (int)(((1u << 24) - (v & 0x7FFFFFu)) >> (12 + o)) : 0;
-        return r < kRanges ? r : kRanges - 1;
-    };
-    for (int t = tid; t < kRanges; t += kOrderT) {
-        first[t] = 0;
-        next[t] = 0;
-    }
-    __syncthreads();
-    constexpr int U = 16;                                                  // loads a thread has under way
-    for (int t0 = tid; t0 < m; t0 += kOrderT * U) {
-        uint64_t k[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) k[u] = t0 + u * kOrderT < m ? keys[t0 + u * kOrderT] : 0;
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (t0 + u * kOrderT < m) atomicAdd(&first[range_of(k[u])], 1);
-    }
-    __syncthreads();
-    int c[4], sum = 0;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        c[u] = first[4 * tid + u];
-        sum += c[u];
-    }
-    const int incl = wave_incl_sum(sum, lane);
-    if (lane == 63) sums[tid >> 6] = incl;
-    __syncthreads();
-    int at = incl - sum;
-    for (int w = 0; w < (tid >> 6); ++w) at += sums[w];
-    // the ranges that begin in [q m / Q, (q + 1) m / Q)
-    const int share0 = (int)((int64_t)m * q / Q), share1 = (int)((int64_t)m * (q + 1) / Q);
-    if (tid < 2) mine[tid] = kRanges;
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int r = 4 * tid + u;
-        first[r] = at;
-        // (the first range that does not begin before a border: one thread finds it, or none)
-        if (at < share0 && at + c[u] >= share0) mine[0] = r + 1;
-        if (at < share1 && at + c[u] >= share1) mine[1] = r + 1;
-        at += c[u];
-    }
-    if (tid == kOrderT - 1) first[kRanges] = at;
-    __syncthreads();
-    const int r0 = q == 0 ? 0 : mine[0], r1 = mine[1];
-    if (r0 >= r1) return;                                                  // uniform: nothing begins there
-    const int from = first[r0], count = first[r1] - from;
-    if (count <= kOrderMost) {
+    if (fill)
+        for (int t = np + q * kOrderT + tid; t < n; t += Q * kOrderT) put(t, 0u, 0u, true);        // every point lies on a sample
+    if (q == 0 && tid == 0) put(0, 0x7F800000u, start_idx ? (uint32_t)start_idx[b] : 0u, false);
+    if (runs == 0 || np <= cl.begin[0]) return;                            // uniform
+    const int all = cl.begin[0], len = np - all;
+    const int s0 = all + (int)((int64_t)len * q / Q), s1 = all + (int)((int64_t)len * (q + 1) / Q);
+    for (int run = 0; run < runs; ++run) {
+        const int r_begin = cl.begin[run], m = cl.begin[run + 1] - r_begin;
+        const int share0 = s0 - r_begin, share1 = s1 - r_begin;            // this workgroup's share of the run's positions
+        if (m <= 0 || share1 <= 0 || share0 >= m) continue;                // uniform
+        const uint64_t* const keys = found_all + (int64_t)b * n + r_begin;
+        const uint32_t bound = cl.low[run];
+        const bool keyed = bound == ~0u;
+        // 1 - f / 2 in place of 1 / (1 + f) inside a power of two: all in whole numbers, and falling with the distance
+        const int low = (int)(bound >> 23);                                // exponent of the bound
+        const int shift = N <= kRanges ? 0 : 32 - __builtin_clz((uint32_t)(N - 1) >> 12);
+        auto range_of = [&](uint64_t k) {
+            const uint32_t p = (uint32_t)(k >> 21);
+            int r;
+            if (keyed) {
+                r = (int)(p >> shift);
+            } else {
+                const uint32_t v = ~p & kTopKey;
+                const int o = (int)(v >> 23) - low;
+                r = o < 12 ? (int)(((1u << 24) - (v & 0x7FFFFFu)) >> (12 + (o > 0 ? o : 0))) : 0;
+            }
+            return r < kRanges ? r : kRanges - 1;
+        };
+        auto emit = [&](int place, uint64_t k) {
+            const uint32_t v = ~(uint32_t)(k >> 21) & kTopKey;
+            put(r_begin + place, keyed ? 0u : v, (uint32_t)k & 0x1FFFFFu, !keyed && v == 0u);
+        };
+        __syncthreads();
+        for (int t = tid; t < kRanges; t += kOrderT) {
+            first[t] = 0;
+            next[t] = 0;
+        }
+        __syncthreads();
+        constexpr int U = 16;                                              // loads a thread has under way
         for (int t0 = tid; t0 < m; t0 += kOrderT * U) {
             uint64_t k[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) k[u] = t0 + u * kOrderT < m ? keys[t0 + u * kOrderT] : 0;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int r = range_of(k[u]);
-                if (t0 + u * kOrderT < m && r >= r0 && r < r1) key[first[r] - from + atomicAdd(&next[r], 1)] = k[u];
-            }
+            for (int u = 0; u < U; ++u)
+                if (t0 + u * kOrderT < m) atomicAdd(&first[range_of(k[u])], 1);
         }
         __syncthreads();
-        for (int t = tid; t < count; t += kOrderT) {
-            const uint64_t k = key[t];
-            const int r = range_of(k), lo = first[r] - from, hi = first[r + 1] - from;
-            int place = first[r];
-            for (int e = lo; e < hi; ++e) place += key[e] < k || (key[e] == k && e < t) ? 1 : 0;
-            idx[1 + place] = (int32_t)(uint32_t)k;
-            if (mdc) mdc[1 + place] = __uint_as_float(~(uint32_t)(k >> 32));
+        int c[4], sum = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            c[u] = first[4 * tid + u];
+            sum += c[u];
         }
-        return;
-    }
-    // many equal distances: each of these keys is counted against all
-    for (int t = tid; t < m; t += kOrderT) {
-        const uint64_t k = keys[t];
-        const int r = range_of(k);
-        if (r < r0 || r >= r1) continue;
-        int place = 0;
-        for (int e = 0; e < m; ++e) place += keys[e] < k || (keys[e] == k && e < t) ? 1 : 0;
-        idx[1 + place] = (int32_t)(uint32_t)k;
-        if (mdc) mdc[1 + place] = __uint_as_float(~(uint32_t)(k >> 32));
+        const int incl = wave_incl_sum(sum, lane);
+        if (lane == 63) sums[tid >> 6] = incl;
+        if (tid < 2) mine[tid] = kRanges;
+        __syncthreads();
+        int at = incl - sum;
+        for (int w = 0; w < (tid >> 6); ++w) at += sums[w];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int r = 4 * tid + u;
+            first[r] = at;
+            // (the first range that does not begin before a border: one thread finds it, or none)
+            if (at < share0 && at + c[u] >= share0) mine[0] = r + 1;
+            if (at < share1 && at + c[u] >= share1) mine[1] = r + 1;
+            at += c[u];
+        }
+        if (tid == kOrderT - 1) first[kRanges] = at;
+        __syncthreads();
+        const int r0 = share0 <= 0 ? 0 : mine[0], r1 = share1 >= m ? kRanges : mine[1];
+        if (r0 >= r1) continue;                                            // uniform: no range begins in the share
+        const int from = first[r0], count = first[r1] - from;
+        if (count <= kOrderMost) {
+            for (int t0 = tid; t0 < m; t0 += kOrderT * U) {
+                uint64_t k[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) k[u] = t0 + u * kOrderT < m ? keys[t0 + u * kOrderT] : 0;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int r = range_of(k[u]);
+                    if (t0 + u * kOrderT < m && r >= r0 && r < r1) key[first[r] - from + atomicAdd(&next[r], 1)] = k[u];
+                }
+            }
+            __syncthreads();
+            for (int t = tid; t < count; t += kOrderT) {
+                const uint64_t k = key[t];
+                const int r = range_of(k), lo = first[r] - from, hi = first[r + 1] - from;
+                int place = first[r];
+                for (int e = lo; e < hi; ++e) place += key[e] < k || (key[e] == k && e < t) ? 1 : 0;
+                emit(place, k);
+            }
+        } else {
+            // many equal distances: each of these keys is counted against all
+            for (int t = tid; t < m; t += kOrderT) {
+                const uint64_t k = keys[t];
+                const int r = range_of(k);
+                if (r < r0 || r >= r1) continue;
+                int place = 0;
+                for (int e = 0; e < m; ++e) place += keys[e] < k || (keys[e] == k && e < t) ? 1 : 0;
+                emit(place, k);
+            }
+        }
     }
 }
 
 }  // namespace
 
-const void* local_fps_kernel_for(int points_per_thread)
+template <int P>
+static const void* pick_kernel(bool bq, bool mdps)
+{
+    if (bq) return mdps ? reinterpret_cast<const void*>(&local_kernel<P, true, true>) : reinterpret_cast<const void*>(&local_kernel<P, true, false>);
+    return mdps ? reinterpret_cast<const void*>(&local_kernel<P, false, true>) : reinterpret_cast<const void*>(&local_kernel<P, false, false>);
+}
+
+const void* local_kernel_for(int points_per_thread, bool bq, bool mdps)
 {
     switch (points_per_thread) {
-        case 1: return reinterpret_cast<const void*>(&local_fps_kernel<1>);
-        case 2: return reinterpret_cast<const void*>(&local_fps_kernel<2>);
-        case 4: return reinterpret_cast<const void*>(&local_fps_kernel<4>);
-        case 8: return reinterpret_cast<const void*>(&local_fps_kernel<8>);
+        case 1: return pick_kernel<1>(bq, mdps);
+        case 2: return pick_kernel<2>(bq, mdps);
+        case 4: return pick_kernel<4>(bq, mdps);
+        case 8: return pick_kernel<8>(bq, mdps);
         default: return nullptr;
     }
 }
 
-hipError_t launch_order_samples(const uint64_t* found, const int32_t* start_idx, int B, int n, int32_t* out_idx,
-                                float* out_mdc, hipStream_t stream)
+hipError_t launch_order_samples(const uint64_t* found, const LocalCloud* cloud, const int32_t* start_idx, int B, int N, int n,
+                                int most, bool fill, int32_t* out_idx, float* out_mdc, int32_t* bq_idx, int32_t* inv,
+                                hipStream_t stream)
 {
-    const int Q = n <= kOrderMost ? 1 : (n + kOrderMost / 2 - 1) / (kOrderMost / 2);
-    hipLaunchKernelGGL(order_samples_kernel, dim3((unsigned)Q, (unsigned)B), dim3(kOrderT), 0, stream, found, start_idx,
-                       n, Q, out_idx, out_mdc);
+    const int Q = most <= kOrderMost / 2 ? 1 : (most + kOrderMost / 2 - 1) / (kOrderMost / 2);
+    hipLaunchKernelGGL(order_samples_kernel, dim3((unsigned)Q, (unsigned)B), dim3(kOrderT), 0, stream, found, cloud,
+                       start_idx, N, n, Q, fill, out_idx, out_mdc, bq_idx, inv);
     return hipGetLastError();
 }
 

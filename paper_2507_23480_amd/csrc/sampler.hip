@@ -42,6 +42,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "estimator.h"
 #include "kernels.h"
 #include "wave.h"
 
@@ -536,36 +537,6 @@ __device__ __forceinline__ void flush_picks(const SamplerArgs& a, Shared<T>& sh,
     flushed = upto;
 }
 
-// x^e for an integer x >= 1 in binary64 using only + - * / (each correctly rounded
-// by IEEE 754), in a fixed order: ln x from the atanh series after scaling x into
-// [sqrt(1/2), sqrt(2)), then exp by its Taylor series after removing a multiple of ln 2.
-// A CPU reference that performs the same operations in the same order gets the same bits.
-__device__ __noinline__ double pow_int_base(int64_t x, double e)
-{
-    const double LN2 = 0.6931471805599453;
-    int k = 63 - __builtin_clzll((unsigned long long)x);
-    double f = (double)x * __longlong_as_double((long long)(1023 - k) << 52);   // exact, in [1,2)
-    if (f > 1.4142135623730951) {
-        f = f * 0.5;
-        k = k + 1;
-    }
-    const double s = (f - 1.0) / (f + 1.0);
-    const double s2 = s * s;
-    double sum = 0.0;
-    // unrolled: the quotients 1/(2t+1) are then constants (rounded correctly when the compiler folds
-    // them, the bits the division gives at run time), and thirteen divisions go away
-#pragma unroll
-    for (int t = 12; t >= 0; --t) sum = sum * s2 + 1.0 / (double)(2 * t + 1);
-    const double lnx = ((double)k * LN2) + ((2.0 * s) * sum);
-    const double y = e * lnx;
-    const double q = floor(y / LN2 + 0.5);
-    const double r = y - q * LN2;
-    double acc = 1.0;
-#pragma unroll 1
-    for (int t = 20; t >= 1; --t) acc = 1.0 + acc * (r / (double)t);
-    return acc * __longlong_as_double((long long)(1023 + (int)q) << 52);
-}
-
 // Cell-ordered variant: which of the first `count` entries of `list` (one entry per lane) this
 // wave has to fold -- those that can lower one of its distances and, in a recording kernel, those
 // whose ball can reach into the wave's box.  `ball` gets the latter: only they need the radius test.
@@ -585,54 +556,6 @@ __device__ __forceinline__ void refresh_bound(Points<P, BQ>& pt)
 #pragma unroll
     for (int p = 1; p < P; ++p) m = max(m, __float_as_uint(pt.d[p]));
     pt.ub = wave_max_u32(m);
-}
-
-// ln v for a normal positive binary64 v and exp y, with + - * / only in a fixed order (the steps
-// pow_int_base is made of): a CPU reference performing the same operations gets the same bits.
-__device__ __noinline__ double ln_fixed(double v)
-{
-    const double LN2 = 0.6931471805599453;
-    const long long bits = __double_as_longlong(v);
-    int k = (int)((bits >> 52) & 0x7FF) - 1023;
-    double f = __longlong_as_double((bits & 0x000FFFFFFFFFFFFFll) | (1023ll << 52));   // in [1,2)
-    if (f > 1.4142135623730951) {
-        f = f * 0.5;
-        k = k + 1;
-    }
-    const double s = (f - 1.0) / (f + 1.0);
-    const double s2 = s * s;
-    double sum = 0.0;
-    // unrolled: the quotients 1/(2t+1) are then constants (rounded correctly when the compiler folds
-    // them, the bits the division gives at run time), and thirteen divisions go away
-#pragma unroll
-    for (int t = 12; t >= 0; --t) sum = sum * s2 + 1.0 / (double)(2 * t + 1);
-    return ((double)k * LN2) + ((2.0 * s) * sum);
-}
-__device__ __noinline__ double exp_fixed(double y)
-{
-    const double LN2 = 0.6931471805599453;
-    if (!(y >= -700.0)) y = -700.0;
-    if (y > 700.0) y = 700.0;
-    const double q = floor(y / LN2 + 0.5);
-    const double r = y - q * LN2;
-    double acc = 1.0;
-#pragma unroll 1
-    for (int t = 20; t >= 1; --t) acc = 1.0 + acc * (r / (double)t);
-    return acc * __longlong_as_double((long long)(1023 + (int)q) << 52);
-}
-
-// One layer of the MLP estimator: neuron `o` (of NOUT) starts from its bias and adds the products
-// with the NIN inputs in ascending order; weights input-major, so the threads of a wave read
-// adjacent words.
-template <int NIN, int NOUT, bool RELU>
-__device__ __forceinline__ void mlp_layer(const float* __restrict__ w, const float* __restrict__ bias,
-                                          const double* in, double* out, int o)
-{
-    if (o >= NOUT) return;
-    double acc = (double)bias[o];
-#pragma unroll 4
-    for (int k = 0; k < NIN; ++k) acc = acc + (double)w[k * NOUT + o] * in[k];
-    out[o] = (RELU && !(acc > 0.0)) ? 0.0 : acc;
 }
 
 // Folds the picks waiting in sh.pend (sample positions base, base+1, ...) into the distances.
@@ -745,15 +668,6 @@ __device__ __forceinline__ void follow_picks(Points<P, BQ>& pt, Shared<T>& sh, c
         if (records) flush_rows<P, BQ>(rw, a, wh, pt, base + handed, s - handed);
         handed = s;
     }
-}
-
-// segment boundary b_l (curve index whose value becomes R_l), l = 1..nseg
-__device__ __forceinline__ int boundary_index(int n, int nseg, int l)
-{
-    int64_t b = ((int64_t)n * l) / nseg;
-    b = b < 1 ? 1 : b;
-    b = b > n - 1 ? n - 1 : b;
-    return (int)b;
 }
 
 // Optional phase timing for tuning (-DFASTPOINT_PHASE_CLOCKS): wall-clock ticks spent in
@@ -2178,79 +2092,7 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
     if constexpr (MODE != 0) if (ok && !pure_fps) {
         // ---- thresholds from the estimated curve (Eq. 1 with a/x^e; estimator call and list radii of Alg. 2)
         __syncthreads();
-        if (a.use_override) {
-            if (wh.tid < a.nseg) sh.thr[wh.tid] = a.thr_override[wh.tid];
-        } else if (a.mlp) {
-            // ---- MLP estimator (Appendix A.3): 32 log-ratios of the prefix curve in, 64 log-ratios
-            //      of the rest of the curve out; every workgroup of the cloud computes the same
-            const float* __restrict__ W1 = a.mlp;
-            const float* __restrict__ b1 = W1 + 32 * 128;
-            const float* __restrict__ W2 = b1 + 128;
-            const float* __restrict__ b2 = W2 + 128 * 128;
-            const float* __restrict__ W3 = b2 + 128;
-            const float* __restrict__ b3 = W3 + 128 * 64;
-            const double last = (double)sh.ring[m & 63];
-            if (wh.tid < 32) {
-                const double ratio = (double)sh.mlp_val[wh.tid] / last;
-                sh.mlp_a[wh.tid] = (ratio >= 1.0 && ratio <= 1e300) ? ln_fixed(ratio) : 0.0;
-            }
-            __syncthreads();
-            mlp_layer<32, 128, true>(W1, b1, sh.mlp_a, sh.mlp_b, wh.tid);
-            __syncthreads();
-            mlp_layer<128, 128, true>(W2, b2, sh.mlp_b, sh.mlp_a, wh.tid);
-            __syncthreads();
-            mlp_layer<128, 64, false>(W3, b3, sh.mlp_a, sh.mlp_b, wh.tid);
-            __syncthreads();
-            if (wh.tid < a.nseg) {
-                // the estimated curve at this level's boundary: the outputs interpolated linearly
-                const int l = wh.tid;
-                const int64_t b = boundary_index(n, a.nseg, l + 1);
-                float r;
-                if (b <= m) {
-                    r = sh.thr_meas[l];
-                } else {
-                    const double u = ((double)(b - m) * 64.0) / (double)(n - 1 - m);
-                    int j0 = (int)floor(u);
-                    if (j0 > 64) j0 = 64;
-                    const double frac = u - (double)j0;
-                    const double v0 = j0 == 0 ? 0.0 : sh.mlp_b[j0 - 1];
-                    const double v1 = j0 >= 64 ? sh.mlp_b[63] : sh.mlp_b[j0];
-                    const double y = v0 + frac * (v1 - v0);
-                    r = (float)((a.bias2 * (double)a.level_scale[l]) * (last * exp_fixed(y)));
-                }
-                if (!(r >= 1.17549435e-38f)) r = 1.17549435e-38f;
-                sh.thr[l] = r;
-            }
-            __syncthreads();
-            if (wh.tid == 0)
-                for (int l = 1; l < a.nseg; ++l)
-                    if (sh.thr[l] > sh.thr[l - 1]) sh.thr[l] = sh.thr[l - 1];
-        } else {
-            const int W = a.fit_window < m ? a.fit_window : m;
-            if (wh.tid < W) {
-                const int ii = m - W + 1 + wh.tid;
-                sh.terms[wh.tid] = (double)sh.ring[ii & 63] * pow_int_base(ii, a.exponent);
-            } else if (wh.tid >= 64 && wh.tid < 64 + a.nseg) {
-                const int l = wh.tid - 64;
-                sh.powb[l] = pow_int_base(boundary_index(n, a.nseg, l + 1), a.exponent);
-            }
-            __syncthreads();
-            if (wh.tid == 0) {
-                double acc = 0.0;
-                for (int t = 0; t < W; ++t) acc += sh.terms[t];
-                acc = acc / (double)W;
-                float prev = 0.0f;
-                for (int l = 0; l < a.nseg; ++l) {
-                    float r;
-                    if (boundary_index(n, a.nseg, l + 1) <= m) r = sh.thr_meas[l];
-                    else r = (float)(((a.bias2 * (double)a.level_scale[l]) * acc) / sh.powb[l]);
-                    if (!(r >= 1.17549435e-38f)) r = 1.17549435e-38f;
-                    if (l >= 1 && r > prev) r = prev;
-                    sh.thr[l] = r;
-                    prev = r;
-                }
-            }
-        }
+        predict_thresholds(a, sh, wh.tid);
         __syncthreads();
         int seg = 0;
         if (wh.tid == 0) {

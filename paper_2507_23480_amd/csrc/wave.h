@@ -153,6 +153,35 @@ __device__ __forceinline__ bool ll_wait(const uint64_t* p, uint32_t stamp, uint3
     }
 }
 
+// The same for one word, with four reads under way a sixth of a trip apart: a trip takes some 700 ns, and waiting for the
+// answer before asking again finds the word half a trip late on average.
+__device__ __forceinline__ bool ll_wait_close(const uint64_t* p, uint32_t stamp, uint32_t& val, int64_t wait_ticks)
+{
+    constexpr int N = 4;
+    uint64_t v[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        v[k] = ll_load(p);
+        if (k + 1 < N) __builtin_amdgcn_s_sleep(3);
+    }
+    int64_t t0 = 0;
+    for (uint32_t spin = 0;; ++spin) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            if ((uint32_t)(v[k] >> 32) == stamp) {
+                val = (uint32_t)v[k];
+                return true;
+            }
+            v[k] = ll_load(p);
+        }
+        if ((spin & 15u) == 15u || wait_ticks <= 0) {
+            const int64_t now = (int64_t)wall_clock64();
+            if (t0 == 0) t0 = now;
+            else if (now - t0 > wait_ticks) return false;
+        }
+    }
+}
+
 struct Rec {          // one arg-max candidate: squared distance bits, index, coordinates
     uint32_t d, idx;
     float x, y, z;

@@ -1,10 +1,10 @@
-"""Exact FPS by local decisions (the cell-ordered fps_exact): the samples and the curve of the index-ordered kernels, bit for
+"""Sampling by local decisions (the cell-ordered fps_exact, and mdps_sample_pruned from 5000 samples on): the samples and the curve of the index-ordered kernels, bit for
 bit, where the sampler and the kernel that puts the samples in sequence change their ways -- one to eight points per
 thread, one workgroup and many, lists at their limits, equal distances, n at the edges of a workgroup's keys."""
 import numpy as np
 import pytest
 
-from tests.routes import exact_by_index
+from tests.routes import exact_by_index, scan
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -69,3 +69,67 @@ def test_duplicates_and_start(fp):
 
 def test_more_clouds_than_fit(fp):
     compare(fp, np.stack([cloud("uniform", 3000 + 0 * b) + b for b in range(60)]), 400, 5)
+
+
+def info_words(fp, info):
+    return [(i.m, i.et_index, list(i.level_start), list(i.level_exhausted), list(i.thr2), i.status)
+            for i in fp.parse_info(info)]
+
+
+def compare_mdps(fp, p, n, G, prm, radius, start=None):
+    """From 5000 samples on the cell-ordered MDPS runs by local decisions: against the index-ordered kernels, the record
+    against the scan of all points."""
+    x = torch.from_numpy(p).cuda()
+    want, winfo = fp.mdps_sample(x, n, prm, want_info=True, start_idx=start)
+    cache = fp.new_bq_cache(x, n)
+    fp.set_wg_per_cloud(G)
+    try:
+        got, info = fp.mdps_sample_pruned(x, n, prm, want_info=True, start_idx=start)
+        rec = fp.mdps_sample_pruned(x, n, prm, start_idx=start, bq_cache=cache, bq_radius=radius)
+        torch.cuda.synchronize()
+    finally:
+        fp.set_wg_per_cloud(0)
+    assert torch.equal(got, want) and torch.equal(rec, want)
+    assert info_words(fp, info) == info_words(fp, winfo)
+    for a, b in zip(fp.ball_query(x, rec, radius, 16, bq_cache=cache), scan(fp, x, rec, radius, 16)):
+        assert torch.equal(a, b)
+    return fp.bq_cache_stats(cache)
+
+
+# bias: levels cut by their quota (0.8), exhausted (1.05), exhausted early, so that most of the samples are a remainder (2.0)
+@pytest.mark.parametrize("bias", [0.8, 1.05, 2.0])
+@pytest.mark.parametrize("order", [0, 1])
+@pytest.mark.parametrize("N,G", [(8192, 1), (8192, 2), (12001, 3), (12001, 12), (40000, 40), (66000, 129)])
+def test_mdps(fp, order, N, G, bias):
+    stats = compare_mdps(fp, cloud("uniform", N)[None], 5000, G, fp.MdpsParams(exponent=0.7, bias=bias, scan_order=order), 0.04)
+    assert stats["cell_order"] and not any(stats["incomplete"])
+
+
+@pytest.mark.parametrize("order", [0, 1])
+@pytest.mark.parametrize("kind", ["sheet", "dense corner", "lattice"])
+def test_mdps_uneven(fp, kind, order):
+    radius = {"sheet": 1.0, "dense corner": 0.03, "lattice": 1.5}[kind]
+    prm = fp.MdpsParams(exponent=1.0, bias=1.05, scan_order=order)
+    compare_mdps(fp, np.stack([cloud(kind, 20480), cloud(kind, 20480)[::-1]]), 5003, 20, prm, radius, start=[20479, 5])
+
+
+@pytest.mark.parametrize("order", [0, 1])
+def test_mdps_duplicates(fp, order):
+    """More samples than different points: exact FPS repeats index 0, in the prefix already or at the end."""
+    for different in (300, 4000):
+        p = np.resize(cloud("uniform", different), (9000, 3))
+        compare_mdps(fp, p[None], 6000, 9, fp.MdpsParams(exponent=0.7, bias=1.05, scan_order=order), 0.05)
+
+
+def test_mdps_given_thresholds_small_record_and_short_prefix(fp):
+    p = cloud("uniform", 20000)[None]
+    x = torch.from_numpy(p).cuda()
+    thr = [0.004, 0.0025, 0.0012]
+    compare_mdps(fp, p, 5000, 20, fp.MdpsParams(p=0.001, nseg=3, m_min=1, thr_override=thr), 0.04)
+    compare_mdps(fp, p, 5000, 20, fp.MdpsParams(p=0.9999, exponent=0.7), 0.04)          # the prefix is everything
+    prm = fp.MdpsParams(exponent=0.7, bias=1.05, scan_order=1)
+    small = fp.new_bq_cache(x, 5000, 256)
+    got = fp.mdps_sample_pruned(x, 5000, prm, bq_cache=small, bq_radius=0.04)
+    assert all(fp.bq_cache_stats(small)["incomplete"])
+    for a, b in zip(fp.ball_query(x, got, 0.04, 16, bq_cache=small), scan(fp, x, got, 0.04, 16)):
+        assert torch.equal(a, b)
