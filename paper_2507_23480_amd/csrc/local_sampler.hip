@@ -76,6 +76,7 @@ struct LocalShared {
     uint32_t full[kMaxGroup / 32];
     uint32_t acc[kList / 32];               // decisions on the candidates of this workgroup's part of the list
     int32_t fail;
+    int32_t in_order;                       // follow_order: samples known to be in sequence
     Rec wrec[2][kNW];
     Rec win[2];
 };
@@ -1023,6 +1024,145 @@ __device__ __forceinline__ int threshold_rounds(Held<P>& h, LocalShared& sh, Lev
     return 0;
 }
 
+// Clouds in sampling order (the gathered samples of an earlier stage), whose samples are 0, 1, 2, ... again: what
+// follow_order of sampler.hip does, on points in cell order.  A wave folds the points of the sequence that come near its
+// boxes and looks at its largest distance in front of each; between two of them that stays, while the curve falls (which
+// is checked), so the last of a stretch decides.  8 x 6000 gathered samples, 1500 of them: 280 -> 104 us.  Returns how many of the first points are the samples in sequence (1: not
+// tried; 0: a wait expired); the distances are left anywhere.
+__device__ __forceinline__ bool agree_in_order(LocalShared& sh, const Seat& me, const LocalArgs& a, uint32_t& round)
+{
+    __syncthreads();
+    if (me.G == 1) return true;
+    ++round;
+    uint64_t* const hdr = a.ll_hdr + (int64_t)(me.grp * 2 + (int)(round & 1u)) * (2 * me.G);
+    if (me.tid == 0) ll_store(hdr + me.g, (uint32_t)sh.in_order, round);
+    __syncthreads();
+    if (me.tid < me.G) {
+        uint32_t val = 0;
+        if (ll_wait_close(hdr + me.tid, round, val, a.wait_ticks)) atomicMin(&sh.in_order, (int)val);
+        else sh.fail = 1;
+    }
+    __syncthreads();
+    return uni(sh.fail) == 0;
+}
+constexpr int64_t kOrderWords = 4 * kHalfWords;             // per workgroup: most points the words hold
+template <int P>
+__device__ __forceinline__ int follow_order(Held<P>& h, LocalShared& sh, const Seat& me, const LocalArgs& a, uint32_t& round)
+{
+    const int n = a.n, N = a.N;
+    const float* __restrict__ cloud = a.xyz + (int64_t)me.c * N * 3;
+    if (n < 16 || n > kOrderWords * me.G || (round & kWipeRounds) > kWipeRounds - 32 || round >= 1u << 18) return 1;
+    {
+        // every workgroup looks at the same points
+        const float x0 = cloud[0], y0 = cloud[1], z0 = cloud[2];
+        const float d1 = dist2(x0, y0, z0, cloud[3], cloud[4], cloud[5]);
+        const int64_t j = ((int64_t)me.tid * N) / kT;
+        const float d = dist2(x0, y0, z0, cloud[3 * j], cloud[3 * j + 1], cloud[3 * j + 2]);
+        if (__syncthreads_or(!(d <= d1) || !(d1 > 0.0f) || !(d1 < __builtin_inff()))) return 1;
+    }
+    if (me.tid == 0) sh.in_order = n;
+    ++round;
+    const uint32_t stamp = round;
+    uint64_t* const words = half_list(a, me, 0, 0);         // (a stamp of 32 bits is no stamp of a candidate's)
+    float* const part = reinterpret_cast<float*>(sh.cand);
+    const Box a0 = sh.wbox[me.w][0], a1 = sh.wbox[me.w][1];
+    refresh_bound<P>(h);                                    // (0 for a wave without points)
+    float last_v = __builtin_inff();
+    int good = 0;                                           // points up to the last one this wave has folded
+    int from = 0, upto = n < 64 ? n : 64;
+    __syncthreads();
+    while (true) {
+        for (int b = (from >> 6) + me.g; 64 * b < upto; b += me.G) {
+            const int k = 64 * b + me.lane, kk = k < N ? k : N - 1;
+            const float kx = cloud[(int64_t)kk * 3], ky = cloud[(int64_t)kk * 3 + 1], kz = cloud[(int64_t)kk * 3 + 2];
+            const int len = (64 / kNW) * (b + 1);
+            uint32_t v = 0x7F800000u;
+            for (int i0 = me.w * len; i0 < (me.w + 1) * len; i0 += 64 / kNW) {
+                const int il = i0 + (me.lane & (64 / kNW - 1)), ij = il < N ? il : N - 1;
+                const float px = cloud[(int64_t)ij * 3], py = cloud[(int64_t)ij * 3 + 1], pz = cloud[(int64_t)ij * 3 + 2];
+#pragma unroll
+                for (int u = 0; u < 64 / kNW; ++u) {
+                    const uint32_t t = __float_as_uint(dist2(rdlane_f(px, u), rdlane_f(py, u), rdlane_f(pz, u), kx, ky, kz));
+                    v = i0 + u < k && t < v ? t : v;
+                }
+            }
+            part[me.tid] = __uint_as_float(v);
+            __syncthreads();
+            if (me.w == 0) {
+#pragma unroll
+                for (int w = 1; w < kNW; ++w) v = min(v, __float_as_uint(part[w * 64 + me.lane]));
+                if (k >= from && k < upto) ll_store(words + k, v, stamp);
+            }
+            __syncthreads();
+        }
+        int bad = n;
+        for (int c = from >> 6; 64 * c < upto && bad == n; ++c) {
+            const int k = 64 * c + me.lane;
+            const bool has = k >= from && k < upto;
+            float kx = 0.0f, ky = 0.0f, kz = 0.0f, v = 0.0f;
+            bool late = false;
+            if (has) {
+                uint32_t val = 0;
+                late = !ll_wait_close(words + k, stamp, val, a.wait_ticks);
+                v = __uint_as_float(val);
+                kx = cloud[(int64_t)k * 3];
+                ky = cloud[(int64_t)k * 3 + 1];
+                kz = cloud[(int64_t)k * 3 + 2];
+            }
+            if (__builtin_amdgcn_ballot_w64(late) != 0) {
+                if (me.lane == 0) sh.fail = 1;
+                break;
+            }
+            float before = __shfl_up(v, 1);
+            if (me.lane == 0 || k == from) before = last_v;
+            const uint64_t rises = __builtin_amdgcn_ballot_w64(has && (!(v <= before) || !(v > 0.0f)));
+            if (rises != 0) bad = 64 * c + first_lane(rises);
+            const int end = upto - 64 * c < 64 ? upto - 64 * c : 64;
+            last_v = rdlane_f(v, end - 1);
+            const float bd = fminf(box_dist2(a0, kx, ky, kz), box_dist2(a1, kx, ky, kz));
+            for (uint64_t near = __builtin_amdgcn_ballot_w64(has && bd < h.ub); near != 0; near &= near - 1) {
+                const int s = first_lane(near);
+                if (64 * c + s >= bad) break;
+                if (h.ub > rdlane_f(v, s)) {
+                    bad = good;
+                    break;
+                }
+                fold<P>(h, rdlane_f(kx, s), rdlane_f(ky, s), rdlane_f(kz, s), __builtin_inff());
+                refresh_bound<P>(h);
+                good = 64 * c + s + 1;
+            }
+        }
+        if (bad < n || h.ub > last_v) bad = min(bad, good); // (what lies behind the last one folded has not been looked at)
+        if (bad < n && me.lane == 0) atomicMin(&sh.in_order, bad);
+        if (!agree_in_order(sh, me, a, round)) return 0;
+        if (uni(sh.in_order) < upto || upto == n) break;
+        from = upto;
+        upto = n / 8 < upto ? n : 8 * upto;
+        __syncthreads();                                    // (in_order has been read by all)
+    }
+    const int known = uni(sh.in_order);
+    __syncthreads();
+    return known > 1 ? known : 1;
+}
+
+// Folds the first `known` points, samples in sequence.
+template <int P>
+__device__ __forceinline__ void fold_order(Held<P>& h, const LocalShared& sh, const Seat& me, const LocalArgs& a, int known)
+{
+    const float* __restrict__ cloud = a.xyz + (int64_t)me.c * a.N * 3;
+    const Box a0 = sh.wbox[me.w][0], a1 = sh.wbox[me.w][1];
+    for (int k0 = 0; k0 < known; k0 += 64) {
+        const int k = k0 + me.lane, kk = k < known ? k : 0;
+        const float kx = cloud[(int64_t)kk * 3], ky = cloud[(int64_t)kk * 3 + 1], kz = cloud[(int64_t)kk * 3 + 2];
+        const float bd = fminf(box_dist2(a0, kx, ky, kz), box_dist2(a1, kx, ky, kz));
+        for (uint64_t near = __builtin_amdgcn_ballot_w64(k < known && bd < h.ub); near != 0; near &= near - 1) {
+            const int s = first_lane(near);
+            fold<P>(h, rdlane_f(kx, s), rdlane_f(ky, s), rdlane_f(kz, s), __builtin_inff());
+        }
+        refresh_bound<P>(h);
+    }
+}
+
 // MDPS false: exact FPS up to a.stop samples; with a.dist, the prefix of Alg. 2, whose distances are kept there.  MDPS true:
 // what follows the prefix -- thresholds, threshold sampling, exact FPS for what remains when the last level is exhausted.
 template <int P, bool BQ, bool MDPS>
@@ -1052,9 +1192,31 @@ __device__ __forceinline__ void run_cloud(const LocalArgs& a, LocalShared& sh, L
         if (me.tid == 0) sh.fail = 0;
         if (me.tid < 4) sh.cnt[me.tid >> 1][me.tid & 1] = 0;
         if constexpr (!MDPS) {
+            int known = 1;
+            if constexpr (!BQ) {
+                if (start == 0 && !a.dist) {
+                    __syncthreads();                        // (fail)
+                    known = follow_order<P>(h, sh, me, a, st.round);
+                    if (known == 0) status = 2;
+                    if (known > 1 && me.g == 0) {
+                        const uint64_t* const words = half_list(a, me, 0, 0);
+                        for (int k = 1 + me.tid; k < known; k += kT) found[k] = found_word((uint32_t)ll_load(words + k), (uint32_t)k);
+                    }
+                    if (known > 1) {
+                        st.np = known;
+                        st.low = __uint_as_float((uint32_t)ll_load(half_list(a, me, 0, 0) + known - 1));
+                    }
+#pragma unroll
+                    for (int p = 0; p < P; ++p) h.d[p] = h.oi[p] != kNoIdx ? __builtin_inff() : 0.0f;
+                }
+            }
             const float* s = a.xyz + ((int64_t)me.c * N + start) * 3;
             h.ub = __builtin_inff();
-            fold_one<P, BQ>(h, sh, me, a, s[0], s[1], s[2], __builtin_inff(), (uint32_t)start);
+            if (known > 1) {
+                if (known < n) fold_order<P>(h, sh, me, a, known);
+            } else {
+                fold_one<P, BQ>(h, sh, me, a, s[0], s[1], s[2], __builtin_inff(), (uint32_t)start);
+            }
         } else {
             refresh_bound<P>(h);
         }
@@ -1067,7 +1229,7 @@ __device__ __forceinline__ void run_cloud(const LocalArgs& a, LocalShared& sh, L
 #endif
         if constexpr (!MDPS) {
             begin_run(a, me, runs, 1, 0);
-            status = exact_rounds<P, BQ>(h, sh, me, a, st, found, a.stop);
+            if (status == 0) status = exact_rounds<P, BQ>(h, sh, me, a, st, found, a.stop);
             if (me.g == 0 && me.tid == 0) cl->low[0] = __float_as_uint(st.low);
         } else {
             st.np = uni(cl->count);

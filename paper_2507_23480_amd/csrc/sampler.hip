@@ -173,6 +173,7 @@ struct Shared {
     alignas(16) uint32_t bin_cnt[kCandWin], bin_first[kCandWin + 4];
     uint32_t seq_d[kCandWin];
     uint16_t seq_id[kCandWin];
+    int32_t in_order;          // follow_order: samples known to be in sequence
 };
 
 // Everything one thread needs to know about where it sits.
@@ -1913,6 +1914,206 @@ __device__ __forceinline__ bool fps_rounds(Points<P, BQ>& pt, Shared<T>& sh, con
     }
 }
 
+// ------------------------------------------------------------------ clouds in sampling order
+// The samples of a farthest point sampling, gathered, are the next stage's cloud of a hierarchy, and sampling that gives
+// 0, 1, 2, ... again.  Following such a sequence takes no search: v_k, the distance of point k to the points before
+// it, is the curve if no point is ever farther from the samples before k than v_k.  follow_order tries whether the cloud is
+// of this kind and returns how many of its first points are the samples in sequence (at least 1; 0 if a wait
+// expired); a cloud that is not in this order shows it by a few hundred points farther from point 0 than point 1 is,
+// before anything is spent on it.  The first 64 points are tried, then 512, then eight times as many a time, so that a sequence
+// that breaks off costs at most a few times what was gained by it.  With BQ the points are recorded once a stretch is known
+// to be samples (an entry that went too far could not be taken back).  `n`: samples wanted -- of MDPS the prefix, after
+// which samples gathered from MDPS are in no such order.  `place`: where the wave's part of the record has got to.
+//
+// v_k is worked out by 64 points at a time (a workgroup per 64, its waves sharing the points before them), and handed to the
+// other workgroups in stamped words; every wave then folds the points one after the other, as in the rounds, but
+// without waiting for a search.  Bound: the fold.  us, before -> now: fps_exact of 16 clouds of 512 gathered samples, 128 of
+// them, 42 -> 27; of 8 x 1500, 375 of them, 108 -> 97; mdps_sample with record of 8 x 6000 samples gathered from MDPS, 1500 of
+// them (the prefix of 150), 546 -> 443.  (Tried beyond the prefix on such clouds it cost 85 us and gained nothing.)
+constexpr int64_t kOrderWords = (int64_t)2 * kCandMax * kCandWords;    // per workgroup: most points the words hold
+
+__device__ __forceinline__ uint64_t* order_words(const SamplerArgs& a, const Where& wh)
+{
+    return a.ll_cd + (int64_t)wh.grp * wh.G * kOrderWords;
+}
+// smallest value over the cloud's workgroups of sh.in_order; false if a wait expired.  All threads call it.
+template <int T>
+__device__ __forceinline__ bool agree_in_order(const SamplerArgs& a, Shared<T>& sh, const Where& wh, uint32_t& seq)
+{
+    __syncthreads();
+    if (wh.G == 1) return true;
+    ++seq;
+    uint64_t* ct = a.ll_ct + (int64_t)(wh.grp * 2 + (int)(seq & 1u)) * wh.G;
+    if (wh.tid == 0) ll_store(ct + wh.g, (uint32_t)sh.in_order, seq);
+    __syncthreads();
+    if (wh.tid < wh.G) {
+        uint32_t val[1];
+        if (ll_wait<1>(ct + wh.tid, seq, val, a.wait_ticks)) atomicMin(&sh.in_order, (int)val[0]);
+        else sh.ctrl[2] = 1;
+    }
+    __syncthreads();
+    return uni(sh.ctrl[2]) == 0;
+}
+
+struct BqPlace {
+    uint32_t cur, lim, nxt;
+    bool dead;
+};
+
+template <int T, int P, bool BQ>
+__device__ __forceinline__ int follow_order(const SamplerArgs& a, Shared<T>& sh, const Where& wh, uint32_t& seq, int n, BqPlace& place)
+{
+    constexpr int NW = T / 64;
+    const int N = a.N;
+    const float* __restrict__ cloud = a.xyz + (int64_t)wh.c * N * 3;
+    if (n < 16 || n > kOrderWords * wh.G) return 1;
+    {
+        // every workgroup looks at the same points
+        const float x0 = cloud[0], y0 = cloud[1], z0 = cloud[2];
+        const float d1 = dist2(x0, y0, z0, cloud[3], cloud[4], cloud[5]);
+        const int j = (int)(((int64_t)(wh.tid & (T - 1)) * N) / T);
+        const float d = dist2(x0, y0, z0, cloud[3 * (int64_t)j], cloud[3 * (int64_t)j + 1], cloud[3 * (int64_t)j + 2]);
+        if (__syncthreads_or(!(d <= d1) || !(d1 > 0.0f) || !(d1 < __builtin_inff()))) return 1;
+    }
+    Points<P, BQ> pt;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int j = ((wh.gw * P + p) << 6) | wh.lane;
+        pt.x[p] = j < N ? cloud[(int64_t)j * 3 + 0] : kPadCoord;
+        pt.y[p] = j < N ? cloud[(int64_t)j * 3 + 1] : kPadCoord;
+        pt.z[p] = j < N ? cloud[(int64_t)j * 3 + 2] : kPadCoord;
+        pt.d[p] = j < N ? __builtin_inff() : 0.0f;
+    }
+    pt.bq_cur = place.cur;
+    pt.bq_lim = place.lim;
+    pt.bq_nxt = place.nxt;
+    pt.bq_dead = place.dead;
+    if (wh.tid == 0) {
+        sh.ctrl[2] = 0;
+        sh.in_order = n;
+    }
+    __syncthreads();
+    uint64_t* const words = order_words(a, wh);
+    const uint32_t stamp = ++seq;
+    float* const part = reinterpret_cast<float*>(sh.cand);
+    static_assert(sizeof(sh.cand) >= NW * 64 * sizeof(float), "a value per lane of the point waves");
+    RowWords<P, BQ> rw;
+    int from = 0, upto = n < 64 ? n : 64;
+    while (true) {
+        // v of the points [from, upto)
+        for (int b = (from >> 6) + wh.g; 64 * b < upto; b += wh.G) {
+            const int k = 64 * b + wh.lane, kk = k < N ? k : N - 1;
+            if (!wh.ctrl) {
+                const float kx = cloud[(int64_t)kk * 3], ky = cloud[(int64_t)kk * 3 + 1], kz = cloud[(int64_t)kk * 3 + 2];
+                const int len = 8 * (b + 1);                            // an eighth of the points up to the last of the 64
+                uint32_t v = 0x7F800000u;
+                for (int i0 = wh.w * len; i0 < (wh.w + 1) * len; i0 += 8) {
+                    const int il = i0 + (wh.lane & 7), ij = il < N ? il : N - 1;
+                    const float px = cloud[(int64_t)ij * 3], py = cloud[(int64_t)ij * 3 + 1], pz = cloud[(int64_t)ij * 3 + 2];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const uint32_t t = __float_as_uint(dist2(rdlane_f(px, u), rdlane_f(py, u), rdlane_f(pz, u), kx, ky, kz));
+                        v = i0 + u < k && t < v ? t : v;
+                    }
+                }
+                part[wh.w * 64 + wh.lane] = __uint_as_float(v);
+            }
+            __syncthreads();
+            if (wh.w == 0) {
+                uint32_t v = __float_as_uint(part[wh.lane]);
+#pragma unroll
+                for (int w = 1; w < NW; ++w) v = min(v, __float_as_uint(part[w * 64 + wh.lane]));
+                if (k >= from && k < upto) ll_store(words + k, v, stamp);
+            }
+            __syncthreads();
+        }
+        // every wave follows the points
+        if (!wh.ctrl) {
+            int bad = n;
+            for (int c = from >> 6; 64 * c < upto && bad == n; ++c) {
+                const int k = 64 * c + wh.lane;
+                const bool has = k >= from && k < upto;
+                float kx = 0.0f, ky = 0.0f, kz = 0.0f, v = 0.0f;
+                bool late = false;
+                if (has) {
+                    uint32_t val[1];
+                    late = !ll_wait<1>(words + k, stamp, val, a.wait_ticks);
+                    v = __uint_as_float(val[0]);
+                    kx = cloud[(int64_t)k * 3];
+                    ky = cloud[(int64_t)k * 3 + 1];
+                    kz = cloud[(int64_t)k * 3 + 2];
+                }
+                if (__builtin_amdgcn_ballot_w64(late) != 0) {
+                    if (wh.lane == 0) sh.ctrl[2] = 1;
+                    break;
+                }
+                const int s0 = from > 64 * c ? from - 64 * c : 0, s1 = upto - 64 * c < 64 ? upto - 64 * c : 64;
+                for (int s = s0; s < s1; ++s) {
+                    const float vs = rdlane_f(v, s);
+                    uint64_t far = 0;
+#pragma unroll
+                    for (int p = 0; p < P; ++p) far |= __builtin_amdgcn_ballot_w64(pt.d[p] > vs);
+                    if (far != 0 || !(vs > 0.0f)) {
+                        bad = 64 * c + s;
+                        break;
+                    }
+                    fold<P, BQ, true, false>(pt, rdlane_f(kx, s), rdlane_f(ky, s), rdlane_f(kz, s), a, wh, 0, rw);
+                }
+            }
+            if (bad < n && wh.lane == 0) atomicMin(&sh.in_order, bad);
+        }
+        if (!agree_in_order<T>(a, sh, wh, seq)) return 0;
+        const int known = uni(sh.in_order);
+        if constexpr (BQ) {
+            const int most = known < upto ? known : upto;
+            if (!wh.ctrl && known > 1) {
+                for (int c = from >> 6; 64 * c < most; ++c) {
+                    const int k = 64 * c + wh.lane, kk = k < most ? k : 0;
+                    const float kx = cloud[(int64_t)kk * 3], ky = cloud[(int64_t)kk * 3 + 1], kz = cloud[(int64_t)kk * 3 + 2];
+                    rw.clear(wh);
+                    const int s0 = from > 64 * c ? from - 64 * c : 0, s1 = most - 64 * c < 64 ? most - 64 * c : 64;
+                    for (int s = s0; s < s1; ++s) {
+                        const float cx = rdlane_f(kx, s), cy = rdlane_f(ky, s), cz = rdlane_f(kz, s);
+#pragma unroll
+                        for (int p = 0; p < P; ++p) {
+                            const uint64_t hits = __builtin_amdgcn_ballot_w64(dist2(cx, cy, cz, pt.x[p], pt.y[p], pt.z[p]) < a.bq_r2);
+                            if (hits != 0) rw.row[p * 64 + s] = hits;
+                        }
+                    }
+                    flush_rows<P, BQ>(rw, a, wh, pt, 64 * c, 64);
+                }
+            }
+        }
+        if (known < upto || upto == n) {
+            __syncthreads();
+            place.cur = pt.bq_cur;
+            place.lim = pt.bq_lim;
+            place.nxt = pt.bq_nxt;
+            place.dead = pt.bq_dead;
+            return known > 1 ? known : 1;
+        }
+        from = upto;
+        upto = n / 8 < upto ? n : 8 * upto;
+        __syncthreads();                            // (in_order has been read by all)
+    }
+}
+
+// v_k of a cloud in sampling order (k >= 1), as follow_order left it.
+__device__ __forceinline__ float order_value(const SamplerArgs& a, const Where& wh, int k)
+{
+    return k == 0 ? __builtin_inff() : __uint_as_float((uint32_t)ll_load(order_words(a, wh) + k));
+}
+
+// The curve's values the thresholds need, from the first `known` points of a cloud in sampling order.
+template <int T>
+__device__ __forceinline__ void curve_in_order(const SamplerArgs& a, Shared<T>& sh, const Where& wh, int known)
+{
+    if (wh.tid < 64 && known - 1 - wh.tid >= 1) sh.ring[(known - 1 - wh.tid) & 63] = order_value(a, wh, known - 1 - wh.tid);
+    if (wh.tid < a.nseg && sh.bl[wh.tid] < known) sh.thr_meas[wh.tid] = order_value(a, wh, sh.bl[wh.tid]);
+    if (wh.tid < 32 && sh.mlp_pos[wh.tid] >= 0 && sh.mlp_pos[wh.tid] < known)
+        sh.mlp_val[wh.tid] = order_value(a, wh, sh.mlp_pos[wh.tid]);
+}
+
 // ------------------------------------------------------------------ one cloud
 // MODE 0: exact FPS only (the code of Alg. 2 is left out of the kernel); 1: MDPS with threshold rounds
 // of kCand candidates; 2: MDPS with threshold rounds of kCandMax candidates; 3: MDPS with the
@@ -1949,6 +2150,26 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
         }
         return;
     }
+
+    if constexpr (BQ) {
+        // a cloud held by one workgroup: its counters in the cache are zeroed here (a barrier
+        // comes before the first entry); with several workgroups a launch in front has done it
+        if (wh.G == 1) {
+            const int nchunks = (int)(a.bq_cap / kBqChunk);
+            for (int t = wh.tid; t < nchunks; t += T + kCtrlThreads) a.bq_fill[(int64_t)wh.c * nchunks + t] = 0u;
+            if (wh.tid == 0) {
+                a.bq_cursor[wh.c] = 0u;
+                a.bq_ovf[wh.c] = 0u;
+            }
+        }
+    }
+    int known = 1;                          // samples known to be 0, 1, 2, ... in sequence
+    BqPlace place = {0, 0, kBqNoChunk, false};
+    // (Not in the recorder for clouds of up to 1024 points: its prefixes are too short to gain, and the code costs its rounds
+    // 3 % through other register allocation.)
+    constexpr bool ORDERED = !PERM && !(BQ && MODE == 1 && P == 2);
+    if constexpr (ORDERED)
+        if (start == 0) known = follow_order<T, P, BQ>(a, sh, wh, seq, MODE == 0 || a.m >= n - 1 ? n : a.m + 1, place);
 
     Points<P, BQ> pt;
     if constexpr (PERM) {
@@ -2013,21 +2234,10 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
             }
         }
     }
-    pt.bq_cur = pt.bq_lim = 0;
-    pt.bq_nxt = kBqNoChunk;
-    pt.bq_dead = false;
-    if constexpr (BQ) {
-        // a cloud held by one workgroup: its counters in the cache are zeroed here (the barrier below
-        // comes before the first entry); with several workgroups a launch in front has done it
-        if (wh.G == 1) {
-            const int nchunks = (int)(a.bq_cap / kBqChunk);
-            for (int t = wh.tid; t < nchunks; t += T + kCtrlThreads) a.bq_fill[(int64_t)wh.c * nchunks + t] = 0u;
-            if (wh.tid == 0) {
-                a.bq_cursor[wh.c] = 0u;
-                a.bq_ovf[wh.c] = 0u;
-            }
-        }
-    }
+    pt.bq_cur = place.cur;
+    pt.bq_lim = place.lim;
+    pt.bq_nxt = place.nxt;
+    pt.bq_dead = place.dead;
     if (wh.tid < kCandWin + 2) sh.live[wh.tid] = 0;    // round tags start at 1 in every cloud
     if (wh.tid == 0) sh.progress = 0;
     if constexpr (PERM && MODE != 3)
@@ -2083,7 +2293,34 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
         for (int k = 0; k < 5; ++k) sh.phase_t[k] = t;
     }
 
-    bool ok = fps_rounds<T, P, BQ, PERM, MODE>(pt, sh, wh, a, it, seq, st, pure_fps ? n : m + 1, !pure_fps);
+    bool ok = true;
+    if constexpr (ORDERED) {
+        ok = known > 0;
+        if (known > 1) {
+            // a cloud in sampling order: the samples are its first points
+            for (int k = wh.tid; wh.g == 0 && k < known; k += T + kCtrlThreads) {
+                a.out_idx[(int64_t)wh.c * n + k] = k;
+                if (BQ) a.bq_idx[(int64_t)wh.c * n + k] = k;
+                if (a.out_mdc) a.out_mdc[(int64_t)wh.c * n + k] = order_value(a, wh, k);
+            }
+            if (!pure_fps) curve_in_order<T>(a, sh, wh, known);
+            st.flushed = st.i = known;
+            st.npend = 0;
+            if (known < n) {
+                st.dlast = order_value(a, wh, known - 1);
+                // (their radius tests are recorded)
+                RowWords<P, BQ> rw;
+                for (int k0 = 0; k0 < known; k0 += 64) {
+                    const int kk = k0 + wh.lane < known ? k0 + wh.lane : 0;
+                    const float kx = cloud[(int64_t)kk * 3], ky = cloud[(int64_t)kk * 3 + 1], kz = cloud[(int64_t)kk * 3 + 2];
+                    for (int s = 0; s < 64 && k0 + s < known; ++s)
+                        fold<P, BQ, true, false>(pt, rdlane_f(kx, s), rdlane_f(ky, s), rdlane_f(kz, s), a, wh, 0, rw);
+                }
+            }
+            __syncthreads();
+        }
+    }
+    if (ok) ok = fps_rounds<T, P, BQ, PERM, MODE>(pt, sh, wh, a, it, seq, st, pure_fps ? n : m + 1, !pure_fps);
 
     if (wh.tid == 0) {
         const long long t = wall_clock64();
