@@ -1205,6 +1205,8 @@ __device__ __forceinline__ void run_cloud(const LocalArgs& a, LocalShared& sh, L
                     if (known > 1) {
                         st.np = known;
                         st.low = __uint_as_float((uint32_t)ll_load(half_list(a, me, 0, 0) + known - 1));
+                        // all have read the values: rounds and the next cloud write over them
+                        if ((known < n || me.c + (int)gridDim.x / me.G < a.B) && !agree_in_order(sh, me, a, st.round)) status = 2;
                     }
 #pragma unroll
                     for (int p = 0; p < P; ++p) h.d[p] = h.oi[p] != kNoIdx ? __builtin_inff() : 0.0f;

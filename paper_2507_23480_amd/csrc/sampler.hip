@@ -2317,6 +2317,8 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
                         fold<P, BQ, true, false>(pt, rdlane_f(kx, s), rdlane_f(ky, s), rdlane_f(kz, s), a, wh, 0, rw);
                 }
             }
+            // all have read the values: rounds and the next cloud write over them
+            if (known < n || wh.c + (int)gridDim.x / wh.G < a.B) ok = agree_in_order<T>(a, sh, wh, seq);
             __syncthreads();
         }
     }

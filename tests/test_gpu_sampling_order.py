@@ -104,3 +104,22 @@ def test_batch_of_both_kinds(fp):
         for b, p in enumerate(ps):
             want = ref.fps_exact(p, 700)[0]
             assert all(np.array_equal(g[b].cpu().numpy(), want) for g in got)
+
+
+def test_several_clouds_to_a_group(fp):
+    """more clouds than groups of workgroups: one group follows cloud after cloud, some of them in order to the end, others
+    up to some point"""
+    p = ordered(6000)
+    q = p.copy()
+    q[900:] = np.random.default_rng(3).permutation(q[900:])
+    x = torch.from_numpy(np.stack([p, q, p, p, q, q, p] * 3)).cuda()
+    want = [ref.fps_exact(c, 1500) for c in (p, q)]
+    for G in (64, 100):                     # 4 groups, 2 groups
+        fp.set_wg_per_cloud(G)
+        try:
+            got = [f(x, 1500, want_mdc=True) for f in (fp.fps_exact, fp.fps_exact_pruned)]
+        finally:
+            fp.set_wg_per_cloud(0)
+        for b, k in enumerate([0, 1, 0, 0, 1, 1, 0] * 3):
+            for idx, mdc in got:
+                assert np.array_equal(idx[b].cpu().numpy(), want[k][0]) and np.array_equal(mdc[b].cpu().numpy(), want[k][1])
