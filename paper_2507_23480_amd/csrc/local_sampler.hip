@@ -57,7 +57,10 @@ constexpr int kOwn = kLocalOwn;             // candidates half a workgroup lists
 constexpr int kWords = kLocalMaskWords;     // words of 32 decisions a workgroup publishes
 constexpr int kUnit = 8;                    // the list is dealt out in units of 8 candidates for the decisions
 constexpr int kLevels = 4;
-static_assert(kLocalList == 4096 && kOwn < 255, "8 bits for a count, 255: more than that");
+constexpr int kSpans = kMaxGroup / 32;      // of 64 halves
+constexpr int32_t kFull = 1 << 20;
+static_assert(kLocalList == 4096 && kOwn < 1023, "a count has 12 bits, 64 of them at most kOwn + 1 each 16");
+static_assert(kLevels == 4 && kSpans * kLevels == 32, "a lane per sum");
 static_assert(kChunks == 64, "a lane per chunk");
 
 struct Box {
@@ -72,8 +75,7 @@ struct LocalShared {
     uint64_t took[kChunks];                 // the round's samples, a bit per candidate
     unsigned long long cnt[2][2];           // per half, points above each level, 16 bits each (of this round and of the next)
     int32_t inc[2][2 * kMaxGroup];          // sums of the halves' counts inside 64 of them, two levels in a word
-    int32_t tot[2][kMaxGroup / 32];
-    uint32_t full[kMaxGroup / 32];
+    int32_t tot[kSpans][kLevels];           // ... of all 64, kFull more where a half has more than it can list
     uint32_t acc[kList / 32];               // decisions on the candidates of this workgroup's part of the list
     int32_t fail;
     int32_t in_order;                       // follow_order: samples known to be in sequence
@@ -435,6 +437,33 @@ __device__ __forceinline__ bool cand_wait(const uint64_t* p, uint32_t stamp, uin
     }
     return true;
 }
+// The counts of a half: a word with such a stamp around four of 12 bits each; waited for like ll_wait_close.
+__device__ __forceinline__ bool hdr_wait(const uint64_t* p, uint32_t stamp, uint64_t& val, int64_t wait_ticks)
+{
+    constexpr int N = 4;
+    uint64_t v[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        v[k] = ll_load(p);
+        if (k + 1 < N) __builtin_amdgcn_s_sleep(3);
+    }
+    int64_t t0 = 0;
+    for (uint32_t spin = 0;; ++spin) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            if ((uint32_t)(v[k] >> 50) == stamp) {
+                val = v[k];
+                return true;
+            }
+            v[k] = ll_load(p);
+        }
+        if ((spin & 15u) == 15u || wait_ticks <= 0) {
+            const int64_t now = (int64_t)wall_clock64();
+            if (t0 == 0) t0 = now;
+            else if (now - t0 > wait_ticks) return false;
+        }
+    }
+}
 __device__ __forceinline__ float4 cand_unpack(const uint64_t (&v)[kCandWords3], uint32_t& d)
 {
     d = (uint32_t)v[0] & 0x7FFFFFFFu;
@@ -544,10 +573,10 @@ __device__ __forceinline__ int make_list(const Held<P>& h, LocalShared& sh, cons
     const uint32_t stamp = ((round & kWipeRounds) >> 1) + 1u;
     if (me.G > 1) {
         if (me.lane == 0 && (me.w & (kHW - 1)) == 0) {
-            uint32_t v = 0;
+            uint64_t v = (uint64_t)stamp << 50;
 #pragma unroll
-            for (int j = 0; j < kLevels; ++j) v |= (uint32_t)(tot[j] <= kOwn ? tot[j] : 255) << (8 * j);
-            ll_store(hdr + me.half, v, round);
+            for (int j = 0; j < kLevels; ++j) v |= (uint64_t)(uint32_t)(tot[j] <= kOwn ? tot[j] : kOwn + 1) << (12 * j);
+            word_store(hdr + me.half, v);
         }
         level = kLevels - 1;
     } else {
@@ -603,56 +632,48 @@ __device__ __forceinline__ int make_list(const Held<P>& h, LocalShared& sh, cons
             chunk_box(sh, k, me.lane, sh.cand[r], sh.dist[r], r < total);
         }
     } else {
-        const int nwv = (halves + 63) >> 6;                // waves that hold counts
-        if (me.w < nwv) {
-            uint32_t v = 0;
+        const int spans = (halves + 63) >> 6;
+        if (me.w < spans) {                                 // a wave takes 64 halves
+            uint64_t v = 0;
             bool bad = false;
-            if (me.tid < halves) bad = !ll_wait_close(hdr + me.tid, round, v, a.wait_ticks);
+            if (me.tid < halves) bad = !hdr_wait(hdr + me.tid, stamp, v, a.wait_ticks);
             v = bad ? 0u : v;
-            const int s01 = wave_incl_sum((int)((v & 0xFFu) | ((v & 0xFF00u) << 8)), me.lane);
-            const int s23 = wave_incl_sum((int)(((v >> 16) & 0xFFu) | ((v >> 8) & 0xFF0000u)), me.lane);
-            uint32_t full = 0;
+            uint32_t n[kLevels];
 #pragma unroll
-            for (int j = 0; j < kLevels; ++j)
-                full |= __builtin_amdgcn_ballot_w64(((v >> (8 * j)) & 0xFFu) == 255u) != 0 ? 1u << j : 0u;
-            sh.inc[0][me.tid] = s01;
-            sh.inc[1][me.tid] = s23;
-            if (me.lane == 63) {
-                sh.tot[0][me.w] = s01;
-                sh.tot[1][me.w] = s23;
-                sh.full[me.w] = full;
+            for (int j = 0; j < kLevels; ++j) n[j] = (uint32_t)(v >> (12 * j)) & 0xFFFu;
+            int mine = 0;
+#pragma unroll
+            for (int k = 0; k < kLevels / 2; ++k) {
+                const uint32_t s = (uint32_t)wave_incl_sum((int)(n[2 * k] | (n[2 * k + 1] << 16)), me.lane);
+                sh.inc[k][me.tid] = (int32_t)s;
+                const uint32_t all = rdlane(s, 63);
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const int full = __builtin_amdgcn_ballot_w64(n[2 * k + e] > (uint32_t)kOwn) != 0 ? kFull : 0;
+                    mine = me.lane == 2 * k + e ? (int)((all >> (16 * e)) & 0xFFFFu) + full : mine;
+                }
             }
+            if (me.lane < kLevels) sh.tot[me.w][me.lane] = mine;
             if (__builtin_amdgcn_ballot_w64(bad) != 0 && me.lane == 0) sh.fail = 1;
         }
         __syncthreads();
         MARK(2);
-        int t01 = 0, t23 = 0;
-        uint32_t full = 0;
-        for (int k = 0; k < nwv; ++k) {
-            t01 += sh.tot[0][k];
-            t23 += sh.tot[1][k];
-            full |= sh.full[k];
-        }
-        t01 = uni(t01);
-        t23 = uni(t23);
-        full = uni(full);
-        level = 0;
-        total = t01 & 0xFFFF;
-        if ((full & 2u) == 0 && (int)((uint32_t)t01 >> 16) <= a.aim) level = 1, total = (int)((uint32_t)t01 >> 16);
-        if ((full & 4u) == 0 && (t23 & 0xFFFF) <= a.aim) level = 2, total = t23 & 0xFFFF;
-        if ((full & 8u) == 0 && (int)((uint32_t)t23 >> 16) <= a.aim) level = 3, total = (int)((uint32_t)t23 >> 16);
+        // lane 4 q + j: level j in the q-th 64 halves
+        const int part = me.lane < kSpans * kLevels ? reinterpret_cast<const int32_t*>(sh.tot)[me.lane] : 0;
+        int sum = part + (int)dpp<0x124>((uint32_t)part);   // row_ror:4
+        sum += (int)dpp<0x128>((uint32_t)sum);              // row_ror:8
+        sum += __shfl_xor(sum, 16);
+        const uint64_t fits = __builtin_amdgcn_ballot_w64(sum <= a.aim) & ((1u << kLevels) - 2u);
+        level = fits != 0 ? 63 - __builtin_clzll(fits) : 0;
+        total = (int)rdlane((uint32_t)sum, level);
         const int shift = (level & 1) * 16;
         const int32_t* const inc = sh.inc[level >> 1];
         // candidates listed before each 64 halves
-        constexpr int NB = kMaxGroup / 32;
-        int bases[NB];
-        {
-            const int32_t* const t = sh.tot[level >> 1];
-            bases[0] = 0;
+        int bases[kSpans];
+        bases[0] = 0;
 #pragma unroll
-            for (int k = 1; k < NB; ++k)
-                bases[k] = k < nwv ? uni(bases[k - 1] + (int)(((uint32_t)t[k - 1] >> shift) & 0xFFFFu)) : kList;
-        }
+        for (int k = 1; k < kSpans; ++k)
+            bases[k] = k < spans ? bases[k - 1] + (int)rdlane((uint32_t)part, kLevels * (k - 1) + level) : kList;
         if (uni(sh.fail) == 0) {
             constexpr int NE = 2;           // chunks a wave has under way at a time
             for (int k0 = me.w; 64 * k0 < total; k0 += NE * kNW) {
@@ -668,7 +689,7 @@ __device__ __forceinline__ int make_list(const Held<P>& h, LocalShared& sh, cons
                         // the half that lists the r-th candidate: the first whose sum exceeds r
                         int q = 0, rr = r;
 #pragma unroll
-                        for (int k = 1; k < NB; ++k)
+                        for (int k = 1; k < kSpans; ++k)
                             if (r >= bases[k]) {
                                 q = k;
                                 rr = r - bases[k];
@@ -824,12 +845,13 @@ __device__ __forceinline__ void fold_one(Held<P>& h, const LocalShared& sh, cons
     refresh_bound<P>(h);
 }
 
-// Clears the candidates this workgroup has published; they are gone once the workgroups have met.
+// Clears the counts and candidates this workgroup has published; they are gone once the workgroups have met.
 __device__ __forceinline__ void clear_lists(const LocalArgs& a, const Seat& me)
 {
     for (int par = 0; par < 2; ++par) {
         uint64_t* own = half_list(a, me, par, me.half);
         for (int t = me.tid & (kT / 2 - 1); t < kHalfWords; t += kT / 2) word_store(own + t, 0ull);
+        if ((me.tid & (kT / 2 - 1)) == 0) word_store(a.ll_hdr + (int64_t)(me.grp * 2 + par) * (2 * me.G) + me.half, 0ull);
     }
     __threadfence();
     __syncthreads();
@@ -1191,6 +1213,7 @@ __device__ __forceinline__ void run_cloud(const LocalArgs& a, LocalShared& sh, L
         load_points<P, BQ, MDPS>(h, sh, me, a);
         if (me.tid == 0) sh.fail = 0;
         if (me.tid < 4) sh.cnt[me.tid >> 1][me.tid & 1] = 0;
+        if (me.tid < kSpans * kLevels) reinterpret_cast<int32_t*>(sh.tot)[me.tid] = 0;
         if constexpr (!MDPS) {
             int known = 1;
             if constexpr (!BQ) {

@@ -4,6 +4,7 @@ thread, one workgroup and many, lists at their limits, equal distances, n at the
 import numpy as np
 import pytest
 
+from oracle import ref
 from tests.routes import exact_by_index, scan
 
 torch = pytest.importorskip("torch")
@@ -133,3 +134,21 @@ def test_mdps_given_thresholds_small_record_and_short_prefix(fp):
     assert all(fp.bq_cache_stats(small)["incomplete"])
     for a, b in zip(fp.ball_query(x, got, 0.04, 16, bq_cache=small), scan(fp, x, got, 0.04, 16)):
         assert torch.equal(a, b)
+
+
+def test_more_above_a_level_than_16_bits_count(fp):
+    """a hemisphere of a million points just below the fourth level of the first list, 66200 of them just above: evenly
+    mixed, so that no part of the cloud has more of them than it may list, and 664 too many for 16 bits"""
+    rng = np.random.default_rng(9)
+    N, above = 1000000, 66200
+    u = rng.normal(size=(N, 3))
+    u[:, 0] = -np.abs(u[:, 0]) - 0.05
+    u /= np.linalg.norm(u, axis=1, keepdims=True)
+    r2 = np.full(N, 0.510)
+    r2[rng.choice(np.arange(2, N), above, replace=False)] = 0.514
+    p = (u * np.sqrt(r2)[:, None]).astype(np.float32)
+    p[0], p[1] = 0.0, (1.0, 0.0, 0.0)
+    n = 300
+    idx, mdc = fp.fps_exact_pruned(torch.from_numpy(p[None]).cuda(), n, want_mdc=True)
+    want, wmdc = ref.fps_exact(p, n)
+    assert np.array_equal(idx.cpu().numpy()[0], want) and np.array_equal(mdc.cpu().numpy()[0], wmdc)
