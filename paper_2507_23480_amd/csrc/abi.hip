@@ -1,5 +1,6 @@
 // Host side of the C ABI declared in include/fastpoint.h: argument checks,
 // launch planning and kernel launches.  No device memory is allocated here.
+#include <algorithm>
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -228,10 +229,15 @@ int64_t rel_exchange_bytes(int32_t B)
 // 2000 / 3000 / 4096: 8 x 24000 -> 6000 (24 workgroups a cloud) 576 / 542 / 562 / 667 / 867 / 1127; 4 x 120000 -> 16384 (64)
 // 1426 / 1119 / 1061 / 1040 / 1067 / 1153; 1000000 -> 65536 (245) 3248 / 2300 / 1949 / 1839 / 1734 / 1710.  (At most 32 units of
 // eight candidates a workgroup, which is what it can publish.)
-int local_aim(int G)
+// Exact FPS has no use for a list much longer than half of the samples it looks for.  us at lists of 288 / 400 / 600 / 1000 /
+// 2100: 60000 -> 1500 of a room 476 / 443 / 410 / 414 / 511, of a cube 428 / 428 / 403 / 417 / 610; prefixes of 600 samples (8 x
+// 24000) 276 / 270 / 284 / 310 / -, of 1638 (4 x 120000) 666 / 617 / 548 / 520 / 591, of 6553 (1000000) 1152 / 1053 / 1018 /
+// 910 / 868.
+int local_aim(int G, int samples)
 {
     const int aim = 256 + 32 * G, most = G > 1 && 256 * G < kLocalList ? 256 * G : kLocalList;
-    return aim < most ? aim : most;
+    const int use = samples < 512 ? 256 : samples / 2 + samples / 8;
+    return std::min({aim, most, use});
 }
 
 int64_t scan_walk_bytes(int32_t B, int32_t N) { return align_up((int64_t)B * N * (int64_t)sizeof(float4), 256); }
@@ -271,7 +277,6 @@ fp_status run_local(const SamplerArgs& s, const Plan& plan, bool mdps, void* wor
     a.found = spatial_sort_spare(s.B, s.N, sort_ws);
     a.cloud = reinterpret_cast<LocalCloud*>(own + lay.cloud);
     a.stop = prefix ? s.m + 1 : s.n;
-    a.aim = local_aim(plan.G);
     while ((plan.G << (a.own_shift + 1)) <= kLocalThreads) ++a.own_shift;
     a.ll_hdr = a.ll_pk + kLlPkWords;
     a.ll_mask = a.ll_hdr + kLocalHdrWords;
@@ -290,6 +295,7 @@ fp_status run_local(const SamplerArgs& s, const Plan& plan, bool mdps, void* wor
                                   stream) != hipSuccess)
                 return FP_ERR_DEVICE;
         }
+        a.aim = local_aim(plan.G, part == 0 ? a.stop : s.n);
         void* kargs[] = {&a};
         const dim3 grid((unsigned)(plan.groups * plan.G)), block((unsigned)kLocalThreads);
         const hipError_t err = plan.G > 1 && g_cooperative.load()
