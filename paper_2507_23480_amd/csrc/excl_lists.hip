@@ -310,9 +310,10 @@ __device__ __forceinline__ int grouped_add(int32_t* counter, int cell, bool todo
     return __shfl(base, lead, 64) + below;
 }
 
+// (rank, where given: how many points of the cell were counted before)
 __global__ __launch_bounds__(256) void grid_count_kernel(const float* __restrict__ xyz, int N,
                                                          const ExclGrid* __restrict__ gp, int32_t* cell_cnt,
-                                                         int maxcells)
+                                                         int maxcells, int32_t* __restrict__ rank)
 {
     const int b = (int)blockIdx.y;
     const int i = (int)(blockIdx.x * 256 + threadIdx.x);
@@ -322,7 +323,8 @@ __global__ __launch_bounds__(256) void grid_count_kernel(const float* __restrict
     const float* p = xyz + ((int64_t)b * N + (valid ? i : 0)) * 3;
     int cx, cy, cz;
     const int c = cell_of(g, p[0], p[1], p[2], cx, cy, cz);
-    grouped_add(cell_cnt + (int64_t)b * maxcells, c, valid, (int)threadIdx.x & 63);
+    const int r = grouped_add(cell_cnt + (int64_t)b * maxcells, c, valid, (int)threadIdx.x & 63);
+    if (rank && valid) rank[(int64_t)b * N + i] = r;
 }
 
 // One workgroup per cloud: cell_start = exclusive scan of the cell counts; the counts become
@@ -393,7 +395,7 @@ __global__ __launch_bounds__(1024) void grid_scan_kernel(const ExclGrid* __restr
     const int base = t * kCellTile;
     if (base >= ncells || gp[b].skip != 0) return;       // uniform over the workgroup
     int32_t* cnt = cell_cnt + (int64_t)b * maxcells + gp[b].cnt_shift;
-    int32_t* st = cell_start + (int64_t)b * (maxcells + 1);
+    int32_t* st = cell_start ? cell_start + (int64_t)b * (maxcells + 1) : nullptr;     // (null: the cursors are enough)
     const bool cnt_wide = (reinterpret_cast<uintptr_t>(cnt) & 15u) == 0;
     const bool st_wide = (reinterpret_cast<uintptr_t>(st) & 15u) == 0;
     const int tid = (int)threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -435,6 +437,7 @@ __global__ __launch_bounds__(1024) void grid_scan_kernel(const ExclGrid* __restr
         for (int u = 0; u < kCellPer; ++u)
             if (c0 + u < ncells) cnt[c0 + u] = v[u];
     }
+    if (!st) return;
     if (full && st_wide) {
 #pragma unroll
         for (int q = 0; q < kCellPer / 4; ++q)
@@ -476,6 +479,25 @@ __global__ __launch_bounds__(256) void grid_scatter_kernel(const float* __restri
     const int c = cell_of(g, x, y, z, cx, cy, cz);
     const int pos = grouped_add(cell_cur + (int64_t)b * maxcells + g.cnt_shift, c, valid, (int)threadIdx.x & 63);
     if (valid) sorted[(int64_t)b * N + pos] = make_float4(x, y, z, __int_as_float(i));
+}
+
+// The same where the count has left each point's rank in its cell: no atomics.
+__global__ __launch_bounds__(256) void rank_scatter_kernel(const float* __restrict__ xyz, int N,
+                                                           const ExclGrid* __restrict__ gp,
+                                                           const int32_t* __restrict__ cell_start,
+                                                           const int32_t* __restrict__ rank,
+                                                           float4* __restrict__ sorted, int maxcells)
+{
+    const int b = (int)blockIdx.y;
+    const int i = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (i >= N) return;
+    const ExclGrid g = gp[b];
+    const float* p = xyz + ((int64_t)b * N + i) * 3;
+    const float x = p[0], y = p[1], z = p[2];
+    int cx, cy, cz;
+    const int c = cell_of(g, x, y, z, cx, cy, cz);
+    const int pos = cell_start[(int64_t)b * maxcells + g.cnt_shift + c] + rank[(int64_t)b * N + i];
+    sorted[(int64_t)b * N + pos] = make_float4(x, y, z, __int_as_float(i));
 }
 
 // ------------------------------------------------------------------ walking the 27 cells
@@ -1683,18 +1705,26 @@ hipError_t launch_spatial_sort(const float* xyz, int B, int N, void* workspace, 
     int32_t* cnt = reinterpret_cast<int32_t*>(base + lay.cnt_off);
     int32_t* st = reinterpret_cast<int32_t*>(base + lay.start_off);
     float4* sorted = reinterpret_cast<float4*>(base + lay.sorted_off);
+    // The starts of the cells are of no use to a sort: the ranks of the points in their cells take their place (where
+    // there are as many cells as points), and the scatter needs no atomics.
+    int32_t* rank = lay.maxcells >= N ? st : nullptr;
     const int64_t ncnt = (int64_t)B * lay.maxcells;
     int initblocks = (int)((ncnt + 255) / 256);
     if (initblocks > 2048) initblocks = 2048;
     hipLaunchKernelGGL(grid_init_kernel, dim3(initblocks), dim3(256), 0, stream, gp, B, cnt, ncnt);
     int bblocks = (N + 2047) / 2048;
-    if (bblocks > 64) bblocks = 64;
+    if (bblocks > 256) bblocks = 256;
     hipLaunchKernelGGL(grid_bounds_kernel, dim3(bblocks, B), dim3(256), 0, stream, xyz, N, gp);
     hipLaunchKernelGGL(sort_setup_kernel, dim3((B + 63) / 64), dim3(64), 0, stream, gp, B, sort_bits(lay.maxcells));
     const dim3 pgrid((unsigned)((N + 255) / 256), (unsigned)B);
-    hipLaunchKernelGGL(grid_count_kernel, pgrid, dim3(256), 0, stream, xyz, N, gp, cnt, lay.maxcells);
-    launch_cell_scan(gp, cnt, st, reinterpret_cast<int32_t*>(base + lay.tiles_off), B, lay.maxcells, stream);
-    hipLaunchKernelGGL(grid_scatter_kernel, pgrid, dim3(256), 0, stream, xyz, N, gp, cnt, sorted, lay.maxcells);
+    hipLaunchKernelGGL(grid_count_kernel, pgrid, dim3(256), 0, stream, xyz, N, gp, cnt, lay.maxcells,
+                       rank);
+    launch_cell_scan(gp, cnt, rank ? nullptr : st, reinterpret_cast<int32_t*>(base + lay.tiles_off), B, lay.maxcells, stream);
+    if (rank)
+        hipLaunchKernelGGL(rank_scatter_kernel, pgrid, dim3(256), 0, stream, xyz, N, gp, (const int32_t*)cnt,
+                           (const int32_t*)rank, sorted, lay.maxcells);
+    else
+        hipLaunchKernelGGL(grid_scatter_kernel, pgrid, dim3(256), 0, stream, xyz, N, gp, cnt, sorted, lay.maxcells);
     return hipGetLastError();
 }
 
@@ -1713,12 +1743,13 @@ hipError_t launch_excl_count(const float* xyz, int B, int N, const float* thr2, 
     if (initblocks > 2048) initblocks = 2048;
     hipLaunchKernelGGL(grid_init_kernel, dim3(initblocks), dim3(256), 0, stream, gp, B, cnt, ncnt);
     int bblocks = (N + 2047) / 2048;
-    if (bblocks > 64) bblocks = 64;
+    if (bblocks > 256) bblocks = 256;
     hipLaunchKernelGGL(grid_bounds_kernel, dim3(bblocks, B), dim3(256), 0, stream, xyz, N, gp);
     hipLaunchKernelGGL(grid_setup_kernel, dim3((B + 63) / 64), dim3(64), 0, stream, gp, B, thr2, L, lay.maxcells,
                        0.0f);
     const dim3 pgrid((unsigned)((N + 255) / 256), (unsigned)B);
-    hipLaunchKernelGGL(grid_count_kernel, pgrid, dim3(256), 0, stream, xyz, N, gp, cnt, lay.maxcells);
+    hipLaunchKernelGGL(grid_count_kernel, pgrid, dim3(256), 0, stream, xyz, N, gp, cnt, lay.maxcells,
+                       (int32_t*)nullptr);
     launch_cell_scan(gp, cnt, st, reinterpret_cast<int32_t*>(base + lay.tiles_off), B, lay.maxcells, stream);
     hipLaunchKernelGGL(grid_scatter_kernel, pgrid, dim3(256), 0, stream, xyz, N, gp, cnt, sorted, lay.maxcells);
     const dim3 wgrid((unsigned)((N + kWaves - 1) / kWaves), (unsigned)B);
@@ -1774,12 +1805,13 @@ hipError_t launch_knn_grid(const float* xyz, int B, int N, const float* sample_x
     hipLaunchKernelGGL(zero_ints_kernel, dim3((B + 255) / 256), dim3(256), 0, stream, count, B);
     hipLaunchKernelGGL(grid_init_kernel, dim3(initblocks), dim3(256), 0, stream, gp, B, cnt, ncnt);
     int bblocks = (n + 2047) / 2048;
-    if (bblocks > 64) bblocks = 64;
+    if (bblocks > 256) bblocks = 256;
     hipLaunchKernelGGL(grid_bounds_kernel, dim3(bblocks, B), dim3(256), 0, stream, sample_xyz, n, gp);
     hipLaunchKernelGGL(grid_setup_kernel, dim3((B + 63) / 64), dim3(64), 0, stream, gp, B,
                        static_cast<const float*>(nullptr), 1, lay.maxcells, r2);
     const dim3 sgrid((unsigned)((n + 255) / 256), (unsigned)B);
-    hipLaunchKernelGGL(grid_count_kernel, sgrid, dim3(256), 0, stream, sample_xyz, n, gp, cnt, lay.maxcells);
+    hipLaunchKernelGGL(grid_count_kernel, sgrid, dim3(256), 0, stream, sample_xyz, n, gp, cnt, lay.maxcells,
+                       (int32_t*)nullptr);
     launch_cell_scan(gp, cnt, st, reinterpret_cast<int32_t*>(base + lay.tiles_off), B, lay.maxcells, stream);
     hipLaunchKernelGGL(grid_scatter_kernel, sgrid, dim3(256), 0, stream, sample_xyz, n, gp, cnt, sorted, lay.maxcells);
     const dim3 pgrid((unsigned)((N + 255) / 256), (unsigned)B);
@@ -1855,7 +1887,7 @@ hipError_t launch_knn_search(const float* xyz, int B, int N, const int32_t* samp
     hipLaunchKernelGGL(zero_ints_kernel, dim3((B + 255) / 256), dim3(256), 0, stream, count, B);
     hipLaunchKernelGGL(grid_init_kernel, dim3(initblocks), dim3(256), 0, stream, gp, B, occ, nzero);
     int bblocks = (n + 2047) / 2048;
-    if (bblocks > 64) bblocks = 64;
+    if (bblocks > 256) bblocks = 256;
     hipLaunchKernelGGL(grid_bounds_kernel, dim3(bblocks, B), dim3(256), 0, stream, samples, n, gp);
     // no radius: the finest grid of at most maxcells cells
     hipLaunchKernelGGL(grid_setup_kernel, dim3((B + 63) / 64), dim3(64), 0, stream, gp, B,
@@ -1898,7 +1930,8 @@ hipError_t launch_bq_grid(const float* xyz, int B, int N, const int32_t* center_
     hipLaunchKernelGGL(bq_setup_kernel, dim3((unsigned)B), dim3(kProbePoints), 0, stream, gp, B, xyz, N, center_idx, M, r2, k,
                        (const uint32_t*)part, parts, lay.maxcells);
     const dim3 pgrid((unsigned)((N + 255) / 256), (unsigned)B);
-    hipLaunchKernelGGL(grid_count_kernel, pgrid, dim3(256), 0, stream, xyz, N, gp, cnt, lay.maxcells);
+    hipLaunchKernelGGL(grid_count_kernel, pgrid, dim3(256), 0, stream, xyz, N, gp, cnt, lay.maxcells,
+                       (int32_t*)nullptr);
     launch_cell_scan(gp, cnt, st, reinterpret_cast<int32_t*>(base + lay.tiles_off), B, lay.maxcells, stream);
     hipLaunchKernelGGL(grid_scatter_kernel, pgrid, dim3(256), 0, stream, xyz, N, gp, cnt, sorted, lay.maxcells);
     hipLaunchKernelGGL(bq_grid_kernel, dim3((unsigned)((M + kWaves - 1) / kWaves), (unsigned)B), dim3(kWaves * 64), 0,
