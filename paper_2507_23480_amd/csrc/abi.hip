@@ -590,7 +590,7 @@ fp_status fp_ball_query(const float* xyz, int32_t B, int32_t N, const int32_t* c
 size_t fp_ball_query_grid_workspace_bytes(int32_t B, int32_t N)
 {
     if (B < 1 || N < 1 || B > 65535 || (int64_t)B * N > ((int64_t)1 << 33)) return 0;
-    return (size_t)spatial_sort_bytes(B, N);
+    return (size_t)bq_grid_bytes(B, N);
 }
 
 fp_status fp_ball_query_grid(const float* xyz, int32_t B, int32_t N, const int32_t* center_idx, int32_t M,

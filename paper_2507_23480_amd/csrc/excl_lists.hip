@@ -490,8 +490,8 @@ __global__ __launch_bounds__(256) void rank_scatter_kernel(const float* __restri
 {
     const int b = (int)blockIdx.y;
     const int i = (int)(blockIdx.x * 256 + threadIdx.x);
-    if (i >= N) return;
     const ExclGrid g = gp[b];
+    if (g.skip != 0 || i >= N) return;
     const float* p = xyz + ((int64_t)b * N + i) * 3;
     const float x = p[0], y = p[1], z = p[2];
     int cx, cy, cz;
@@ -1685,6 +1685,9 @@ static int sort_bits(int maxcells)
 
 int64_t spatial_sort_bytes(int B, int N) { return excl_layout(B, N, 1).bytes; }
 
+// (the ball query reads the starts of its cells: the ranks of the points in them lie behind)
+int64_t bq_grid_bytes(int B, int N) { return excl_layout(B, N, 1).bytes + (int64_t)B * N * 4; }
+
 const float4* spatial_sorted(int B, int N, const void* workspace)
 {
     return reinterpret_cast<const float4*>(reinterpret_cast<const unsigned char*>(workspace) +
@@ -1930,10 +1933,11 @@ hipError_t launch_bq_grid(const float* xyz, int B, int N, const int32_t* center_
     hipLaunchKernelGGL(bq_setup_kernel, dim3((unsigned)B), dim3(kProbePoints), 0, stream, gp, B, xyz, N, center_idx, M, r2, k,
                        (const uint32_t*)part, parts, lay.maxcells);
     const dim3 pgrid((unsigned)((N + 255) / 256), (unsigned)B);
-    hipLaunchKernelGGL(grid_count_kernel, pgrid, dim3(256), 0, stream, xyz, N, gp, cnt, lay.maxcells,
-                       (int32_t*)nullptr);
+    int32_t* const rank = reinterpret_cast<int32_t*>(base + lay.bytes);
+    hipLaunchKernelGGL(grid_count_kernel, pgrid, dim3(256), 0, stream, xyz, N, gp, cnt, lay.maxcells, rank);
     launch_cell_scan(gp, cnt, st, reinterpret_cast<int32_t*>(base + lay.tiles_off), B, lay.maxcells, stream);
-    hipLaunchKernelGGL(grid_scatter_kernel, pgrid, dim3(256), 0, stream, xyz, N, gp, cnt, sorted, lay.maxcells);
+    hipLaunchKernelGGL(rank_scatter_kernel, pgrid, dim3(256), 0, stream, xyz, N, gp, (const int32_t*)cnt,
+                       (const int32_t*)rank, sorted, lay.maxcells);
     hipLaunchKernelGGL(bq_grid_kernel, dim3((unsigned)((M + kWaves - 1) / kWaves), (unsigned)B), dim3(kWaves * 64), 0,
                        stream, xyz, N, center_idx, M, r2, k, out_idx, out_cnt, gp, st, sorted, lay.maxcells);
     if (N < kProbeFrom) return hipGetLastError();

@@ -228,6 +228,7 @@ ExclLayout excl_layout(int B, int N, int L);
 // numbered along a Hilbert curve; leaves records (x, y, z, index bits) at spatial_sorted().
 hipError_t launch_spatial_sort(const float* xyz, int B, int N, void* workspace, hipStream_t stream);
 int64_t spatial_sort_bytes(int B, int N);
+int64_t bq_grid_bytes(int B, int N);
 const float4* spatial_sorted(int B, int N, const void* workspace);
 // Room for [B][N] 64-bit words in the same workspace that the sorted records do not need (N up to 2^21).
 uint64_t* spatial_sort_spare(int B, int N, void* workspace);
