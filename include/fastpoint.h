@@ -171,7 +171,8 @@ fp_status fp_fps_exact_static(const float* xyz, int32_t B, int32_t N, int32_t n,
  * updates that cannot change anything).  The cloud is first put into the order of a uniform
  * grid traversed along a Hilbert curve, so that the points a wavefront holds lie in a small
  * box; a new sample is folded into a wavefront's distances only if it is closer to that box
- * than the largest distance the wavefront still holds.  Arguments as fp_fps_exact without the
+ * than the largest distance the wavefront still holds.  Samples are found many at a time: a point is one as soon as no point
+ * with a larger distance (or an equal one and a lower index) lies closer to it than its own distance.  Arguments as fp_fps_exact without the
  * ball-query cache; the workspace is larger (it also receives the reordered cloud).  Calls for fewer samples than
  * earn the sort back run on the cloud as it is.
  */
@@ -207,7 +208,7 @@ fp_status fp_mdps_sample(const float* xyz, int32_t B, int32_t N, int32_t n,
  * threshold-guided picks are folded only into the wavefronts they can affect.  The points are
  * no longer held in index order, so the next available points in the scan order (by index, or by
  * place in the walk of prm->scan_order = 1) are found through a sliding window of that key: a
- * round takes all available points of the window, up to 256, and settles which of them the
+ * round takes all available points of the window, up to 256 (from 5000 samples on up to 4096), and settles which of them the
  * rule of Section 4.1 step 3 would accept one after the other from the pairwise "closer than
  * R_l" relation between them.  Arguments as fp_mdps_sample; workspace of
  * fp_fps_pruned_workspace_bytes(B, N) bytes.  With a bq_cache the radius tests are recorded as

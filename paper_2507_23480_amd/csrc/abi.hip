@@ -97,6 +97,9 @@ constexpr int kOneWgPoints = 2048;
 // us: 1500 samples 771 / 971, 3000: 1474 / 1398).  Scanner clouds are 1.09-1.19 at 1500 samples (exact FPS), 0.91-1.04 at
 // 3000; a cloud with 95 % of its points in a clump 1.1-1.4 and 0.8-1.2; one with a far point 1.1-1.3 and 0.9-1.1 (of a
 // million points, whose counters then queue up, 1.4-2.0 and 1.2-1.4).
+// (Exact FPS in cell order was settled in sweeps when these were measured.  By local decisions it takes 0.4 to 0.95 of that time, e.g.
+// us: 8 x 24000 -> 6000 850 / 525, 1 x 6000 -> 1500 446 / 346, 64 x 8000 -> 3000 663 / 526, scanner 40 x 6000 -> 1500 560 / 398; more only for
+// uniform cubes that one workgroup holds, 140 x 8000 -> 3000 1184 / 1430, 256 x 6000 -> 3000 1337 / 1396.)
 // fp_fps_exact takes the cell order from kCellOrderFrom points on, when its workspace has room for it; the _pruned
 // entry points leave it below kCellOrderSamples, and for clouds that one workgroup holds.  A call with a record keeps
 // its entry point's layout: it is the order of the record's blocks.
