@@ -125,7 +125,8 @@ struct SamplerArgs {
 // The sampler by local decisions (local_sampler.hip).
 constexpr int kLocalThreads = 1024;     // of a workgroup
 constexpr int kLocalList = 4096;        // candidates of a round
-constexpr int kLocalOwn = 511;          // ... of half a workgroup
+constexpr int kLocalOwn = 511;          // ... of half a workgroup (191: 94 and 67 rounds for C5 and C4, 383: 87 and 61, 511: 85 and 56, 767: 81 and 56
+                                        // at the same time; half as much memory again)
 constexpr int kLocalCandWords = 3;      // words of a published candidate
 constexpr int kLocalMaskWords = 8;      // words of 32 decisions a workgroup publishes
 constexpr int kOrderMost = 4096;        // keys a workgroup puts in order
