@@ -60,8 +60,8 @@ GRAPH = "four streams, step replayed as one HIP graph"
 TRAFFIC_BYTES = {"C2": {"fps_exact": 427967, "mdps_sample+record": 2364746, "ball_query_cached": 1948914,
                         "ball_query": 2004582},
                  # (C4, C5: the step's recorder is the cell-ordered one, its reader the one for cell-ordered records)
-                 "C4": {"fps_exact": 202751712, "mdps_sample+record": 284120000, "ball_query_cached": 59760896},
-                 "C5": {"fps_exact": 199127232, "mdps_sample+record": 249951690, "ball_query_cached": 29248181}}
+                 "C4": {"fps_exact": 208865400, "mdps_sample+record": 341887000, "ball_query_cached": 60371400},
+                 "C5": {"fps_exact": 353529000, "mdps_sample+record": 1133064000, "ball_query_cached": 29255500}}
 
 
 PRUNED_RECORD_FROM = 1 << 14
