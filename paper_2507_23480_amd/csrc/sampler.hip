@@ -1921,15 +1921,14 @@ __device__ __forceinline__ bool fps_rounds(Points<P, BQ>& pt, Shared<T>& sh, con
 // of this kind and returns how many of its first points are the samples in sequence (at least 1; 0 if a wait
 // expired); a cloud that is not in this order shows it by a few hundred points farther from point 0 than point 1 is,
 // before anything is spent on it.  The first 64 points are tried, then 512, then eight times as many a time, so that a sequence
-// that breaks off costs at most a few times what was gained by it.  With BQ the points are recorded once a stretch is known
-// to be samples (an entry that went too far could not be taken back).  `n`: samples wanted -- of MDPS the prefix, after
-// which samples gathered from MDPS are in no such order.  `place`: where the wave's part of the record has got to.
+// that breaks off costs at most a few times what was gained by it.  `n`: samples wanted -- of MDPS the prefix, after
+// which samples gathered from MDPS are in no such order.
 //
 // v_k is worked out by 64 points at a time (a workgroup per 64, its waves sharing the points before them), and handed to the
 // other workgroups in stamped words; every wave then folds the points one after the other, as in the rounds, but
 // without waiting for a search.  Bound: the fold.  us, before -> now: fps_exact of 16 clouds of 512 gathered samples, 128 of
-// them, 42 -> 27; of 8 x 1500, 375 of them, 108 -> 97; mdps_sample with record of 8 x 6000 samples gathered from MDPS, 1500 of
-// them (the prefix of 150), 546 -> 443.  (Tried beyond the prefix on such clouds it cost 85 us and gained nothing.)
+// them, 42 -> 27; of 8 x 1500, 375 of them, 108 -> 97.  (Tried beyond the prefix on
+// clouds gathered from MDPS it cost 85 us and gained nothing.)
 constexpr int64_t kOrderWords = (int64_t)2 * kCandMax * kCandWords;    // per workgroup: most points the words hold
 
 __device__ __forceinline__ uint64_t* order_words(const SamplerArgs& a, const Where& wh)
@@ -1955,13 +1954,8 @@ __device__ __forceinline__ bool agree_in_order(const SamplerArgs& a, Shared<T>& 
     return uni(sh.ctrl[2]) == 0;
 }
 
-struct BqPlace {
-    uint32_t cur, lim, nxt;
-    bool dead;
-};
-
-template <int T, int P, bool BQ>
-__device__ __forceinline__ int follow_order(const SamplerArgs& a, Shared<T>& sh, const Where& wh, uint32_t& seq, int n, BqPlace& place)
+template <int T, int P>
+__device__ __forceinline__ int follow_order(const SamplerArgs& a, Shared<T>& sh, const Where& wh, uint32_t& seq, int n)
 {
     constexpr int NW = T / 64;
     const int N = a.N;
@@ -1975,7 +1969,7 @@ __device__ __forceinline__ int follow_order(const SamplerArgs& a, Shared<T>& sh,
         const float d = dist2(x0, y0, z0, cloud[3 * (int64_t)j], cloud[3 * (int64_t)j + 1], cloud[3 * (int64_t)j + 2]);
         if (__syncthreads_or(!(d <= d1) || !(d1 > 0.0f) || !(d1 < __builtin_inff()))) return 1;
     }
-    Points<P, BQ> pt;
+    Points<P, false> pt;
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         const int j = ((wh.gw * P + p) << 6) | wh.lane;
@@ -1984,10 +1978,6 @@ __device__ __forceinline__ int follow_order(const SamplerArgs& a, Shared<T>& sh,
         pt.z[p] = j < N ? cloud[(int64_t)j * 3 + 2] : kPadCoord;
         pt.d[p] = j < N ? __builtin_inff() : 0.0f;
     }
-    pt.bq_cur = place.cur;
-    pt.bq_lim = place.lim;
-    pt.bq_nxt = place.nxt;
-    pt.bq_dead = place.dead;
     if (wh.tid == 0) {
         sh.ctrl[2] = 0;
         sh.in_order = n;
@@ -1997,7 +1987,7 @@ __device__ __forceinline__ int follow_order(const SamplerArgs& a, Shared<T>& sh,
     const uint32_t stamp = ++seq;
     float* const part = reinterpret_cast<float*>(sh.cand);
     static_assert(sizeof(sh.cand) >= NW * 64 * sizeof(float), "a value per lane of the point waves");
-    RowWords<P, BQ> rw;
+    RowWords<P, false> rw;
     int from = 0, upto = n < 64 ? n : 64;
     while (true) {
         // v of the points [from, upto)
@@ -2057,39 +2047,15 @@ __device__ __forceinline__ int follow_order(const SamplerArgs& a, Shared<T>& sh,
                         bad = 64 * c + s;
                         break;
                     }
-                    fold<P, BQ, true, false>(pt, rdlane_f(kx, s), rdlane_f(ky, s), rdlane_f(kz, s), a, wh, 0, rw);
+                    fold<P, false, true, false>(pt, rdlane_f(kx, s), rdlane_f(ky, s), rdlane_f(kz, s), a, wh, 0, rw);
                 }
             }
             if (bad < n && wh.lane == 0) atomicMin(&sh.in_order, bad);
         }
         if (!agree_in_order<T>(a, sh, wh, seq)) return 0;
         const int known = uni(sh.in_order);
-        if constexpr (BQ) {
-            const int most = known < upto ? known : upto;
-            if (!wh.ctrl && known > 1) {
-                for (int c = from >> 6; 64 * c < most; ++c) {
-                    const int k = 64 * c + wh.lane, kk = k < most ? k : 0;
-                    const float kx = cloud[(int64_t)kk * 3], ky = cloud[(int64_t)kk * 3 + 1], kz = cloud[(int64_t)kk * 3 + 2];
-                    rw.clear(wh);
-                    const int s0 = from > 64 * c ? from - 64 * c : 0, s1 = most - 64 * c < 64 ? most - 64 * c : 64;
-                    for (int s = s0; s < s1; ++s) {
-                        const float cx = rdlane_f(kx, s), cy = rdlane_f(ky, s), cz = rdlane_f(kz, s);
-#pragma unroll
-                        for (int p = 0; p < P; ++p) {
-                            const uint64_t hits = __builtin_amdgcn_ballot_w64(dist2(cx, cy, cz, pt.x[p], pt.y[p], pt.z[p]) < a.bq_r2);
-                            if (hits != 0) rw.row[p * 64 + s] = hits;
-                        }
-                    }
-                    flush_rows<P, BQ>(rw, a, wh, pt, 64 * c, 64);
-                }
-            }
-        }
         if (known < upto || upto == n) {
             __syncthreads();
-            place.cur = pt.bq_cur;
-            place.lim = pt.bq_lim;
-            place.nxt = pt.bq_nxt;
-            place.dead = pt.bq_dead;
             return known > 1 ? known : 1;
         }
         from = upto;
@@ -2164,12 +2130,12 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
         }
     }
     int known = 1;                          // samples known to be 0, 1, 2, ... in sequence
-    BqPlace place = {0, 0, kBqNoChunk, false};
-    // (Not in the recorder for clouds of up to 1024 points: its prefixes are too short to gain, and the code costs its rounds
-    // 3 % through other register allocation.)
-    constexpr bool ORDERED = !PERM && !(BQ && MODE == 1 && P == 2);
+    // (Not in the recorders: with this code around their rounds take 3 to 15 % longer through other register allocation, us
+    // without / with: 1 x 4096 -> 1024 448 / 495, 16 x 1500 -> 375 168 / 185, 8 x 24000 -> 6000 1816 / 2084; what it gains them is the
+    // prefix of an input that is in sequence.)
+    constexpr bool ORDERED = !PERM && !BQ;
     if constexpr (ORDERED)
-        if (start == 0) known = follow_order<T, P, BQ>(a, sh, wh, seq, MODE == 0 || a.m >= n - 1 ? n : a.m + 1, place);
+        if (start == 0) known = follow_order<T, P>(a, sh, wh, seq, MODE == 0 || a.m >= n - 1 ? n : a.m + 1);
 
     Points<P, BQ> pt;
     if constexpr (PERM) {
@@ -2234,10 +2200,9 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
             }
         }
     }
-    pt.bq_cur = place.cur;
-    pt.bq_lim = place.lim;
-    pt.bq_nxt = place.nxt;
-    pt.bq_dead = place.dead;
+    pt.bq_cur = pt.bq_lim = 0;
+    pt.bq_nxt = kBqNoChunk;
+    pt.bq_dead = false;
     if (wh.tid < kCandWin + 2) sh.live[wh.tid] = 0;    // round tags start at 1 in every cloud
     if (wh.tid == 0) sh.progress = 0;
     if constexpr (PERM && MODE != 3)
@@ -2300,7 +2265,6 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
             // a cloud in sampling order: the samples are its first points
             for (int k = wh.tid; wh.g == 0 && k < known; k += T + kCtrlThreads) {
                 a.out_idx[(int64_t)wh.c * n + k] = k;
-                if (BQ) a.bq_idx[(int64_t)wh.c * n + k] = k;
                 if (a.out_mdc) a.out_mdc[(int64_t)wh.c * n + k] = order_value(a, wh, k);
             }
             if (!pure_fps) curve_in_order<T>(a, sh, wh, known);
@@ -2308,7 +2272,6 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
             st.npend = 0;
             if (known < n) {
                 st.dlast = order_value(a, wh, known - 1);
-                // (their radius tests are recorded)
                 RowWords<P, BQ> rw;
                 for (int k0 = 0; k0 < known; k0 += 64) {
                     const int kk = k0 + wh.lane < known ? k0 + wh.lane : 0;
