@@ -400,10 +400,10 @@ __device__ __forceinline__ Rec plain_pick(const Held<P>& h, LocalShared& sh, con
 }
 
 // A published candidate: three words with a stamp of 14 bits each around distance (31 bits, it is not negative),
-// coordinates and index (21 bits).  The stamp is never 0 and does not come twice within kWipeRounds rounds, after which
-// the words are cleared.
+// coordinates and index (21 bits).  The stamp is never 0 and does not come twice in the rounds up to the next one whose
+// last bits (LocalArgs::wipe) are zero, in front of which the words are cleared.
 constexpr int kCandWords3 = kLocalCandWords;
-constexpr uint32_t kWipeRounds = 0x3FFFu;
+static_assert((kLocalStampRounds >> 1) < 1 << 14, "14 bits for a stamp");
 static_assert(kMaxGroup * 8192 <= 1 << 21, "21 bits for an index");
 constexpr int64_t kHalfWords = (int64_t)(kOwn + 1) * kCandWords3;
 __device__ __forceinline__ uint64_t* half_list(const LocalArgs& a, const Seat& me, int par, int half)
@@ -571,7 +571,7 @@ __device__ __forceinline__ int make_list(const Held<P>& h, LocalShared& sh, cons
     for (int j = 0; j < kLevels; ++j) tot[j] = (int)((uint32_t)(sum >> (16 * j)) & 0xFFFFu);
     const int halves = 2 * me.G;
     uint64_t* const hdr = a.ll_hdr + (int64_t)(me.grp * 2 + par) * halves;
-    const uint32_t stamp = ((round & kWipeRounds) >> 1) + 1u;
+    const uint32_t stamp = ((round & a.wipe) >> 1) + 1u;
     if (me.G > 1) {
         if (me.lane == 0 && (me.w & (kHW - 1)) == 0) {
             uint64_t v = (uint64_t)stamp << 50;
@@ -859,7 +859,8 @@ __device__ __forceinline__ void clear_lists(const LocalArgs& a, const Seat& me)
 }
 
 // The stamps of published candidates start again: all workgroups meet when they are done with the last list, clear
-// their words and meet once more.  False if a wait expired.
+// their words and meet once more.  False if a wait expired.  (The rounds go on without a gap: each of them clears the
+// counters in LDS that the next one adds to.)
 template <int P>
 __device__ __forceinline__ bool renew_stamps(const Held<P>& h, LocalShared& sh, const Seat& me, const LocalArgs& a, uint32_t& it,
                                              uint32_t& seq)
@@ -908,10 +909,6 @@ __device__ __forceinline__ int exact_rounds(Held<P>& h, LocalShared& sh, const S
     float step = 0.8f;                      // ratio of a round's levels
     int dry = 0, most_dry = 3;
     while (st.np < stop) {
-        if ((st.round & kWipeRounds) == kWipeRounds) {
-            ++st.round;
-            if (!renew_stamps<P>(h, sh, me, a, st.it, st.seq)) return 2;
-        }
         if (!(tau > 0.0f)) {
             const Rec r = plain_pick<P>(h, sh, me, a, st.it, st.seq);
             if (uni(r.fail) != 0) return 2;
@@ -933,6 +930,7 @@ __device__ __forceinline__ int exact_rounds(Held<P>& h, LocalShared& sh, const S
             dry = 0;
             continue;
         }
+        if ((st.round & a.wipe) == a.wipe && !renew_stamps<P>(h, sh, me, a, st.it, st.seq)) return 2;
         ++st.round;
         ++st.rounds;
         Levels lv;
@@ -1005,10 +1003,7 @@ __device__ __forceinline__ int threshold_rounds(Held<P>& h, LocalShared& sh, Lev
             }
             enter();
         }
-        if ((st.round & kWipeRounds) == kWipeRounds) {
-            ++st.round;
-            if (!renew_stamps<P>(h, sh, me, a, st.it, st.seq)) return 2;
-        }
+        if ((st.round & a.wipe) == a.wipe && !renew_stamps<P>(h, sh, me, a, st.it, st.seq)) return 2;
         ++st.round;
         ++st.rounds;
         const int room = (level_end < n ? level_end : n) - st.np;
@@ -1074,7 +1069,7 @@ __device__ __forceinline__ int follow_order(Held<P>& h, LocalShared& sh, const S
 {
     const int n = a.n, N = a.N;
     const float* __restrict__ cloud = a.xyz + (int64_t)me.c * N * 3;
-    if (n < 16 || n > kOrderWords * me.G || (round & kWipeRounds) > kWipeRounds - 32 || round >= 1u << 18) return 1;
+    if (n < 16 || n > kOrderWords * me.G || (round & a.wipe) > a.wipe - 32 || round >= 1u << 18) return 1;
     {
         // every workgroup looks at the same points
         const float x0 = cloud[0], y0 = cloud[1], z0 = cloud[2];

@@ -136,6 +136,42 @@ def test_mdps_given_thresholds_small_record_and_short_prefix(fp):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("G", [1, 3, 8])
+def test_stamps_start_again_in_a_cloud(fp, G):
+    """Equal distances take a round a sample: the stamps of published candidates start again (after 128 rounds with a
+    number of workgroups forced) several times in one cloud, with one workgroup there is nothing to renew."""
+    x = torch.from_numpy(cloud("lattice", 8192)[None]).cuda()
+    want = exact_by_index(fp, x, 3000, want_mdc=True)
+    fp.set_wg_per_cloud(G)
+    try:
+        idx, mdc, info = fp.fps_exact_pruned(x, 3000, want_mdc=True, want_info=True)
+    finally:
+        fp.set_wg_per_cloud(0)
+    assert fp.parse_info(info)[0].status == 0 and fp.parse_info(info)[0].rounds > 3 * 128
+    assert torch.equal(idx, want[0]) and torch.equal(mdc.view(torch.int32), want[1].view(torch.int32))
+
+
+@pytest.mark.parametrize("order", [0, 1])
+@pytest.mark.parametrize("G", [1, 64, 128])
+def test_stamps_start_again_between_clouds(fp, G, order):
+    """The rounds of a group go on over its clouds."""
+    clouds = 256 // G * 10
+    x = torch.stack([torch.from_numpy(cloud("uniform", 8192) + np.float32(b)).cuda() for b in range(5)]).repeat(clouds // 5, 1, 1)
+    prm = fp.MdpsParams(exponent=0.7, bias=1.05, scan_order=order)
+    want = [fp.mdps_sample(x[:5], 5000, prm), exact_by_index(fp, x[:5], 3000)]
+    fp.set_wg_per_cloud(G)
+    try:
+        got, info = fp.mdps_sample_pruned(x, 5000, prm, want_info=True)
+        got, info = [got, None], [info, None]
+        got[1], info[1] = fp.fps_exact_pruned(x, 3000, want_info=True)
+    finally:
+        fp.set_wg_per_cloud(0)
+    for g, w, i in zip(got, want, info):
+        rounds = [k.rounds for k in fp.parse_info(i)]
+        assert sum(rounds[::256 // G]) > 2 * 128 and all(k.status == 0 for k in fp.parse_info(i))
+        assert all(torch.equal(g[b], w[b % 5]) for b in range(clouds))
+
+
 def test_more_above_a_level_than_16_bits_count(fp):
     """a hemisphere of a million points just below the fourth level of the first list, 66200 of them just above: evenly
     mixed, so that no part of the cloud has more of them than it may list, and 664 too many for 16 bits"""
