@@ -1079,7 +1079,11 @@ __device__ __forceinline__ int follow_order(Held<P>& h, LocalShared& sh, const S
         if (__syncthreads_or(!(d <= d1) || !(d1 > 0.0f) || !(d1 < __builtin_inff()))) return 1;
     }
     if (me.tid == 0) sh.in_order = n;
-    ++round;
+    // Behind another cloud of the group the workgroups meet first: some may still be reading that one's last list and counts,
+    // which the words and the agreement on them write over (a workgroup without a share of the decisions is
+    // waited for by nobody).
+    if (me.G == 1 || round == 0) ++round;
+    else if (!agree_in_order(sh, me, a, round)) return 0;
     const uint32_t stamp = round;
     uint64_t* const words = half_list(a, me, 0, 0);         // (a stamp of 32 bits is no stamp of a candidate's)
     float* const part = reinterpret_cast<float*>(sh.cand);

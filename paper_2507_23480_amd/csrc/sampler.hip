@@ -1983,8 +1983,12 @@ __device__ __forceinline__ int follow_order(const SamplerArgs& a, Shared<T>& sh,
         sh.in_order = n;
     }
     __syncthreads();
+    // Behind another cloud of the group the workgroups meet first: some may still be reading that one's last candidates and
+    // counts, which the words and the agreement on them write over (nobody waits for a workgroup to have read a list).
+    if (wh.G == 1 || seq == 0) ++seq;
+    else if (!agree_in_order<T>(a, sh, wh, seq)) return 0;
     uint64_t* const words = order_words(a, wh);
-    const uint32_t stamp = ++seq;
+    const uint32_t stamp = seq;
     float* const part = reinterpret_cast<float*>(sh.cand);
     static_assert(sizeof(sh.cand) >= NW * 64 * sizeof(float), "a value per lane of the point waves");
     RowWords<P, false> rw;

@@ -1,4 +1,5 @@
-"""Protocol of the sampler by local decisions (csrc/local_sampler.hip) on a model: the workgroups of a cloud as programs
+"""Protocol of the sampler by local decisions (csrc/local_sampler.hip), and of what it has in common with the index-ordered
+one (csrc/sampler.hip), on a model: the workgroups of a cloud as programs
 that take turns in a random sequence of single reads and writes, with the words, stamps, parities and counters of the kernels.
 A wait for a word that never comes leaves no program able to go on.  The faulty forms the model has been used
 to find are kept as switches: the tests show that it still tells them from the present ones."""
@@ -63,9 +64,36 @@ class Workgroup:
         yield None
         yield from self.meet()
 
-    def list_round(self, skip):
+    def agree(self):                                    # agree_in_order
+        if self.mem.G == 1:
+            return
+        self.round += 1
+        r, par = self.round, self.round & 1
+        self.mem.word["hdr", par, self.g] = ("agree", r), None
+        yield None
+        for t in range(self.mem.G):
+            yield self.stamped(("agree", r), "hdr", par, t)
+
+    def follow(self, points, meet_first):
+        """follow_order on a cloud that is in order to the end: the values of its points take the place of candidates."""
+        G, word = self.mem.G, self.mem.word
+        if not meet_first or G == 1 or self.round == 0:
+            self.round += 1
+        else:
+            yield from self.agree()
+        stamp = "value", self.round
+        for k in range(points):
+            if k % G == self.g:
+                word["list", 0, 0, k] = stamp, None
+                yield None
+        for k in range(points):
+            yield self.stamped(stamp, "list", 0, 0, k)
+        yield from self.agree()
+        yield from self.agree()                         # (all have read the values)
+
+    def list_round(self, skip=False, decisions=True):
         """Scan, list and decisions of a round; checks every candidate read.  The workgroups from `deciding` on have no share
-        of the list and publish no decisions."""
+        of the list and publish no decisions; in the index-ordered sampler nobody does."""
         G, word = self.mem.G, self.mem.word
         if (self.round & WIPE) == WIPE:
             if skip:
@@ -91,7 +119,7 @@ class Workgroup:
             for k in range(n):
                 yield self.stamped(stamp, "list", par, t, k)
                 assert self.mem.get("list", par, t, k)[1] == (r, t, k)
-        deciding = max(1, G // 2)
+        deciding = max(1, G // 2) if decisions else 0
         if self.g < deciding:
             word["mask", par, self.g] = r, None
             yield None
@@ -118,3 +146,37 @@ def test_stamps_start_again(G):
 def test_a_round_left_out_at_the_renewal_is_found(G):
     with pytest.raises(AssertionError if G == 1 else Stuck):
         finish(G, 0, 0, skip=True)
+
+
+def clouds(G, seed, slow, decisions, meet_first=True):
+    """Clouds of a group in turn: rounds, a cloud followed to its end, rounds, two followed."""
+    rng, mem = random.Random(seed), Cloud(G)
+
+    def program(wg):
+        for kind in "RFRFFRRF":
+            wg.cnt = [0, 0]
+            if kind == "F":
+                yield from wg.follow(1 + seed % 5, meet_first)
+            else:
+                for _ in range(1 + seed % 3):
+                    yield from wg.list_round(decisions=decisions)
+    run([program(Workgroup(mem, g, seed)) for g in range(G)], rng, slow)
+
+
+@pytest.mark.parametrize("decisions", [True, False])
+@pytest.mark.parametrize("G", [1, 2, 3, 5])
+def test_followed_clouds_between_others(G, decisions):
+    for seed in range(40):
+        clouds(G, seed, seed % G, decisions)
+
+
+@pytest.mark.parametrize("decisions", [True, False])
+@pytest.mark.parametrize("G", [3, 5])
+def test_values_written_over_a_list_still_read_are_found(G, decisions):
+    stuck = 0
+    for seed in range(40):
+        try:
+            clouds(G, seed, seed % G, decisions, meet_first=False)
+        except (Stuck, AssertionError, TypeError):
+            stuck += 1
+    assert stuck > 0

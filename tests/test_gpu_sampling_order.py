@@ -123,3 +123,22 @@ def test_several_clouds_to_a_group(fp):
         for b, k in enumerate([0, 1, 0, 0, 1, 1, 0] * 3):
             for idx, mdc in got:
                 assert np.array_equal(idx[b].cpu().numpy(), want[k][0]) and np.array_equal(mdc[b].cpu().numpy(), want[k][1])
+
+
+@pytest.mark.parametrize("G", [5, 33, 128])
+def test_followed_behind_searched(fp, G):
+    """clouds in order next to clouds in none in the turn of a group, with few samples and so short lists, which most
+    workgroups have no share of"""
+    p = ordered(3000)
+    q = np.random.default_rng(4).permutation(p)
+    kinds = ([0] * (256 // G) + [1] * (256 // G)) * 6
+    x = torch.stack([torch.from_numpy(p).cuda(), torch.from_numpy(q).cuda()])[torch.tensor(kinds)].contiguous()
+    for n in (20, 300):
+        want = [ref.fps_exact(c, n)[0] for c in (p, q)]
+        fp.set_wg_per_cloud(G)
+        try:
+            got = [f(x, n).cpu().numpy() for f in (fp.fps_exact, fp.fps_exact_pruned)]
+        finally:
+            fp.set_wg_per_cloud(0)
+        for b, k in enumerate(kinds):
+            assert all(np.array_equal(g[b], want[k]) for g in got)
