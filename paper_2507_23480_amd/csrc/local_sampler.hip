@@ -1376,9 +1376,37 @@ __global__ __launch_bounds__(kT) void local_kernel(LocalArgs a)
 // distances are spread over 4096 ranges of equal width (the n-th of evenly spread samples is found at a distance that
 // falls with 1 / n on surfaces, with n ** (-2 / 3) in space).  Every workgroup counts all keys by range (65536 keys are 0.5 MB, read
 // by 32 workgroups), takes the ranges that begin in its share of the sequence, gathers their keys in LDS and
-// places each among those of its range (a few dozen at most in the workloads).  Bound: the two passes over the keys.
+// places each among those of its range (a few dozen at most in the workloads; where one has more, all of them are sorted).
+// A range of more keys than a share has places (equal distances, or a smallest distance so far below the others that
+// these are all in the first range) is divided among the workgroups by place: each looks for the first and the last
+// key of its share, twelve bits of the key at a time, and sorts those between.  Bound: the passes over the keys, two, or seven.
+// fps_exact_pruned of 20000 points, all of them sampled, most of which are in one range: 0.85 ms; 23.9 ms where one workgroup
+// compared all of them with each other.
 constexpr int kOrderT = 1024;
 constexpr int kRanges = 4096;                   // 2^12
+constexpr int kShare = kOrderMost / 2;          // places of a workgroup at most
+constexpr int kFewKeys = 128;                   // keys of a range up to which each is placed by comparing it with the others
+
+// Puts the first `count` keys in order; `key` has room for the next power of two.
+__device__ __forceinline__ void sort_keys(uint64_t* key, int count, int tid)
+{
+    int size = 64;
+    while (size < count) size <<= 1;
+    for (int t = count + tid; t < size; t += kOrderT) key[t] = ~0ull;
+    for (int k = 2; k <= size; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            __syncthreads();
+            for (int t = tid; t < size / 2; t += kOrderT) {
+                const int lo = (t & ~(j - 1)) * 2 | (t & (j - 1)), hi = lo | j;
+                const uint64_t u = key[lo], v = key[hi];
+                if ((u > v) == ((lo & k) == 0)) {
+                    key[lo] = v;
+                    key[hi] = u;
+                }
+            }
+        }
+    __syncthreads();
+}
 
 __global__ __launch_bounds__(kOrderT) void order_samples_kernel(const uint64_t* __restrict__ found_all,
                                                                 const LocalCloud* __restrict__ clouds,
@@ -1391,7 +1419,9 @@ __global__ __launch_bounds__(kOrderT) void order_samples_kernel(const uint64_t* 
     __shared__ int32_t first[kRanges + 1];              // counts, then keys in front of the range
     __shared__ int32_t next[kRanges];
     __shared__ int32_t sums[kOrderT / 64];
-    __shared__ int32_t mine[2];
+    __shared__ int32_t mine[4];
+    __shared__ int32_t bin[2][3];                       // of the first and the last key looked for: digit, keys of it, keys in front
+    __shared__ int32_t gathered;
     const int b = (int)blockIdx.y, q = (int)blockIdx.x, tid = (int)threadIdx.x, lane = tid & 63;
     const LocalCloud& cl = clouds[b];
     const int np = cl.count, runs = cl.runs;
@@ -1418,8 +1448,9 @@ __global__ __launch_bounds__(kOrderT) void order_samples_kernel(const uint64_t* 
     const int s0 = all + (int)((int64_t)len * q / Q), s1 = all + (int)((int64_t)len * (q + 1) / Q);
     for (int run = 0; run < runs; ++run) {
         const int r_begin = cl.begin[run], m = cl.begin[run + 1] - r_begin;
-        const int share0 = s0 - r_begin, share1 = s1 - r_begin;            // this workgroup's share of the run's positions
-        if (m <= 0 || share1 <= 0 || share0 >= m) continue;                // uniform
+        // this workgroup's share of the run's positions
+        const int share0 = s0 > r_begin ? s0 - r_begin : 0, share1 = s1 - r_begin < m ? s1 - r_begin : m;
+        if (share0 >= share1) continue;                                    // uniform
         const uint64_t* const keys = found_all + (int64_t)b * n + r_begin;
         const uint32_t bound = cl.low[run];
         const bool keyed = bound == ~0u;
@@ -1466,7 +1497,6 @@ __global__ __launch_bounds__(kOrderT) void order_samples_kernel(const uint64_t* 
         }
         const int incl = wave_incl_sum(sum, lane);
         if (lane == 63) sums[tid >> 6] = incl;
-        if (tid < 2) mine[tid] = kRanges;
         __syncthreads();
         int at = incl - sum;
         for (int w = 0; w < (tid >> 6); ++w) at += sums[w];
@@ -1474,17 +1504,19 @@ __global__ __launch_bounds__(kOrderT) void order_samples_kernel(const uint64_t* 
         for (int u = 0; u < 4; ++u) {
             const int r = 4 * tid + u;
             first[r] = at;
-            // (the first range that does not begin before a border: one thread finds it, or none)
-            if (at < share0 && at + c[u] >= share0) mine[0] = r + 1;
-            if (at < share1 && at + c[u] >= share1) mine[1] = r + 1;
+            // the ranges that hold the first and the last place of the share (one thread finds each)
+            if (at <= share0 && share0 < at + c[u]) mine[0] = r;
+            if (at < share1 && share1 <= at + c[u]) mine[1] = r;
             at += c[u];
         }
         if (tid == kOrderT - 1) first[kRanges] = at;
         __syncthreads();
-        const int r0 = share0 <= 0 ? 0 : mine[0], r1 = share1 >= m ? kRanges : mine[1];
-        if (r0 >= r1) continue;                                            // uniform: no range begins in the share
-        const int from = first[r0], count = first[r1] - from;
-        if (count <= kOrderMost) {
+        const int ra = uni(mine[0]), rb = uni(mine[1]);
+        const int ra0 = uni(first[ra]), ra1 = uni(first[ra + 1]), rb0 = uni(first[rb]), rb1 = uni(first[rb + 1]);
+        // the ranges that begin in the share, without the last one if that is longer than a share
+        const int r0 = ra0 < share0 ? ra + 1 : ra, r1 = rb1 - rb0 > kShare ? rb : rb + 1;
+        if (r0 < r1) {
+            const int from = ra0 < share0 ? ra1 : ra0, count = (r1 == rb ? rb0 : rb1) - from;      // at most kOrderMost
             for (int t0 = tid; t0 < m; t0 += kOrderT * U) {
                 uint64_t k[U];
 #pragma unroll
@@ -1495,23 +1527,110 @@ __global__ __launch_bounds__(kOrderT) void order_samples_kernel(const uint64_t* 
                     if (t0 + u * kOrderT < m && r >= r0 && r < r1) key[first[r] - from + atomicAdd(&next[r], 1)] = k[u];
                 }
             }
-            __syncthreads();
-            for (int t = tid; t < count; t += kOrderT) {
-                const uint64_t k = key[t];
-                const int r = range_of(k), lo = first[r] - from, hi = first[r + 1] - from;
-                int place = first[r];
-                for (int e = lo; e < hi; ++e) place += key[e] < k || (key[e] == k && e < t) ? 1 : 0;
-                emit(place, k);
+            bool many = false;
+            for (int r = r0 + tid; r < r1; r += kOrderT) many = many || first[r + 1] - first[r] > kFewKeys;
+            if (__syncthreads_or(many)) {
+                sort_keys(key, count, tid);
+                for (int t = tid; t < count; t += kOrderT) emit(from + t, key[t]);
+            } else {
+                for (int t = tid; t < count; t += kOrderT) {
+                    const uint64_t k = key[t];
+                    const int r = range_of(k), lo = first[r] - from, hi = first[r + 1] - from;
+                    int place = first[r];
+                    for (int e = lo; e < hi; ++e) place += key[e] < k || (key[e] == k && e < t) ? 1 : 0;
+                    emit(place, k);
+                }
             }
-        } else {
-            // many equal distances: each of these keys is counted against all
-            for (int t = tid; t < m; t += kOrderT) {
-                const uint64_t k = keys[t];
-                const int r = range_of(k);
-                if (r < r0 || r >= r1) continue;
-                int place = 0;
-                for (int e = 0; e < m; ++e) place += keys[e] < k || (keys[e] == k && e < t) ? 1 : 0;
-                emit(place, k);
+        }
+        // the ranges longer than a share: at most the one it begins in and the one it ends in
+        for (int part = 0; part < 2; ++part) {
+            const int r = part == 0 ? ra : rb, begin = part == 0 ? ra0 : rb0, end = part == 0 ? ra1 : rb1;
+            if (end - begin <= kShare || (part == 1 && ra == rb)) continue;                        // uniform
+            const int g0 = begin > share0 ? begin : share0, g1 = end < share1 ? end : share1;
+            uint64_t top[2] = {0, 0};                                      // the keys at places g0 and g1 - 1, as far as known
+            int place[2] = {g0 - begin, g1 - 1 - begin}, equal[2] = {0, 0};
+            for (int bit = 40; bit >= -8; bit -= 12) {
+                const int down = bit > 0 ? bit : 0, digits = bit > 0 ? 12 : 12 + bit;
+                const bool same = top[0] == top[1];
+                __syncthreads();
+                for (int t = tid; t < kRanges; t += kOrderT) {
+                    first[t] = 0;
+                    next[t] = 0;
+                }
+                __syncthreads();
+                for (int t0 = tid; t0 < m; t0 += kOrderT * U) {
+                    uint64_t k[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) k[u] = t0 + u * kOrderT < m ? keys[t0 + u * kOrderT] : 0;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const bool in = t0 + u * kOrderT < m && range_of(k[u]) == r;
+                        const uint64_t above = k[u] >> (down + digits);
+                        const int digit = (int)(k[u] >> down) & ((1 << digits) - 1);
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            if (e == 1 && same) break;
+                            int32_t* const h = e == 0 ? first : next;
+                            // (the lanes with the digit of the first of them together: equal distances share most of them)
+                            const uint64_t who = __builtin_amdgcn_ballot_w64(in && above == top[e]);
+                            if (who == 0) continue;
+                            const int lead = first_lane(who), d0 = (int)rdlane((uint32_t)digit, lead);
+                            const uint64_t alike = __builtin_amdgcn_ballot_w64(digit == d0) & who;
+                            if (lane == lead) atomicAdd(&h[d0], (int)__builtin_popcountll(alike));
+                            else if ((((who & ~alike) >> lane) & 1ull) != 0) atomicAdd(&h[digit], 1);
+                        }
+                    }
+                }
+                __syncthreads();
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const int32_t* const h = e == 1 && !same ? next : first;
+                    int own = 0;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) own += h[4 * tid + u];
+                    const int upto = wave_incl_sum(own, lane);
+                    if (lane == 63) sums[tid >> 6] = upto;
+                    __syncthreads();
+                    int before = upto - own;
+                    for (int w = 0; w < (tid >> 6); ++w) before += sums[w];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int n_u = h[4 * tid + u];
+                        if (before <= place[e] && place[e] < before + n_u) {
+                            bin[e][0] = 4 * tid + u;
+                            bin[e][1] = n_u;
+                            bin[e][2] = before;
+                        }
+                        before += n_u;
+                    }
+                    __syncthreads();
+                }
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    top[e] = (top[e] << digits) | (uint64_t)(uint32_t)uni(bin[e][0]);
+                    equal[e] = uni(bin[e][1]);
+                    place[e] -= uni(bin[e][2]);
+                }
+            }
+            // places g0 ... : the first key (again, where keys are equal), the keys between, the last key (again)
+            const bool one = top[0] == top[1];
+            const int inner0 = one ? g1 : g0 + equal[0] - place[0], inner1 = one ? g1 : g1 - 1 - place[1];
+            for (int t = g0 + tid; t < inner0; t += kOrderT) emit(t, top[0]);
+            for (int t = inner1 + tid; t < g1; t += kOrderT) emit(t, top[1]);
+            if (inner0 < inner1) {                                         // uniform
+                if (tid == 0) gathered = 0;
+                __syncthreads();
+                for (int t0 = tid; t0 < m; t0 += kOrderT * U) {
+                    uint64_t k[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) k[u] = t0 + u * kOrderT < m ? keys[t0 + u * kOrderT] : 0;
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (t0 + u * kOrderT < m && k[u] > top[0] && k[u] < top[1]) key[atomicAdd(&gathered, 1)] = k[u];
+                }
+                __syncthreads();
+                sort_keys(key, inner1 - inner0, tid);
+                for (int t = tid; t < inner1 - inner0; t += kOrderT) emit(inner0 + t, key[t]);
             }
         }
     }
@@ -1541,7 +1660,7 @@ hipError_t launch_order_samples(const uint64_t* found, const LocalCloud* cloud, 
                                 int most, bool fill, int32_t* out_idx, float* out_mdc, int32_t* bq_idx, int32_t* inv,
                                 hipStream_t stream)
 {
-    const int Q = most <= kOrderMost / 2 ? 1 : (most + kOrderMost / 2 - 1) / (kOrderMost / 2);
+    const int Q = most <= kShare ? 1 : (most + kShare - 1) / kShare;
     hipLaunchKernelGGL(order_samples_kernel, dim3((unsigned)Q, (unsigned)B), dim3(kOrderT), 0, stream, found, cloud,
                        start_idx, N, n, Q, fill, out_idx, out_mdc, bq_idx, inv);
     return hipGetLastError();

@@ -63,6 +63,41 @@ def test_equal_distances(fp, N, n, G):
     compare(fp, cloud("lattice", N)[None], n, G)
 
 
+# Ranges of more samples than a workgroup has places for in the kernel that puts the samples in sequence: all points sampled,
+# the smallest distance far below the others; more than 4096 samples at one distance; both beside ranges of a few
+@pytest.mark.parametrize("kind,N,n", [("uniform", 2049, 2049), ("uniform", 3000, 3000), ("uniform", 20000, 20000), ("uniform", 20000, 19000),
+                                      ("dense corner", 12289, 12289), ("near", 20000, 19990), ("near", 6145, 6145),
+                                      ("lattice", 32768, 16384), ("lattice", 16384, 16384)])
+def test_long_ranges(fp, kind, N, n):
+    p = cloud("uniform" if kind == "near" else kind, N)
+    if kind == "near":                          # a pair of points, the closer the more ranges lie above the others
+        p[5] = p[6] + np.float32(1e-7) * np.arange(3, dtype=np.float32)
+    compare(fp, p[None], n, 8)
+
+
+def test_equal_samples_of_a_prefix(fp):
+    """index 0 some thousand times, at the end of a prefix longer than the cloud has different points"""
+    p = np.resize(cloud("uniform", 700), (60000, 3))
+    compare_mdps(fp, p[None], 50000, 60, fp.MdpsParams(exponent=0.7, bias=1.05, p=0.2), 0.05)
+
+
+def test_all_points_sampled_in_time(fp):
+    """Twice the samples, the last of them at distances far below the others, take about twice the time."""
+    x = torch.from_numpy(cloud("uniform", 20000)[None]).cuda()
+
+    def best(n):
+        times = []
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            fp.fps_exact_pruned(x, n)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+    assert best(20000) < 4.0 * best(10000)
+
+
 def test_duplicates_and_start(fp):
     p = np.repeat(cloud("uniform", 700), 9, axis=0)
     compare(fp, np.stack([p, p[::-1]]), 5000, 6, start=[6299, 17])
