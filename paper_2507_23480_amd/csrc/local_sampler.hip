@@ -1138,9 +1138,13 @@ __device__ __forceinline__ int follow_order(Held<P>& h, LocalShared& sh, const S
             float before = __shfl_up(v, 1);
             if (me.lane == 0 || k == from) before = last_v;
             const uint64_t rises = __builtin_amdgcn_ballot_w64(has && (!(v <= before) || !(v > 0.0f)));
-            if (rises != 0) bad = 64 * c + first_lane(rises);
             const int end = upto - 64 * c < 64 ? upto - 64 * c : 64;
-            last_v = rdlane_f(v, end - 1);
+            if (rises != 0) {
+                bad = 64 * c + first_lane(rises);
+                last_v = rdlane_f(before, first_lane(rises));
+            } else {
+                last_v = rdlane_f(v, end - 1);
+            }
             const float bd = fminf(box_dist2(a0, kx, ky, kz), box_dist2(a1, kx, ky, kz));
             for (uint64_t near = __builtin_amdgcn_ballot_w64(has && bd < h.ub); near != 0; near &= near - 1) {
                 const int s = first_lane(near);
@@ -1154,7 +1158,8 @@ __device__ __forceinline__ int follow_order(Held<P>& h, LocalShared& sh, const S
                 good = 64 * c + s + 1;
             }
         }
-        if (bad < n || h.ub > last_v) bad = min(bad, good); // (what lies behind the last one folded has not been looked at)
+        // up to where the curve falls the last value decides (a wave without points has no objection)
+        if (h.ub > last_v) bad = min(bad, good);
         if (bad < n && me.lane == 0) atomicMin(&sh.in_order, bad);
         if (!agree_in_order(sh, me, a, round)) return 0;
         if (uni(sh.in_order) < upto || upto == n) break;

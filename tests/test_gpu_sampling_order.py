@@ -75,6 +75,22 @@ def test_breaks_off(fp, N, n, at, how):
     check(fp, p, n)
 
 
+@pytest.mark.parametrize("how", ["swap", "shuffle"])
+@pytest.mark.parametrize("N,n,at", [(6000, 1500, 513), (6000, 1500, 1000), (6000, 1500, 1400), (9000, 5000, 4097)])
+def test_goes_on_where_it_breaks_off(fp, N, n, at, how):
+    """The samples in front of the break are kept: the rounds are those for the rest, a part of those for the cloud in no
+    order (some waves of both sizes hold no points)."""
+    p = ordered(N)
+    q = np.random.default_rng(1).permutation(p)
+    if how == "swap":
+        p[[at, at + 7]] = p[[at + 7, at]]
+    else:
+        p[at:] = np.random.default_rng(at).permutation(p[at:])
+    rounds = [fp.parse_info(fp.fps_exact_pruned(torch.from_numpy(c[None]).cuda(), n, want_info=True)[1])[0].rounds for c in (p, q)]
+    # (the curve falls with the number of samples, and the lists follow it down by some factor a round)
+    assert rounds[0] < (0.5 if at < n / 2 else 0.25) * rounds[1]
+
+
 def test_moved_equal_and_other_start(fp):
     p = ordered(6000)
     check(fp, p, 1600, starts=5)
