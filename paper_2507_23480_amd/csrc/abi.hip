@@ -291,7 +291,7 @@ fp_status run_local(const SamplerArgs& s, const Plan& plan, bool mdps, void* wor
     int32_t* const inv = bq_cache ? reinterpret_cast<int32_t*>(own + lay.inv) : nullptr;
     const int P = plan.T * plan.P / kLocalThreads;
     for (int part = 0; part < (prefix ? 2 : 1); ++part) {
-        const void* fn = local_kernel_for(P, bq_cache != nullptr, part == 1);
+        const void* fn = local_kernel_for(P, bq_cache != nullptr, part == 1, a.walk_inv == 0);
         if (!fn) return FP_ERR_SHAPE;
         const int64_t list_words = plan.G > 1 ? (int64_t)plan.groups * plan.G * kLocalWgWords : 0;
         if (plan.G > 1 || (zero_words > 0 && part == 0)) {

@@ -155,8 +155,8 @@ struct LocalArgs : SamplerArgs {
     float* curve;                       // [B][n] distances of the prefix in sequence
     uint2* bq_at;                       // [B][waves] where a wave's chunk of the record has got to
 };
-// mdps: what follows the prefix
-const void* local_kernel_for(int points_per_thread, bool bq, bool mdps);
+// mdps: what follows the prefix; chains: its keys are indices, which may follow each other along the cloud
+const void* local_kernel_for(int points_per_thread, bool bq, bool mdps, bool chains);
 // Positions [from, cloud.count) of every cloud; fill: and the rest up to n.  curve: distances, [B][n] (NULL: none);
 // inv: [B][N], position of a sample by its index (NULL: not wanted)
 hipError_t launch_order_samples(const uint64_t* found, const LocalCloud* cloud, const int32_t* start_idx, int B, int N, int n,

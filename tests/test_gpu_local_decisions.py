@@ -30,6 +30,12 @@ def cloud(kind, N):
         return p.astype(np.float32)
     if kind == "lattice":
         return rng.permutation(np.stack(np.unravel_index(np.arange(N), (64, 64, (N + 4095) // 4096)), -1)).astype(np.float32)
+    if kind == "path":                          # indices follow a curve, a sensor on its way
+        t = np.linspace(0.0, 200.0, N)
+        p = np.stack([30.0 * np.cos(t / 7.0) + t / 10.0, 30.0 * np.sin(t / 9.0), 0.02 * t], axis=-1)
+        return (p + 0.01 * rng.normal(size=(N, 3))).astype(np.float32)
+    if kind == "rows":                          # a lattice by rows and layers
+        return np.stack(np.unravel_index(np.arange(N), ((N + 1023) // 1024, 32, 32)), axis=-1).astype(np.float32)
     return rng.random((N, 3), dtype=np.float32)
 
 
@@ -147,6 +153,30 @@ def test_mdps_uneven(fp, kind, order):
     radius = {"sheet": 1.0, "dense corner": 0.03, "lattice": 1.5}[kind]
     prm = fp.MdpsParams(exponent=1.0, bias=1.05, scan_order=order)
     compare_mdps(fp, np.stack([cloud(kind, 20480), cloud(kind, 20480)[::-1]]), 5003, 20, prm, radius, start=[20479, 5])
+
+
+# Samples that wait for one another: lists settled in order.  Levels cut by their quota inside a list, exhausted, followed by a
+# remainder; a list's candidates in one wave and in all; one workgroup and many; both scan orders
+@pytest.mark.parametrize("order", [0, 1])
+@pytest.mark.parametrize("kind,N,G,R", [("path", 8192, 1, 0.9), ("path", 8192, 3, 0.9), ("path", 40000, 40, 0.9), ("path", 40000, 7, 2.0),
+                                        ("path", 40000, 256, 0.2), ("rows", 8192, 2, 2.5), ("rows", 32768, 32, 3.1)])
+def test_mdps_chains(fp, kind, N, G, R, order):
+    p = cloud(kind, N)
+    thr = [(f * R) ** 2 for f in (1.6, 1.0, 0.6, 0.25)]
+    prm = fp.MdpsParams(p=0.002, nseg=4, m_min=4, thr_override=thr, scan_order=order)
+    compare_mdps(fp, np.stack([p, p[::-1]]), 5000, G, prm, R, start=[N - 1, 3])
+
+
+def test_mdps_chains_take_few_rounds(fp):
+    """A path of 40000 points, 6000 samples: 256 candidates settled in order a round take 248 to 760 rounds, a sample per chain
+    and round 1228 to 3242."""
+    x = torch.from_numpy(cloud("path", 40000)[None]).cuda()
+    r = 200 * 4.0 / 6000
+    for prm in (fp.MdpsParams(p=0.01, exponent=2.0), fp.MdpsParams(p=0.001, exponent=2.0),
+                fp.MdpsParams(p=0.001, nseg=3, thr_override=[(1.6 * r) ** 2, r ** 2, (0.5 * r) ** 2])):
+        got, info = fp.mdps_sample_pruned(x, 6000, prm, want_info=True)
+        assert fp.parse_info(info)[0].rounds < 300
+        assert torch.equal(got, fp.mdps_sample(x, 6000, prm))
 
 
 @pytest.mark.parametrize("order", [0, 1])
