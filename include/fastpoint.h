@@ -394,7 +394,7 @@ fp_status fp_plan(int32_t B, int32_t N, int32_t* wg_per_cloud, int32_t* threads,
 
 /* Force the number of workgroups per cloud (0 = automatic, the default).  Lets a test run a
  * small cloud through the multi-workgroup exchange, and, in the samplers that find many samples
- * at a time, through the renewal of the stamps its words carry (every 128 rounds instead of
+ * at a time, through the renewal of the stamps its words carry (after 100 rounds instead of
  * 16384). */
 void fp_set_wg_per_cloud(int32_t wg_per_cloud);
 

@@ -280,7 +280,7 @@ fp_status run_local(const SamplerArgs& s, const Plan& plan, bool mdps, void* wor
     a.found = spatial_sort_spare(s.B, s.N, sort_ws);
     a.cloud = reinterpret_cast<LocalCloud*>(own + lay.cloud);
     a.stop = prefix ? s.m + 1 : s.n;
-    a.wipe = (g_force_wg_per_cloud.load() == 0 ? kLocalStampRounds : kLocalStampRoundsForced) - 1u;
+    a.first_round = g_force_wg_per_cloud.load() == 0 ? 0u : kLocalFirstRoundForced;
     while ((plan.G << (a.own_shift + 1)) <= kLocalThreads) ++a.own_shift;
     a.ll_hdr = a.ll_pk + kLlPkWords;
     a.ll_mask = a.ll_hdr + kLocalHdrWords;

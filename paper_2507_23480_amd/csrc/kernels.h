@@ -130,7 +130,7 @@ constexpr int kLocalOwn = 511;          // ... of half a workgroup (191: 94 and 
 constexpr int kLocalCandWords = 3;      // words of a published candidate
 constexpr int kLocalMaskWords = 8;      // words of 32 decisions a workgroup publishes
 constexpr uint32_t kLocalStampRounds = 16384;       // rounds after which the stamps of published candidates start again
-constexpr uint32_t kLocalStampRoundsForced = 128;   // ... under the hook that forces a number of workgroups: a test's small cloud gets there
+constexpr uint32_t kLocalFirstRoundForced = kLocalStampRounds - 101;     // first round under the hook that forces a number of workgroups
 constexpr int kOrderMost = 4096;        // keys a workgroup puts in order
 constexpr int kLocalRuns = FP_MAX_SEG + 2;
 // What the launches of a call hand on per cloud: the samples found, in runs that follow each other in the output and are
@@ -146,7 +146,7 @@ struct LocalArgs : SamplerArgs {
     LocalCloud* cloud;                  // [B]
     int32_t stop;                       // exact FPS ends with this many samples
     int32_t aim;                        // candidates a round takes at most
-    uint32_t wipe;                      // rounds after which the stamps start again, a power of two less one
+    uint32_t first_round;               // 0; a test's small cloud gets to the renewal of the stamps from a later one
     int32_t own_shift;                  // 2^own_shift threads of a workgroup per workgroup of the cloud
     uint64_t* ll_hdr;                   // [groups][2][2 G] counts
     uint64_t* ll_mask;                  // [groups][2][G][kLocalMaskWords] decisions

@@ -79,11 +79,11 @@ struct LocalShared {
     int32_t inc[2][2 * kMaxGroup];          // sums of the halves' counts inside 64 of them, two levels in a word
     int32_t tot[kSpans][kLevels];           // ... of all 64, kFull more where a half has more than it can list
     uint32_t acc[kList / 32];               // decisions on the candidates of this workgroup's part of the list
-    uint64_t settled[kSettle / 64];         // settle_in_order: samples among 64 candidates that follow each other
     int32_t fail;
     int32_t in_order;                       // follow_order: samples known to be in sequence
     Rec wrec[2][kNW];
     Rec win[2];
+    uint64_t settled[kSettle / 64];         // settle_in_order: samples among 64 candidates that follow each other
 };
 
 // Threshold phase: where the thresholds are worked out, and the bookkeeping of the levels.
@@ -403,8 +403,9 @@ __device__ __forceinline__ Rec plain_pick(const Held<P>& h, LocalShared& sh, con
 
 // A published candidate: three words with a stamp of 14 bits each around distance (31 bits, it is not negative),
 // coordinates and index (21 bits).  The stamp is never 0 and does not come twice in the rounds up to the next one whose
-// last bits (LocalArgs::wipe) are zero, in front of which the words are cleared.
+// last bits (kWipe) are zero, in front of which the words are cleared.
 constexpr int kCandWords3 = kLocalCandWords;
+constexpr uint32_t kWipe = kLocalStampRounds - 1;
 static_assert((kLocalStampRounds >> 1) < 1 << 14, "14 bits for a stamp");
 static_assert(kMaxGroup * 8192 <= 1 << 21, "21 bits for an index");
 constexpr int64_t kHalfWords = (int64_t)(kOwn + 1) * kCandWords3;
@@ -573,7 +574,7 @@ __device__ __forceinline__ int make_list(const Held<P>& h, LocalShared& sh, cons
     for (int j = 0; j < kLevels; ++j) tot[j] = (int)((uint32_t)(sum >> (16 * j)) & 0xFFFFu);
     const int halves = 2 * me.G;
     uint64_t* const hdr = a.ll_hdr + (int64_t)(me.grp * 2 + par) * halves;
-    const uint32_t stamp = ((round & a.wipe) >> 1) + 1u;
+    const uint32_t stamp = ((round & kWipe) >> 1) + 1u;
     if (me.G > 1) {
         if (me.lane == 0 && (me.w & (kHW - 1)) == 0) {
             uint64_t v = (uint64_t)stamp << 50;
@@ -966,6 +967,7 @@ __device__ __forceinline__ int exact_rounds(Held<P>& h, LocalShared& sh, const S
     float step = 0.8f;                      // ratio of a round's levels
     int dry = 0, most_dry = 3;
     while (st.np < stop) {
+        if ((st.round & kWipe) == kWipe && !renew_stamps<P>(h, sh, me, a, st.it, st.seq)) return 2;
         if (!(tau > 0.0f)) {
             const Rec r = plain_pick<P>(h, sh, me, a, st.it, st.seq);
             if (uni(r.fail) != 0) return 2;
@@ -987,7 +989,6 @@ __device__ __forceinline__ int exact_rounds(Held<P>& h, LocalShared& sh, const S
             dry = 0;
             continue;
         }
-        if ((st.round & a.wipe) == a.wipe && !renew_stamps<P>(h, sh, me, a, st.it, st.seq)) return 2;
         ++st.round;
         ++st.rounds;
         Levels lv;
@@ -1071,7 +1072,7 @@ __device__ __forceinline__ int threshold_rounds(Held<P>& h, LocalShared& sh, Lev
             }
             enter();
         }
-        if ((st.round & a.wipe) == a.wipe && !renew_stamps<P>(h, sh, me, a, st.it, st.seq)) return 2;
+        if ((st.round & kWipe) == kWipe && !renew_stamps<P>(h, sh, me, a, st.it, st.seq)) return 2;
         ++st.round;
         ++st.rounds;
         const int room = (level_end < n ? level_end : n) - st.np;
@@ -1159,7 +1160,7 @@ __device__ __forceinline__ int follow_order(Held<P>& h, LocalShared& sh, const S
 {
     const int n = a.n, N = a.N;
     const float* __restrict__ cloud = a.xyz + (int64_t)me.c * N * 3;
-    if (n < 16 || n > kOrderWords * me.G || (round & a.wipe) > a.wipe - 32 || round >= 1u << 18) return 1;
+    if (n < 16 || n > kOrderWords * me.G || (round & kWipe) > kWipe - 32 || round >= 1u << 18) return 1;
     {
         // every workgroup looks at the same points
         const float x0 = cloud[0], y0 = cloud[1], z0 = cloud[2];
@@ -1172,7 +1173,7 @@ __device__ __forceinline__ int follow_order(Held<P>& h, LocalShared& sh, const S
     // Behind another cloud of the group the workgroups meet first: some may still be reading that one's last list and counts,
     // which the words and the agreement on them write over (a workgroup without a share of the decisions is
     // waited for by nobody).
-    if (me.G == 1 || round == 0) ++round;
+    if (me.G == 1 || round == a.first_round) ++round;
     else if (!agree_in_order(sh, me, a, round)) return 0;
     const uint32_t stamp = round;
     uint64_t* const words = half_list(a, me, 0, 0);         // (a stamp of 32 bits is no stamp of a candidate's)
@@ -1461,7 +1462,8 @@ __global__ __launch_bounds__(kT) void local_kernel(LocalArgs a)
             *reinterpret_cast<BqHeader*>(a.bq_base) = bq_layout(a.B, a.N, a.n, a.bq_r2, a.bq_cap, 1);
     }
     Progress st;
-    st.it = st.seq = st.round = 0;
+    st.it = st.seq = 0;
+    st.round = a.first_round;
     for (int c = me.grp; c < a.B; c += ngroups) {
         me.c = c;
         run_cloud<P, BQ, MDPS, CHAINS>(a, sh, ls, me, st);
@@ -1623,8 +1625,9 @@ __global__ __launch_bounds__(kOrderT) void order_samples_kernel(const uint64_t* 
                     if (t0 + u * kOrderT < m && r >= r0 && r < r1) key[first[r] - from + atomicAdd(&next[r], 1)] = k[u];
                 }
             }
-            bool many = false;
-            for (int r = r0 + tid; r < r1; r += kOrderT) many = many || first[r + 1] - first[r] > kFewKeys;
+            bool many = false;                                             // (a range of keys has 512 of them at most)
+            if (!keyed)
+                for (int r = r0 + tid; r < r1; r += kOrderT) many = many || first[r + 1] - first[r] > kFewKeys;
             if (__syncthreads_or(many)) {
                 sort_keys(key, count, tid);
                 for (int t = tid; t < count; t += kOrderT) emit(from + t, key[t]);

@@ -203,8 +203,8 @@ def test_mdps_given_thresholds_small_record_and_short_prefix(fp):
 
 @pytest.mark.parametrize("G", [1, 3, 8])
 def test_stamps_start_again_in_a_cloud(fp, G):
-    """Equal distances take a round a sample: the stamps of published candidates start again (after 128 rounds with a
-    number of workgroups forced) several times in one cloud, with one workgroup there is nothing to renew."""
+    """Equal distances take a round a sample: the stamps of published candidates start again (after 100 rounds with a
+    number of workgroups forced) within one cloud; with one workgroup there is nothing to renew."""
     x = torch.from_numpy(cloud("lattice", 8192)[None]).cuda()
     want = exact_by_index(fp, x, 3000, want_mdc=True)
     fp.set_wg_per_cloud(G)
@@ -212,7 +212,7 @@ def test_stamps_start_again_in_a_cloud(fp, G):
         idx, mdc, info = fp.fps_exact_pruned(x, 3000, want_mdc=True, want_info=True)
     finally:
         fp.set_wg_per_cloud(0)
-    assert fp.parse_info(info)[0].status == 0 and fp.parse_info(info)[0].rounds > 3 * 128
+    assert fp.parse_info(info)[0].status == 0 and fp.parse_info(info)[0].rounds > 3 * 100
     assert torch.equal(idx, want[0]) and torch.equal(mdc.view(torch.int32), want[1].view(torch.int32))
 
 
@@ -233,7 +233,7 @@ def test_stamps_start_again_between_clouds(fp, G, order):
         fp.set_wg_per_cloud(0)
     for g, w, i in zip(got, want, info):
         rounds = [k.rounds for k in fp.parse_info(i)]
-        assert sum(rounds[::256 // G]) > 2 * 128 and all(k.status == 0 for k in fp.parse_info(i))
+        assert sum(rounds[::256 // G]) > 2 * 100 and all(k.status == 0 for k in fp.parse_info(i))
         assert all(torch.equal(g[b], w[b % 5]) for b in range(clouds))
 
 
