@@ -2121,18 +2121,6 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
         return;
     }
 
-    if constexpr (BQ) {
-        // a cloud held by one workgroup: its counters in the cache are zeroed here (a barrier
-        // comes before the first entry); with several workgroups a launch in front has done it
-        if (wh.G == 1) {
-            const int nchunks = (int)(a.bq_cap / kBqChunk);
-            for (int t = wh.tid; t < nchunks; t += T + kCtrlThreads) a.bq_fill[(int64_t)wh.c * nchunks + t] = 0u;
-            if (wh.tid == 0) {
-                a.bq_cursor[wh.c] = 0u;
-                a.bq_ovf[wh.c] = 0u;
-            }
-        }
-    }
     int known = 1;                          // samples known to be 0, 1, 2, ... in sequence
     // (Not in the recorders: with this code around their rounds take 3 to 15 % longer through other register allocation, us
     // without / with: 1 x 4096 -> 1024 448 / 495, 16 x 1500 -> 375 168 / 185, 8 x 24000 -> 6000 1816 / 2084; what it gains them is the
@@ -2207,6 +2195,19 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
     pt.bq_cur = pt.bq_lim = 0;
     pt.bq_nxt = kBqNoChunk;
     pt.bq_dead = false;
+    if constexpr (BQ) {
+        // a cloud held by one workgroup: its counters in the cache are zeroed here (a barrier
+        // comes before the first entry); with several workgroups a launch in front has done it.  (In front of the
+        // loads of the points it costs the kernel with eight points per thread 9 %: 140 x 4000 -> 1000 628 / 684 us.)
+        if (wh.G == 1) {
+            const int nchunks = (int)(a.bq_cap / kBqChunk);
+            for (int t = wh.tid; t < nchunks; t += T + kCtrlThreads) a.bq_fill[(int64_t)wh.c * nchunks + t] = 0u;
+            if (wh.tid == 0) {
+                a.bq_cursor[wh.c] = 0u;
+                a.bq_ovf[wh.c] = 0u;
+            }
+        }
+    }
     if (wh.tid < kCandWin + 2) sh.live[wh.tid] = 0;    // round tags start at 1 in every cloud
     if (wh.tid == 0) sh.progress = 0;
     if constexpr (PERM && MODE != 3)
