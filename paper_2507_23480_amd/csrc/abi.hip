@@ -98,8 +98,8 @@ constexpr int kOneWgPoints = 2048;
 // 3000; a cloud with 95 % of its points in a clump 1.1-1.4 and 0.8-1.2; one with a far point 1.1-1.3 and 0.9-1.1 (of a
 // million points, whose counters then queue up, 1.4-2.0 and 1.2-1.4).
 // (Exact FPS in cell order was settled in sweeps when these were measured.  By local decisions it takes 0.4 to 0.95 of that time, e.g.
-// us: 8 x 24000 -> 6000 850 / 525, 1 x 6000 -> 1500 446 / 346, 64 x 8000 -> 3000 663 / 526, scanner 40 x 6000 -> 1500 560 / 398; more only for
-// uniform cubes that one workgroup holds, 140 x 8000 -> 3000 1184 / 1430, 256 x 6000 -> 3000 1337 / 1396.)
+// us: 8 x 24000 -> 6000 850 / 525, 1 x 6000 -> 1500 446 / 346, 64 x 8000 -> 3000 663 / 526, scanner 40 x 6000 -> 1500 560 / 398; clouds that one
+// workgroup holds 140 x 8000 -> 3000 1262 / 1198 (uniform), 1298 / 1144 (rooms), 256 x 6000 -> 3000 1439 / 1223.)
 // fp_fps_exact takes the cell order from kCellOrderFrom points on, when its workspace has room for it; the _pruned
 // entry points leave it below kCellOrderSamples, and for clouds that one workgroup holds.  A call with a record keeps
 // its entry point's layout: it is the order of the record's blocks.
@@ -113,6 +113,7 @@ constexpr int kCellOrderSamplesLowest = 2000;
 //   samples                      1500-2000   3000        4100        5000        6000        12000       30000
 //   lowest index first           1.1-1.5     0.9-1.3     0.9-1.1     0.8-1.0     0.7-1.0     0.5-0.8     0.4-0.6
 //   scattered scan order         1.0-1.4     0.9-1.3     0.9-1.1     0.8-1.0     0.8-1.0     0.5-0.8     0.4-0.6
+// (Clouds that one workgroup holds, 140 x 8000 -> 5000: lowest index first 0.76-0.88, scattered 1.09 uniform, 0.96 rooms, 0.91 rings.)
 // Exact FPS gains from the first size on at which the sort pays.
 constexpr int kLocalMdpsSamples = 5000;
 
@@ -232,13 +233,15 @@ int64_t rel_exchange_bytes(int32_t B)
 // 2000 / 3000 / 4096: 8 x 24000 -> 6000 (24 workgroups a cloud) 576 / 542 / 562 / 667 / 867 / 1127; 4 x 120000 -> 16384 (64)
 // 1426 / 1119 / 1061 / 1040 / 1067 / 1153; 1000000 -> 65536 (245) 3248 / 2300 / 1949 / 1839 / 1734 / 1710.  (At most 32 units of
 // eight candidates a workgroup, which is what it can publish.)
+// One workgroup for the cloud decides all of the list: us at lists of 160 / 200 / 288 / 416 / 576, 140 x 8000 -> 3000 uniform - / 1351 /
+// 1396 / 1524 / 1639, 200 x 4000 -> 3000 793 / 822 / 875 / 1020 / 1234, rooms 140 x 8000 -> 5000 1604 / 1619 / 1750 / 1828 / 1991.
 // Exact FPS has no use for a list much longer than half of the samples it looks for.  us at lists of 288 / 400 / 600 / 1000 /
 // 2100: 60000 -> 1500 of a room 476 / 443 / 410 / 414 / 511, of a cube 428 / 428 / 403 / 417 / 610; prefixes of 600 samples (8 x
 // 24000) 276 / 270 / 284 / 310 / -, of 1638 (4 x 120000) 666 / 617 / 548 / 520 / 591, of 6553 (1000000) 1152 / 1053 / 1018 /
 // 910 / 868.
 int local_aim(int G, int samples)
 {
-    const int aim = 256 + 32 * G, most = G > 1 && 256 * G < kLocalList ? 256 * G : kLocalList;
+    const int aim = G == 1 ? 200 : 256 + 32 * G, most = G > 1 && 256 * G < kLocalList ? 256 * G : kLocalList;
     const int use = samples < 512 ? 256 : samples / 2 + samples / 8;
     return std::min({aim, most, use});
 }

@@ -1313,7 +1313,10 @@ __device__ __forceinline__ void run_cloud(const LocalArgs& a, LocalShared& sh, L
         if (me.tid < kSpans * kLevels) reinterpret_cast<int32_t*>(sh.tot)[me.tid] = 0;
         if constexpr (!MDPS) {
             int known = 1;
-            if constexpr (!BQ) {
+            // (Not with eight points per thread, clouds of 4097 to 8192 points that one workgroup holds: around this code their rounds
+            // spill more, us without / with: 140 x 8000 -> 3000 uniform 1255 / 1403, rooms 1166 / 1298, rings 1338 / 1490.)
+            constexpr bool FOLLOWS = !BQ && P < 8;
+            if constexpr (FOLLOWS) {
                 if (start == 0 && !a.dist) {
                     __syncthreads();                        // (fail)
                     known = follow_order<P>(h, sh, me, a, st.round);
@@ -1334,7 +1337,7 @@ __device__ __forceinline__ void run_cloud(const LocalArgs& a, LocalShared& sh, L
             }
             const float* s = a.xyz + ((int64_t)me.c * N + start) * 3;
             h.ub = __builtin_inff();
-            if (known > 1) {
+            if (FOLLOWS && known > 1) {
                 if (known < n) fold_order<P>(h, sh, me, a, known);
             } else {
                 fold_one<P, BQ>(h, sh, me, a, s[0], s[1], s[2], __builtin_inff(), (uint32_t)start);
