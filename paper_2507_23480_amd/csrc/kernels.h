@@ -157,8 +157,8 @@ struct LocalArgs : SamplerArgs {
 };
 // mdps: what follows the prefix; chains: its keys are indices, which may follow each other along the cloud
 const void* local_kernel_for(int points_per_thread, bool bq, bool mdps, bool chains);
-// Positions [from, cloud.count) of every cloud; fill: and the rest up to n.  curve: distances, [B][n] (NULL: none);
-// inv: [B][N], position of a sample by its index (NULL: not wanted)
+// Puts the samples found in sequence, run by run, from the first run's begin up to cloud.count (`most` at most); fill: and the
+// rest up to n.  out_mdc: distances, [B][n] (NULL: none); inv: [B][N], position of a sample by its index (NULL: not wanted)
 hipError_t launch_order_samples(const uint64_t* found, const LocalCloud* cloud, const int32_t* start_idx, int B, int N, int n,
                                 int most, bool fill, int32_t* out_idx, float* out_mdc, int32_t* bq_idx, int32_t* inv,
                                 hipStream_t stream);

@@ -107,7 +107,7 @@ struct Held {
 };
 
 #ifdef FASTPOINT_PHASE_CLOCKS
-__shared__ long long clk[16];               // tuning builds: ticks of thread 0 in the parts of a round, in info.thr2
+__shared__ long long clk[16];               // tuning builds: ticks of thread 0 in the parts of a round, left behind the words of the decisions
 __shared__ long long clk_at;
 #define MARK(k) do { if (threadIdx.x == 0) { const long long now__ = wall_clock64(); clk[k] += now__ - clk_at; clk_at = now__; } } while (0)
 #else
@@ -149,14 +149,6 @@ __device__ __forceinline__ float ord2f(uint32_t u)
 {
     return __uint_as_float(u ^ ((u >> 31) != 0 ? 0x80000000u : 0xFFFFFFFFu));
 }
-// smallest and largest of the lanes' values, over those that count
-__device__ __forceinline__ void wave_range(float v, bool counts, float& lo, float& hi)
-{
-    const uint32_t u = f2ord(v);
-    lo = ord2f(wave_min_u32(counts ? u : 0xFF800000u));     // +inf
-    hi = ord2f(wave_max_u32(counts ? u : 0x007FFFFFu));     // -inf
-}
-
 // (a distance that is not a number is larger than any other as an integer: such a point keeps its distance)
 template <int P>
 __device__ __forceinline__ void fold(Held<P>& h, float cx, float cy, float cz, float v)
@@ -238,15 +230,15 @@ __device__ __forceinline__ void refresh_bound(Held<P>& h)
     h.ub = __uint_as_float(wave_max_u32(m));
 }
 
-// Loads the wave's points and finds their boxes.  (Where the curve leaves a thin layer of occupied cells and comes back
-// elsewhere, one box would span the cloud and the wave would fold every sample: 7000 to 10000 of 16384 instead of
-// some 400 for one or two waves of a LiDAR sweep.)
 // Where a wave with points keeps its place in the record from one launch to the next.
 __device__ __forceinline__ uint2& bq_place(const LocalArgs& a, const Seat& me, int P)
 {
     return a.bq_at[(int64_t)me.c * ((a.N + 64 * P - 1) / (64 * P)) + me.half * kHW + (me.w & (kHW - 1))];
 }
 
+// Loads the wave's points and finds their boxes.  (Where the curve leaves a thin layer of occupied cells and comes back
+// elsewhere, one box would span the cloud and the wave would fold every sample: 7000 to 10000 of 16384 instead of
+// some 400 for one or two waves of a LiDAR sweep.)
 template <int P, bool BQ, bool MDPS>
 __device__ __forceinline__ void load_points(Held<P>& h, LocalShared& sh, const Seat& me, const LocalArgs& a)
 {
