@@ -2121,10 +2121,29 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
         return;
     }
 
+    // a cloud held by one workgroup: its counters in the cache are zeroed here (a barrier
+    // comes before the first entry); with several workgroups a launch in front has done it.  Where it stands makes other
+    // register allocation: in front of the points' loads / behind them, us, eight points per thread, one workgroup 140 x 4000 ->
+    // 1000 668 / 616, 256 x 3000 -> 700 424 / 391, sixteen, cell-ordered 140 x 8000 -> 2100 1874 / 1832; all others are faster with it in
+    // front: 4 x 120000 -> 4000 1788 / 1831, 8 x 24000 -> 4000 1427 / 1456, 1 x 4096 -> 1024 415 / 420.
+    constexpr bool ZERO_LATE = P == 16 || (P == 8 && MODE == 1);
+    auto zero_counters = [&]() {
+        if (wh.G == 1) {
+            const int nchunks = (int)(a.bq_cap / kBqChunk);
+            for (int t = wh.tid; t < nchunks; t += T + kCtrlThreads) a.bq_fill[(int64_t)wh.c * nchunks + t] = 0u;
+            if (wh.tid == 0) {
+                a.bq_cursor[wh.c] = 0u;
+                a.bq_ovf[wh.c] = 0u;
+            }
+        }
+    };
+    if constexpr (BQ && !ZERO_LATE) zero_counters();
     int known = 1;                          // samples known to be 0, 1, 2, ... in sequence
     // (Not in the recorders: with this code around their rounds take 3 to 15 % longer through other register allocation, us
     // without / with: 1 x 4096 -> 1024 448 / 495, 16 x 1500 -> 375 168 / 185, 8 x 24000 -> 6000 1816 / 2084; what it gains them is the
-    // prefix of an input that is in sequence.)
+    // prefix of an input that is in sequence.  MDPS without a record pays 0.3 to 1.1 % on clouds in no order, 8 x 24000 -> 6000 1602 /
+    // 1618, 1 x 4096 -> 1024 314 / 317 (sixteen points per thread gain, 140 x 8000 -> 1000 797 / 507), for its prefix on those that are:
+    // 8 x 6000 -> 1500 431 / 329, 8 x 1500 -> 375 113 / 98, 4 x 16384 -> 2000 600 / 446.)
     constexpr bool ORDERED = !PERM && !BQ;
     if constexpr (ORDERED)
         if (start == 0) known = follow_order<T, P>(a, sh, wh, seq, MODE == 0 || a.m >= n - 1 ? n : a.m + 1);
@@ -2195,19 +2214,7 @@ __device__ __forceinline__ void run_cloud(const SamplerArgs& a, Shared<T>& sh, c
     pt.bq_cur = pt.bq_lim = 0;
     pt.bq_nxt = kBqNoChunk;
     pt.bq_dead = false;
-    if constexpr (BQ) {
-        // a cloud held by one workgroup: its counters in the cache are zeroed here (a barrier
-        // comes before the first entry); with several workgroups a launch in front has done it.  (In front of the
-        // loads of the points it costs the kernel with eight points per thread 9 %: 140 x 4000 -> 1000 628 / 684 us.)
-        if (wh.G == 1) {
-            const int nchunks = (int)(a.bq_cap / kBqChunk);
-            for (int t = wh.tid; t < nchunks; t += T + kCtrlThreads) a.bq_fill[(int64_t)wh.c * nchunks + t] = 0u;
-            if (wh.tid == 0) {
-                a.bq_cursor[wh.c] = 0u;
-                a.bq_ovf[wh.c] = 0u;
-            }
-        }
-    }
+    if constexpr (BQ && ZERO_LATE) zero_counters();
     if (wh.tid < kCandWin + 2) sh.live[wh.tid] = 0;    // round tags start at 1 in every cloud
     if (wh.tid == 0) sh.progress = 0;
     if constexpr (PERM && MODE != 3)
