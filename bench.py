@@ -56,12 +56,12 @@ GRAPH = "four streams, step replayed as one HIP graph"
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs (profiles/bench_C5_hbm_traffic.md, bench_C4_hbm_traffic.md,
 # bench_C2_hbm_traffic.md), keyed by workload and kernel.  None where no counter run is recorded.  The
 # samplers keep the cloud in registers: what they move beyond reading it once is the polling of the
-# words exchanged between the workgroups of a cloud.
+# words exchanged between the workgroups of a cloud and, by local decisions, registers in scratch memory.
 TRAFFIC_BYTES = {"C2": {"fps_exact": 427967, "mdps_sample+record": 2364746, "ball_query_cached": 1948914,
                         "ball_query": 2004582},
                  # (C4, C5: the step's recorder is the cell-ordered one, its reader the one for cell-ordered records)
-                 "C4": {"fps_exact": 208865400, "mdps_sample+record": 341887000, "ball_query_cached": 60371400},
-                 "C5": {"fps_exact": 353529000, "mdps_sample+record": 1133064000, "ball_query_cached": 29255500}}
+                 "C4": {"fps_exact": 208899000, "mdps_sample+record": 343609000, "ball_query_cached": 60311600},
+                 "C5": {"fps_exact": 301705000, "mdps_sample+record": 1029930000, "ball_query_cached": 29258800}}
 
 
 PRUNED_RECORD_FROM = 1 << 14

@@ -87,19 +87,17 @@ constexpr int kOneWgPoints = 2048;
 // Layout.  A cell-ordered run sorts the cloud first and gains on every pick after the first some hundred, so the number
 // of samples decides, much the same for clouds of 3000 and of a million points.  Time of a cell-ordered run over
 // that of an index-ordered one (sort included; uniform points to rooms, single clouds and batches of 4 to 100):
-//   samples                      256         1024        1500        2048        3000
-//   exact FPS                    1.15-1.94   0.99-1.28   0.89-1.11   0.78-0.91   0.65-0.88
-//   MDPS, scattered scan order   1.16-1.61   0.93-1.32   0.82-1.16   0.72-0.97   0.67-0.95
-//   MDPS, lowest index first     1.39-1.9    1.08-1.4    0.94-1.2    0.85-1.0    0.77-1.0
+//   samples                      256         512         1024        1500        2048        3000
+//   exact FPS                    1.07-1.47   0.91-1.33   0.73-1.03   0.62-0.88   0.57-0.81   0.50-0.68
+//   ... one or two workgroups    1.69-2.21   1.39-1.62   1.02-1.16   0.86-0.96   0.76-0.86   0.64-0.75
+//   MDPS, scattered scan order   1.16-1.61               0.93-1.32   0.82-1.16   0.72-0.97   0.67-0.95
+//   MDPS, lowest index first     1.39-1.9                1.08-1.4    0.94-1.2    0.85-1.0    0.77-1.0
 // (MDPS, lowest index first, on rooms of 60000 points and more: 1.1-2.1 up to 3000 samples; 65536 of a million
-// clustered points 0.3.)  Where a batch leaves a cloud one or two workgroups, which then work out the relations of all
-// candidates among themselves, the line of exact FPS lies twice as high (256 x 6000 points, index-ordered / cell-ordered,
-// us: 1500 samples 771 / 971, 3000: 1474 / 1398).  Scanner clouds are 1.09-1.19 at 1500 samples (exact FPS), 0.91-1.04 at
-// 3000; a cloud with 95 % of its points in a clump 1.1-1.4 and 0.8-1.2; one with a far point 1.1-1.3 and 0.9-1.1 (of a
-// million points, whose counters then queue up, 1.4-2.0 and 1.2-1.4).
-// (Exact FPS in cell order was settled in sweeps when these were measured.  By local decisions it takes 0.4 to 0.95 of that time, e.g.
-// us: 8 x 24000 -> 6000 850 / 525, 1 x 6000 -> 1500 446 / 346, 64 x 8000 -> 3000 663 / 526, scanner 40 x 6000 -> 1500 560 / 398; clouds that one
-// workgroup holds 140 x 8000 -> 3000 1262 / 1198 (uniform), 1298 / 1144 (rooms), 256 x 6000 -> 3000 1439 / 1223.)
+// clustered points 0.3.)  The lines of exact FPS lie higher than its rows say: they were drawn when exact FPS in cell order was
+// settled in sweeps (0.89-1.11 at 1500 samples, twice as many for clouds of one or two workgroups, which then worked out the
+// relations of all candidates among themselves).  What lies between stays index-ordered and could gain: us, index-ordered / by
+// local decisions, 1 x 4096 -> 1024 338 / 328, 8 x 24000 -> 1024 476 / 371, 4 x 120000 -> 1024 805 / 588, 64 x 8000 -> 2048 621 / 490,
+// 140 x 6000 rooms -> 2048 1007 / 769.
 // fp_fps_exact takes the cell order from kCellOrderFrom points on, when its workspace has room for it; the _pruned
 // entry points leave it below kCellOrderSamples, and for clouds that one workgroup holds.  A call with a record keeps
 // its entry point's layout: it is the order of the record's blocks.
