@@ -31,12 +31,12 @@
 // key, and the radius is the level's.  MDPS takes two launches, for the prefix and for the rest: the thresholds need the
 // prefix's curve in sequence.
 //
-// Bound: latency.  A round takes 11 us on 24 workgroups, 15 on 64 and 245: three trips through memory (counts 2-4.7 us with the
+// Bound: latency.  A round takes 11 us on 24 workgroups, 15 on 64, 17 on 245: three trips through memory (counts 2-4.7 us with the
 // wait for the slowest workgroup, list 2-4.5, decisions 2-2.6), the rest of its parts 1-2 us each.  Rounds of exact FPS for the
 // workloads below: 85, 56 and 40, against 436, 207 and 82 rounds of 256 candidates settled in sweeps before (94, 67 and 43 with
 // lists that ended where half a workgroup had more than 191 points).
 // us, before -> now: fps_exact_pruned million points -> 65536 5190 -> 1600, 4 x 120000 -> 16384 2750 -> 960, 8 x 24000 -> 6000
-// 850 -> 525; mdps_sample_pruned in the scattered order with record 6250 -> 2060, 4530 -> 2370, 1070 -> 860.  (1024 threads; with
+// 850 -> 525; mdps_sample_pruned in the scattered order with record 6250 -> 2080, 4530 -> 2320, 1070 -> 830.  (1024 threads; with
 // 512 and twice the points per thread exact FPS took 10, 8 and 1 % longer.)  Comparing a candidate with the whole list instead
 // of the chunks near it took 10-20 us a round.
 #include <hip/hip_runtime.h>
